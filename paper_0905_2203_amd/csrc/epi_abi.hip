@@ -175,9 +175,11 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return key[a] < key[b]; });
     std::vector<int32_t> h_types((size_t)kMaxN * m, 0);
     std::vector<T> h_lo((size_t)(kMaxN - 1) * m, 0), h_hi((size_t)(kMaxN - 1) * m, 0);
+    std::vector<uint8_t> h_N(m);
     cs.groups.clear();
     for (int64_t s = 0; s < m; ++s) {
         const int32_t c = order[s];
+        h_N[s] = N[c];
         for (int j = 0; j < kMaxN; ++j) h_types[(size_t)j * m + s] = j < N[c] ? types[(int64_t)c * 8 + j] : 0;
         for (int j = 0; j + 1 < kMaxN; ++j) {
             h_lo[(size_t)j * m + s] = j + 1 < N[c] ? (T)lo[(int64_t)c * 7 + j] : T(0);
@@ -192,6 +194,7 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
             g.begin = s;
             g.end = s;
             g.hspan = 0;
+            g.lomax = 0;
             cs.groups.push_back(g);
         }
         Group &g = cs.groups.back();
@@ -199,6 +202,7 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
         int64_t sp = 0;
         for (int j = 0; j + 1 < N[c]; ++j) {
             sp += hi[(int64_t)c * 7 + j];
+            g.lomax = std::max(g.lomax, lo[(int64_t)c * 7 + j]);
             g.Q = std::max<int>(g.Q, queue_class(queue_bound(lo[(int64_t)c * 7 + j], hi[(int64_t)c * 7 + j])));
         }
         g.hspan = std::max(g.hspan, sp);
@@ -209,6 +213,7 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
     if ((e = cs.lo.alloc(sizeof(T) * h_lo.size())) != hipSuccess) return e;
     if ((e = cs.hi.alloc(sizeof(T) * h_hi.size())) != hipSuccess) return e;
     if ((e = cs.orig.alloc(sizeof(int32_t) * m)) != hipSuccess) return e;
+    if ((e = cs.cN.alloc((size_t)m)) != hipSuccess) return e;
     if ((e = cs.counts.alloc(sizeof(int32_t) * m)) != hipSuccess) return e;
     if ((e = cs.tau.alloc(sizeof(T) * m)) != hipSuccess) return e;
     if (m > 0) {
@@ -224,6 +229,7 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
         if ((e = hipMemcpyAsync(cs.orig.p, order.data(), sizeof(int32_t) * m, hipMemcpyHostToDevice, st)) !=
             hipSuccess)
             return e;
+        if ((e = hipMemcpyAsync(cs.cN.p, h_N.data(), (size_t)m, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
     }
     cs.h_order = order;
     // host staging vectors die here: wait for the copies
@@ -561,7 +567,7 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
                            "reading times");
                     B = b32;
                 }
-                HIPTRY(ctx, launch_count_append(*s, *cs, B, ctx->c.flags.as<int32_t>(), st), "counting appended events");
+                HIPTRY(ctx, launch_count_append(*s, *cs, B, ctx->c.opt, ctx->c.flags.as<int32_t>(), st), "counting appended events");
                 // deep episodes: counted again over the whole stream
                 HIPTRY(ctx, count_deep_subset(*s, *cs, st), "counting deep episodes");
             }

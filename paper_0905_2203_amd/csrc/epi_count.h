@@ -54,6 +54,7 @@ struct CountArgs {
     const int32_t *perm;  // lane slot -> candidate slot (scheduler order); null = identity
     int32_t *work;        // work log: kWork counters per candidate (submission order); null = off
     int64_t *cycles;      // work log: wall-clock start/end per work item; null = off
+    const uint8_t *cN;    // epi_wave.hip: episode size of every slot of the set
 };
 
 // Persistent form: one work item = (unit, lane block, segment).
@@ -144,5 +145,29 @@ template <typename T>
 hipError_t lane_launch_persistent(int N, bool pk, bool wl, unsigned grid, int W, uint32_t lds, hipStream_t st,
                                   const CountArgs<T> *units, const WorkItem *items, int64_t n_items, int64_t item_base,
                                   unsigned long long *queue);
+
+// ---- wave chains (epi_wave.hip) ------------------------------------------------
+// One wave counts one (candidate, segment), of any size.  A launch takes slots
+// [begin, begin + G) of a set and, for P > 1, reconciles the segments.
+constexpr int kWaveChunks = 4;   // events per node and window, in 64s
+constexpr int kWaveGap = 63;     // Stream::gap is the least t[i + kWaveGap] - t[i] of one type
+
+// Whether the chains' bounds hold for episodes of the given longest span and
+// largest lower bound on a stream of the given gap: fewer than 64 events of a
+// type within any lower bound (the entries a list hands on fit a wave), fewer
+// than 64 at one time (a window always advances), spans below 2^29.
+inline bool wave_ok(int64_t gap, int64_t hspan, int64_t lomax) {
+    return gap >= 1 && gap >= lomax && hspan >= 0 && hspan < (int64_t(1) << 29);
+}
+int wave_waves_per_cu();
+template <typename T>
+hipError_t wave_launch(const CountArgs<T> &a, hipStream_t st);
+template <typename T>
+hipError_t wave_launch_append(const CountArgs<T> &a, T B, hipStream_t st);
+// units, items, queue: as lane_launch_persistent, an item's block being 64
+// slots; segmented: some unit has P > 1.
+template <typename T>
+hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WorkItem *items,
+                                  int64_t n_items, unsigned long long *queue, bool segmented);
 
 }  // namespace epi

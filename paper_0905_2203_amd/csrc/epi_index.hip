@@ -19,7 +19,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "epi_internal.h"
+#include "epi_count.h"
 
 namespace epi {
 
@@ -190,6 +190,48 @@ __global__ void k_offsets(const int32_t *__restrict__ base, int32_t K, int64_t B
     if (k == K) off[K] = (int32_t)n;
 }
 
+// out = min over events i with an event i + kWaveGap of the same type of the
+// time between them (out holds the type's maximum before).
+constexpr int kGapBlock = 256, kGapItems = 16;
+template <typename T>
+__global__ __launch_bounds__(kGapBlock) void k_gap(const T *__restrict__ ts, int64_t n,
+                                                   const int32_t *__restrict__ off, int32_t K,
+                                                   unsigned long long *__restrict__ out) {
+    const int64_t b0 = (int64_t)blockIdx.x * kGapBlock * kGapItems;
+    // type of the block's first event: the last with off <= b0
+    int lo = 0, hi = K - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (off[mid] <= b0) lo = mid; else hi = mid - 1;
+    }
+    int ty = lo;
+    unsigned long long best = INT64_MAX;
+    for (int q = 0; q < kGapItems; ++q) {
+        const int64_t i = b0 + q * kGapBlock + threadIdx.x;
+        if (i + kWaveGap >= n) break;
+        while (off[ty + 1] <= i) ++ty;
+        if (i + kWaveGap < off[ty + 1]) {
+            const unsigned long long d = (unsigned long long)ts[i + kWaveGap] - (unsigned long long)ts[i];
+            best = d < best ? d : best;
+        }
+    }
+    for (int d = 1; d < kWave; d <<= 1) {
+        const unsigned long long o = __shfl_xor(best, d, kWave);
+        best = o < best ? o : best;
+    }
+    // one atomic a block, and only where it lowers the minimum (a stale read
+    // only costs an atomic): thousands on one address would serialise
+    __shared__ unsigned long long part[kGapBlock / kWave];
+    if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = best;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kGapBlock / kWave; ++q) best = part[q] < best ? part[q] : best;
+        if (best < *(volatile unsigned long long *)out) atomicMin(out, best);
+    }
+}
+
+__global__ void k_gap_init(unsigned long long *out) { *out = INT64_MAX; }
+
 // g[i] = times[min(i * step, n - 1)], i < ng
 template <typename T>
 __global__ void k_sample_times(const T *__restrict__ times, int64_t n, int64_t step, int64_t ng, T *__restrict__ g) {
@@ -286,7 +328,8 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
     const int64_t B = n > 0 ? (n + TT - 1) / TT : 0;
     s.B = B;
     if ((e = s.type_off.alloc(sizeof(int32_t) * (K + 1))) != hipSuccess) return e;
-    if ((e = s.ts_by_type.alloc(s.ts_bytes() * (size_t)n)) != hipSuccess) return e;
+    // (padded: the wave chains load whole windows)
+    if ((e = s.ts_by_type.alloc(s.ts_bytes() * ((size_t)n + kWaveChunks * kWave))) != hipSuccess) return e;
     if ((e = s.pos_by_type.alloc(sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
     if ((e = s.tiled_ts.alloc(s.ts_bytes() * (size_t)B * TT)) != hipSuccess) return e;
     if ((e = s.tile_loff.alloc(sizeof(uint16_t) * (size_t)B * (K + 1))) != hipSuccess) return e;
@@ -322,6 +365,20 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
                                                     s.tile_loff.as<uint16_t>(), s.tile_t0.as<int32_t>(), TT);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    DevBuf gap;
+    if ((e = gap.alloc(sizeof(unsigned long long))) != hipSuccess) return e;
+    k_gap_init<<<1, 1, 0, st>>>(gap.as<unsigned long long>());
+    if (n > kWaveGap) {
+        const unsigned blocks = (unsigned)((n + kGapBlock * kGapItems - 1) / (kGapBlock * kGapItems));
+        if (s.ts_kind == EPI_TS_I64)
+            k_gap<int64_t><<<blocks, kGapBlock, 0, st>>>(s.ts_by_type.as<int64_t>(), n, s.type_off.as<int32_t>(), K,
+                                                         gap.as<unsigned long long>());
+        else
+            k_gap<int32_t><<<blocks, kGapBlock, 0, st>>>(s.ts_by_type.as<int32_t>(), n, s.type_off.as<int32_t>(), K,
+                                                         gap.as<unsigned long long>());
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(&s.gap, gap.p, sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     // the temporaries are freed when this returns: wait for the kernels first
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     s.h_off.resize(K + 1);

@@ -180,6 +180,7 @@ struct Stream {
     std::vector<int32_t> h_off;  // host copy of type_off
     std::vector<int64_t> h_tile_t0;  // host copy of tile_t0 (widened)
     int64_t max_tile_span = -1;      // longest time from a tile's first event to the next tile's (or the last event)
+    int64_t gap = 0;                 // least time from one event to the 63rd after it of the same type (INT64_MAX: no type has 64)
     size_t ts_bytes() const { return ts_kind == EPI_TS_I64 ? 8 : 4; }
 };
 
@@ -190,6 +191,8 @@ struct Group {
     int C = 0;                   // most ring entries of one episode: sum of its intervals' bounds (lane machines)
     int64_t begin = 0, end = 0;  // slots [begin, end) of the grouped layout
     int64_t hspan = -1;          // longest span (sum of upper bounds) of its episodes (-1: unknown)
+    int64_t lomax = INT64_MAX;   // largest lower bound of its episodes' intervals
+    double cost_sum = 0, cost_max = 0;  // summed event counts of its episodes' types: all, the costliest (candidate_costs)
 };
 
 // Launch classes of the register-indexed lane machines: an episode's ring
@@ -225,6 +228,8 @@ struct CandSet {
     DevBuf types;   // int32 [8][m]
     DevBuf lo, hi;  // T [7][m]
     DevBuf orig;    // int32 [m]
+    DevBuf cN;      // uint8 [m]: episode sizes
+    int64_t cost_n = -1;  // stream events the groups' costs were taken at
     DevBuf counts;  // int32 [m], submission order
     DevBuf tau;     // T [m], submission order: each episode's last completion (type minimum: none)
     int64_t counted_n = -1;  // stream events covered by the counts (-1: never counted)
@@ -479,7 +484,8 @@ hipError_t launch_count_tracking(const Stream &s, CandSet &c, hipStream_t st);
 hipError_t count_deep_subset(const Stream &s, CandSet &c, hipStream_t st);
 // Add to set c's counts the occurrences completed by the stream's events
 // after the first c.counted_n (B = the first of their times).
-hipError_t launch_count_append(const Stream &s, CandSet &c, int64_t B, int32_t *d_flags, hipStream_t st);
+hipError_t launch_count_append(const Stream &s, CandSet &c, int64_t B, const CountOptions &opt, int32_t *d_flags,
+                               hipStream_t st);
 // Batched count of several candidate sets (possibly on different streams) in
 // one graph launch of persistent kernels, one per episode size.  sched:
 // EPI_SCHED_RR (submission order), EPI_SCHED_LEARNED (the cost model's

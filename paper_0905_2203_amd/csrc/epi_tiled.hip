@@ -960,13 +960,140 @@ bool lane_group_ok(const Stream &s, const CandSet &c, const Group &g, const Coun
            lane_rel_ok(s.max_tile_span, g.hspan);
 }
 
+// Whether the wave chains count group g of stream s.
+bool wave_group_ok(const Stream &s, const CandSet &c, const Group &g, const CountOptions &opt) {
+    return opt.lane_engine && !opt.worklog && !c.compact && c.cN.p && s.n > 0 && wave_ok(s.gap, g.hspan, g.lomax);
+}
+
+// Summed event counts of the types of a set's episodes, per group (the events
+// a count reads): all of them, and the costliest episode's.
+void candidate_costs(const Stream &s, CandSet &c) {
+    if (c.cost_n == s.n || c.compact || (int64_t)c.h_N.size() != c.m || (int64_t)s.h_off.size() != (int64_t)s.K + 1)
+        return;
+    for (Group &g : c.groups) {
+        g.cost_sum = g.cost_max = 0;
+        for (int64_t i = g.begin; i < g.end; ++i) {
+            const int64_t o = c.h_order[i];
+            const int32_t *ty = c.h_types.data() + o * kMaxN;
+            double w = 0;
+            for (int j = 0; j < c.h_N[o]; ++j) w += (double)(s.h_off[ty[j] + 1] - s.h_off[ty[j]]);
+            g.cost_sum += w;
+            g.cost_max = std::max(g.cost_max, w);
+        }
+    }
+    c.cost_n = s.n;
+}
+
+// Segments of episodes counted by the wave chains (and the tiles per segment,
+// *S_out): the costliest (episode, segment) takes about a third of what each
+// resident wave has to do of the whole launch, so that no wave is left running
+// alone at its end; a segment holds at least kWaveMinEvents of the costliest
+// episode's events, below which its start and reconciliation cost more than
+// they spread.  EPI_OPT_TARGET_LANES scales the resident waves aimed at.
+constexpr double kWaveMinEvents = 2048;
+int64_t wave_segments(const Stream &s, double cost_max, double cost_all, const CountOptions &opt, int waves,
+                      int64_t *S_out) {
+    int64_t P = 1;
+    if (opt.segments > 0) {
+        P = opt.segments;
+    } else if (cost_all > 0) {
+        const double aim = 3.0 * (double)waves * ((double)opt.target_lanes / 262144.0);
+        P = (int64_t)std::min(std::ceil(aim * cost_max / cost_all), cost_max / kWaveMinEvents);
+    }
+    P = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(P, s.B), 65535));
+    const int64_t S = (std::max<int64_t>(s.B, 1) + P - 1) / P;
+    P = std::max<int64_t>(1, (s.B + S - 1) / S);
+    *S_out = S;
+    return P;
+}
+
+hipError_t wave_resident(int *waves) {
+    int dev = 0, ncu = 0;
+    hipError_t e;
+    if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+    if ((e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+    static const int per = wave_waves_per_cu();  // a property of the kernel
+    *waves = ncu * per;
+    return hipSuccess;
+}
+
+// What the wave chains read of a stream and a set.
+template <typename T>
+CountArgs<T> wave_args(const Stream &s, const CandSet &c, int32_t *d_flags) {
+    CountArgs<T> a{};
+    a.tile_t0 = s.tile_t0.as<T>();
+    a.ts_by_type = s.ts_by_type.as<T>();
+    a.type_off = s.type_off.as<int32_t>();
+    a.B = s.B;
+    a.K = s.K;
+    a.ctypes = c.types.as<int32_t>();
+    a.clo = c.lo.as<T>();
+    a.chi = c.hi.as<T>();
+    a.cN = c.cN.as<uint8_t>();
+    a.m = c.m;
+    a.orig = c.orig.as<int32_t>();
+    a.counts = c.counts.as<int32_t>();
+    a.tau = c.tau.p ? c.tau.as<T>() : nullptr;
+    a.flags = d_flags;
+    a.P = 1;
+    a.S = std::max<int64_t>(s.B, 1);
+    return a;
+}
+
+// Plain count of slots [begin, end) of set c by the wave chains.
+template <typename T>
+hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end, double cost_max, double cost_all,
+                        const CountOptions &opt, int32_t *d_flags, hipStream_t st, unsigned char *ext_scratch,
+                        size_t ext_bytes) {
+    hipError_t e;
+    int waves = 0;
+    if ((e = wave_resident(&waves)) != hipSuccess) return e;
+    CountArgs<T> a = wave_args<T>(s, c, d_flags);
+    const int64_t P = wave_segments(s, cost_max, cost_all, opt, waves, &a.S);
+    a.P = (int32_t)P;
+    int64_t step = end - begin;
+    if (P > 1 && ext_scratch) {
+        // the caller's scratch: as many episodes at a time as it holds records for
+        step = std::min<int64_t>(step, (int64_t)(ext_bytes / record_bytes<T>(P, 1)));
+        if (step < 1) return hipErrorOutOfMemory;
+    } else if (P > 1 && c.scratch.bytes < record_bytes<T>(P, step)) {
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        if ((e = c.scratch.alloc(record_bytes<T>(P, step))) != hipSuccess) return e;
+    }
+    for (int64_t b = begin; b < end; b += step) {
+        a.begin = b;
+        a.G = std::min(step, end - b);
+        if (P > 1) set_records<T>(a, ext_scratch ? ext_scratch : c.scratch.as<unsigned char>(), P, a.G);
+        if ((e = wave_launch<T>(a, st)) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <typename T>
 hipError_t count_t(const Stream &s, CandSet &c, const CountOptions &opt, int32_t *d_flags, hipStream_t st,
                    unsigned char *ext_scratch, size_t ext_bytes) {
     hipError_t e;
-    for (const Group &g : c.groups) {
+    candidate_costs(s, c);
+    for (size_t gi = 0; gi < c.groups.size(); ++gi) {
+        const Group &g = c.groups[gi];
         const int64_t G = g.end - g.begin;
         if (G <= 0) continue;
+        if (wave_group_ok(s, c, g, opt)) {
+            // adjacent groups in one launch (a wave takes an episode of any size)
+            int64_t end = g.end;
+            double cmax = g.cost_max, call = g.cost_sum;
+            while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end &&
+                   wave_group_ok(s, c, c.groups[gi + 1], opt)) {
+                const Group &h = c.groups[++gi];
+                end = h.end;
+                cmax = std::max(cmax, h.cost_max);
+                call += h.cost_sum;
+            }
+            if ((e = wave_count_t<T>(s, c, g.begin, end, cmax, call, opt, d_flags, st, ext_scratch, ext_bytes)) !=
+                hipSuccess)
+                return e;
+            continue;
+        }
         if (s.n == 0) {  // no events: every count is zero
             k_zero_counts<T><<<(unsigned)((G + 255) / 256), 256, 0, st>>>(
                 c.compact ? nullptr : c.orig.as<int32_t>() + g.begin, G, c.counts.as<int32_t>() + (c.compact ? g.begin : 0),
@@ -1070,12 +1197,25 @@ hipError_t count_t(const Stream &s, CandSet &c, const CountOptions &opt, int32_t
 // The events of the stream appended since set c was counted (B: the first
 // appended time): one lane per candidate resumes its machine (k_count_append).
 template <typename T>
-hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, int32_t *d_flags, hipStream_t st) {
+hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOptions &opt, int32_t *d_flags,
+                          hipStream_t st) {
     hipError_t e;
     if (c.compact || !c.tau.p) return hipErrorInvalidValue;
-    for (const Group &g : c.groups) {
+    for (size_t gi = 0; gi < c.groups.size(); ++gi) {
+        const Group &g = c.groups[gi];
         const int64_t G = g.end - g.begin;
         if (G <= 0) continue;
+        if (wave_group_ok(s, c, g, opt)) {
+            CountArgs<T> a = wave_args<T>(s, c, d_flags);
+            a.begin = g.begin;
+            int64_t end = g.end;
+            while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end &&
+                   wave_group_ok(s, c, c.groups[gi + 1], opt))
+                end = c.groups[++gi].end;
+            a.G = end - a.begin;
+            if ((e = wave_launch_append<T>(a, (T)B, st)) != hipSuccess) return e;
+            continue;
+        }
         AFn<T> fn = pick_append<T>(g.N);
         if (!fn) return hipErrorInvalidValue;
         const Layout<T> L = layout<T>(g.N, g.Q, kRecLanes, s.K, false, false, 0);
@@ -1109,9 +1249,10 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, int32_t *d_fla
 
 }  // namespace
 
-hipError_t launch_count_append(const Stream &s, CandSet &c, int64_t B, int32_t *d_flags, hipStream_t st) {
-    if (s.ts_kind == EPI_TS_I64) return count_append_t<int64_t>(s, c, B, d_flags, st);
-    return count_append_t<int32_t>(s, c, B, d_flags, st);
+hipError_t launch_count_append(const Stream &s, CandSet &c, int64_t B, const CountOptions &opt, int32_t *d_flags,
+                               hipStream_t st) {
+    if (s.ts_kind == EPI_TS_I64) return count_append_t<int64_t>(s, c, B, opt, d_flags, st);
+    return count_append_t<int32_t>(s, c, B, opt, d_flags, st);
 }
 
 hipError_t launch_count(const Stream &s, CandSet &c, const CountOptions &opt, int32_t *d_flags, hipStream_t st,
@@ -1215,6 +1356,7 @@ std::vector<int64_t> plan_key(const std::vector<BatchRef> &sets, const std::vect
         k.push_back(s.B);
         k.push_back(s.T);
         k.push_back(s.max_tile_span);
+        k.push_back(s.gap);
         P(s.tiled_ts.p);
         P(s.tile_loff.p);
         P(s.tile_t0.p);
@@ -1227,6 +1369,7 @@ std::vector<int64_t> plan_key(const std::vector<BatchRef> &sets, const std::vect
         P(c.lo.p);
         P(c.hi.p);
         P(c.orig.p);
+        P(c.cN.p);
         P(c.counts.p);
         P(c.tau.p);
         P(c.work.p);
@@ -1244,6 +1387,7 @@ std::vector<int64_t> plan_key(const std::vector<BatchRef> &sets, const std::vect
             k.push_back(g.begin);
             k.push_back(g.end);
             k.push_back(g.hspan);
+            k.push_back(g.lomax);
         }
     }
     return k;
@@ -1278,6 +1422,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     // class), adjacent ones of one size merged per EPI_OPT_RING_CLASSES
     // (fewer, larger groups: the cost order spans more episodes, so each
     // wave's lanes are closer in work; the rings take the group's largest)
+    for (auto &r : sets) candidate_costs(*r.s, *r.c);
     std::vector<std::vector<Group>> mg(sets.size());
     for (size_t si = 0; si < sets.size(); ++si) {
         auto bucket = [&](const Group &g) {
@@ -1295,6 +1440,9 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
                     b.Q = std::max(b.Q, g.Q);
                     b.C = std::max(b.C, g.C);
                     b.hspan = std::max(b.hspan, g.hspan);
+                    b.lomax = std::max(b.lomax, g.lomax);
+                    b.cost_sum += g.cost_sum;
+                    b.cost_max = std::max(b.cost_max, g.cost_max);
                     continue;
                 }
             }
@@ -1332,10 +1480,17 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     struct UnitH {
         int set, N, Q, W;
         int64_t begin, G, P, S;
-        bool filt, rel, lane, pk;
+        bool filt, rel, lane, pk, wave;
         int C;
+        double cost_sum, cost_max;
     };
     std::vector<UnitH> units;
+    int waves = 0;
+    if ((e = wave_resident(&waves)) != hipSuccess) return e;
+    double wave_cost = 0;  // of all groups the wave chains count
+    for (size_t si = 0; si < sets.size(); ++si)
+        for (const Group &g : mg[si])
+            if (wave_group_ok(*sets[si].s, *sets[si].c, g, opt)) wave_cost += g.cost_sum;
     std::vector<std::pair<size_t, Group>> empty_groups;  // groups of sets on streams without events
     for (size_t si = 0; si < sets.size(); ++si) {
         const Stream &s = *sets[si].s;
@@ -1354,6 +1509,14 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             u.begin = g.begin;
             u.G = G;
             u.filt = c.compact && c.pred_bits && c.succ_bits;
+            u.cost_sum = c.compact ? (double)G * (double)g.N * (double)s.n / std::max(1.0, (double)s.K) : g.cost_sum;
+            u.cost_max = g.cost_max;
+            u.wave = wave_group_ok(s, c, g, opt);
+            if (u.wave) {
+                u.P = wave_segments(s, u.cost_max, wave_cost, opt, waves, &u.S);
+                units.push_back(u);
+                continue;
+            }
             u.lane = lane_group_ok<T>(s, c, g, opt);
             u.pk = u.lane && lane_pk_ok(s.max_tile_span);
             u.rel = !u.lane && rel_ok<T>(s, g.hspan);
@@ -1372,9 +1535,11 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     // time type); the lane machines by (episode size, ring-entries class,
     // key form); each with one lane width and LDS layout for its units
     constexpr int kQClasses = 8;  // Q = 1, 2, 3, 4, 6, 8, 12, 16
-    constexpr int kRingClasses = (kMaxN + 1) * kQClasses * 2;
-    constexpr int kClasses = kRingClasses + (kMaxN + 1) * kCapClasses * 2;
+    static constexpr int kRingClasses = (kMaxN + 1) * kQClasses * 2;
+    static constexpr int kWaveClass = kRingClasses + (kMaxN + 1) * kCapClasses * 2;  // the wave chains: any size
+    constexpr int kClasses = kWaveClass + 1;
     auto cls_of = [](const UnitH &u) {
+        if (u.wave) return kWaveClass;
         if (u.lane) return kRingClasses + (u.N * kCapClasses + cap_class_index(u.C)) * 2 + (u.pk ? 1 : 0);
         static constexpr int kQ[kQClasses] = {1, 2, 3, 4, 6, 8, 12, 16};
         int q = 0;
@@ -1402,6 +1567,10 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
         if (clsN[cl] <= 0) continue;
         crank[cl] = (int)corder.size();
         corder.push_back(cl);
+        if (cl == kWaveClass) {
+            Wn[cl] = 64;  // slots per work item
+            continue;
+        }
         if (laneN[cl]) {
             Wn[cl] = lane_pick_width(lane_persistent_fn<T>(clsN[cl], pkN[cl], opt.worklog), clsC[cl], maxK[cl], maxT[cl],
                                      opt.lanes);
@@ -1461,6 +1630,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
         a.ctypes = c.types.as<int32_t>();
         a.clo = c.lo.as<T>();
         a.chi = c.hi.as<T>();
+        a.cN = c.cN.p ? c.cN.as<uint8_t>() : nullptr;
         a.t16 = c.compact ? c.t16.as<uint16_t>() : nullptr;
         a.iv = c.compact ? c.iv.as<uint8_t>() : nullptr;
         a.menu = c.compact ? c.menu.as<T>() : nullptr;
@@ -1485,7 +1655,9 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             set_records<T>(a, plan.rec.as<unsigned char>() + ro, u.P, u.G);
             ro += (record_bytes<T>(u.P, u.G) + 64) & ~size_t(15);
         }
-        if (laneN[cl]) {
+        if (u.wave) {
+            // static LDS
+        } else if (laneN[cl]) {
             const LaneLayout L = lane_layout(clsC[cl], Wn[cl], maxK[cl], maxT[cl]);
             a.off_qse = L.off_ring;
             a.off_tbuf = L.off_tbuf;
@@ -1508,28 +1680,22 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     // the branch balance: each class's work as the summed event counts of
     // its episodes' types (the events its lanes visit), from host copies
     std::vector<double> ccost(kClasses, 0.0);
-    for (size_t ui = 0; ui < units.size(); ++ui) {
-        const UnitH &u = units[ui];
-        const Stream &s = *sets[u.set].s;
-        const CandSet &c = *sets[u.set].c;
-        double w = 0;
-        if (!c.compact && (int64_t)c.h_N.size() == c.m && (int64_t)s.h_off.size() == (int64_t)s.K + 1) {
-            // slots -> submission indices are the set's grouping order; the
-            // unit's slots hold the candidates of one launch group, whose
-            // work the host knows per candidate
-            for (int64_t i = 0; i < u.G; ++i) {
-                const int64_t o = c.h_order.empty() ? u.begin + i : c.h_order[u.begin + i];
-                const int32_t *ty = c.h_types.data() + o * kMaxN;
-                for (int j = 0; j < c.h_N[o]; ++j) w += (double)(s.h_off[ty[j] + 1] - s.h_off[ty[j]]);
-            }
-        } else {
-            w = (double)u.G * (double)u.N * (double)s.n / std::max(1.0, (double)s.K);
-        }
-        ccost[cls_of(u)] += w;
+    bool wave_segmented = false;
+    for (const UnitH &u : units) {
+        ccost[cls_of(u)] += u.cost_sum;
+        wave_segmented = wave_segmented || (u.wave && u.P > 1);
     }
+    // the wave chains' units costliest episodes first (round robin keeps this
+    // order): no long item starts last
+    std::vector<size_t> uorder(units.size());
+    std::iota(uorder.begin(), uorder.end(), size_t(0));
+    std::vector<double> ukey(units.size(), 0.0);
+    for (size_t ui = 0; ui < units.size(); ++ui)
+        if (units[ui].wave) ukey[ui] = units[ui].cost_sum / ((double)units[ui].G * (double)units[ui].P);
+    std::stable_sort(uorder.begin(), uorder.end(), [&](size_t x, size_t y) { return ukey[x] > ukey[y]; });
     for (int cl = 0; cl < kClasses; ++cl) {
         ioff[cl] = (int64_t)tmpl.size();
-        for (size_t ui = 0; ui < units.size(); ++ui) {
+        for (size_t ui : uorder) {
             const UnitH &u = units[ui];
             if (cls_of(u) != cl) continue;
             const int64_t nb = (u.G + Wn[cl] - 1) / Wn[cl];
@@ -1634,7 +1800,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     // other branches' last kernels instead
     auto reconcile_class = [&](int cl, hipStream_t bst) -> hipError_t {
         for (size_t ui = 0; ui < units.size(); ++ui) {
-            if (units[ui].P <= 1 || cls_of(units[ui]) != cl) continue;
+            if (units[ui].P <= 1 || units[ui].wave || cls_of(units[ui]) != cl) continue;
             const int N = units[ui].N;
             const hipError_t x = launch_reconcile<T>(ua[ui], N, layout<T>(N, clsQ[cl], kRecLanes, maxK[cl], false, false, 0), bst);
             if (x != hipSuccess) return x;
@@ -1651,6 +1817,13 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
         const int64_t ncl = ioff[cl + 1] - ioff[cl];
         if (ncl <= 0) continue;
         int per = 0;
+        if (cl == kWaveClass) {
+            const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ncl * 64, waves));
+            e = wave_launch_persistent<T>((unsigned)grid, cache.br[bi], plan.units.as<CountArgs<T>>(),
+                                          plan.items.as<WorkItem>() + ioff[cl], ncl,
+                                          plan.queue.as<unsigned long long>() + cl, wave_segmented);
+            continue;
+        }
         if (laneN[cl]) {
             const void *lfn = lane_persistent_fn<T>(N, pkN[cl], opt.worklog);
             const LaneLayout L = lane_layout(clsC[cl], Wn[cl], maxK[cl], maxT[cl]);

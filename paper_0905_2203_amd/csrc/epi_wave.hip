@@ -1,0 +1,632 @@
+// Wave chains: the count of one candidate episode over a range of time by one
+// 64-lane wave, parallel over the events of each node's type.
+//
+// For episode alpha and node k, the chain events are the events x of type
+// alpha[k] that end an occurrence of alpha[1..k]; L_k(x) is the latest start of
+// such an occurrence (L_1(x) = t_x).  Along a node's chain events L_k is
+// non-decreasing, so the best predecessor of x is the latest chain event y of
+// node k-1 with t_y < t_x - lo (if t_x <= t_y + hi): one binary search per
+// event (Sec. IV-C), and only the chain events go on to the next node
+// (Sec. IV-D/E).  The count is the greedy of Alg. 1 over the last node's
+// (L_N(x), t_x): the next kept event is the first with L > the last kept one's
+// time.  These are the completions of the serial state machine (Sec. III-A with
+// starts admitted only strictly after the last completion), so segments, their
+// records and the reconciliation are those of epi_tiled.hip.
+//
+// The wave walks time in windows.  A window starts at the earliest next event
+// of the episode's types and ends where some type would have more than kCap
+// events in it, so every node's events fit R registers a lane.  Node by node,
+// the lanes read the node's events (coalesced, from the per-type index), search
+// the previous node's chain list in LDS (R independent searches a lane in
+// lockstep), and append the hits in time order.  From one window to the next a
+// list hands on the entries a later event can still reach: those less than lo
+// before the window's end, and the latest one before them (any other is
+// dominated); that is at most 64 when the type has no 64 events within lo
+// (wave_ok, a property of the stream that the host checks).
+//
+// What bounds it: instruction issue and LDS latency.  A state machine lane
+// takes its events one at a time (135 VALU instructions over the loop's paths,
+// nearly all issued by a diverged wave, 64 events a pass); here a wave spends
+// about 50 VALU instructions on 64 events of a node, whatever the events do,
+// and needs no tile staging, rings or rebasing.  80k episodes of 2-8 nodes over
+// 20M events of 256 types: 199 -> 76 ms; 5k episodes of 1-6 nodes over 1.5M
+// events: 24.9 -> 0.88 ms; 992 pairs over 10k events: 2.8 ms -> 63 us (a lane
+// each had left the chip idle).
+// Times are the stream's own; an entry's age and its distance to a window's end
+// are 32-bit (an episode spans less than 2^29).
+#include <algorithm>
+#include <type_traits>
+
+#include "epi_count.h"
+
+namespace epi {
+
+namespace {
+
+constexpr int kW = 64;
+constexpr int kR = kWaveChunks;
+constexpr int kCap = kR * kW;
+constexpr int kList = kCap + kW;       // handed-on entries + a window's events
+
+// Chain lists: an entry's time and its age, the time since the latest start of
+// an occurrence ending there.  Entries handed on keep their time as the distance
+// to the window's end (both below 2^29).
+template <typename T>
+struct WaveLds {
+    T t[2][kList];
+    int32_t age[2][kList];
+    int32_t cd[kMaxN - 1][kW];
+    int32_t ca[kMaxN - 1][kW];
+};
+
+// One candidate's episode as the wave holds it: lane k keeps node k's next
+// index position and end, and interval k (between nodes k and k+1).
+template <typename T>
+struct WaveEp {
+    int N;
+    int32_t cur, end;
+    int32_t lo, hi;
+    T H;  // longest span
+};
+
+__device__ __forceinline__ int rdlane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ int bcast(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t bcast(int64_t v) {
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)b << 32) | a);
+}
+__device__ __forceinline__ int64_t rdlane(int64_t v, int l) {
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
+    return (int64_t)(((uint64_t)b << 32) | a);
+}
+__device__ __forceinline__ int below(uint64_t m) {  // set bits of m below this lane
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// LDS operations of a wave complete in order; this only keeps the compiler
+// from moving one lane's read before another lane's write.
+__device__ __forceinline__ void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// All lanes meet here after one lane's stores: without it the compiler may send
+// the other lanes into a loop's next round on their own (it knows that they
+// skip every lane-0 branch), where they would read a queue position that only
+// lane 0 fetches.
+__device__ __forceinline__ void rejoin() { __builtin_amdgcn_wave_barrier(); }
+
+template <typename T>
+__device__ __forceinline__ WaveEp<T> load_episode(const CountArgs<T> &a, int64_t slot, int lane) {
+    WaveEp<T> ep;
+    ep.N = bcast((int)a.cN[slot]);
+    ep.cur = ep.end = 0;
+    ep.lo = ep.hi = 0;
+    if (lane < ep.N) {
+        const int32_t ty = a.ctypes[(int64_t)lane * a.m + slot];
+        ep.cur = a.type_off[ty];
+        ep.end = a.type_off[ty + 1];
+    }
+    if (lane + 1 < ep.N) {
+        ep.lo = (int32_t)a.clo[(int64_t)lane * a.m + slot];
+        ep.hi = (int32_t)a.chi[(int64_t)lane * a.m + slot];
+    }
+    int h = ep.hi;  // the span is below 2^29
+    for (int d = 1; d < 8; d <<= 1) h += __shfl_xor(h, d, 8);
+    ep.H = (T)bcast(h);
+    return ep;
+}
+
+// Move every node's position to its first event after time x: eight lanes a
+// node, 9-ary search (six dependent loads for 200k events instead of eighteen).
+template <typename T>
+__device__ __forceinline__ void seek(const T *__restrict__ ts, WaveEp<T> &ep, T x, int lane) {
+    const int node = lane >> 3, sub = lane & 7;
+    int32_t lo = __shfl(ep.cur, node, kW), hi = __shfl(ep.end, node, kW);
+    while (__ballot(lo < hi)) {
+        const int32_t len = hi - lo;
+        const int32_t at = lo + (int32_t)(((int64_t)len * (sub + 1)) / 9);  // < hi when len > 0
+        const bool le = len > 0 && ts[at] <= x;
+        const int c = __popc((uint32_t)(__ballot(le) >> (node * 8)) & 0xffu);  // pivots at or before x
+        const int32_t nlo = c > 0 ? lo + (int32_t)(((int64_t)len * c) / 9) + 1 : lo;
+        const int32_t nhi = c < 8 ? lo + (int32_t)(((int64_t)len * (c + 1)) / 9) : hi;
+        if (len > 0) {
+            lo = nlo;
+            hi = nhi < nlo ? nlo : nhi;
+        }
+    }
+    const int32_t v = __shfl(lo, (lane & 7) * 8, kW);
+    if (lane < ep.N) ep.cur = v;
+}
+
+// Node k's next kCap events into x (the index is padded by kCap entries);
+// returns how many its type has left.
+template <typename T>
+__device__ __forceinline__ int load_events(const T *__restrict__ ts, const WaveEp<T> &ep, int k, int lane, T (&x)[kR]) {
+    const int c = rdlane(ep.cur, k);
+    const T *p = ts + c;
+#pragma unroll
+    for (int r = 0; r < kR; ++r) x[r] = p[r * kW + lane];
+    return rdlane(ep.end, k) - c;
+}
+
+// What a run hands back, and what it is checked against.
+template <typename T>
+struct WaveOut {
+    int32_t cnt = 0;   // completions at or after Bp
+    T last;            // the last of them (unset when none)
+    bool synced = false;
+};
+// The record of a segment's speculative run that a re-run may meet.
+template <typename T>
+struct WaveRec {
+    int32_t c = 0;       // its completions
+    T first[kRecFirst];  // the first of them
+    T sync_t;            // Bp + H
+};
+
+// Count the completions of the episode over the events from its positions on
+// and before Ep, given the last completion e0 (type minimum: none); every event
+// from the positions on is after e0.  SYNC: a re-run that stops where it meets
+// the speculative record (see rerun_segment in epi_tiled.hip); out.cnt then
+// includes the record's remaining completions.
+template <typename T, bool SYNC>
+__device__ __forceinline__ void wave_run(const T *__restrict__ ts, WaveLds<T> &w, WaveEp<T> &ep, T e0, T Bp, T Ep,
+                                         int lane, T *__restrict__ first_out, int64_t first_stride,
+                                         const WaveRec<T> *rec, WaveOut<T> &out) {
+    using U = std::make_unsigned_t<T>;  // differences of ordered times: exact in it
+    constexpr T kEnd = TsLimits<T>::hi();
+    constexpr T kMin = TsLimits<T>::lo();
+    const int N = ep.N;
+    T tau = bcast(e0);
+    T te = 0;    // the window's end
+    int nc = 0;  // lane k: entries node k's list handed on
+    int32_t cnt = 0;
+    while (true) {
+        T h = kEnd, f = kEnd;
+        if (lane < N && ep.cur < ep.end) {
+            h = ts[ep.cur];
+            const int64_t fi = (int64_t)ep.cur + kCap;
+            if (fi < (int64_t)ep.end) f = ts[fi];
+        }
+#pragma unroll
+        for (int d = 1; d < 8; d <<= 1) {
+            const T oh = __shfl_xor(h, d, 8), of = __shfl_xor(f, d, 8);
+            h = oh < h ? oh : h;
+            f = of < f ? of : f;
+        }
+        h = bcast(h);
+        f = bcast(f);
+        if (h >= Ep) break;
+        const T tp = te;  // what was handed on is relative to it
+        te = f < Ep ? f : Ep;
+        const bool all = h >= Bp;
+        const int32_t cnt0 = cnt;
+        int n = 0;  // entries of the previous node's list
+        T x[kR];
+        int left = load_events(ts, ep, 0, lane, x);
+        for (int k = 0; k < N; ++k) {
+            T v[kR];
+            int g[kR];  // ages
+            uint64_t ok[kR];
+            int nx = 0;
+#pragma unroll
+            for (int r = 0; r < kR; ++r) {
+                v[r] = x[r];
+                ok[r] = __ballot(v[r] < te && lane < left - r * kW);
+                nx += __popcll(ok[r]);
+            }
+            // the next node's events, ahead of this node's work
+            if (k + 1 < N) left = load_events(ts, ep, k + 1, lane, x);
+            if (lane == k) ep.cur += nx;
+            const int pb = (k & 1) ^ 1, qb = k & 1;  // previous list, this node's list
+            if (k == 0) {
+#pragma unroll
+                for (int r = 0; r < kR; ++r) g[r] = 0;
+            } else if (n == 0 || nx == 0) {
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    g[r] = 0;
+                    ok[r] = 0;
+                }
+            } else {
+                const int lo = rdlane(ep.lo, k - 1), hi = rdlane(ep.hi, k - 1);
+                T q[kR];
+                int p[kR];
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    q[r] = (T)((U)v[r] - (U)lo);
+                    p[r] = 0;
+                }
+                // entries before q: halving search, one length for all
+                int len = n;
+                while (len > 1) {
+                    const int half = len >> 1;
+#pragma unroll
+                    for (int r = 0; r < kR; ++r) {
+                        const int m = p[r] + half;
+                        p[r] = w.t[pb][m - 1] < q[r] ? m : p[r];
+                    }
+                    len -= half;
+                }
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    // one entry is left to test: the latest before q is p's or the one before it
+                    const T y0 = w.t[pb][p[r]];
+                    const int i1 = p[r] > 0 ? p[r] - 1 : 0;
+                    const T y1 = w.t[pb][i1];
+                    const bool in = y0 < q[r];
+                    const T y = in ? y0 : y1;
+                    const U d = (U)v[r] - (U)y;
+                    g[r] = w.age[pb][in ? p[r] : i1] + (int)d;
+                    ok[r] &= __ballot(y < q[r] && d <= (U)hi);
+                }
+            }
+            if (k + 1 < N) {
+                // this node's list: what it handed on, then the hits in order
+                n = rdlane(nc, k);
+                if (lane < n) {
+                    w.t[qb][lane] = tp - (T)w.cd[k][lane];
+                    w.age[qb][lane] = w.ca[k][lane];
+                }
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    if ((ok[r] >> lane) & 1) {
+                        const int o = n + below(ok[r]);
+                        w.t[qb][o] = v[r];
+                        w.age[qb][o] = g[r];
+                    }
+                    n += __popcll(ok[r]);
+                }
+                lds_order();
+                // what later windows can reach
+                const int lo = rdlane(ep.lo, k), hi = rdlane(ep.hi, k);
+                const int i = n - kW + lane;
+                U d = ~U(0);  // from the entry to the window's end
+                int ag = 0;
+                if (i >= 0) {
+                    d = (U)te - (U)w.t[qb][i];
+                    ag = w.age[qb][i];
+                }
+                const int fut = __popcll(__ballot(d <= (U)lo));
+                const int live = __popcll(__ballot(d <= (U)hi));
+                const int keep = fut + 1 < live ? fut + 1 : live;
+                if (lane >= kW - keep) {
+                    w.cd[k][lane - (kW - keep)] = (int)d;
+                    w.ca[k][lane - (kW - keep)] = ag;
+                }
+                if (lane == k) nc = keep;
+                lds_order();
+            } else {
+                // the greedy of Alg. 1
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    const T L = ((ok[r] >> lane) & 1) ? (T)((U)v[r] - (U)g[r]) : kMin;
+                    uint64_t m = __ballot(L > tau);
+                    while (m) {
+                        tau = rdlane(v[r], __builtin_ctzll(m));
+                        if (all || tau >= Bp) {
+                            if constexpr (SYNC) {
+                                int hit = -1;
+#pragma unroll
+                                for (int j = 0; j < kRecFirst; ++j)
+                                    if (j < rec->c && rec->first[j] == tau) hit = j;
+                                if (hit >= 0) {
+                                    out.cnt = cnt + 1 + (rec->c - hit - 1);
+                                    out.synced = true;
+                                    return;
+                                }
+                            } else if (first_out && cnt < kRecFirst) {
+                                if (lane == 0) first_out[cnt * first_stride] = tau;
+                            }
+                            ++cnt;
+                        }
+                        m = __ballot(L > tau);
+                    }
+                }
+            }
+        }
+        if (cnt != cnt0) out.last = tau;
+        if constexpr (SYNC) {
+            // no completion of either run up to here, and no partial
+            // occurrence from before Bp left: the states agree
+            if (cnt == 0 && te >= rec->sync_t && (rec->c == 0 || rec->first[0] >= te)) {
+                out.cnt = rec->c;
+                out.synced = true;
+                return;
+            }
+        }
+    }
+    out.cnt = cnt;
+}
+
+template <typename T>
+__device__ __forceinline__ int64_t slot_of(const CountArgs<T> &a, int64_t s) {
+    return a.perm ? (int64_t)bcast(a.perm[a.begin + s]) : a.begin + s;
+}
+
+// Segment p's first and end time.
+template <typename T>
+__device__ __forceinline__ void seg_bounds(const CountArgs<T> &a, int p, T &Bp, T &Ep) {
+    const int64_t b0 = (int64_t)p * a.S;
+    const int64_t b1 = b0 + a.S < a.B ? b0 + a.S : a.B;
+    Bp = bcast(p == 0 ? TsLimits<T>::lo() : a.tile_t0[b0]);
+    Ep = bcast(p == a.P - 1 ? TsLimits<T>::hi() : a.tile_t0[b1]);
+}
+
+// Candidate s of unit a over segment p: the whole count (P = 1) or the
+// segment's speculative record.
+template <typename T>
+__device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int p, WaveLds<T> &w, int lane) {
+    constexpr T kMin = TsLimits<T>::lo();
+    const int64_t slot = slot_of(a, s);
+    WaveEp<T> ep = load_episode(a, slot, lane);
+    T Bp, Ep;
+    seg_bounds(a, p, Bp, Ep);
+    T e0 = kMin;
+    if (p > 0) {
+        e0 = (T)(Bp - ep.H - 1);
+        seek(a.ts_by_type, ep, e0, lane);
+    }
+    WaveOut<T> out;
+    out.last = kMin;
+    const int64_t ro = (int64_t)p * a.G + s;
+    T *first = a.P > 1 ? a.rec_first + (int64_t)p * kRecFirst * a.G + s : nullptr;
+    wave_run<T, false>(a.ts_by_type, w, ep, e0, Bp, Ep, lane, first, a.G, nullptr, out);
+    if (lane == 0) {
+        if (a.P == 1) {
+            const int64_t o = a.orig[slot];
+            a.counts[o] = out.cnt;
+            if (a.tau) a.tau[o] = out.last;
+        } else {
+            a.rec_cnt[ro] = out.cnt;
+            a.rec_last[ro] = out.last;
+        }
+    }
+    rejoin();
+}
+
+// Segment p's completions and last completion given the last completion tau
+// before it (see rerun_segment in epi_tiled.hip).
+template <typename T>
+__device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds<T> &w,
+                                                    int lane, const WaveEp<T> &ep0) {
+    T Bp, Ep;
+    seg_bounds(a, p, Bp, Ep);
+    const int64_t ro = (int64_t)p * a.G + s;
+    const int32_t c = bcast(a.rec_cnt[ro]);
+    const T last = bcast(a.rec_last[ro]);
+    if (p == 0 || tau < (T)(Bp - ep0.H)) {
+        if (c > 0) tau = last;
+        return c;
+    }
+    WaveRec<T> rec;
+    rec.c = c;
+    rec.sync_t = (T)(Bp + ep0.H);
+#pragma unroll
+    for (int j = 0; j < kRecFirst; ++j)
+        rec.first[j] = j < c ? bcast(a.rec_first[((int64_t)p * kRecFirst + j) * a.G + s]) : TsLimits<T>::hi();
+    WaveEp<T> ep = ep0;
+    seek(a.ts_by_type, ep, tau, lane);
+    WaveOut<T> out;
+    out.last = tau;
+    wave_run<T, true>(a.ts_by_type, w, ep, tau, TsLimits<T>::lo(), Ep, lane, nullptr, 0, &rec, out);
+    if (out.synced) {
+        if (c > 0) tau = last;
+    } else {
+        tau = out.last;
+    }
+    return out.cnt;
+}
+
+// Pre-pass of candidate s, segment p >= 1: its true completions if the earlier
+// records' last completion is the true one.
+template <typename T>
+__device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds<T> &w, int lane) {
+    T tau = TsLimits<T>::lo();
+    for (int q = p - 1; q >= 0; --q) {
+        if (bcast(a.rec_cnt[(int64_t)q * a.G + s]) > 0) {
+            tau = bcast(a.rec_last[(int64_t)q * a.G + s]);
+            break;
+        }
+    }
+    const WaveEp<T> ep = load_episode(a, slot_of(a, s), lane);
+    const T tau0 = tau;
+    const int32_t c = wave_fix_segment(a, s, p, tau, w, lane, ep);
+    if (lane == 0) {
+        const int64_t o = (int64_t)p * a.G + s;
+        a.pre_tau[o] = tau0;
+        a.pre_cnt[o] = c;
+        a.pre_last[o] = tau;
+    }
+    rejoin();
+}
+
+// The count of candidate s from its segments: the pre-pass's results where the
+// last completion they assumed is the true one (all lanes test 64 segments at
+// once), a re-run elsewhere.
+template <typename T>
+__device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds<T> &w, int lane) {
+    T tau = TsLimits<T>::lo();
+    int32_t total = bcast(a.rec_cnt[s]);
+    if (total > 0) tau = bcast(a.rec_last[s]);
+    const int64_t slot = slot_of(a, s);
+    int p = 1;
+    while (p < a.P) {
+        const int i = p + lane;
+        const int64_t o = (int64_t)i * a.G + s;
+        const bool in = i < a.P;
+        int32_t c = 0;
+        T assumed = 0, end = 0;
+        if (in) {
+            c = a.pre_cnt[o];
+            assumed = a.pre_tau[o];
+            end = a.pre_last[o];
+        }
+        // the true last completion before segment i, if all before it held
+        const T prev = __shfl_up(end, 1, kW);
+        const uint64_t bad = __ballot(in && assumed != (lane == 0 ? tau : prev));
+        const int good = bad ? __builtin_ctzll(bad) : (a.P - p < kW ? a.P - p : kW);
+        int32_t v = lane < good ? c : 0;
+        for (int d = 1; d < kW; d <<= 1) v += __shfl_xor(v, d, kW);
+        total += bcast(v);
+        if (good > 0) tau = bcast((T)__shfl(end, good - 1, kW));
+        p += good;
+        if (bad) {
+            const WaveEp<T> ep = load_episode(a, slot, lane);
+            total += wave_fix_segment(a, s, p, tau, w, lane, ep);
+            ++p;
+        }
+    }
+    if (lane == 0) {
+        const int64_t o = a.orig[slot];
+        a.counts[o] = total;
+        if (a.tau) a.tau[o] = tau;
+    }
+    rejoin();
+}
+
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_count(CountArgs<T> a) {
+    __shared__ WaveLds<T> w;
+    wave_item<T>(a, blockIdx.x, blockIdx.y, w, threadIdx.x);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_pre(CountArgs<T> a) {
+    __shared__ WaveLds<T> w;
+    wave_pre<T>(a, blockIdx.x, blockIdx.y + 1, w, threadIdx.x);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_sum(CountArgs<T> a) {
+    __shared__ WaveLds<T> w;
+    wave_sum<T>(a, blockIdx.x, w, threadIdx.x);
+}
+
+// Appended events (see k_count_append in epi_tiled.hip): the run resumes right
+// after max(tau, B - H - 1); every completion it finds is at or after B.
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_append(CountArgs<T> a, T B) {
+    __shared__ WaveLds<T> w;
+    const int lane = threadIdx.x;
+    const int64_t s = blockIdx.x;
+    const int64_t slot = slot_of(a, s);
+    WaveEp<T> ep = load_episode(a, slot, lane);
+    const int64_t o = bcast(a.orig[slot]);
+    const T tau = bcast(a.tau[o]);
+    const T from = tau > (T)(B - ep.H - 1) ? tau : (T)(B - ep.H - 1);
+    seek(a.ts_by_type, ep, from, lane);
+    WaveOut<T> out;
+    out.last = tau;
+    wave_run<T, false>(a.ts_by_type, w, ep, from, TsLimits<T>::lo(), TsLimits<T>::hi(), lane, nullptr, 0, nullptr, out);
+    if (lane == 0) {
+        a.counts[o] += out.cnt;
+        a.tau[o] = out.last;
+    }
+}
+
+// Batched form.  A work item is (unit, block of 64 slots, segment); a wave
+// takes one slot of it at a time from the queue.
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__restrict__ units,
+                                                        const WorkItem *__restrict__ items, int64_t n_items,
+                                                        unsigned long long *__restrict__ queue) {
+    __shared__ WaveLds<T> w;
+    const int lane = threadIdx.x;
+    while (true) {
+        rejoin();
+        int64_t q = 0;
+        if (lane == 0) q = (int64_t)atomicAdd(queue, 1ull);
+        rejoin();
+        q = bcast(q);
+        // unsigned: any counter value beyond the items ends the loop
+        if ((uint64_t)q >= (uint64_t)n_items * kW) break;
+        const WorkItem it = items[q / kW];
+        const CountArgs<T> &a = units[it.unit];
+        const int64_t s = it.blk * kW + (q % kW);
+        if (s < a.G) wave_item<T>(a, s, it.p, w, lane);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_pre_all(const CountArgs<T> *__restrict__ units,
+                                                     const WorkItem *__restrict__ items, int64_t n_items) {
+    __shared__ WaveLds<T> w;
+    for (int64_t q = blockIdx.x; q < n_items * kW; q += gridDim.x) {
+        const WorkItem it = items[q / kW];
+        const CountArgs<T> &a = units[it.unit];
+        const int64_t s = it.blk * kW + (q % kW);
+        if (s < a.G && it.p > 0) wave_pre<T>(a, s, it.p, w, threadIdx.x);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kW) void k_wave_sum_all(const CountArgs<T> *__restrict__ units,
+                                                     const WorkItem *__restrict__ items, int64_t n_items) {
+    __shared__ WaveLds<T> w;
+    for (int64_t q = blockIdx.x; q < n_items * kW; q += gridDim.x) {
+        const WorkItem it = items[q / kW];
+        const CountArgs<T> &a = units[it.unit];
+        const int64_t s = it.blk * kW + (q % kW);
+        if (s < a.G && it.p == 0 && a.P > 1) wave_sum<T>(a, s, w, threadIdx.x);
+    }
+}
+
+unsigned grid_of(int64_t n) { return (unsigned)std::min<int64_t>(std::max<int64_t>(n, 1), int64_t(1) << 16); }
+
+}  // namespace
+
+int wave_waves_per_cu() {
+    int per = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wave_persistent<int64_t>, kW, 0) != hipSuccess || per < 1) {
+        (void)hipGetLastError();
+        per = 8;
+    }
+    return per;
+}
+
+template <typename T>
+hipError_t wave_launch(const CountArgs<T> &a, hipStream_t st) {
+    if (a.G <= 0) return hipSuccess;
+    if (a.P < 1 || a.P > 65535 || !a.cN || !a.orig || a.G > INT32_MAX) return hipErrorInvalidValue;
+    k_wave_count<T><<<dim3((unsigned)a.G, (unsigned)a.P), kW, 0, st>>>(a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.P == 1) return e;
+    k_wave_pre<T><<<dim3((unsigned)a.G, (unsigned)(a.P - 1)), kW, 0, st>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    k_wave_sum<T><<<(unsigned)a.G, kW, 0, st>>>(a);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t wave_launch_append(const CountArgs<T> &a, T B, hipStream_t st) {
+    if (a.G <= 0) return hipSuccess;
+    if (!a.cN || !a.orig || !a.tau || a.G > INT32_MAX) return hipErrorInvalidValue;
+    k_wave_append<T><<<(unsigned)a.G, kW, 0, st>>>(a, B);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WorkItem *items,
+                                  int64_t n_items, unsigned long long *queue, bool segmented) {
+    k_wave_persistent<T><<<grid, kW, 0, st>>>(units, items, n_items, queue);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !segmented) return e;
+    k_wave_pre_all<T><<<grid_of(n_items * kW), kW, 0, st>>>(units, items, n_items);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    k_wave_sum_all<T><<<grid_of(n_items * kW), kW, 0, st>>>(units, items, n_items);
+    return hipGetLastError();
+}
+
+template hipError_t wave_launch<int32_t>(const CountArgs<int32_t> &, hipStream_t);
+template hipError_t wave_launch<int64_t>(const CountArgs<int64_t> &, hipStream_t);
+template hipError_t wave_launch_append<int32_t>(const CountArgs<int32_t> &, int32_t, hipStream_t);
+template hipError_t wave_launch_append<int64_t>(const CountArgs<int64_t> &, int64_t, hipStream_t);
+template hipError_t wave_launch_persistent<int32_t>(unsigned, hipStream_t, const CountArgs<int32_t> *, const WorkItem *,
+                                                    int64_t, unsigned long long *, bool);
+template hipError_t wave_launch_persistent<int64_t>(unsigned, hipStream_t, const CountArgs<int64_t> *, const WorkItem *,
+                                                    int64_t, unsigned long long *, bool);
+
+}  // namespace epi
