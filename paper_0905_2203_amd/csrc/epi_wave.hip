@@ -27,13 +27,12 @@
 // What bounds it: instruction issue and LDS latency.  A state machine lane
 // takes its events one at a time (135 VALU instructions over the loop's paths,
 // nearly all issued by a diverged wave, 64 events a pass); here a wave spends
-// about 50 VALU instructions on 64 events of a node, whatever the events do,
-// and needs no tile staging, rings or rebasing.  80k episodes of 2-8 nodes over
-// 20M events of 256 types: 199 -> 76 ms; 5k episodes of 1-6 nodes over 1.5M
-// events: 24.9 -> 0.88 ms; 992 pairs over 10k events: 2.8 ms -> 63 us (a lane
-// each had left the chip idle).
-// Times are the stream's own; an entry's age and its distance to a window's end
-// are 32-bit (an episode spans less than 2^29).
+// about 46 VALU and 36 SALU instructions on 64 events of a node, whatever the
+// events do, and needs no tile staging, rings or rebasing.  80k episodes of 2-8
+// nodes over 20M events of 256 types: 199 -> 52 ms (VALU issue 0.71; the index
+// comes at 5 TB/s from beyond L2: cutting time so that a stretch stays in L2 gained
+// nothing); 5k episodes of 1-6 nodes over 1.5M events: 24.5 -> 0.54 ms; 992 pairs
+// over 10k events: 2.6 ms -> 52 us (a lane each had left the chip idle).
 #include <algorithm>
 #include <type_traits>
 
@@ -46,17 +45,46 @@ namespace {
 constexpr int kW = 64;
 constexpr int kR = kWaveChunks;
 constexpr int kCap = kR * kW;
-constexpr int kList = kCap + kW;       // handed-on entries + a window's events
+constexpr int kRunMin = 6;            // hits of 64 from which the greedy takes runs at a time
+constexpr int kList = 1 + kCap + kW;   // a sentinel, handed-on entries, a window's events
 
-// Chain lists: an entry's time and its age, the time since the latest start of
-// an occurrence ending there.  Entries handed on keep their time as the distance
-// to the window's end (both below 2^29).
+// Chain lists.  An entry is one 64-bit word, a time above the latest start of an
+// occurrence ending there, so that one LDS access moves both.  int32 times: the
+// two times themselves.  int64 times: the time from the window's first event
+// (signed, 35 bits) above the start's low 29 bits (it is less than 2^29 before),
+// so that one compare orders entries by time; 8 bytes an entry instead of 12 let
+// a CU hold 18 waves instead of 14.  Entry 0 is a sentinel before every time: a
+// search always ends on an entry.
 template <typename T>
+struct Entry {
+    static constexpr bool kRel = sizeof(T) == 8;  // times from the window's first event
+    static constexpr int kLow = kRel ? 29 : 32;
+    static constexpr uint64_t kSpan = (uint64_t(1) << (63 - kLow)) - 1;  // longest window
+    using Key = std::conditional_t<kRel, int64_t, int32_t>;   // what a search compares
+    using UKey = std::make_unsigned_t<Key>;
+    static constexpr int kKeyAt = kRel ? 0 : 4;               // byte of it in the entry
+    static constexpr int kUp = kRel ? kLow : 0;               // a time's shift in a key
+    static __device__ __forceinline__ Key key(T v, T h) {
+        if constexpr (kRel) return (Key)(((uint64_t)v - (uint64_t)h) << kLow);
+        else return v;
+    }
+    static __device__ __forceinline__ UKey len(int t) { return (UKey)(uint32_t)t << kUp; }
+    static __device__ __forceinline__ int64_t make(Key k, uint32_t start) {
+        if constexpr (kRel) return k | (int64_t)start;
+        else return (int64_t)(((uint64_t)(uint32_t)k << 32) | start);
+    }
+    static __device__ __forceinline__ UKey key_of(int64_t e) {  // (with the start bits below it)
+        return kRel ? (UKey)e : (UKey)((uint64_t)e >> 32);
+    }
+    static __device__ __forceinline__ uint32_t start_bits(T v) { return (uint32_t)v & (kRel ? (1u << 29) - 1 : ~0u); }
+    static __device__ __forceinline__ T start(T v, uint32_t bits) {
+        if constexpr (kRel) return (T)((uint64_t)v - (uint64_t)(((uint32_t)v - bits) & ((1u << 29) - 1)));
+        else return (T)bits;
+    }
+};
 struct WaveLds {
-    T t[2][kList];
-    int32_t age[2][kList];
-    int32_t cd[kMaxN - 1][kW];
-    int32_t ca[kMaxN - 1][kW];
+    int64_t e[2][kList];
+    int64_t c[kMaxN - 1][kW];  // handed on per node
 };
 
 // One candidate's episode as the wave holds it: lane k keeps node k's next
@@ -81,9 +109,19 @@ __device__ __forceinline__ int64_t rdlane(int64_t v, int l) {
     const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), l);
     return (int64_t)(((uint64_t)b << 32) | a);
 }
-__device__ __forceinline__ int below(uint64_t m) {  // set bits of m below this lane
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+__device__ __forceinline__ int below(uint64_t m, int base) {  // base + set bits of m below this lane
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
 }
+// The stream's times as global memory: a pointer read from a unit in memory
+// would else make flat loads, which also count as LDS operations, so that every
+// wait for a search would wait for the next node's events too.
+template <typename T>
+using Times = const __attribute__((address_space(1))) T *;
+// the first n lanes
+__device__ __forceinline__ uint64_t lanes_below(int n) {
+    return n >= kW ? ~uint64_t(0) : n <= 0 ? 0 : (uint64_t(1) << n) - 1;
+}
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 // LDS operations of a wave complete in order; this only keeps the compiler
 // from moving one lane's read before another lane's write.
 __device__ __forceinline__ void lds_order() {
@@ -121,7 +159,7 @@ __device__ __forceinline__ WaveEp<T> load_episode(const CountArgs<T> &a, int64_t
 // Move every node's position to its first event after time x: eight lanes a
 // node, 9-ary search (six dependent loads for 200k events instead of eighteen).
 template <typename T>
-__device__ __forceinline__ void seek(const T *__restrict__ ts, WaveEp<T> &ep, T x, int lane) {
+__device__ __forceinline__ void seek(Times<T> ts, WaveEp<T> &ep, T x, int lane) {
     const int node = lane >> 3, sub = lane & 7;
     int32_t lo = __shfl(ep.cur, node, kW), hi = __shfl(ep.end, node, kW);
     while (__ballot(lo < hi)) {
@@ -143,12 +181,25 @@ __device__ __forceinline__ void seek(const T *__restrict__ ts, WaveEp<T> &ep, T 
 // Node k's next kCap events into x (the index is padded by kCap entries);
 // returns how many its type has left.
 template <typename T>
-__device__ __forceinline__ int load_events(const T *__restrict__ ts, const WaveEp<T> &ep, int k, int lane, T (&x)[kR]) {
+__device__ __forceinline__ int load_events(Times<T> ts, const WaveEp<T> &ep, int k, int lane, T (&x)[kR]) {
     const int c = rdlane(ep.cur, k);
-    const T *p = ts + c;
+    Times<T> p = ts + c;
 #pragma unroll
     for (int r = 0; r < kR; ++r) x[r] = p[r * kW + lane];
     return rdlane(ep.end, k) - c;
+}
+
+// Every node's next event, and the one that a full window of its type ends
+// before (the type maximum where there is none): lane k, node k.
+template <typename T>
+__device__ __forceinline__ void load_heads(Times<T> ts, const WaveEp<T> &ep, int lane, T &h, T &f) {
+    h = f = TsLimits<T>::hi();
+    if (lane < ep.N) {  // (positions stay inside the padded index)
+        const int left = ep.end - ep.cur;
+        const T a = ts[ep.cur], b = ts[(int64_t)ep.cur + (left > kCap ? kCap : 0)];
+        if (left > 0) h = a;
+        if (left > kCap) f = b;
+    }
 }
 
 // What a run hands back, and what it is checked against.
@@ -172,24 +223,28 @@ struct WaveRec {
 // the speculative record (see rerun_segment in epi_tiled.hip); out.cnt then
 // includes the record's remaining completions.
 template <typename T, bool SYNC>
-__device__ __forceinline__ void wave_run(const T *__restrict__ ts, WaveLds<T> &w, WaveEp<T> &ep, T e0, T Bp, T Ep,
+__device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep, T e0, T Bp, T Ep,
                                          int lane, T *__restrict__ first_out, int64_t first_stride,
                                          const WaveRec<T> *rec, WaveOut<T> &out) {
     using U = std::make_unsigned_t<T>;  // differences of ordered times: exact in it
+    using E = Entry<T>;
+    using Key = typename E::Key;
+    using UKey = typename E::UKey;
     constexpr T kEnd = TsLimits<T>::hi();
     constexpr T kMin = TsLimits<T>::lo();
     const int N = ep.N;
     T tau = bcast(e0);
-    T te = 0;    // the window's end
+    T h0 = 0, te = 0;  // the window's first event and end
+    if (lane < 2) w.e[lane][0] = INT64_MIN;
+    lds_order();
     int nc = 0;  // lane k: entries node k's list handed on
     int32_t cnt = 0;
+    // a window's first loads are issued in the one before it
+    T hv, fv, x[kR];
+    load_heads(ts, ep, lane, hv, fv);
+    int left = load_events(ts, ep, 0, lane, x);
     while (true) {
-        T h = kEnd, f = kEnd;
-        if (lane < N && ep.cur < ep.end) {
-            h = ts[ep.cur];
-            const int64_t fi = (int64_t)ep.cur + kCap;
-            if (fi < (int64_t)ep.end) f = ts[fi];
-        }
+        T h = hv, f = fv;
 #pragma unroll
         for (int d = 1; d < 8; d <<= 1) {
             const T oh = __shfl_xor(h, d, 8), of = __shfl_xor(f, d, 8);
@@ -199,111 +254,128 @@ __device__ __forceinline__ void wave_run(const T *__restrict__ ts, WaveLds<T> &w
         h = bcast(h);
         f = bcast(f);
         if (h >= Ep) break;
-        const T tp = te;  // what was handed on is relative to it
+        // past a silence longer than any interval nothing handed on reaches
+        if ((U)h - (U)te > (U(1) << 30)) nc = 0;
+        const int64_t shift = E::kRel ? (int64_t)(((uint64_t)h - (uint64_t)h0) << E::kUp) : 0;
+        h0 = h;
         te = f < Ep ? f : Ep;
+        if constexpr (E::kRel)
+            if ((uint64_t)te - (uint64_t)h > E::kSpan) te = (T)((uint64_t)h + E::kSpan);
+        const Key te_k = E::key(te, h);
         const bool all = h >= Bp;
         const int32_t cnt0 = cnt;
         int n = 0;  // entries of the previous node's list
-        T x[kR];
-        int left = load_events(ts, ep, 0, lane, x);
         for (int k = 0; k < N; ++k) {
             T v[kR];
-            int g[kR];  // ages
+            Key xs[kR];
+            uint32_t st[kR];  // start bits
             uint64_t ok[kR];
             int nx = 0;
 #pragma unroll
             for (int r = 0; r < kR; ++r) {
                 v[r] = x[r];
-                ok[r] = __ballot(v[r] < te && lane < left - r * kW);
-                nx += __popcll(ok[r]);
+                ok[r] = __ballot(v[r] < te);
+                xs[r] = E::key(v[r], h);
             }
-            // the next node's events, ahead of this node's work
-            if (k + 1 < N) left = load_events(ts, ep, k + 1, lane, x);
+            if (left < kCap) {
+#pragma unroll
+                for (int r = 0; r < kR; ++r) ok[r] &= lanes_below(left - r * kW);
+            }
+#pragma unroll
+            for (int r = 0; r < kR; ++r) nx += __popcll(ok[r]);
             if (lane == k) ep.cur += nx;
+            // the next node's events, ahead of this node's work
+            if (k + 1 == N) load_heads(ts, ep, lane, hv, fv);
+            left = load_events(ts, ep, k + 1 < N ? k + 1 : 0, lane, x);
             const int pb = (k & 1) ^ 1, qb = k & 1;  // previous list, this node's list
             if (k == 0) {
 #pragma unroll
-                for (int r = 0; r < kR; ++r) g[r] = 0;
+                for (int r = 0; r < kR; ++r) st[r] = E::start_bits(v[r]);
             } else if (n == 0 || nx == 0) {
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
-                    g[r] = 0;
+                    st[r] = 0;
                     ok[r] = 0;
                 }
             } else {
-                const int lo = rdlane(ep.lo, k - 1), hi = rdlane(ep.hi, k - 1);
-                T q[kR];
-                int p[kR];
+                const UKey lo = E::len(rdlane(ep.lo, k - 1)), hi = E::len(rdlane(ep.hi, k - 1));
+                Key q[kR];
+                uint32_t p[kR];  // byte offset of the latest entry known to be before q
+                const char *list = reinterpret_cast<const char *>(w.e);
+                const uint32_t base = (uint32_t)pb * (uint32_t)sizeof(w.e[0]);
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
-                    q[r] = (T)((U)v[r] - (U)lo);
-                    p[r] = 0;
+                    q[r] = (Key)((UKey)xs[r] - lo);
+                    p[r] = base;
                 }
-                // entries before q: halving search, one length for all
-                int len = n;
+                // halving search of the sentinel and the n entries, one length for all
+                int len = n + 1;
                 while (len > 1) {
                     const int half = len >> 1;
+                    const uint32_t hb = (uint32_t)half * 8u;
 #pragma unroll
                     for (int r = 0; r < kR; ++r) {
-                        const int m = p[r] + half;
-                        p[r] = w.t[pb][m - 1] < q[r] ? m : p[r];
+                        const uint32_t m = p[r] + hb;
+                        p[r] = *reinterpret_cast<const Key *>(list + m + E::kKeyAt) < q[r] ? m : p[r];
                     }
                     len -= half;
                 }
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
-                    // one entry is left to test: the latest before q is p's or the one before it
-                    const T y0 = w.t[pb][p[r]];
-                    const int i1 = p[r] > 0 ? p[r] - 1 : 0;
-                    const T y1 = w.t[pb][i1];
-                    const bool in = y0 < q[r];
-                    const T y = in ? y0 : y1;
-                    const U d = (U)v[r] - (U)y;
-                    g[r] = w.age[pb][in ? p[r] : i1] + (int)d;
-                    ok[r] &= __ballot(y < q[r] && d <= (U)hi);
+                    // (the entry's start bits only lower the difference, by less than one unit of time)
+                    const int64_t y = *reinterpret_cast<const int64_t *>(list + p[r]);
+                    ok[r] &= __ballot((UKey)xs[r] - E::key_of(y) <= hi);
+                    st[r] = E::start_bits((T)y);
                 }
             }
             if (k + 1 < N) {
                 // this node's list: what it handed on, then the hits in order
                 n = rdlane(nc, k);
-                if (lane < n) {
-                    w.t[qb][lane] = tp - (T)w.cd[k][lane];
-                    w.age[qb][lane] = w.ca[k][lane];
-                }
+                if (lane < n) w.e[qb][1 + lane] = (int64_t)((uint64_t)w.c[k][lane] - (uint64_t)shift);
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
-                    if ((ok[r] >> lane) & 1) {
-                        const int o = n + below(ok[r]);
-                        w.t[qb][o] = v[r];
-                        w.age[qb][o] = g[r];
-                    }
+                    const int o = below(ok[r], n + 1);
+                    if (in_mask(ok[r])) w.e[qb][o] = E::make(xs[r], st[r]);
                     n += __popcll(ok[r]);
                 }
                 lds_order();
                 // what later windows can reach
-                const int lo = rdlane(ep.lo, k), hi = rdlane(ep.hi, k);
+                const UKey lo = E::len(rdlane(ep.lo, k)), hi = E::len(rdlane(ep.hi, k));
                 const int i = n - kW + lane;
-                U d = ~U(0);  // from the entry to the window's end
-                int ag = 0;
+                int64_t y = 0;
+                UKey d = ~UKey(0);  // from the entry to the window's end
                 if (i >= 0) {
-                    d = (U)te - (U)w.t[qb][i];
-                    ag = w.age[qb][i];
+                    y = w.e[qb][1 + i];
+                    d = (UKey)te_k - E::key_of(y);
                 }
-                const int fut = __popcll(__ballot(d <= (U)lo));
-                const int live = __popcll(__ballot(d <= (U)hi));
+                const int fut = __popcll(__ballot(d <= lo));
+                const int live = __popcll(__ballot(d <= hi));
                 const int keep = fut + 1 < live ? fut + 1 : live;
-                if (lane >= kW - keep) {
-                    w.cd[k][lane - (kW - keep)] = (int)d;
-                    w.ca[k][lane - (kW - keep)] = ag;
-                }
+                if (lane >= kW - keep) w.c[k][lane - (kW - keep)] = y;
                 if (lane == k) nc = keep;
                 lds_order();
             } else {
                 // the greedy of Alg. 1
+                const bool plain = !SYNC && all && (!first_out || cnt >= kRecFirst);
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
-                    const T L = ((ok[r] >> lane) & 1) ? (T)((U)v[r] - (U)g[r]) : kMin;
-                    uint64_t m = __ballot(L > tau);
+                    const T L = E::start(v[r], st[r]);
+                    uint64_t m = __ballot(L > tau) & ok[r];
+                    if (plain && __popcll(ok[r]) > kRunMin) {
+                        // many hits: from a kept one on, all hits are kept up to the first that
+                        // starts at or before the hit ahead of it (one step a run)
+                        const uint64_t before = ok[r] & ((uint64_t(1) << lane) - 1);
+                        const T pv = __shfl(v[r], before ? 63 - __clzll(before) : 0, kW);
+                        const uint64_t stop = ok[r] & ~__ballot(L > pv);
+                        while (m) {
+                            const uint64_t from = ~uint64_t(0) << __builtin_ctzll(m);
+                            const uint64_t end = stop & (from << 1);
+                            const uint64_t run = ok[r] & from & (end ? (end & -end) - 1 : ~uint64_t(0));
+                            cnt += __popcll(run);
+                            tau = rdlane(v[r], 63 - __builtin_clzll(run));
+                            m = __ballot(L > tau) & ok[r];
+                        }
+                    }
                     while (m) {
                         tau = rdlane(v[r], __builtin_ctzll(m));
                         if (all || tau >= Bp) {
@@ -322,7 +394,7 @@ __device__ __forceinline__ void wave_run(const T *__restrict__ ts, WaveLds<T> &w
                             }
                             ++cnt;
                         }
-                        m = __ballot(L > tau);
+                        m = __ballot(L > tau) & ok[r];
                     }
                 }
             }
@@ -358,7 +430,7 @@ __device__ __forceinline__ void seg_bounds(const CountArgs<T> &a, int p, T &Bp, 
 // Candidate s of unit a over segment p: the whole count (P = 1) or the
 // segment's speculative record.
 template <typename T>
-__device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int p, WaveLds<T> &w, int lane) {
+__device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int p, WaveLds &w, int lane) {
     constexpr T kMin = TsLimits<T>::lo();
     const int64_t slot = slot_of(a, s);
     WaveEp<T> ep = load_episode(a, slot, lane);
@@ -367,13 +439,13 @@ __device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int 
     T e0 = kMin;
     if (p > 0) {
         e0 = (T)(Bp - ep.H - 1);
-        seek(a.ts_by_type, ep, e0, lane);
+        seek((Times<T>)a.ts_by_type, ep, e0, lane);
     }
     WaveOut<T> out;
     out.last = kMin;
     const int64_t ro = (int64_t)p * a.G + s;
     T *first = a.P > 1 ? a.rec_first + (int64_t)p * kRecFirst * a.G + s : nullptr;
-    wave_run<T, false>(a.ts_by_type, w, ep, e0, Bp, Ep, lane, first, a.G, nullptr, out);
+    wave_run<T, false>((Times<T>)a.ts_by_type, w, ep, e0, Bp, Ep, lane, first, a.G, nullptr, out);
     if (lane == 0) {
         if (a.P == 1) {
             const int64_t o = a.orig[slot];
@@ -390,7 +462,7 @@ __device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int 
 // Segment p's completions and last completion given the last completion tau
 // before it (see rerun_segment in epi_tiled.hip).
 template <typename T>
-__device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds<T> &w,
+__device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds &w,
                                                     int lane, const WaveEp<T> &ep0) {
     T Bp, Ep;
     seg_bounds(a, p, Bp, Ep);
@@ -408,10 +480,10 @@ __device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64
     for (int j = 0; j < kRecFirst; ++j)
         rec.first[j] = j < c ? bcast(a.rec_first[((int64_t)p * kRecFirst + j) * a.G + s]) : TsLimits<T>::hi();
     WaveEp<T> ep = ep0;
-    seek(a.ts_by_type, ep, tau, lane);
+    seek((Times<T>)a.ts_by_type, ep, tau, lane);
     WaveOut<T> out;
     out.last = tau;
-    wave_run<T, true>(a.ts_by_type, w, ep, tau, TsLimits<T>::lo(), Ep, lane, nullptr, 0, &rec, out);
+    wave_run<T, true>((Times<T>)a.ts_by_type, w, ep, tau, TsLimits<T>::lo(), Ep, lane, nullptr, 0, &rec, out);
     if (out.synced) {
         if (c > 0) tau = last;
     } else {
@@ -423,7 +495,7 @@ __device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64
 // Pre-pass of candidate s, segment p >= 1: its true completions if the earlier
 // records' last completion is the true one.
 template <typename T>
-__device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds<T> &w, int lane) {
+__device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds &w, int lane) {
     T tau = TsLimits<T>::lo();
     for (int q = p - 1; q >= 0; --q) {
         if (bcast(a.rec_cnt[(int64_t)q * a.G + s]) > 0) {
@@ -447,7 +519,7 @@ __device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p
 // last completion they assumed is the true one (all lanes test 64 segments at
 // once), a re-run elsewhere.
 template <typename T>
-__device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds<T> &w, int lane) {
+__device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds &w, int lane) {
     T tau = TsLimits<T>::lo();
     int32_t total = bcast(a.rec_cnt[s]);
     if (total > 0) tau = bcast(a.rec_last[s]);
@@ -489,19 +561,19 @@ __device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveL
 
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_count(CountArgs<T> a) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     wave_item<T>(a, blockIdx.x, blockIdx.y, w, threadIdx.x);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_pre(CountArgs<T> a) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     wave_pre<T>(a, blockIdx.x, blockIdx.y + 1, w, threadIdx.x);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_sum(CountArgs<T> a) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     wave_sum<T>(a, blockIdx.x, w, threadIdx.x);
 }
 
@@ -509,7 +581,7 @@ __global__ __launch_bounds__(kW) void k_wave_sum(CountArgs<T> a) {
 // after max(tau, B - H - 1); every completion it finds is at or after B.
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_append(CountArgs<T> a, T B) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     const int lane = threadIdx.x;
     const int64_t s = blockIdx.x;
     const int64_t slot = slot_of(a, s);
@@ -517,10 +589,10 @@ __global__ __launch_bounds__(kW) void k_wave_append(CountArgs<T> a, T B) {
     const int64_t o = bcast(a.orig[slot]);
     const T tau = bcast(a.tau[o]);
     const T from = tau > (T)(B - ep.H - 1) ? tau : (T)(B - ep.H - 1);
-    seek(a.ts_by_type, ep, from, lane);
+    seek((Times<T>)a.ts_by_type, ep, from, lane);
     WaveOut<T> out;
     out.last = tau;
-    wave_run<T, false>(a.ts_by_type, w, ep, from, TsLimits<T>::lo(), TsLimits<T>::hi(), lane, nullptr, 0, nullptr, out);
+    wave_run<T, false>((Times<T>)a.ts_by_type, w, ep, from, TsLimits<T>::lo(), TsLimits<T>::hi(), lane, nullptr, 0, nullptr, out);
     if (lane == 0) {
         a.counts[o] += out.cnt;
         a.tau[o] = out.last;
@@ -533,7 +605,7 @@ template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__restrict__ units,
                                                         const WorkItem *__restrict__ items, int64_t n_items,
                                                         unsigned long long *__restrict__ queue) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     const int lane = threadIdx.x;
     while (true) {
         rejoin();
@@ -553,7 +625,7 @@ __global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__re
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_pre_all(const CountArgs<T> *__restrict__ units,
                                                      const WorkItem *__restrict__ items, int64_t n_items) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     for (int64_t q = blockIdx.x; q < n_items * kW; q += gridDim.x) {
         const WorkItem it = items[q / kW];
         const CountArgs<T> &a = units[it.unit];
@@ -565,7 +637,7 @@ __global__ __launch_bounds__(kW) void k_wave_pre_all(const CountArgs<T> *__restr
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_sum_all(const CountArgs<T> *__restrict__ units,
                                                      const WorkItem *__restrict__ items, int64_t n_items) {
-    __shared__ WaveLds<T> w;
+    __shared__ WaveLds w;
     for (int64_t q = blockIdx.x; q < n_items * kW; q += gridDim.x) {
         const WorkItem it = items[q / kW];
         const CountArgs<T> &a = units[it.unit];
