@@ -55,6 +55,7 @@ struct CountArgs {
     int32_t *work;        // work log: kWork counters per candidate (submission order); null = off
     int64_t *cycles;      // work log: wall-clock start/end per work item; null = off
     const uint8_t *cN;    // epi_wave.hip: episode size of every slot of the set
+    int64_t seg_cost;     // epi_wave.hip: events of an episode per segment, at most P segments (0: P segments each)
 };
 
 // Persistent form: one work item = (unit, lane block, segment).

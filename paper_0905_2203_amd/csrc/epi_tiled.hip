@@ -1007,6 +1007,11 @@ int64_t wave_segments(const Stream &s, double cost_max, double cost_all, const C
     return P;
 }
 
+// Events of an episode that make up one segment: the costliest is cut into P.
+int64_t wave_seg_cost(const CountOptions &opt, double cost_max, int64_t P) {
+    return opt.segments > 0 || P < 2 ? 0 : std::max<int64_t>(1, (int64_t)(cost_max / (double)P));
+}
+
 hipError_t wave_resident(int *waves) {
     int dev = 0, ncu = 0;
     hipError_t e;
@@ -1051,6 +1056,7 @@ hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end,
     CountArgs<T> a = wave_args<T>(s, c, d_flags);
     const int64_t P = wave_segments(s, cost_max, cost_all, opt, waves, &a.S);
     a.P = (int32_t)P;
+    a.seg_cost = wave_seg_cost(opt, cost_max, P);
     int64_t step = end - begin;
     if (P > 1 && ext_scratch) {
         // the caller's scratch: as many episodes at a time as it holds records for
@@ -1656,7 +1662,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             ro += (record_bytes<T>(u.P, u.G) + 64) & ~size_t(15);
         }
         if (u.wave) {
-            // static LDS
+            a.seg_cost = wave_seg_cost(opt, u.cost_max, u.P);
         } else if (laneN[cl]) {
             const LaneLayout L = lane_layout(clsC[cl], Wn[cl], maxK[cl], maxT[cl]);
             a.off_qse = L.off_ring;

@@ -95,6 +95,8 @@ struct WaveEp {
     int32_t cur, end;
     int32_t lo, hi;
     T H;  // longest span
+    int32_t P;  // its segments
+    int64_t S;  // tiles each
 };
 
 __device__ __forceinline__ int rdlane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
@@ -153,6 +155,20 @@ __device__ __forceinline__ WaveEp<T> load_episode(const CountArgs<T> &a, int64_t
     int h = ep.hi;  // the span is below 2^29
     for (int d = 1; d < 8; d <<= 1) h += __shfl_xor(h, d, 8);
     ep.H = (T)bcast(h);
+    // segments by the episode's own events, so that light episodes are not cut
+    // into pieces that cost more to start and reconcile than to count
+    ep.P = a.P;
+    ep.S = a.S;
+    if (a.P > 1 && a.seg_cost > 0) {
+        int64_t c = ep.end - ep.cur;
+        for (int d = 1; d < 8; d <<= 1) c += __shfl_xor(c, d, 8);
+        const int64_t want = bcast(c) / a.seg_cost + 1;
+        const int32_t B = (int32_t)a.B, P = want < a.P ? (int32_t)want : a.P;
+        ep.S = (B + P - 1) / P;
+        ep.P = (B + (int32_t)ep.S - 1) / (int32_t)ep.S;
+    }
+    ep.P = bcast(ep.P);
+    ep.S = bcast(ep.S);
     return ep;
 }
 
@@ -178,6 +194,9 @@ __device__ __forceinline__ void seek(Times<T> ts, WaveEp<T> &ep, T x, int lane) 
     if (lane < ep.N) ep.cur = v;
 }
 
+template <int NR>
+using Chunks = std::integral_constant<int, NR>;
+
 // Node k's next kCap events into x (the index is padded by kCap entries);
 // returns how many its type has left.
 template <typename T>
@@ -189,17 +208,12 @@ __device__ __forceinline__ int load_events(Times<T> ts, const WaveEp<T> &ep, int
     return rdlane(ep.end, k) - c;
 }
 
-// Every node's next event, and the one that a full window of its type ends
-// before (the type maximum where there is none): lane k, node k.
+// Every node's next event, and the one kCap after it (lane k: node k; lanes past
+// the last node and types with fewer left read something in the padded index).
 template <typename T>
-__device__ __forceinline__ void load_heads(Times<T> ts, const WaveEp<T> &ep, int lane, T &h, T &f) {
-    h = f = TsLimits<T>::hi();
-    if (lane < ep.N) {  // (positions stay inside the padded index)
-        const int left = ep.end - ep.cur;
-        const T a = ts[ep.cur], b = ts[(int64_t)ep.cur + (left > kCap ? kCap : 0)];
-        if (left > 0) h = a;
-        if (left > kCap) f = b;
-    }
+__device__ __forceinline__ void load_heads(Times<T> ts, const WaveEp<T> &ep, T &h, T &f) {
+    h = ts[ep.cur];
+    f = ts[(int64_t)ep.cur + (ep.end - ep.cur > kCap ? kCap : 0)];
 }
 
 // What a run hands back, and what it is checked against.
@@ -241,10 +255,10 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
     int32_t cnt = 0;
     // a window's first loads are issued in the one before it
     T hv, fv, x[kR];
-    load_heads(ts, ep, lane, hv, fv);
+    load_heads(ts, ep, hv, fv);
     int left = load_events(ts, ep, 0, lane, x);
     while (true) {
-        T h = hv, f = fv;
+        T h = ep.cur < ep.end ? hv : kEnd, f = ep.end - ep.cur > kCap ? fv : kEnd;
 #pragma unroll
         for (int d = 1; d < 8; d <<= 1) {
             const T oh = __shfl_xor(h, d, 8), of = __shfl_xor(f, d, 8);
@@ -285,7 +299,7 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
             for (int r = 0; r < kR; ++r) nx += __popcll(ok[r]);
             if (lane == k) ep.cur += nx;
             // the next node's events, ahead of this node's work
-            if (k + 1 == N) load_heads(ts, ep, lane, hv, fv);
+            if (k + 1 == N) load_heads(ts, ep, hv, fv);
             left = load_events(ts, ep, k + 1 < N ? k + 1 : 0, lane, x);
             const int pb = (k & 1) ^ 1, qb = k & 1;  // previous list, this node's list
             if (k == 0) {
@@ -299,34 +313,41 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
                 }
             } else {
                 const UKey lo = E::len(rdlane(ep.lo, k - 1)), hi = E::len(rdlane(ep.hi, k - 1));
-                Key q[kR];
-                uint32_t p[kR];  // byte offset of the latest entry known to be before q
-                const char *list = reinterpret_cast<const char *>(w.e);
-                const uint32_t base = (uint32_t)pb * (uint32_t)sizeof(w.e[0]);
+                auto search = [&](auto chunks) __attribute__((always_inline)) {
+                    constexpr int NR = decltype(chunks)::value;
+                    Key q[NR];
+                    uint32_t p[NR];  // byte offset of the latest entry known to be before q
+                    const char *list = reinterpret_cast<const char *>(w.e);
+                    const uint32_t base = (uint32_t)pb * (uint32_t)sizeof(w.e[0]);
 #pragma unroll
-                for (int r = 0; r < kR; ++r) {
-                    q[r] = (Key)((UKey)xs[r] - lo);
-                    p[r] = base;
-                }
-                // halving search of the sentinel and the n entries, one length for all
-                int len = n + 1;
-                while (len > 1) {
-                    const int half = len >> 1;
-                    const uint32_t hb = (uint32_t)half * 8u;
-#pragma unroll
-                    for (int r = 0; r < kR; ++r) {
-                        const uint32_t m = p[r] + hb;
-                        p[r] = *reinterpret_cast<const Key *>(list + m + E::kKeyAt) < q[r] ? m : p[r];
+                    for (int r = 0; r < NR; ++r) {
+                        q[r] = (Key)((UKey)xs[r] - lo);
+                        p[r] = base;
                     }
-                    len -= half;
-                }
+                    // halving search of the sentinel and the n entries, one length for all
+                    int len = n + 1;
+                    while (len > 1) {
+                        const int half = len >> 1;
+                        const uint32_t hb = (uint32_t)half * 8u;
 #pragma unroll
-                for (int r = 0; r < kR; ++r) {
-                    // (the entry's start bits only lower the difference, by less than one unit of time)
-                    const int64_t y = *reinterpret_cast<const int64_t *>(list + p[r]);
-                    ok[r] &= __ballot((UKey)xs[r] - E::key_of(y) <= hi);
-                    st[r] = E::start_bits((T)y);
-                }
+                        for (int r = 0; r < NR; ++r) {
+                            const uint32_t m = p[r] + hb;
+                            p[r] = *reinterpret_cast<const Key *>(list + m + E::kKeyAt) < q[r] ? m : p[r];
+                        }
+                        len -= half;
+                    }
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        // (the entry's start bits only lower the difference, by less than one unit of time)
+                        const int64_t y = *reinterpret_cast<const int64_t *>(list + p[r]);
+                        ok[r] &= __ballot((UKey)xs[r] - E::key_of(y) <= hi);
+                        st[r] = E::start_bits((T)y);
+                    }
+                };
+                // where another of the episode's types is much busier, one chunk holds the
+                // events of this one
+                if (nx <= kW) search(Chunks<1>());
+                else search(Chunks<kR>());
             }
             if (k + 1 < N) {
                 // this node's list: what it handed on, then the hits in order
@@ -359,6 +380,7 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
                 const bool plain = !SYNC && all && (!first_out || cnt >= kRecFirst);
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
+                    if (ok[r] == 0) continue;
                     const T L = E::start(v[r], st[r]);
                     uint64_t m = __ballot(L > tau) & ok[r];
                     if (plain && __popcll(ok[r]) > kRunMin) {
@@ -420,11 +442,11 @@ __device__ __forceinline__ int64_t slot_of(const CountArgs<T> &a, int64_t s) {
 
 // Segment p's first and end time.
 template <typename T>
-__device__ __forceinline__ void seg_bounds(const CountArgs<T> &a, int p, T &Bp, T &Ep) {
-    const int64_t b0 = (int64_t)p * a.S;
-    const int64_t b1 = b0 + a.S < a.B ? b0 + a.S : a.B;
+__device__ __forceinline__ void seg_bounds(const CountArgs<T> &a, const WaveEp<T> &ep, int p, T &Bp, T &Ep) {
+    const int64_t b0 = (int64_t)p * ep.S;
+    const int64_t b1 = b0 + ep.S < a.B ? b0 + ep.S : a.B;
     Bp = bcast(p == 0 ? TsLimits<T>::lo() : a.tile_t0[b0]);
-    Ep = bcast(p == a.P - 1 ? TsLimits<T>::hi() : a.tile_t0[b1]);
+    Ep = bcast(p == ep.P - 1 ? TsLimits<T>::hi() : a.tile_t0[b1]);
 }
 
 // Candidate s of unit a over segment p: the whole count (P = 1) or the
@@ -434,8 +456,10 @@ __device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int 
     constexpr T kMin = TsLimits<T>::lo();
     const int64_t slot = slot_of(a, s);
     WaveEp<T> ep = load_episode(a, slot, lane);
+    if (p >= ep.P) return;
+    const bool whole = ep.P == 1;
     T Bp, Ep;
-    seg_bounds(a, p, Bp, Ep);
+    seg_bounds(a, ep, p, Bp, Ep);
     T e0 = kMin;
     if (p > 0) {
         e0 = (T)(Bp - ep.H - 1);
@@ -444,10 +468,10 @@ __device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int 
     WaveOut<T> out;
     out.last = kMin;
     const int64_t ro = (int64_t)p * a.G + s;
-    T *first = a.P > 1 ? a.rec_first + (int64_t)p * kRecFirst * a.G + s : nullptr;
+    T *first = !whole ? a.rec_first + (int64_t)p * kRecFirst * a.G + s : nullptr;
     wave_run<T, false>((Times<T>)a.ts_by_type, w, ep, e0, Bp, Ep, lane, first, a.G, nullptr, out);
     if (lane == 0) {
-        if (a.P == 1) {
+        if (whole) {
             const int64_t o = a.orig[slot];
             a.counts[o] = out.cnt;
             if (a.tau) a.tau[o] = out.last;
@@ -465,7 +489,7 @@ template <typename T>
 __device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds &w,
                                                     int lane, const WaveEp<T> &ep0) {
     T Bp, Ep;
-    seg_bounds(a, p, Bp, Ep);
+    seg_bounds(a, ep0, p, Bp, Ep);
     const int64_t ro = (int64_t)p * a.G + s;
     const int32_t c = bcast(a.rec_cnt[ro]);
     const T last = bcast(a.rec_last[ro]);
@@ -496,6 +520,8 @@ __device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64
 // records' last completion is the true one.
 template <typename T>
 __device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds &w, int lane) {
+    const WaveEp<T> ep = load_episode(a, slot_of(a, s), lane);
+    if (p >= ep.P) return;
     T tau = TsLimits<T>::lo();
     for (int q = p - 1; q >= 0; --q) {
         if (bcast(a.rec_cnt[(int64_t)q * a.G + s]) > 0) {
@@ -503,7 +529,6 @@ __device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p
             break;
         }
     }
-    const WaveEp<T> ep = load_episode(a, slot_of(a, s), lane);
     const T tau0 = tau;
     const int32_t c = wave_fix_segment(a, s, p, tau, w, lane, ep);
     if (lane == 0) {
@@ -520,15 +545,17 @@ __device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p
 // once), a re-run elsewhere.
 template <typename T>
 __device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds &w, int lane) {
+    const int64_t slot = slot_of(a, s);
+    const WaveEp<T> ep = load_episode(a, slot, lane);
+    if (ep.P == 1) return;  // counted whole
     T tau = TsLimits<T>::lo();
     int32_t total = bcast(a.rec_cnt[s]);
     if (total > 0) tau = bcast(a.rec_last[s]);
-    const int64_t slot = slot_of(a, s);
     int p = 1;
-    while (p < a.P) {
+    while (p < ep.P) {
         const int i = p + lane;
         const int64_t o = (int64_t)i * a.G + s;
-        const bool in = i < a.P;
+        const bool in = i < ep.P;
         int32_t c = 0;
         T assumed = 0, end = 0;
         if (in) {
@@ -539,14 +566,13 @@ __device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveL
         // the true last completion before segment i, if all before it held
         const T prev = __shfl_up(end, 1, kW);
         const uint64_t bad = __ballot(in && assumed != (lane == 0 ? tau : prev));
-        const int good = bad ? __builtin_ctzll(bad) : (a.P - p < kW ? a.P - p : kW);
+        const int good = bad ? __builtin_ctzll(bad) : (ep.P - p < kW ? ep.P - p : kW);
         int32_t v = lane < good ? c : 0;
         for (int d = 1; d < kW; d <<= 1) v += __shfl_xor(v, d, kW);
         total += bcast(v);
         if (good > 0) tau = bcast((T)__shfl(end, good - 1, kW));
         p += good;
         if (bad) {
-            const WaveEp<T> ep = load_episode(a, slot, lane);
             total += wave_fix_segment(a, s, p, tau, w, lane, ep);
             ++p;
         }
