@@ -1130,19 +1130,7 @@ epi_status epi_mlp_train(epi_ctx *ctx, const float *X, const float *t, int64_t B
     HostToDev dx, dt;
     HIPTRY(ctx, dx.put(X, sizeof(float) * B * net.F, st), "copy");
     HIPTRY(ctx, dt.put(t, sizeof(float) * B, st), "copy");
-    for (int32_t ep = 0; ep < epochs; ++ep) {
-        double acc = 0;
-        for (int64_t b0 = 0; b0 < B; b0 += batch) {
-            const int64_t nb = std::min<int64_t>(batch, B - b0);
-            float L = 0;
-            HIPTRY(ctx, mlp_grad_device(net, dx.d.as<float>() + b0 * net.F, dt.d.as<float>() + b0, nb,
-                                        net.g.as<float>(), losses ? &L : nullptr, st),
-                   "gradient");
-            HIPTRY(ctx, mlp_adam_device(net, net.g.as<float>(), st), "adam");
-            acc += (double)L * nb;
-        }
-        if (losses) losses[ep] = (float)(acc / (double)B);
-    }
+    HIPTRY(ctx, mlp_train_device(net, dx.d.as<float>(), dt.d.as<float>(), B, epochs, batch, losses, st), "training");
     HIPTRY(ctx, hipStreamSynchronize(st), "sync");
     return EPI_OK;
 }

@@ -364,7 +364,6 @@ struct Mlp {
     int step = 0;
     float lr = 1e-3f, b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     DevBuf p, m, v, g, act;
-    size_t cap = 0;
     // standardisation of the cost model around the network:
     // prediction = y_sd * net((x - x_mu) * x_isd) + y_mu (identity after init)
     std::vector<float> x_mu, x_isd;
@@ -529,6 +528,9 @@ hipError_t mlp_init(Mlp &net, int F, uint64_t seed);
 hipError_t mlp_forward_device(Mlp &net, const float *dX, int64_t B, float *dy, hipStream_t st);
 hipError_t mlp_grad_device(Mlp &net, const float *dX, const float *dt, int64_t B, float *dg, float *loss,
                            hipStream_t st);
+// `epochs` passes of Adam over consecutive mini-batches; losses (may be null): each epoch's mean loss.
+hipError_t mlp_train_device(Mlp &net, const float *dX, const float *dt, int64_t B, int32_t epochs, int32_t batch,
+                            float *losses, hipStream_t st);
 hipError_t mlp_adam_device(Mlp &net, const float *dg, hipStream_t st);
 hipError_t mlp_set_scaling(Mlp &net, const float *x_mu, const float *x_isd, float y_mu, float y_sd);
 // the cost model's prediction for B device samples; standardises dX in place

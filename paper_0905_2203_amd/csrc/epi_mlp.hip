@@ -8,15 +8,16 @@
 // Parameters: one flat FP32 vector W1[F][64], b1[64], W2[64][64], b2[64],
 // w3[64], b3[1].
 //
-// k_mlp_sample: one thread per sample; weights staged in LDS; computes the
-//   forward pass and, when training, the per-sample back-propagated terms
-//   dz1, dz2 (64 each) and dy, stored for the reduction.
-// k_mlp_reduce: one thread per parameter; sums its gradient over the batch in
-//   a fixed order (deterministic), e.g. dL/dW2[a][j] = sum_i h1[i][a] dz2[i][j].
-// k_mlp_adam:   one thread per parameter; Adam step k.
+// k_mlp_rows:   one wave per tile of 4 or 8 samples, lane j = hidden unit j: the
+//   forward pass and, when training, the back-propagated terms and the tile's
+//   gradient, added up over the wave's tiles in a part of its own.
+// k_mlp_sum:    sums the parts of each parameter's gradient in a fixed order
+//   (deterministic) and, in a training step, applies Adam step k.
+// k_mlp_adam:   one thread per parameter; Adam step k with a given gradient.
 // k_standardize, k_affine_base: the cost model's input and output scaling
 //   around the network, (x - mu) * isd per feature and y * sd + mu, plus the
 //   raw base feature (the network predicts the correction to it).
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -30,88 +31,204 @@ constexpr int kH = kMlpHidden;
 
 __host__ __device__ inline int64_t n_params_of(int F) { return (int64_t)F * kH + kH + kH * kH + kH + kH + 1; }
 
-__global__ __launch_bounds__(256) void k_mlp_sample(const float *__restrict__ p, int F, const float *__restrict__ X,
-                                                    const float *__restrict__ t, int64_t B, float *__restrict__ y,
-                                                    float *__restrict__ h1s, float *__restrict__ dz1s,
-                                                    float *__restrict__ dz2s, float *__restrict__ h2s,
-                                                    float *__restrict__ dys, float *__restrict__ sqerr) {
-    extern __shared__ float w[];
-    const int64_t np = n_params_of(F);
-    for (int64_t i = threadIdx.x; i < np; i += blockDim.x) w[i] = p[i];
-    __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B) return;
-    const float *W1 = w, *b1 = w + F * kH, *W2 = b1 + kH, *b2 = W2 + kH * kH, *w3 = b2 + kH, *b3 = w3 + kH;
-    float h1[kH];
+// What bounds a training step is latency: 512 samples are 9 million multiply-adds,
+// nothing for the chip, in a chain of forward, backward, gradient and update.  One
+// thread a sample with all weights broadcast from LDS (79 us), then one thread a
+// parameter summing 512 samples in a row (134 us), then the loss fetched by the
+// host took 262 us a step; a wave a tile spreads the batch over 128 waves and
+// leaves sums of at most kParts, 11 us a step (16 steps of 512: 4.2 -> 0.2 ms).
+constexpr int kMlpWaves = 4;     // waves per workgroup, sharing the staged W2
+constexpr int kParts = 256;      // most gradient parts (waves of a training launch)
+constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of bank conflicts
+
+// y[s] for every sample; TRAIN also the gradient parts part[wave][n_params] of
+// the loss over B samples, and the squared errors.  S samples a tile.
+template <bool TRAIN, int S>
+__global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__restrict__ p, int F,
+                                                             const float *__restrict__ X, const float *__restrict__ t,
+                                                             int64_t B, float *__restrict__ y, float *__restrict__ part,
+                                                             float *__restrict__ sqerr) {
+    __shared__ float W2[kH * kRow];
+    __shared__ __align__(16) float W1s[kH * kH];  // W1, for up to 64 inputs
+    __shared__ __align__(16) float xb[kMlpWaves][kH][S];  // 64 inputs of the tile's samples
+    __shared__ __align__(16) float hb[kMlpWaves][kH][S];  // h1
+    __shared__ __align__(16) float db[kMlpWaves][kH][S];  // dz2
+    const int j = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const float *W1 = p, *b1 = p + (int64_t)F * kH, *pW2 = b1 + kH, *b2 = pW2 + kH * kH, *w3 = b2 + kH, *b3 = w3 + kH;
+    float(*x)[S] = xb[wv], (*h)[S] = hb[wv], (*d)[S] = db[wv];
+    const float vb1 = b1[j], vb2 = b2[j], vw3 = w3[j], vb3 = b3[0];
+    const bool staged = F <= kH;
+    {
+        // all loads in flight together (the rows start on 16 bytes)
+        constexpr int kN = kH * kH / (4 * 64 * kMlpWaves);
+        float4 a[kN], b[kN];
+        const int nw1 = staged ? F * kH / 4 : 0;
 #pragma unroll
-    for (int j = 0; j < kH; ++j) h1[j] = b1[j];
-    for (int f = 0; f < F; ++f) {
-        const float x = X[s * F + f];
+        for (int r = 0; r < kN; ++r) {
+            const int i = r * 64 * kMlpWaves + (int)threadIdx.x;
+            a[r] = reinterpret_cast<const float4 *>(pW2)[i];
+            b[r] = i < nw1 ? reinterpret_cast<const float4 *>(W1)[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
 #pragma unroll
-        for (int j = 0; j < kH; ++j) h1[j] = fmaf(x, W1[f * kH + j], h1[j]);
+        for (int r = 0; r < kN; ++r) {
+            const int i = r * 64 * kMlpWaves + (int)threadIdx.x;
+            float *o = W2 + (i / (kH / 4)) * kRow + (i % (kH / 4)) * 4;
+            o[0] = a[r].x;
+            o[1] = a[r].y;
+            o[2] = a[r].z;
+            o[3] = a[r].w;
+            reinterpret_cast<float4 *>(W1s)[i] = b[r];
+        }
     }
+    __syncthreads();  // (the only barrier: from here on the waves work alone)
+    const int64_t wave = (int64_t)blockIdx.x * kMlpWaves + wv, waves = (int64_t)gridDim.x * kMlpWaves;
+    float *g = TRAIN ? part + wave * n_params_of(F) : nullptr;
+    bool first = true;
+    for (int64_t s0 = wave * S; s0 < B; s0 += waves * S) {
+        const int ns = B - s0 < S ? (int)(B - s0) : S;
+        // inputs f0 .. f0+63 of the tile (zero for the samples past the batch)
+        auto stage = [&](int f0) {
+            __builtin_amdgcn_wave_barrier();
+            float v[S];
+            const int f = f0 + j < F ? f0 + j : F - 1;
 #pragma unroll
-    for (int j = 0; j < kH; ++j) h1[j] = h1[j] > 0.f ? h1[j] : 0.f;  // z1 > 0 <=> h1 > 0
-    float out = b3[0];
-    float z2[kH];
+            for (int q = 0; q < S; ++q) v[q] = X[(s0 + (q < ns ? q : 0)) * F + f];
 #pragma unroll
-    for (int j = 0; j < kH; ++j) z2[j] = b2[j];
-    for (int a = 0; a < kH; ++a) {
-        const float v = h1[a];
+            for (int q = 0; q < S; ++q) x[j][q] = q < ns && f0 + j < F ? v[q] : 0.f;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        float h1[S], z2[S], out[S], tq[S];
 #pragma unroll
-        for (int j = 0; j < kH; ++j) z2[j] = fmaf(v, W2[a * kH + j], z2[j]);
-    }
+        for (int q = 0; q < S; ++q) {
+            h1[q] = vb1;
+            tq[q] = TRAIN && q < ns ? t[s0 + q] : 0.f;
+        }
+        for (int f0 = 0; f0 < F; f0 += kH) {
+            stage(f0);
+            const int nf = F - f0 < kH ? F - f0 : kH;
+            auto column = [&](const float *w1) {
+#pragma unroll 8
+                for (int f = 0; f < nf; ++f) {
+                    const float wt = w1[f * kH + j];
 #pragma unroll
-    for (int j = 0; j < kH; ++j) out = fmaf(z2[j] > 0.f ? z2[j] : 0.f, w3[j], out);
-    y[s] = out;
-    if (!t) return;
-    const float r = out - t[s];
-    sqerr[s] = r * r;
-    const float dy = 2.f * r / (float)B;
-    dys[s] = dy;
-    // dz2 = dy * w3 * [z2 > 0];  dz1 = (dz2 W2^T) * [z1 > 0]
+                    for (int q = 0; q < S; ++q) h1[q] = fmaf(x[f][q], wt, h1[q]);
+                }
+            };
+            if (staged) column(W1s);
+            else column(W1 + (int64_t)f0 * kH);
+        }
 #pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        const float h2 = z2[j] > 0.f ? z2[j] : 0.f;
-        h2s[s * kH + j] = h2;
-        z2[j] = z2[j] > 0.f ? dy * w3[j] : 0.f;  // now dz2
-        dz2s[s * kH + j] = z2[j];
-    }
-    for (int a = 0; a < kH; ++a) {
-        float acc = 0.f;
+        for (int q = 0; q < S; ++q) {
+            h1[q] = h1[q] > 0.f ? h1[q] : 0.f;  // z1 > 0 <=> h1 > 0
+            h[j][q] = h1[q];
+            z2[q] = vb2;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 8
+        for (int a = 0; a < kH; ++a) {
+            const float wt = W2[a * kRow + j];
 #pragma unroll
-        for (int j = 0; j < kH; ++j) acc = fmaf(z2[j], W2[a * kH + j], acc);
-        h1s[s * kH + a] = h1[a];
-        dz1s[s * kH + a] = h1[a] > 0.f ? acc : 0.f;
+            for (int q = 0; q < S; ++q) z2[q] = fmaf(h[a][q], wt, z2[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            float v = z2[q] > 0.f ? z2[q] * vw3 : 0.f;
+            for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+            out[q] = v + vb3;
+            if (j == q && q < ns) y[s0 + q] = out[q];
+        }
+        if constexpr (TRAIN) {
+            // dz2 = dy * w3 * [z2 > 0];  dz1 = (dz2 W2^T) * [z1 > 0]
+            float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, dz1[S], dz2[S];
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                const float r = q < ns ? out[q] - tq[q] : 0.f;
+                if (j == q && q < ns) sqerr[s0 + q] = r * r;
+                const float dy = 2.f * r / (float)B;
+                dz2[q] = z2[q] > 0.f ? dy * vw3 : 0.f;
+                gw3 = fmaf(z2[q] > 0.f ? z2[q] : 0.f, dy, gw3);
+                gb2 += dz2[q];
+                gb3 += dy;
+                d[j][q] = dz2[q];
+                dz1[q] = 0.f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll 8
+            for (int k = 0; k < kH; ++k) {  // lane j = unit j of the first layer
+                const float wt = W2[j * kRow + k];
+#pragma unroll
+                for (int q = 0; q < S; ++q) dz1[q] = fmaf(d[k][q], wt, dz1[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < S; ++q) {
+                dz1[q] = h1[q] > 0.f ? dz1[q] : 0.f;
+                gb1 += dz1[q];
+            }
+            // the tile's gradient onto the wave's part (each lane its own parameters)
+            auto put = [&](int64_t o, float v) { g[o] = first ? v : g[o] + v; };
+            for (int f0 = 0; f0 < F; f0 += kH) {
+                if (F > kH) stage(f0);  // (else the inputs are still there)
+                const int nf = F - f0 < kH ? F - f0 : kH;
+#pragma unroll 4
+                for (int f = 0; f < nf; ++f) {  // W1[f][j]: x_f dz1_j
+                    float v = 0.f;
+#pragma unroll
+                    for (int q = 0; q < S; ++q) v = fmaf(x[f][q], dz1[q], v);
+                    put((int64_t)(f0 + f) * kH + j, v);
+                }
+            }
+            const int64_t o1 = (int64_t)F * kH;
+            put(o1 + j, gb1);
+#pragma unroll 4
+            for (int a = 0; a < kH; ++a) {  // W2[a][j]: h1_a dz2_j
+                float v = 0.f;
+#pragma unroll
+                for (int q = 0; q < S; ++q) v = fmaf(h[a][q], dz2[q], v);
+                put(o1 + kH + a * kH + j, v);
+            }
+            const int64_t o2 = o1 + kH + kH * kH;
+            put(o2 + j, gb2);
+            put(o2 + kH + j, gw3);
+            if (j == 0) put(o2 + 2 * kH, gb3);
+            first = false;
+        }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-// gradient of one parameter, summed over the batch in sample order
-__global__ __launch_bounds__(256) void k_mlp_reduce(int F, const float *__restrict__ X, int64_t B,
-                                                    const float *__restrict__ h1s, const float *__restrict__ dz1s,
-                                                    const float *__restrict__ dz2s, const float *__restrict__ h2s,
-                                                    const float *__restrict__ dys, float *__restrict__ g) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t np = n_params_of(F);
-    if (q >= np) return;
+__device__ __forceinline__ void adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v, int64_t q,
+                                     float gq, float lr, float b1, float b2, float eps, float c1, float c2) {
+    const float mq = b1 * m[q] + (1.f - b1) * gq;
+    const float vq = b2 * v[q] + (1.f - b2) * gq * gq;
+    m[q] = mq;
+    v[q] = vq;
+    p[q] -= lr * (mq / c1) / (sqrtf(vq / c2) + eps);
+}
+
+// g = the sum of the parts, four threads a parameter, each over every fourth
+// part; ADAM: and the step with it.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_mlp_sum(const float *__restrict__ part, int parts, int64_t n,
+                                                 float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
+                                                 float *__restrict__ v, float lr, float b1, float b2, float eps,
+                                                 float c1, float c2) {
+    __shared__ float sum[4][64];
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t q = (int64_t)blockIdx.x * 64 + l;
     float acc = 0.f;
-    int64_t o = q;
-    if (o < (int64_t)F * kH) {  // W1[f][j]: x_f dz1_j
-        const int f = (int)(o / kH), j = (int)(o % kH);
-        for (int64_t i = 0; i < B; ++i) acc = fmaf(X[i * F + f], dz1s[i * kH + j], acc);
-    } else if ((o -= (int64_t)F * kH) < kH) {  // b1
-        for (int64_t i = 0; i < B; ++i) acc += dz1s[i * kH + o];
-    } else if ((o -= kH) < kH * kH) {  // W2[a][j]: h1_a dz2_j
-        const int a = (int)(o / kH), j = (int)(o % kH);
-        for (int64_t i = 0; i < B; ++i) acc = fmaf(h1s[i * kH + a], dz2s[i * kH + j], acc);
-    } else if ((o -= kH * kH) < kH) {  // b2
-        for (int64_t i = 0; i < B; ++i) acc += dz2s[i * kH + o];
-    } else if ((o -= kH) < kH) {  // w3[j]: h2_j dy
-        for (int64_t i = 0; i < B; ++i) acc = fmaf(h2s[i * kH + o], dys[i], acc);
-    } else {  // b3
-        for (int64_t i = 0; i < B; ++i) acc += dys[i];
+    if (q < n) {
+#pragma unroll 16
+        for (int i = w; i < parts; i += 4) acc += part[i * n + q];
     }
+    sum[w][l] = acc;
+    __syncthreads();
+    if (w != 0 || q >= n) return;
+    acc = (sum[0][l] + sum[1][l]) + (sum[2][l] + sum[3][l]);
     g[q] = acc;
+    if constexpr (ADAM) adam(p, m, v, q, acc, lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void k_mlp_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -119,12 +236,7 @@ __global__ void k_mlp_adam(float *__restrict__ p, const float *__restrict__ g, f
                            float c2) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
-    const float gq = g[q];
-    const float mq = b1 * m[q] + (1.f - b1) * gq;
-    const float vq = b2 * v[q] + (1.f - b2) * gq * gq;
-    m[q] = mq;
-    v[q] = vq;
-    p[q] -= lr * (mq / c1) / (sqrtf(vq / c2) + eps);
+    adam(p, m, v, q, g[q], lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void k_standardize(float *__restrict__ X, int64_t n, int F, const float *__restrict__ norm) {
@@ -178,39 +290,97 @@ hipError_t costmodel_predict_device(Mlp &net, float *dX, int64_t B, float *dy, h
     return hipGetLastError();
 }
 
+// The inputs a model may have on the device: its parameters in 64 KiB of LDS.
+// (The kernels need less; the bound keeps what a model accepts.)
+static bool mlp_fits(const Mlp &net) { return sizeof(float) * (size_t)n_params_of(net.F) <= 64 * 1024; }
+
 hipError_t mlp_forward_device(Mlp &net, const float *dX, int64_t B, float *dy, hipStream_t st) {
     if (B == 0) return hipSuccess;
-    const size_t lds = sizeof(float) * (size_t)n_params_of(net.F);
-    k_mlp_sample<<<(unsigned)((B + 255) / 256), 256, lds, st>>>(net.p.as<float>(), net.F, dX, nullptr, B, dy, nullptr,
-                                                               nullptr, nullptr, nullptr, nullptr, nullptr);
+    if (!mlp_fits(net)) return hipErrorInvalidValue;
+    constexpr int S = 8;
+    const int64_t tiles = (B + S - 1) / S, blocks = (tiles + kMlpWaves - 1) / kMlpWaves;
+    // (staging W2 is amortised over a wave's tiles: no more workgroups than the chip holds)
+    k_mlp_rows<false, S><<<(unsigned)std::min<int64_t>(blocks, 1024), 64 * kMlpWaves, 0, st>>>(
+        net.p.as<float>(), net.F, dX, nullptr, B, dy, nullptr, nullptr);
     return hipGetLastError();
+}
+
+// Gradient over B device samples into dg, the squared errors into sq (device);
+// step: then the Adam step with it.
+static hipError_t grad_launch(Mlp &net, const float *dX, const float *dt, int64_t B, float *dg, float *sq, bool step,
+                              hipStream_t st) {
+    hipError_t e;
+    if (!mlp_fits(net)) return hipErrorInvalidValue;
+    constexpr int S = 4;
+    const int64_t np = n_params_of(net.F);
+    const size_t need = sizeof(float) * ((size_t)kParts * np + (size_t)B);
+    if (net.act.bytes < need) {
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        if ((e = net.act.alloc(need)) != hipSuccess) return e;
+    }
+    float *part = net.act.as<float>(), *ys = part + (size_t)kParts * np;
+    const int64_t tiles = (B + S - 1) / S;
+    const unsigned blocks = (unsigned)std::min<int64_t>((tiles + kMlpWaves - 1) / kMlpWaves, kParts / kMlpWaves);
+    // (a wave without a tile writes no part)
+    const int parts = (int)std::min<int64_t>(tiles, (int64_t)blocks * kMlpWaves);
+    k_mlp_rows<true, S><<<blocks, 64 * kMlpWaves, 0, st>>>(net.p.as<float>(), net.F, dX, dt, B, ys, part, sq);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const unsigned sb = (unsigned)((np + 63) / 64);
+    if (step) {
+        net.step += 1;
+        const float c1 = 1.f - std::pow(net.b1, (float)net.step);
+        const float c2 = 1.f - std::pow(net.b2, (float)net.step);
+        k_mlp_sum<true><<<sb, 256, 0, st>>>(part, parts, np, dg, net.p.as<float>(), net.m.as<float>(),
+                                            net.v.as<float>(), net.lr, net.b1, net.b2, net.eps, c1, c2);
+    } else {
+        k_mlp_sum<false><<<sb, 256, 0, st>>>(part, parts, np, dg, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 0.f,
+                                             0.f);
+    }
+    return hipGetLastError();
+}
+
+static double sum_of(const float *h, int64_t n) {
+    double acc = 0;
+    for (int64_t i = 0; i < n; ++i) acc += h[i];
+    return acc;
 }
 
 hipError_t mlp_grad_device(Mlp &net, const float *dX, const float *dt, int64_t B, float *dg, float *loss,
                            hipStream_t st) {
+    DevBuf sq;
     hipError_t e;
-    if ((size_t)B > net.cap) {
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        if ((e = net.act.alloc(sizeof(float) * (size_t)B * (4 * kH + 3))) != hipSuccess) return e;
-        net.cap = (size_t)B;
-    }
-    float *base = net.act.as<float>();
-    float *h1s = base, *dz1s = h1s + B * kH, *dz2s = dz1s + B * kH, *h2s = dz2s + B * kH;
-    float *dys = h2s + B * kH, *ys = dys + B, *sq = ys + B;
-    const size_t lds = sizeof(float) * (size_t)n_params_of(net.F);
-    k_mlp_sample<<<(unsigned)((B + 255) / 256), 256, lds, st>>>(net.p.as<float>(), net.F, dX, dt, B, ys, h1s, dz1s,
-                                                               dz2s, h2s, dys, sq);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const int64_t np = n_params_of(net.F);
-    k_mlp_reduce<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(net.F, dX, B, h1s, dz1s, dz2s, h2s, dys, dg);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (loss) {
-        std::vector<float> h(B);
-        if ((e = hipMemcpyAsync(h.data(), sq, sizeof(float) * B, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    if ((e = sq.alloc(sizeof(float) * B)) != hipSuccess) return e;
+    if ((e = grad_launch(net, dX, dt, B, dg, sq.as<float>(), false, st)) != hipSuccess) return e;
+    std::vector<float> h(B);
+    if ((e = hipMemcpyAsync(h.data(), sq.p, sizeof(float) * B, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    if (loss) *loss = (float)(sum_of(h.data(), B) / (double)B);
+    return hipSuccess;
+}
+
+hipError_t mlp_train_device(Mlp &net, const float *dX, const float *dt, int64_t B, int32_t epochs, int32_t batch,
+                            float *losses, hipStream_t st) {
+    hipError_t e;
+    DevBuf sq;
+    if ((e = sq.alloc(sizeof(float) * B)) != hipSuccess) return e;
+    std::vector<float> h(losses ? B : 0);
+    for (int32_t ep = 0; ep < epochs; ++ep) {
+        for (int64_t b0 = 0; b0 < B && e == hipSuccess; b0 += batch)
+            e = grad_launch(net, dX + b0 * net.F, dt + b0, std::min<int64_t>(batch, B - b0), net.g.as<float>(),
+                            sq.as<float>() + b0, true, st);
+        // the epoch's squared errors in one copy (the steps do not wait for it)
+        if (e == hipSuccess && losses)
+            e = hipMemcpyAsync(h.data(), sq.p, sizeof(float) * B, hipMemcpyDeviceToHost, st);
+        const hipError_t w = losses || ep + 1 == epochs || e != hipSuccess ? hipStreamSynchronize(st) : hipSuccess;
+        if (e == hipSuccess) e = w;
+        if (e != hipSuccess) return e;
+        if (!losses) continue;
         double acc = 0;
-        for (float x : h) acc += x;
-        *loss = (float)(acc / (double)B);
+        for (int64_t b0 = 0; b0 < B; b0 += batch) {
+            const int64_t nb = std::min<int64_t>(batch, B - b0);
+            acc += (double)(float)(sum_of(h.data() + b0, nb) / (double)nb) * nb;
+        }
+        losses[ep] = (float)(acc / (double)B);
     }
     return hipSuccess;
 }
