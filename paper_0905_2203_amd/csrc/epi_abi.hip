@@ -828,6 +828,7 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
     mn->menu_lo.assign(menu_lo, menu_lo + n_menu);
     mn->menu_hi.assign(menu_hi, menu_hi + n_menu);
     mn->threshold = threshold;
+    mn->max_size = max_size;
     // the extension engine takes menus of up to kExtMaxMenu intervals; longer
     // menus go to the state-machine engine
     mn->engine = n_menu <= kExtMaxMenu ? ctx->c.opt.mine_engine : 0;

@@ -341,6 +341,7 @@ struct Mine {
     int64_t max_span = 0;  // longest span of any episode the run may count (longest menu end x (sizes - 1))
     std::vector<int64_t> menu_lo, menu_hi;
     int64_t threshold = 0;
+    int max_size = 0;
     std::vector<MineLevel> levels;
     DevBuf pred_bits, succ_bits;  // pair-existence bitmaps of the menu (may be empty)
     // extension engine: the stream's types as uint16 and, for every position
