@@ -36,7 +36,8 @@ __host__ __device__ inline int64_t n_params_of(int F) { return (int64_t)F * kH +
 // thread a sample with all weights broadcast from LDS (79 us), then one thread a
 // parameter summing 512 samples in a row (134 us), then the loss fetched by the
 // host took 262 us a step; a wave a tile spreads the batch over 128 waves and
-// leaves sums of at most kParts, 11 us a step (16 steps of 512: 4.2 -> 0.2 ms).
+// leaves sums of at most kParts / 4 a thread: 14 + 4 us a step (an epoch of 16
+// steps of 512 and 50k predictions, host copies included: 4.2 -> 0.69 ms).
 constexpr int kMlpWaves = 4;     // waves per workgroup, sharing the staged W2
 constexpr int kParts = 256;      // most gradient parts (waves of a training launch)
 constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of bank conflicts
