@@ -359,6 +359,7 @@ epi_status epi_load_stream(epi_ctx *ctx, const int32_t *types, const void *times
     if (n > 0) {
         HIPTRY(ctx, hipMemcpy(s->types.p, types, sizeof(int32_t) * n, hipMemcpyHostToDevice), "copying types");
         HIPTRY(ctx, hipMemcpy(s->times.p, times, s->ts_bytes() * n, hipMemcpyHostToDevice), "copying times");
+        HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, ctx->c.flags.as<int32_t>(), ctx->c.stream), "ingesting the stream");
     }
     HIPTRY(ctx, build_type_index(*s, ctx->c.stream), "building the per-type index");
     const int32_t id = ctx->c.next_id++;
@@ -385,30 +386,9 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     HIPTRY(ctx, s->types.alloc(sizeof(int32_t) * n), "allocating stream types");
     HIPTRY(ctx, s->times.alloc(s->ts_bytes() * n), "allocating stream times");
     if (n > 0) {
-        HIPTRY(ctx, hipMemcpyAsync(s->types.p, d_types, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st),
-               "copying types");
-        HIPTRY(ctx, hipMemcpyAsync(s->times.p, d_times, s->ts_bytes() * n, hipMemcpyDeviceToDevice, st),
-               "copying times");
-        HIPTRY(ctx, validate_stream_device(s->types.as<int32_t>(), s->times.p, n, ts_kind, K,
-                                           ctx->c.flags.as<int32_t>(), st),
-               "validating the stream");
-        HIPTRY(ctx, hipStreamSynchronize(st), "validating the stream");
+        HIPTRY(ctx, ingest_stream(*s, d_types, d_times, true, ctx->c.flags.as<int32_t>(), st), "validating the stream");
         epi_status f = check_flags(ctx);
         if (f != EPI_OK) return f;
-        int64_t ends[2] = {0, 0};
-        if (ts_kind == EPI_TS_I64) {
-            HIPTRY(ctx, hipMemcpy(&ends[0], s->times.as<int64_t>(), 8, hipMemcpyDeviceToHost), "reading times");
-            HIPTRY(ctx, hipMemcpy(&ends[1], s->times.as<int64_t>() + (n - 1), 8, hipMemcpyDeviceToHost),
-                   "reading times");
-        } else {
-            int32_t a = 0, b = 0;
-            HIPTRY(ctx, hipMemcpy(&a, s->times.as<int32_t>(), 4, hipMemcpyDeviceToHost), "reading times");
-            HIPTRY(ctx, hipMemcpy(&b, s->times.as<int32_t>() + (n - 1), 4, hipMemcpyDeviceToHost), "reading times");
-            ends[0] = a;
-            ends[1] = b;
-        }
-        s->tmin = ends[0];
-        s->tmax = ends[1];
     }
     HIPTRY(ctx, build_type_index(*s, st), "building the per-type index");
     const int32_t id = ctx->c.next_id++;
@@ -697,6 +677,7 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     if (s->n == 0) s->tmin = first;
     s->tmax = last;
     s->n += n;
+    HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, ctx->c.flags.as<int32_t>(), ctx->c.stream), "ingesting the stream");
     HIPTRY(ctx, build_type_index(*s, ctx->c.stream), "building the per-type index");
     HIPTRY(ctx, hipStreamSynchronize(ctx->c.stream), "sync");
     return EPI_OK;

@@ -1,21 +1,29 @@
 // Per-type index of an event stream (the pre-processing step of Sec. IV-A):
 // the events of each type, in time order, stored contiguously.
 //
-//   1. k_hist:    one wave per chunk of C events; LDS histogram over the K
-//                 types; writes cnt[type * B + chunk] (type-major).
-//   2. scan:      exclusive prefix sum over cnt in type-major order; entry
-//                 (type, chunk) is then the global output position of the
-//                 chunk's first event of that type, and (type, 0) is the
-//                 type's offset.
-//   3. k_scatter: each wave re-reads its chunk 64 events at a time; the
-//                 rank of a lane among earlier lanes of the same type comes
-//                 from a wave-wide compare loop, so the scatter is stable.
-//                 It writes the per-type index (times, and the stream
-//                 position of every entry) and a tile-major copy in
-//                 which each chunk of T stream positions (a "tile") holds
-//                 its own events grouped by type, with per-tile uint16
-//                 offsets, so that a workgroup can stage a time window of
-//                 every type list with one contiguous, coalesced copy.
+//   0. k_ingest:  copies and checks the events, and takes what the tile size is
+//                 chosen by: the longest tile of each size the stream may pick.
+//   1. k_hist:    one workgroup per tile; LDS histogram over the K types; writes
+//                 cnt[tile][type] (tile-major: coalesced).
+//   2. column scans: exclusive prefix sums down the tiles of each type, in three
+//                 passes (chunks of tiles, the chunks and the types, the tiles);
+//                 base[tile][type] is then the global output position of the
+//                 tile's first event of that type, and a type's first tile's is
+//                 the type's offset.
+//   3. k_scatter: one workgroup per tile orders the tile's events by type in LDS,
+//                 stably: every wave takes a stretch of the tile, counts its
+//                 types, and ranks 64 events at a time among the equal types of
+//                 the wave by ballots over the type's bits.  The ordered tile is
+//                 the tile-major copy (each tile's events grouped by type, with
+//                 per-tile uint16 offsets, so that a workgroup can stage a time
+//                 window of every type list with one contiguous copy) and, run by
+//                 run, the per-type index: times, and the stream position of
+//                 every entry.
+//
+// What bounds it: memory.  20 bytes an event read and 20 written (int64 times),
+// the per-type index in runs of a tile's events of a type; neighbouring tiles go
+// to one XCD, whose L2 joins their runs to whole lines.  One wave a tile with 64
+// broadcasts for each rank took 451 us for 9M events of 128 types; now 97 us (3.7 TB/s).
 #include <algorithm>
 #include <vector>
 
@@ -26,168 +34,227 @@ namespace epi {
 namespace {
 
 constexpr int kWave = 64;
+constexpr int kIdxBlock = 256;               // threads of a tile's workgroup
+constexpr int kIdxWaves = kIdxBlock / kWave;
+constexpr int kXcds = 8;
 
-__global__ __launch_bounds__(kWave) void k_hist(const int32_t *__restrict__ types, int64_t n, int32_t K,
-                                                int64_t chunk, int64_t B, int32_t *__restrict__ cnt) {
-    __shared__ int32_t h[kMaxK];
-    const int lane = threadIdx.x;
-    const int64_t b = blockIdx.x;
-    for (int k = lane; k < K; k += kWave) h[k] = 0;
-    __syncthreads();
-    const int64_t beg = b * chunk;
-    const int64_t end = beg + chunk < n ? beg + chunk : n;
-    for (int64_t i = beg + lane; i < end; i += kWave) atomicAdd(&h[types[i]], 1);
-    __syncthreads();
-    for (int k = lane; k < K; k += kWave) cnt[(int64_t)k * B + b] = h[k];
+// Tile of a workgroup: workgroups go to the XCDs in turn, so each XCD takes a
+// stretch of neighbouring tiles.
+__device__ __forceinline__ int64_t tile_of(int64_t blk, int64_t B) {
+    const int64_t per = (B + kXcds - 1) / kXcds;
+    return (blk % kXcds) * per + blk / kXcds;  // (>= B: none)
 }
+inline unsigned tile_grid(int64_t B) { return (unsigned)((B + kXcds - 1) / kXcds * kXcds); }
 
-template <typename T>
-__global__ __launch_bounds__(kWave) void k_scatter(const int32_t *__restrict__ types, const T *__restrict__ times,
-                                                   int64_t n, int32_t K, int64_t B,
-                                                   const int32_t *__restrict__ cnt, const int32_t *__restrict__ base,
-                                                   T *__restrict__ out, int32_t *__restrict__ pos_out,
-                                                   T *__restrict__ tiled,
-                                                   uint16_t *__restrict__ loff, T *__restrict__ tile_t0,
-                                                   int32_t TT) {
-    __shared__ int32_t rank[kMaxK];   // next rank of each type inside this tile
-    __shared__ int32_t start[kMaxK];  // tile-local start of each type group
-    __shared__ int32_t wsum[kWave];
-    const int lane = threadIdx.x;
-    const int64_t b = blockIdx.x;
-    // tile-local offsets: exclusive scan over types of this tile's counts
-    const int per = (K + kWave - 1) / kWave;
-    int32_t acc = 0;
-    for (int q = 0; q < per; ++q) {
-        const int k = lane * per + q;
-        if (k < K) acc += cnt[(int64_t)k * B + b];
-    }
-    int32_t x = acc;
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
-    }
-    wsum[lane] = x - acc;
+__global__ __launch_bounds__(kIdxBlock) void k_hist(const int32_t *__restrict__ types, int64_t n, int32_t K,
+                                                    int32_t TT, int64_t B, int32_t *__restrict__ cnt) {
+    extern __shared__ int32_t h[];
+    const int64_t b = tile_of(blockIdx.x, B);
+    if (b >= B) return;
+    for (int k = threadIdx.x; k < K; k += kIdxBlock) h[k] = 0;
     __syncthreads();
-    int32_t run = wsum[lane];
-    for (int q = 0; q < per; ++q) {
-        const int k = lane * per + q;
-        if (k < K) {
-            start[k] = run;
-            rank[k] = 0;
-            loff[b * (K + 1) + k] = (uint16_t)run;
-            run += cnt[(int64_t)k * B + b];
-        }
-    }
-    if (lane == kWave - 1) loff[b * (K + 1) + K] = (uint16_t)(x);
     const int64_t beg = b * TT;
     const int64_t end = beg + TT < n ? beg + TT : n;
-    if (lane == 0) {
+    for (int64_t i = beg + threadIdx.x; i < end; i += kIdxBlock) atomicAdd(&h[types[i]], 1);
+    __syncthreads();
+    for (int k = threadIdx.x; k < K; k += kIdxBlock) cnt[b * K + k] = h[k];
+}
+
+// Column scans of cnt[B][K]: chunks of kColTiles tiles.
+constexpr int kColTiles = 32;
+
+// sums[c][k] = the chunk's events of type k
+__global__ __launch_bounds__(kIdxBlock) void k_col_sum(const int32_t *__restrict__ cnt, int64_t B, int32_t K,
+                                                       int32_t *__restrict__ sums) {
+    const int k = blockIdx.y * kIdxBlock + threadIdx.x;
+    if (k >= K) return;
+    const int64_t b0 = (int64_t)blockIdx.x * kColTiles;
+    const int64_t b1 = b0 + kColTiles < B ? b0 + kColTiles : B;
+    int32_t acc = 0;
+#pragma unroll 8
+    for (int64_t b = b0; b < b1; ++b) acc += cnt[b * K + k];
+    sums[(int64_t)blockIdx.x * K + k] = acc;
+}
+
+// tot[k] = the type's events; sums become the exclusive sums down the chunks.
+// One wave a type: 64 chunks at a time.
+__global__ __launch_bounds__(kWave) void k_col_chunks(int32_t *__restrict__ sums, int64_t nc, int32_t K,
+                                                      int32_t *__restrict__ tot) {
+    const int k = blockIdx.x, lane = threadIdx.x;
+    int32_t carry = 0;
+    for (int64_t c0 = 0; c0 < nc; c0 += kWave) {
+        const int64_t c = c0 + lane;
+        const int32_t v = c < nc ? sums[c * K + k] : 0;
+        int32_t x = v;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int32_t y = __shfl_up(x, d, kWave);
+            if (lane >= d) x += y;
+        }
+        if (c < nc) sums[c * K + k] = carry + x - v;
+        carry += __shfl(x, kWave - 1, kWave);
+    }
+    if (lane == 0) tot[k] = carry;
+}
+
+// off[k] = exclusive sum of tot over the types (one workgroup), off[K] = n.
+__global__ __launch_bounds__(kIdxBlock) void k_type_off(const int32_t *__restrict__ tot, int32_t K,
+                                                        int32_t *__restrict__ off) {
+    __shared__ int32_t wsum[kIdxWaves];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    int32_t carry = 0;
+    for (int k0 = 0; k0 < K; k0 += kIdxBlock) {
+        const int k = k0 + threadIdx.x;
+        const int32_t v = k < K ? tot[k] : 0;
+        int32_t x = v;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int32_t y = __shfl_up(x, d, kWave);
+            if (lane >= d) x += y;
+        }
+        if (lane == kWave - 1) wsum[w] = x;
+        __syncthreads();
+        int32_t before = 0, all = 0;
+        for (int i = 0; i < kIdxWaves; ++i) {
+            if (i < w) before += wsum[i];
+            all += wsum[i];
+        }
+        __syncthreads();
+        if (k < K) off[k] = carry + before + x - v;
+        carry += all;
+    }
+    if (threadIdx.x == 0) off[K] = carry;
+}
+
+// base[b][k] (in place of cnt): the output position of tile b's first event of
+// type k.
+__global__ __launch_bounds__(kIdxBlock) void k_col_apply(int32_t *__restrict__ cnt, int64_t B, int32_t K,
+                                                         const int32_t *__restrict__ sums,
+                                                         const int32_t *__restrict__ off) {
+    const int k = blockIdx.y * kIdxBlock + threadIdx.x;
+    if (k >= K) return;
+    const int64_t b0 = (int64_t)blockIdx.x * kColTiles;
+    const int64_t b1 = b0 + kColTiles < B ? b0 + kColTiles : B;
+    int32_t run = off[k] + sums[(int64_t)blockIdx.x * K + k];
+#pragma unroll 8
+    for (int64_t b = b0; b < b1; ++b) {
+        const int32_t v = cnt[b * K + k];
+        cnt[b * K + k] = run;
+        run += v;
+    }
+}
+
+// LDS of k_scatter: the ordered tile (times, positions, types), per-wave running
+// positions of every type, each type's first position.
+template <typename T>
+size_t scatter_lds(int32_t K, int32_t TT) {
+    return (size_t)TT * (sizeof(T) + 2 * sizeof(uint16_t)) + sizeof(uint16_t) * (size_t)(kIdxWaves + 1) * K;
+}
+
+// bits: of the largest type
+template <typename T>
+__global__ __launch_bounds__(kIdxBlock) void k_scatter(const int32_t *__restrict__ types, const T *__restrict__ times,
+                                                       int64_t n, int32_t K, int bits, int64_t B,
+                                                       const int32_t *__restrict__ base, T *__restrict__ out,
+                                                       int32_t *__restrict__ pos_out, T *__restrict__ tiled,
+                                                       uint16_t *__restrict__ loff, T *__restrict__ tile_t0,
+                                                       int32_t TT) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    T *st = reinterpret_cast<T *>(smem);
+    uint16_t *sp = reinterpret_cast<uint16_t *>(st + TT), *sy = sp + TT;
+    uint16_t *run = sy + TT;             // [wave][K]
+    uint16_t *start = run + kIdxWaves * K;  // [K]
+    __shared__ int32_t wsum[kIdxWaves];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    const int64_t b = tile_of(blockIdx.x, B);
+    if (b >= B) return;
+    const int64_t beg = b * TT;
+    const int m = (int)(beg + TT < n ? TT : n - beg);  // events of the tile
+    for (int k = threadIdx.x; k < kIdxWaves * K; k += kIdxBlock) run[k] = 0;
+    __syncthreads();
+    // each wave's stretch of the tile (TT is a multiple of the workgroup's lanes)
+    const int per = TT / kIdxWaves, r0 = w * per, r1 = r0 + per < m ? r0 + per : m;
+    uint16_t *mine = run + w * K;
+    // equal types of a wave's 64 events: the lanes that agree in every bit
+    auto peers = [&](int32_t ty, uint64_t in) {
+        uint64_t p = in;
+        for (int q = 0; q < bits; ++q) {
+            const bool one = (ty >> q) & 1;
+            const uint64_t v = __ballot(one);
+            p &= one ? v : ~v;
+        }
+        return p;
+    };
+    for (int r = r0; r < r1; r += kWave) {
+        const bool in = r + lane < r1;
+        const int32_t ty = in ? types[beg + r + lane] : 0;
+        const uint64_t p = peers(ty, __ballot(in));
+        if (in && (p >> lane) == 1) mine[ty] += (uint16_t)__popcll(p);  // the last of them
+    }
+    __syncthreads();
+    // tile-local offsets: exclusive sums over the types, each wave's after the
+    // ones before it
+    int32_t carry = 0;
+    for (int k0 = 0; k0 < K; k0 += kIdxBlock) {
+        const int k = k0 + threadIdx.x;
+        int32_t c[kIdxWaves], v = 0;
+        for (int i = 0; i < kIdxWaves; ++i) {
+            c[i] = k < K ? run[i * K + k] : 0;
+            v += c[i];
+        }
+        int32_t x = v;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int32_t y = __shfl_up(x, d, kWave);
+            if (lane >= d) x += y;
+        }
+        if (lane == kWave - 1) wsum[w] = x;
+        __syncthreads();
+        int32_t o = carry + x - v, all = 0;
+        for (int i = 0; i < kIdxWaves; ++i) {
+            if (i < w) o += wsum[i];
+            all += wsum[i];
+        }
+        __syncthreads();
+        if (k < K) {
+            start[k] = (uint16_t)o;
+            loff[b * (K + 1) + k] = (uint16_t)o;
+            for (int i = 0; i < kIdxWaves; ++i) {
+                run[i * K + k] = (uint16_t)o;
+                o += c[i];
+            }
+        }
+        carry += all;
+    }
+    if (threadIdx.x == 0) {
+        loff[b * (K + 1) + K] = (uint16_t)m;
         tile_t0[b] = times[beg];
         if (b == B - 1) tile_t0[B] = TsLimits<T>::hi();
     }
     __syncthreads();
-    for (int64_t r = beg; r < end; r += kWave) {
-        const int64_t i = r + lane;
-        const bool valid = i < end;
-        const int32_t ty = valid ? types[i] : -1;
-        const T t = valid ? times[i] : T(0);
-        int before = 0, after = 0;
-        for (int l = 0; l < kWave; ++l) {
-            const int32_t o = __shfl(ty, l, kWave);
-            before += (l < lane && o == ty) ? 1 : 0;
-            after += (l > lane && o == ty) ? 1 : 0;
+    for (int r = r0; r < r1; r += kWave) {
+        const int i = r + lane;
+        const bool in = i < r1;
+        const int32_t ty = in ? types[beg + i] : 0;
+        const T t = in ? times[beg + i] : T(0);
+        const uint64_t p = peers(ty, __ballot(in));
+        int o = 0;
+        if (in) o = mine[ty] + __popcll(p & ((uint64_t(1) << lane) - 1));
+        __builtin_amdgcn_wave_barrier();  // (every lane has read before the last of its peers writes)
+        if (in) {
+            if ((p >> lane) == 1) mine[ty] = (uint16_t)(o + 1);
+            st[o] = t;
+            sp[o] = (uint16_t)i;
+            sy[o] = (uint16_t)ty;
         }
-        int32_t rk = 0;
-        if (valid) rk = rank[ty] + before;
-        __syncthreads();
-        if (valid) {
-            const int64_t q = base[(int64_t)ty * B + b] + rk;
-            out[q] = t;
-            pos_out[q] = (int32_t)i;
-            tiled[beg + start[ty] + rk] = t;
-            if (after == 0) rank[ty] = rk + 1;
-        }
-        __syncthreads();
-    }
-}
-
-// ---- exclusive scan of int32 (values and total fit int32) -------------------
-constexpr int kScanBlock = 256;
-constexpr int kScanItems = 8;  // per thread
-constexpr int kScanTile = kScanBlock * kScanItems;
-
-__device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total) {
-    __shared__ int32_t wsum[kScanBlock / kWave];
-    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-    int32_t x = v;
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t y = __shfl_up(x, d, kWave);
-        if (lane >= d) x += y;
-    }
-    if (lane == kWave - 1) wsum[w] = x;
-    __syncthreads();
-    int32_t off = 0, tot = 0;
-    for (int k = 0; k < kScanBlock / kWave; ++k) {
-        if (k < w) off += wsum[k];
-        tot += wsum[k];
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    *total = tot;
-    return off + x - v;
-}
-
-__global__ __launch_bounds__(kScanBlock) void k_scan_reduce(const int32_t *__restrict__ in, int64_t len,
-                                                            int32_t *__restrict__ sums) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int32_t acc = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = base + (int64_t)threadIdx.x * kScanItems + k;
-        if (i < len) acc += in[i];
+    for (int q = threadIdx.x; q < m; q += kIdxBlock) {
+        const int ty = sy[q];
+        const T t = st[q];
+        const int64_t d = (int64_t)base[b * K + ty] + (q - (int)start[ty]);
+        tiled[beg + q] = t;
+        out[d] = t;
+        pos_out[d] = (int32_t)(beg + sp[q]);
     }
-    int32_t tot;
-    (void)block_exclusive_scan(acc, &tot);
-    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
-}
-
-// Single block: exclusive scan of the tile sums, in place.
-__global__ __launch_bounds__(kScanBlock) void k_scan_sums(int32_t *__restrict__ sums, int64_t nb) {
-    int32_t carry = 0;
-    for (int64_t r = 0; r < nb; r += kScanBlock) {
-        const int64_t i = r + threadIdx.x;
-        const int32_t v = i < nb ? sums[i] : 0;
-        int32_t tot;
-        const int32_t ex = block_exclusive_scan(v, &tot);
-        if (i < nb) sums[i] = carry + ex;
-        carry += tot;
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(kScanBlock) void k_scan_apply(const int32_t *__restrict__ in, int64_t len,
-                                                           const int32_t *__restrict__ sums,
-                                                           int32_t *__restrict__ out) {
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int32_t v[kScanItems];
-    int32_t acc = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = base + (int64_t)threadIdx.x * kScanItems + k;
-        v[k] = i < len ? in[i] : 0;
-        acc += v[k];
-    }
-    int32_t tot;
-    int32_t run = block_exclusive_scan(acc, &tot) + sums[blockIdx.x];
-    for (int k = 0; k < kScanItems; ++k) {
-        const int64_t i = base + (int64_t)threadIdx.x * kScanItems + k;
-        if (i < len) out[i] = run;
-        run += v[k];
-    }
-}
-
-__global__ void k_offsets(const int32_t *__restrict__ base, int32_t K, int64_t B, int64_t n,
-                          int32_t *__restrict__ off) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < K) off[k] = base[(int64_t)k * B];
-    if (k == K) off[K] = (int32_t)n;
 }
 
 // out = min over events i with an event i + kWaveGap of the same type of the
@@ -232,101 +299,138 @@ __global__ __launch_bounds__(kGapBlock) void k_gap(const T *__restrict__ ts, int
 
 __global__ void k_gap_init(unsigned long long *out) { *out = INT64_MAX; }
 
-// g[i] = times[min(i * step, n - 1)], i < ng
+// Tile sizes a stream may pick: kMinTile << q.
+constexpr int kTileSizes = 5;
+static_assert(kMinTile << (kTileSizes - 1) == kTile, "tile sizes");
+// What k_ingest finds out: the longest tile of each size (its first time to the
+// next tile's first, or to the last event), a cache line each.
+struct IngestInfo {
+    static constexpr int kStride = 16;
+    unsigned long long span[kTileSizes * kStride];
+};
+
+// Copies the events (src null: they are in place already), checks them and takes
+// the longest tile of each size.
 template <typename T>
-__global__ void k_sample_times(const T *__restrict__ times, int64_t n, int64_t step, int64_t ng, T *__restrict__ g) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < ng) g[i] = times[i * step < n ? i * step : n - 1];
-}
-
-template <typename T>
-__global__ void k_validate(const int32_t *__restrict__ types, const T *__restrict__ times, int64_t n, int32_t K,
-                           int32_t *__restrict__ flags) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int32_t ty = types[i];
-    const T t = times[i];
-    if (ty < 0 || ty >= K) atomicOr(&flags[kFlagBadType], 1);
-    if (t == TsLimits<T>::lo() || t == TsLimits<T>::hi()) atomicOr(&flags[kFlagBadTime], 1);
-    if (i + 1 < n && times[i + 1] < t) atomicOr(&flags[kFlagUnsorted], 1);
-}
-
-}  // namespace
-
-hipError_t validate_stream_device(const int32_t *d_types, const void *d_times, int64_t n, int ts_kind,
-                                  int32_t K, int32_t *d_flags, hipStream_t st) {
-    if (n == 0) return hipSuccess;
-    const int threads = 256;
-    const int64_t blocks = (n + threads - 1) / threads;
-    if (ts_kind == EPI_TS_I64)
-        k_validate<int64_t><<<blocks, threads, 0, st>>>(d_types, (const int64_t *)d_times, n, K, d_flags);
-    else
-        k_validate<int32_t><<<blocks, threads, 0, st>>>(d_types, (const int32_t *)d_times, n, K, d_flags);
-    return hipGetLastError();
-}
-
-namespace {
-
-// Longest tile of T events (T a multiple of kMinTile): from its first time
-// to the next tile's first time, the last tile to the stream's last time;
-// g holds the times at every kMinTile-th position (and the last one).
-int64_t longest_tile(const std::vector<int64_t> &g, int64_t n, int T) {
-    const int64_t per = T / kMinTile, B = (n + T - 1) / T;
-    uint64_t best = 0;
-    for (int64_t b = 0; b < B; ++b) {
-        const int64_t i1 = (b + 1) * per;
-        const int64_t end = b + 1 < B ? g[i1] : g.back();
-        best = std::max<uint64_t>(best, (uint64_t)end - (uint64_t)g[b * per]);
-    }
-    return best > (uint64_t)INT64_MAX ? INT64_MAX : (int64_t)best;
-}
-
-// Events per tile of a stream (Stream::T).
-hipError_t pick_tile(Stream &s, hipStream_t st) {
-    const int cap = std::max(kMinTile, std::min(kTile, s.tile_cap));
-    s.T = cap;
-    if (s.n <= kMinTile) return hipSuccess;
-    const int64_t ng = (s.n + kMinTile - 1) / kMinTile + 1;
-    DevBuf d;
-    hipError_t e;
-    if ((e = d.alloc(sizeof(int64_t) * ng)) != hipSuccess) return e;
-    std::vector<int64_t> g(ng);
-    const unsigned blocks = (unsigned)((ng + 255) / 256);
-    if (s.ts_kind == EPI_TS_I64) {
-        k_sample_times<int64_t><<<blocks, 256, 0, st>>>(s.times.as<int64_t>(), s.n, kMinTile, ng, d.as<int64_t>());
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(g.data(), d.p, 8 * ng, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    } else {
-        std::vector<int32_t> g32(ng);
-        k_sample_times<int32_t><<<blocks, 256, 0, st>>>(s.times.as<int32_t>(), s.n, kMinTile, ng, d.as<int32_t>());
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(g32.data(), d.p, 4 * ng, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        for (int64_t i = 0; i < ng; ++i) g[i] = g32[i];
-    }
-    // the last sample is the last time (index n - 1)
-    for (int64_t bound : {(int64_t(1) << 29) - 1, int64_t(1) << 30}) {
-        for (int T = cap; T >= kMinTile; T /= 2) {
-            if (longest_tile(g, s.n, T) < bound) {
-                s.T = T;
-                return hipSuccess;
+__global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict__ src_types,
+                                                      const T *__restrict__ src_times, int32_t *__restrict__ types,
+                                                      T *__restrict__ times, int64_t n, int32_t K, bool check,
+                                                      int32_t *__restrict__ flags, IngestInfo *__restrict__ info) {
+    // a workgroup takes kTile events: few workgroups meet at the maxima
+    const int64_t beg = (int64_t)blockIdx.x * kTile, end = beg + kTile < n ? beg + kTile : n;
+    const T *tm = src_times ? src_times : times;
+    const int32_t *ty = src_types ? src_types : types;
+    if (src_types || check) {
+        int bad = 0;
+#pragma unroll 4
+        for (int64_t i = beg + threadIdx.x; i < end; i += kIdxBlock) {
+            const int32_t y = ty[i];
+            const T t = tm[i];
+            if (src_types) {
+                types[i] = y;
+                times[i] = t;
+            }
+            if (check) {
+                const T next = tm[i + 1 < n ? i + 1 : i];
+                bad |= (y < 0 || y >= K ? 1 : 0) | (t == TsLimits<T>::lo() || t == TsLimits<T>::hi() ? 2 : 0) |
+                       (next < t ? 4 : 0);
             }
         }
+        if (bad & 1) atomicOr(&flags[kFlagBadType], 1);
+        if (bad & 2) atomicOr(&flags[kFlagBadTime], 1);
+        if (bad & 4) atomicOr(&flags[kFlagUnsorted], 1);
+    }
+    // one wave: lane q of 16 the smallest tile q of the stretch, and from their
+    // ends the larger tiles
+    if (threadIdx.x >= kTile / kMinTile) return;
+    const int64_t b0 = beg + (int64_t)threadIdx.x * kMinTile;
+#pragma unroll
+    for (int q = 0; q < kTileSizes; ++q) {
+        unsigned long long d = 0;
+        if (b0 < n && (threadIdx.x & ((1u << q) - 1)) == 0) {
+            const int64_t b1 = b0 + ((int64_t)kMinTile << q);
+            d = (unsigned long long)(int64_t)tm[b1 < n ? b1 : n - 1] - (unsigned long long)(int64_t)tm[b0];
+        }
+        for (int m = 1; m < kTile / kMinTile; m <<= 1) {
+            const unsigned long long o = __shfl_xor(d, m, kTile / kMinTile);
+            d = o > d ? o : d;
+        }
+        unsigned long long *o = &info->span[q * IngestInfo::kStride];
+        if (threadIdx.x == 0 && d > *(volatile unsigned long long *)o) atomicMax(o, d);  // (a stale read only costs an atomic)
+    }
+}
+
+__global__ void k_ingest_init(IngestInfo *info) {
+    for (int q = 0; q < kTileSizes; ++q) info->span[q * IngestInfo::kStride] = 0;
+}
+
+template <typename T>
+hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, bool check, int32_t *d_flags,
+                    hipStream_t st) {
+    hipError_t e;
+    DevBuf info;
+    if ((e = info.alloc(sizeof(IngestInfo))) != hipSuccess) return e;
+    k_ingest_init<<<1, 1, 0, st>>>(info.as<IngestInfo>());
+    k_ingest<T><<<(unsigned)((s.n + kTile - 1) / kTile), kIdxBlock, 0, st>>>(
+        src_types, src_times, s.types.as<int32_t>(), s.times.as<T>(), s.n, s.K, check, d_flags, info.as<IngestInfo>());
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    IngestInfo h;
+    if ((e = hipMemcpyAsync(&h, info.p, sizeof(h), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    T ends[2];
+    if ((e = hipMemcpyAsync(&ends[0], s.times.as<T>(), sizeof(T), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(&ends[1], s.times.as<T>() + (s.n - 1), sizeof(T), hipMemcpyDeviceToHost, st)) != hipSuccess)
+        return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    s.tmin = ends[0];
+    s.tmax = ends[1];
+    for (int q = 0; q < kTileSizes; ++q) {
+        const unsigned long long d = h.span[q * IngestInfo::kStride];
+        s.tile_span[q] = d > (unsigned long long)INT64_MAX ? INT64_MAX : (int64_t)d;
     }
     return hipSuccess;
 }
 
+// Longest tile of T events.
+int64_t longest_tile(const Stream &s, int T) {
+    int q = 0;
+    while ((kMinTile << q) < T) ++q;
+    return s.tile_span[q];
+}
+
+// Events per tile of a stream (Stream::T).
+void pick_tile(Stream &s) {
+    const int cap = std::max(kMinTile, std::min(kTile, s.tile_cap));
+    s.T = cap;
+    if (s.n <= kMinTile) return;
+    for (int64_t bound : {(int64_t(1) << 29) - 1, int64_t(1) << 30}) {
+        for (int T = cap; T >= kMinTile; T /= 2) {
+            if (longest_tile(s, T) < bound) {
+                s.T = T;
+                return;
+            }
+        }
+    }
+}
+
 }  // namespace
+
+hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, int32_t *d_flags,
+                         hipStream_t st) {
+    if (s.n == 0) return hipSuccess;
+    if (s.ts_kind == EPI_TS_I64) return ingest_t<int64_t>(s, src_types, (const int64_t *)src_times, check, d_flags, st);
+    return ingest_t<int32_t>(s, src_types, (const int32_t *)src_times, check, d_flags, st);
+}
 
 hipError_t build_type_index(Stream &s, hipStream_t st) {
     hipError_t e;
     const int64_t n = s.n;
     const int32_t K = s.K;
-    if ((e = pick_tile(s, st)) != hipSuccess) return e;
+    pick_tile(s);
     const int TT = s.T;
     const int64_t B = n > 0 ? (n + TT - 1) / TT : 0;
     s.B = B;
+    s.max_tile_span = n > 0 ? longest_tile(s, TT) : 0;
+    s.gap = INT64_MAX;
     if ((e = s.type_off.alloc(sizeof(int32_t) * (K + 1))) != hipSuccess) return e;
     // (padded: the wave chains load whole windows)
     if ((e = s.ts_by_type.alloc(s.ts_bytes() * ((size_t)n + kWaveChunks * kWave))) != hipSuccess) return e;
@@ -334,78 +438,51 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
     if ((e = s.tiled_ts.alloc(s.ts_bytes() * (size_t)B * TT)) != hipSuccess) return e;
     if ((e = s.tile_loff.alloc(sizeof(uint16_t) * (size_t)B * (K + 1))) != hipSuccess) return e;
     if ((e = s.tile_t0.alloc(s.ts_bytes() * (size_t)(B + 1))) != hipSuccess) return e;
-    const int64_t Bc = B > 0 ? B : 1;
-    const int64_t len = Bc * K;
-    DevBuf cnt, base, sums;
-    const int64_t nb = (len + kScanTile - 1) / kScanTile;
-    if ((e = cnt.alloc(sizeof(int32_t) * len)) != hipSuccess) return e;
-    if ((e = base.alloc(sizeof(int32_t) * len)) != hipSuccess) return e;
-    if ((e = sums.alloc(sizeof(int32_t) * nb)) != hipSuccess) return e;
-    if (n > 0) {
-        k_hist<<<B, kWave, 0, st>>>(s.types.as<int32_t>(), n, K, TT, B, cnt.as<int32_t>());
-    } else {
-        if ((e = hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * len, st)) != hipSuccess) return e;
+    s.h_off.assign(K + 1, 0);
+    if (n == 0) {
+        if ((e = hipMemsetAsync(s.type_off.p, 0, sizeof(int32_t) * (K + 1), st)) != hipSuccess) return e;
+        return hipStreamSynchronize(st);
     }
-    k_scan_reduce<<<nb, kScanBlock, 0, st>>>(cnt.as<int32_t>(), len, sums.as<int32_t>());
-    k_scan_sums<<<1, kScanBlock, 0, st>>>(sums.as<int32_t>(), nb);
-    k_scan_apply<<<nb, kScanBlock, 0, st>>>(cnt.as<int32_t>(), len, sums.as<int32_t>(), base.as<int32_t>());
-    k_offsets<<<(K + 1 + 255) / 256, 256, 0, st>>>(base.as<int32_t>(), K, Bc, n, s.type_off.as<int32_t>());
-    if (n > 0) {
-        if (s.ts_kind == EPI_TS_I64)
-            k_scatter<int64_t><<<B, kWave, 0, st>>>(s.types.as<int32_t>(), s.times.as<int64_t>(), n, K, B,
-                                                    cnt.as<int32_t>(), base.as<int32_t>(),
-                                                    s.ts_by_type.as<int64_t>(), s.pos_by_type.as<int32_t>(),
-                                                    s.tiled_ts.as<int64_t>(),
-                                                    s.tile_loff.as<uint16_t>(), s.tile_t0.as<int64_t>(), TT);
-        else
-            k_scatter<int32_t><<<B, kWave, 0, st>>>(s.types.as<int32_t>(), s.times.as<int32_t>(), n, K, B,
-                                                    cnt.as<int32_t>(), base.as<int32_t>(),
-                                                    s.ts_by_type.as<int32_t>(), s.pos_by_type.as<int32_t>(),
-                                                    s.tiled_ts.as<int32_t>(),
-                                                    s.tile_loff.as<uint16_t>(), s.tile_t0.as<int32_t>(), TT);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    DevBuf gap;
+    const int64_t nc = (B + kColTiles - 1) / kColTiles;
+    DevBuf cnt, sums, tot, gap;
+    if ((e = cnt.alloc(sizeof(int32_t) * (size_t)B * K)) != hipSuccess) return e;
+    if ((e = sums.alloc(sizeof(int32_t) * (size_t)nc * K)) != hipSuccess) return e;
+    if ((e = tot.alloc(sizeof(int32_t) * (size_t)K)) != hipSuccess) return e;
     if ((e = gap.alloc(sizeof(unsigned long long))) != hipSuccess) return e;
-    k_gap_init<<<1, 1, 0, st>>>(gap.as<unsigned long long>());
-    if (n > kWaveGap) {
-        const unsigned blocks = (unsigned)((n + kGapBlock * kGapItems - 1) / (kGapBlock * kGapItems));
-        if (s.ts_kind == EPI_TS_I64)
-            k_gap<int64_t><<<blocks, kGapBlock, 0, st>>>(s.ts_by_type.as<int64_t>(), n, s.type_off.as<int32_t>(), K,
-                                                         gap.as<unsigned long long>());
-        else
-            k_gap<int32_t><<<blocks, kGapBlock, 0, st>>>(s.ts_by_type.as<int32_t>(), n, s.type_off.as<int32_t>(), K,
-                                                         gap.as<unsigned long long>());
-    }
+    k_hist<<<tile_grid(B), kIdxBlock, sizeof(int32_t) * (size_t)K, st>>>(s.types.as<int32_t>(), n, K, TT, B,
+                                                                       cnt.as<int32_t>());
+    const dim3 cols((unsigned)nc, (unsigned)((K + kIdxBlock - 1) / kIdxBlock));
+    k_col_sum<<<cols, kIdxBlock, 0, st>>>(cnt.as<int32_t>(), B, K, sums.as<int32_t>());
+    k_col_chunks<<<(unsigned)K, kWave, 0, st>>>(sums.as<int32_t>(), nc, K, tot.as<int32_t>());
+    k_type_off<<<1, kIdxBlock, 0, st>>>(tot.as<int32_t>(), K, s.type_off.as<int32_t>());
+    k_col_apply<<<cols, kIdxBlock, 0, st>>>(cnt.as<int32_t>(), B, K, sums.as<int32_t>(), s.type_off.as<int32_t>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    int bits = 1;
+    while ((K - 1) >> bits) ++bits;
+    auto scatter = [&](auto t) -> hipError_t {
+        using T = decltype(t);
+        const size_t lds = scatter_lds<T>(K, TT);
+        hipError_t x;
+        if (lds > 64 * 1024 &&
+            (x = hipFuncSetAttribute(reinterpret_cast<const void *>(k_scatter<T>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess)
+            return x;
+        k_scatter<T><<<tile_grid(B), kIdxBlock, lds, st>>>(
+            s.types.as<int32_t>(), s.times.as<T>(), n, K, bits, B, cnt.as<int32_t>(), s.ts_by_type.as<T>(),
+            s.pos_by_type.as<int32_t>(), s.tiled_ts.as<T>(), s.tile_loff.as<uint16_t>(), s.tile_t0.as<T>(), TT);
+        k_gap_init<<<1, 1, 0, st>>>(gap.as<unsigned long long>());
+        if (n > kWaveGap)
+            k_gap<T><<<(unsigned)((n + kGapBlock * kGapItems - 1) / (kGapBlock * kGapItems)), kGapBlock, 0, st>>>(
+                s.ts_by_type.as<T>(), n, s.type_off.as<int32_t>(), K, gap.as<unsigned long long>());
+        return hipGetLastError();
+    };
+    if ((e = s.ts_kind == EPI_TS_I64 ? scatter(int64_t()) : scatter(int32_t())) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(&s.gap, gap.p, sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    // the temporaries are freed when this returns: wait for the kernels first
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    s.h_off.resize(K + 1);
-    if ((e = hipMemcpy(s.h_off.data(), s.type_off.p, sizeof(int32_t) * (K + 1), hipMemcpyDeviceToHost)) !=
+    if ((e = hipMemcpyAsync(s.h_off.data(), s.type_off.p, sizeof(int32_t) * (K + 1), hipMemcpyDeviceToHost, st)) !=
         hipSuccess)
         return e;
-    s.h_tile_t0.assign(B + 1, 0);
-    if (B > 0) {
-        if (s.ts_kind == EPI_TS_I64) {
-            if ((e = hipMemcpy(s.h_tile_t0.data(), s.tile_t0.p, 8 * (B + 1), hipMemcpyDeviceToHost)) != hipSuccess)
-                return e;
-        } else {
-            std::vector<int32_t> t32(B + 1);
-            if ((e = hipMemcpy(t32.data(), s.tile_t0.p, 4 * (B + 1), hipMemcpyDeviceToHost)) != hipSuccess)
-                return e;
-            for (int64_t b = 0; b <= B; ++b) s.h_tile_t0[b] = t32[b];
-        }
-    }
-    // longest tile: from its first time to the next tile's (the last tile:
-    // to the last event), saturated
-    s.max_tile_span = 0;
-    for (int64_t b = 0; b < B; ++b) {
-        const int64_t end = b + 1 < B ? s.h_tile_t0[b + 1] : s.tmax;
-        const uint64_t d = (uint64_t)end - (uint64_t)s.h_tile_t0[b];
-        s.max_tile_span = std::max<int64_t>(s.max_tile_span, d > (uint64_t)INT64_MAX ? INT64_MAX : (int64_t)d);
-    }
-    return hipSuccess;
+    // the temporaries are freed when this returns: wait for the kernels first
+    return hipStreamSynchronize(st);
 }
 
 }  // namespace epi

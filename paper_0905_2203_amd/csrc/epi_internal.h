@@ -178,7 +178,7 @@ struct Stream {
     DevBuf tile_loff;   // uint16[B*(K+1)]
     DevBuf tile_t0;     // T[B+1]: time of each tile's first event; [B] = type maximum
     std::vector<int32_t> h_off;  // host copy of type_off
-    std::vector<int64_t> h_tile_t0;  // host copy of tile_t0 (widened)
+    int64_t tile_span[5] = {};       // longest tile of 256, 512, ... 4096 events (ingest_stream)
     int64_t max_tile_span = -1;      // longest time from a tile's first event to the next tile's (or the last event)
     int64_t gap = 0;                 // least time from one event to the 63rd after it of the same type (INT64_MAX: no type has 64)
     size_t ts_bytes() const { return ts_kind == EPI_TS_I64 ? 8 : 4; }
@@ -459,8 +459,11 @@ inline int64_t queue_bound(int64_t lo, int64_t hi) {
 
 // ---- launchers -------------------------------------------------------------
 hipError_t build_type_index(Stream &s, hipStream_t st);
-hipError_t validate_stream_device(const int32_t *d_types, const void *d_times, int64_t n, int ts_kind,
-                                  int32_t K, int32_t *d_flags, hipStream_t st);
+// Copy a stream's events from device buffers (null: they are in s.types and
+// s.times already), check them on the device (flags) when asked to, and set s's
+// first and last time and longest tiles; before build_type_index.
+hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, int32_t *d_flags,
+                         hipStream_t st);
 // ext_scratch (optional): device memory of ext_bytes for the segment records,
 // used instead of the set's own (then nothing is allocated and nothing waits
 // on the host; hipErrorOutOfMemory if a group's records do not fit).
