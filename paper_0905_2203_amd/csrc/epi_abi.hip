@@ -261,6 +261,17 @@ CandSet *find_set(epi_ctx *ctx, int32_t id) {
 
 hipStream_t pick_stream(epi_ctx *ctx, void *s) { return s ? (hipStream_t)s : ctx->c.stream; }
 
+// Index an ingested stream and hand out its id.
+epi_status finish_load(epi_ctx *ctx, std::unique_ptr<Stream> s, hipStream_t st, int32_t *stream_id) {
+    const hipError_t e = build_type_index(*s, st);
+    if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
+    HIPTRY(ctx, e, "building the per-type index");
+    const int32_t id = ctx->c.next_id++;
+    ctx->c.streams[id] = std::move(s);
+    *stream_id = id;
+    return EPI_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -306,6 +317,7 @@ void epi_destroy(epi_ctx *ctx) {
     ctx->c.streams.clear();
     ctx->c.flags.reset();
     ctx->c.cache.release();
+    ctx->c.idle.release();
     if (ctx->c.stage) (void)hipHostFree(ctx->c.stage);
     if (ctx->c.stream) (void)hipStreamDestroy(ctx->c.stream);
     delete ctx;
@@ -343,29 +355,34 @@ epi_status epi_load_stream(epi_ctx *ctx, const int32_t *types, const void *times
                            int32_t K, int32_t *stream_id) {
     if (!ctx || !stream_id) return fail(ctx, EPI_EINVAL, "null argument");
     std::string msg;
-    epi_status v = check_stream(types, times, n, ts_kind, K, &msg);
+    // shape checks only; the element checks run on the device
+    epi_status v = check_stream(nullptr, nullptr, 0, ts_kind, K, &msg);
     if (v != EPI_OK) return fail(ctx, v, "%s", msg.c_str());
+    if (n < 0 || n >= (int64_t(1) << 31)) return fail(ctx, EPI_ESIZE, "n must be in [0, 2^31)");
+    if (n > 0 && (!types || !times)) return fail(ctx, EPI_EINVAL, "null stream pointer");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    CacheScope scope(&ctx->c.idle);
+    hipStream_t st = ctx->c.stream;
     auto s = std::make_unique<Stream>();
     s->n = n;
     s->K = K;
     s->ts_kind = ts_kind;
-    if (n > 0) {
-        s->tmin = ts_kind == EPI_TS_I64 ? ((const int64_t *)times)[0] : ((const int32_t *)times)[0];
-        s->tmax = ts_kind == EPI_TS_I64 ? ((const int64_t *)times)[n - 1] : ((const int32_t *)times)[n - 1];
-    }
     HIPTRY(ctx, s->types.alloc(sizeof(int32_t) * n), "allocating stream types");
     HIPTRY(ctx, s->times.alloc(s->ts_bytes() * n), "allocating stream times");
     if (n > 0) {
-        HIPTRY(ctx, hipMemcpy(s->types.p, types, sizeof(int32_t) * n, hipMemcpyHostToDevice), "copying types");
-        HIPTRY(ctx, hipMemcpy(s->times.p, times, s->ts_bytes() * n, hipMemcpyHostToDevice), "copying times");
-        HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, ctx->c.flags.as<int32_t>(), ctx->c.stream), "ingesting the stream");
+        hipError_t e = hipMemcpyAsync(s->types.p, types, sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = hipMemcpyAsync(s->times.p, times, s->ts_bytes() * n, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = ingest_stream(*s, nullptr, nullptr, true, ctx->c.flags.as<int32_t>(), st);
+        if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
+        HIPTRY(ctx, e, "copying the stream");
+        epi_status f = check_flags(ctx);
+        if (f != EPI_OK) {
+            // the first violation in stream order, and its message
+            v = check_stream(types, times, n, ts_kind, K, &msg);
+            return v != EPI_OK ? fail(ctx, v, "%s", msg.c_str()) : f;
+        }
     }
-    HIPTRY(ctx, build_type_index(*s, ctx->c.stream), "building the per-type index");
-    const int32_t id = ctx->c.next_id++;
-    ctx->c.streams[id] = std::move(s);
-    *stream_id = id;
-    return EPI_OK;
+    return finish_load(ctx, std::move(s), st, stream_id);
 }
 
 epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const void *d_times, int64_t n, int ts_kind,
@@ -378,6 +395,7 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     if (n < 0 || n >= (int64_t(1) << 31)) return fail(ctx, EPI_ESIZE, "n must be in [0, 2^31)");
     if (n > 0 && (!d_types || !d_times)) return fail(ctx, EPI_EINVAL, "null stream pointer");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    CacheScope scope(&ctx->c.idle);
     hipStream_t st = pick_stream(ctx, hip_stream);
     auto s = std::make_unique<Stream>();
     s->n = n;
@@ -386,15 +404,13 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     HIPTRY(ctx, s->types.alloc(sizeof(int32_t) * n), "allocating stream types");
     HIPTRY(ctx, s->times.alloc(s->ts_bytes() * n), "allocating stream times");
     if (n > 0) {
-        HIPTRY(ctx, ingest_stream(*s, d_types, d_times, true, ctx->c.flags.as<int32_t>(), st), "validating the stream");
+        const hipError_t e = ingest_stream(*s, d_types, d_times, true, ctx->c.flags.as<int32_t>(), st);
+        if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
+        HIPTRY(ctx, e, "validating the stream");
         epi_status f = check_flags(ctx);
         if (f != EPI_OK) return f;
     }
-    HIPTRY(ctx, build_type_index(*s, st), "building the per-type index");
-    const int32_t id = ctx->c.next_id++;
-    ctx->c.streams[id] = std::move(s);
-    *stream_id = id;
-    return EPI_OK;
+    return finish_load(ctx, std::move(s), st, stream_id);
 }
 
 epi_status epi_stream_info(epi_ctx *ctx, int32_t stream_id, int64_t *n, int32_t *K, int *ts_kind) {
@@ -450,12 +466,16 @@ epi_status epi_submit_candidates(epi_ctx *ctx, int32_t stream_id, int64_t m, con
                         (long long)c);
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    CacheScope scope(&ctx->c.idle);
     auto cs = std::make_unique<CandSet>();
     cs->stream_id = stream_id;
     cs->m = m;
     hipError_t e = s->ts_kind == EPI_TS_I64 ? upload_candidates<int64_t>(*cs, m, N, types, lo, hi, ctx->c.stream)
                                             : upload_candidates<int32_t>(*cs, m, N, types, lo, hi, ctx->c.stream);
-    if (e != hipSuccess) return hipfail(ctx, e, "uploading candidates");
+    if (e != hipSuccess) {
+        (void)hipDeviceSynchronize();  // (the buffers go back idle)
+        return hipfail(ctx, e, "uploading candidates");
+    }
     cs->stream_order = ctx->c.opt.stream_order;
     cs->max_span = max_span;
     {
@@ -521,6 +541,7 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
             return fail(ctx, EPI_ESTATE, "set %d has no work log to schedule by", set_ids[i]);
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle);
     hipStream_t st = pick_stream(ctx, hip_stream);
     if (mode == EPI_MODE_INCREMENTAL) {
         // sets never counted: a full count; sets counted before an append:
@@ -618,7 +639,10 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
     for (int32_t i = 0; i < k; ++i) {
         CandSet *cs = find_set(ctx, set_ids[i]);
         Stream *s = find_stream(ctx, cs->stream_id);
-        HIPTRY(ctx, launch_count(*s, *cs, ctx->c.opt, ctx->c.flags.as<int32_t>(), st), "launching the count");
+        {
+            CacheScope scope(&ctx->c.idle);  // (the set's segment records)
+            HIPTRY(ctx, launch_count(*s, *cs, ctx->c.opt, ctx->c.flags.as<int32_t>(), st), "launching the count");
+        }
         HIPTRY(ctx, count_deep_subset(*s, *cs, st), "counting deep episodes");
         cs->counted = true;
         cs->counted_n = s->n;
@@ -663,15 +687,25 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     HIPTRY(ctx, hipDeviceSynchronize(), "sync");
     ctx->c.batch.evict_all();
     const size_t tb = s->ts_bytes();
+    CacheScope scope(&ctx->c.idle);
+    hipStream_t st = ctx->c.stream;
     DevBuf ty, tm;
     HIPTRY(ctx, ty.alloc(sizeof(int32_t) * (size_t)(s->n + n)), "allocating stream types");
     HIPTRY(ctx, tm.alloc(tb * (size_t)(s->n + n)), "allocating stream times");
-    if (s->n > 0) {
-        HIPTRY(ctx, hipMemcpy(ty.p, s->types.p, sizeof(int32_t) * s->n, hipMemcpyDeviceToDevice), "copying types");
-        HIPTRY(ctx, hipMemcpy(tm.p, s->times.p, tb * s->n, hipMemcpyDeviceToDevice), "copying times");
+    {
+        hipError_t e = hipSuccess;
+        if (s->n > 0) {
+            e = hipMemcpyAsync(ty.p, s->types.p, sizeof(int32_t) * s->n, hipMemcpyDeviceToDevice, st);
+            if (e == hipSuccess) e = hipMemcpyAsync(tm.p, s->times.p, tb * s->n, hipMemcpyDeviceToDevice, st);
+        }
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(ty.as<int32_t>() + s->n, types, sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(tm.as<unsigned char>() + tb * s->n, times, tb * n, hipMemcpyHostToDevice, st);
+        // the old buffers go back idle
+        const hipError_t w = hipStreamSynchronize(st);
+        HIPTRY(ctx, e != hipSuccess ? e : w, "copying the events");
     }
-    HIPTRY(ctx, hipMemcpy(ty.as<int32_t>() + s->n, types, sizeof(int32_t) * n, hipMemcpyHostToDevice), "copying types");
-    HIPTRY(ctx, hipMemcpy(tm.as<unsigned char>() + tb * s->n, times, tb * n, hipMemcpyHostToDevice), "copying times");
     s->types = std::move(ty);
     s->times = std::move(tm);
     if (s->n == 0) s->tmin = first;
@@ -790,6 +824,7 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
     if (s->n > 0 && (s->tmax > thi - 1 - span || s->tmin < tlo + 1 + span))
         return fail(ctx, EPI_EOVERFLOW, "stream times +- the longest span leave the timestamp type");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle);
     // the levels run on the context's stream, after the work already queued
     // on the caller's; every buffer of the run comes from the context's cache
     hipStream_t st = ctx->c.stream;
@@ -997,6 +1032,14 @@ epi_status epi_mine_release(epi_ctx *ctx, int32_t mine_id) {
 
 namespace {
 
+// Waits for the stream where a call returns, on every path: declared after the
+// call's temporaries, it ends before they are given back.
+struct IdleExit {
+    hipStream_t st;
+    explicit IdleExit(hipStream_t s) : st(s) {}
+    ~IdleExit() { (void)hipStreamSynchronize(st); }
+};
+
 struct HostToDev {
     DevBuf d;
     hipError_t put(const void *h, size_t bytes, hipStream_t st) {
@@ -1060,9 +1103,11 @@ epi_status epi_mlp_forward(epi_ctx *ctx, const float *X, int64_t B, float *y) {
     if (!ctx || (B > 0 && (!X || !y))) return fail(ctx, EPI_EINVAL, "null argument");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     HostToDev dx;
     DevBuf dy;
+    IdleExit idle(st);
     HIPTRY(ctx, dx.put(X, sizeof(float) * B * ctx->c.mlp.F, st), "copy");
     HIPTRY(ctx, dy.alloc(sizeof(float) * B), "alloc");
     HIPTRY(ctx, mlp_forward_device(ctx->c.mlp, dx.d.as<float>(), B, dy.as<float>(), st), "forward");
@@ -1075,9 +1120,11 @@ epi_status epi_mlp_grad(epi_ctx *ctx, const float *X, const float *t, int64_t B,
     if (!ctx || B < 1 || !X || !t || !g) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     const int64_t np = mlp_n_params(ctx->c.mlp.F);
     HostToDev dx, dt;
+    IdleExit idle(st);
     HIPTRY(ctx, dx.put(X, sizeof(float) * B * ctx->c.mlp.F, st), "copy");
     HIPTRY(ctx, dt.put(t, sizeof(float) * B, st), "copy");
     float L = 0;
@@ -1106,10 +1153,12 @@ epi_status epi_mlp_train(epi_ctx *ctx, const float *X, const float *t, int64_t B
     if (!ctx || B < 1 || !X || !t || epochs < 1 || batch < 1) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     Mlp &net = ctx->c.mlp;
     net.lr = lr;
     HostToDev dx, dt;
+    IdleExit idle(st);
     HIPTRY(ctx, dx.put(X, sizeof(float) * B * net.F, st), "copy");
     HIPTRY(ctx, dt.put(t, sizeof(float) * B, st), "copy");
     HIPTRY(ctx, mlp_train_device(net, dx.d.as<float>(), dt.d.as<float>(), B, epochs, batch, losses, st), "training");
@@ -1570,6 +1619,7 @@ epi_status epi_count_noalloc(epi_ctx *ctx, int32_t set_id, int64_t segments, voi
                         (long long)P, (long long)G, need, noalloc_scratch_bytes());
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle);
     hipStream_t st = pick_stream(ctx, hip_stream);
     HIPTRY(ctx, launch_count(*s, *cs, opt, ctx->c.flags.as<int32_t>(), st, scr, noalloc_scratch_bytes()),
            "launching the count");

@@ -34,15 +34,21 @@ struct TsLimits {
     static constexpr T hi() { return std::numeric_limits<T>::max(); }
 };
 
-// Device blocks kept for reuse, for work that runs on one stream only: a
-// block given back while kernels queued on that stream still use it is handed
-// out again only to later work of the same stream, which runs after them.
+// Device blocks kept for reuse.  A context holds two caches:
+//   * of the mining runs, whose work runs on one stream only: a block given back
+//     while kernels queued on that stream still use it is handed out again only
+//     to later work of the same stream, which runs after them;
+//   * of streams, candidate sets and calls' temporaries, which take blocks for
+//     any stream and give them back only when no queued work uses them (after a
+//     synchronisation).
 // Blocks are taken best fit among those at most twice the request (plus
-// 1 MiB); new ones come from hipMalloc.  Every block is freed by release(),
-// which the owner calls after synchronising the stream.
+// 1 MiB); new ones come from hipMalloc.  At most `limit` bytes are kept; every
+// block is freed by release(), which the owner calls after synchronising, and
+// which an allocation that fails calls, too, for its own cache and for the
+// thread's spare one (SpareScope).
 class BlockCache {
 public:
-    BlockCache() = default;
+    explicit BlockCache(size_t limit = SIZE_MAX) : limit_(limit) {}
     BlockCache(const BlockCache &) = delete;
     BlockCache &operator=(const BlockCache &) = delete;
     ~BlockCache() { release(); }
@@ -52,30 +58,60 @@ public:
         if (it != free_.end() && it->first <= 2 * b + ((size_t)1 << 20)) {
             *p = it->second;
             *got = it->first;
+            kept_ -= it->first;
             free_.erase(it);
             return hipSuccess;
         }
-        hipError_t e = hipMalloc(p, b);
-        if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-            // give the kept blocks back to the device (once no queued work
-            // can use them) and try once more
-            (void)hipGetLastError();
-            (void)hipDeviceSynchronize();
-            release();
-            e = hipMalloc(p, b);
-        }
+        hipError_t e = fresh(p, b, this);
         if (e != hipSuccess) return e;
         *got = b;
         return hipSuccess;
     }
-    void put(void *p, size_t bytes) { free_.emplace(bytes, p); }
+    void put(void *p, size_t bytes) {
+        if (bytes > limit_ || kept_ > limit_ - bytes) {
+            (void)hipFree(p);
+            return;
+        }
+        free_.emplace(bytes, p);
+        kept_ += bytes;
+    }
     void release() {
         for (auto &kv : free_) (void)hipFree(kv.second);
         free_.clear();
+        kept_ = 0;
+    }
+    // hipMalloc; where memory is out, once more after the kept blocks of `own`
+    // (may be null) and of the thread's spare cache went back to the device
+    // (once no queued work can use them).
+    static hipError_t fresh(void **p, size_t b, BlockCache *own) {
+        hipError_t e = hipMalloc(p, b);
+        if ((e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) && (own || spare())) {
+            (void)hipGetLastError();
+            (void)hipDeviceSynchronize();
+            if (own) own->release();
+            if (spare()) spare()->release();
+            e = hipMalloc(p, b);
+        }
+        return e;
+    }
+    static BlockCache *&spare() {
+        static thread_local BlockCache *c = nullptr;
+        return c;
     }
 
 private:
     std::multimap<size_t, void *> free_;
+    size_t limit_, kept_ = 0;
+};
+
+// While alive, failing allocations of the calling thread give back this cache's
+// blocks, too.
+struct SpareScope {
+    BlockCache *prev;
+    explicit SpareScope(BlockCache *c) : prev(BlockCache::spare()) { BlockCache::spare() = c; }
+    ~SpareScope() { BlockCache::spare() = prev; }
+    SpareScope(const SpareScope &) = delete;
+    SpareScope &operator=(const SpareScope &) = delete;
 };
 
 // While a CacheScope is alive, DevBuf::alloc of the calling thread takes its
@@ -139,7 +175,7 @@ struct DevBuf {
             e = c->get(b, &p, &block);
             if (e == hipSuccess) cache = c;
         } else {
-            e = hipMalloc(&p, b);
+            e = BlockCache::fresh(&p, b, nullptr);
         }
         if (e != hipSuccess) {
             p = nullptr;
@@ -438,6 +474,11 @@ struct Ctx {
     // blocks of the mining working set (all of it runs on `stream`), kept for
     // reuse until the context is destroyed
     BlockCache cache;
+    // blocks of released streams and sets and of calls' temporaries, for the
+    // next ones: a hipMalloc and hipFree cost 50-200 us, a small query's load,
+    // count and release took thirty of each
+    static constexpr size_t kIdleLimit = size_t(4) << 30;
+    BlockCache idle{kIdleLimit};
     int64_t *stage = nullptr;  // pinned host slots of the mining runs (kStageSlots)
     std::string err;
     std::map<int32_t, std::unique_ptr<Stream>> streams;

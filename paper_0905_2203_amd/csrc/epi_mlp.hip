@@ -351,10 +351,12 @@ hipError_t mlp_grad_device(Mlp &net, const float *dX, const float *dt, int64_t B
     DevBuf sq;
     hipError_t e;
     if ((e = sq.alloc(sizeof(float) * B)) != hipSuccess) return e;
-    if ((e = grad_launch(net, dX, dt, B, dg, sq.as<float>(), false, st)) != hipSuccess) return e;
     std::vector<float> h(B);
-    if ((e = hipMemcpyAsync(h.data(), sq.p, sizeof(float) * B, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    e = grad_launch(net, dX, dt, B, dg, sq.as<float>(), false, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), sq.p, sizeof(float) * B, hipMemcpyDeviceToHost, st);
+    const hipError_t w = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = w;
+    if (e != hipSuccess) return e;
     if (loss) *loss = (float)(sum_of(h.data(), B) / (double)B);
     return hipSuccess;
 }

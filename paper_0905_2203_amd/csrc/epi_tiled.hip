@@ -1063,7 +1063,8 @@ hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end,
         step = std::min<int64_t>(step, (int64_t)(ext_bytes / record_bytes<T>(P, 1)));
         if (step < 1) return hipErrorOutOfMemory;
     } else if (P > 1 && c.scratch.bytes < record_bytes<T>(P, step)) {
-        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        // (the records of the set's last count, on any stream, are done with)
+        if (c.scratch.p && (e = hipDeviceSynchronize()) != hipSuccess) return e;
         if ((e = c.scratch.alloc(record_bytes<T>(P, step))) != hipSuccess) return e;
     }
     for (int64_t b = begin; b < end; b += step) {
@@ -1175,7 +1176,7 @@ hipError_t count_t(const Stream &s, CandSet &c, const CountOptions &opt, int32_t
                 set_records<T>(a, ext_scratch, P, G);
             } else {
                 if (c.scratch.bytes < need) {
-                    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+                    if (c.scratch.p && (e = hipDeviceSynchronize()) != hipSuccess) return e;
                     if ((e = c.scratch.alloc(need)) != hipSuccess) return e;
                 }
                 set_records<T>(a, c.scratch.as<unsigned char>(), P, G);

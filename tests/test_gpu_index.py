@@ -58,3 +58,26 @@ def test_index(n, K):
         part = ctx.epi_load_stream(s["types"][:cut], s["times"][:cut], K)
         ctx.epi_append_stream(part, s["types"][cut:], s["times"][cut:])
         check(ctx, part, s)
+
+
+def test_blocks_of_released_streams_and_sets():
+    """Streams and sets of changing sizes loaded, counted on another stream and released in turn: the device memory
+    they leave to the next ones is not in use any more."""
+    rng = np.random.default_rng(2)
+    side = torch.cuda.Stream()
+    with epi.Context(0) as ctx:
+        for i in range(12):
+            n, K = int(rng.integers(500, 60000)), int(rng.integers(4, 40))
+            s = make(rng, n, K, i % 2, 5)
+            c = sg.random_candidates(rng, int(rng.integers(50, 900)), K, 1, 4, 3)
+            d = [torch.from_numpy(s[k]).cuda() for k in ("types", "times")]
+            torch.cuda.synchronize()
+            sid = (ctx.epi_load_stream_device(d[0], d[1], K, side.cuda_stream) if i % 3 else
+                   ctx.epi_load_stream(s["types"], s["times"], K))
+            cid = ctx.epi_submit_candidates(sid, c)
+            ctx.epi_count([cid], hip_stream=side.cuda_stream if i % 4 else None)
+            if i % 2:
+                got = ctx.epi_read_counts(cid, c["N"].size)
+                assert np.array_equal(got, oracle.count(s, c)), i
+            ctx.epi_release_set(cid)  # (the even rounds' counts still run)
+            ctx.epi_release_stream(sid)
