@@ -990,7 +990,7 @@ void candidate_costs(const Stream &s, CandSet &c) {
 // alone at its end; a segment holds at least kWaveMinEvents of the costliest
 // episode's events, below which its start and reconciliation cost more than
 // they spread.  EPI_OPT_TARGET_LANES scales the resident waves aimed at.
-constexpr double kWaveMinEvents = 2048;
+constexpr double kWaveMinEvents = 4096;
 int64_t wave_segments(const Stream &s, double cost_max, double cost_all, const CountOptions &opt, int waves,
                       int64_t *S_out) {
     int64_t P = 1;
@@ -1255,6 +1255,13 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOpt
 }
 
 }  // namespace
+
+bool wave_counts_all(const Stream &s, const CandSet &c, const CountOptions &opt) {
+    if (c.deep || c.groups.empty()) return false;
+    for (const Group &g : c.groups)
+        if (!wave_group_ok(s, c, g, opt)) return false;
+    return true;
+}
 
 hipError_t launch_count_append(const Stream &s, CandSet &c, int64_t B, const CountOptions &opt, int32_t *d_flags,
                                hipStream_t st) {
