@@ -585,7 +585,17 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
             CandSet *cs = find_set(ctx, set_ids[i]);
             Stream *s = find_stream(ctx, cs->stream_id);
             cs->logged = false;
-            HIPTRY(ctx, launch_count_tracking(*s, *cs, st), "counting by tracking");
+            if (!cs->stream_order && wave_counts_all(*s, *cs, ctx->c.opt)) {
+                // the same method, a wave walking each (episode, segment): the
+                // tracking engine's passes over a node's events, some thirty
+                // launches, only where the waves do not go (dense types, stream
+                // order, deep intervals)
+                CacheScope scope(&ctx->c.idle);
+                HIPTRY(ctx, launch_count(*s, *cs, ctx->c.opt, ctx->c.flags.as<int32_t>(), st), "counting by tracking");
+                HIPTRY(ctx, hipStreamSynchronize(st), "counting by tracking");
+            } else {
+                HIPTRY(ctx, launch_count_tracking(*s, *cs, st), "counting by tracking");
+            }
             cs->counted = true;
             cs->counted_n = s->n;
         }
@@ -937,25 +947,20 @@ hipError_t host_counts(MineLevel &L) {
     return hipMemcpy(L.counts.data(), L.dcounts.p, sizeof(int32_t) * L.m, hipMemcpyDeviceToHost);
 }
 
-// Episode r of a level: explicit candidate, implicit candidate, or (when
-// frequent) the frequent-episode arrays; writes the ABI layout.
+// Candidate r of a level (explicit levels: or frequent episode r), in the ABI
+// layout.
 void mine_episode(const Mine &mn, int level, bool frequent, int64_t r, uint8_t *N, int32_t *types, int64_t *lo,
                   int64_t *hi, int32_t *counts) {
     const MineLevel &L = mn.levels[level - 1];
     int32_t ty[kMaxN];
     int ivs[kMaxN];
     int64_t c;
-    if (frequent && L.implicit) {
-        c = L.freq[r];
-        extend_frequent(mn, level, r, ty, ivs);
+    c = frequent ? L.freq[r] : r;
+    if (L.implicit) {
+        implicit_candidate(mn, level, c, ty, ivs);
     } else {
-        c = frequent ? L.freq[r] : r;
-        if (L.implicit) {
-            implicit_candidate(mn, level, c, ty, ivs);
-        } else {
-            for (int k = 0; k < L.N; ++k) ty[k] = L.types[(size_t)k * L.m + c];
-            for (int k = 0; k + 1 < L.N; ++k) ivs[k] = L.iv[(size_t)k * L.m + c];
-        }
+        for (int k = 0; k < L.N; ++k) ty[k] = L.types[(size_t)k * L.m + c];
+        for (int k = 0; k + 1 < L.N; ++k) ivs[k] = L.iv[(size_t)k * L.m + c];
     }
     N[0] = (uint8_t)L.N;
     for (int k = 0; k < kMaxN; ++k) types[k] = k < L.N ? ty[k] : -1;
@@ -977,12 +982,19 @@ epi_status epi_mine_read(epi_ctx *ctx, int32_t mine_id, int32_t level, int frequ
     Mine &mn = *it->second;
     if (level < 1 || level > (int32_t)mn.levels.size()) return fail(ctx, EPI_ESTATE, "no level %d", level);
     MineLevel &L = mn.levels[level - 1];
-    HIPTRY(ctx, host_counts(L), "reading counts");
-    if (mn.engine == 1) HIPTRY(ctx, extend_host_view(mn, level), "reading a level");
     const int64_t want = frequent_only ? L.nf : L.m;
     if (m != want) return fail(ctx, EPI_EINVAL, "level %d has %lld entries, not %lld", level, (long long)want,
                                (long long)m);
     if (m > 0 && (!N || !types || !lo || !hi || !counts)) return fail(ctx, EPI_EINVAL, "null output");
+    if (frequent_only && L.implicit) {
+        HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+        CacheScope scope(&ctx->c.idle);
+        HIPTRY(ctx, extend_read_frequent(mn, level, types, lo, hi, counts, ctx->c.stream), "reading a level");
+        std::fill(N, N + m, (uint8_t)L.N);
+        return EPI_OK;
+    }
+    HIPTRY(ctx, host_counts(L), "reading counts");
+    if (mn.engine == 1) HIPTRY(ctx, extend_host_view(mn, level), "reading a level");
     for (int64_t r = 0; r < m; ++r)
         mine_episode(mn, level, frequent_only != 0, r, N + r, types + r * 8, lo + r * 7, hi + r * 7, counts + r);
     return EPI_OK;

@@ -1401,7 +1401,78 @@ void frequent_nodes(const Mine &mn, int level, int64_t f, int32_t *types, int *i
     }
 }
 
+// Rows of a level's frequent episodes in the ABI's layout, a thread each: types and
+// interval ids come from its chain of prefix parents.
+struct RowArgs {
+    int32_t N;
+    int64_t nf;
+    const uint16_t *last[kMaxN];  // per level: last type (level 1: the frequent types)
+    const uint8_t *iv[kMaxN];     //   last interval id (level >= 2)
+    const int32_t *par[kMaxN];    //   prefix parent
+    const int64_t *fcand;
+    const int32_t *counts;
+    int64_t menu_lo[kExtMaxMenu], menu_hi[kExtMaxMenu];
+    int64_t *lo, *hi;   // [nf][7]
+    int32_t *types;     // [nf][8]
+    int32_t *out;       // [nf]
+};
+__global__ __launch_bounds__(kBlock) void k_mine_rows(RowArgs a) {
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r >= a.nf) return;
+    int64_t f = r;
+    for (int k = kMaxN - 1; k >= 0; --k) {
+        const bool live = k < a.N;
+        a.types[r * kMaxN + k] = live ? (int32_t)a.last[k][f] : -1;
+        if (k > 0) {
+            const int v = live ? a.iv[k][f] : 0;
+            a.lo[r * (kMaxN - 1) + k - 1] = live ? a.menu_lo[v] : 0;
+            a.hi[r * (kMaxN - 1) + k - 1] = live ? a.menu_hi[v] : 0;
+            if (live) f = a.par[k][f];
+        }
+    }
+    a.out[r] = a.counts[a.fcand[r]];
+}
+
 }  // namespace
+
+hipError_t extend_read_frequent(const Mine &mn, int level, int32_t *types, int64_t *lo, int64_t *hi, int32_t *counts,
+                                hipStream_t st) {
+    const MineLevel &L = mn.levels[level - 1];
+    const size_t nf = (size_t)L.nf;
+    if (nf == 0) return hipSuccess;
+    RowArgs a{};
+    a.N = L.N;
+    a.nf = L.nf;
+    for (int k = 0; k < level; ++k) {
+        const MineLevel &V = mn.levels[k];
+        a.last[k] = V.d_flast.as<uint16_t>();
+        if (k == 0) continue;
+        a.iv[k] = V.d_fliv.as<uint8_t>();
+        a.par[k] = V.d_fpar.as<int32_t>();
+    }
+    a.fcand = L.d_fcand.as<int64_t>();
+    a.counts = L.dcounts.as<int32_t>();
+    for (size_t i = 0; i < mn.menu_lo.size(); ++i) {
+        a.menu_lo[i] = mn.menu_lo[i];
+        a.menu_hi[i] = mn.menu_hi[i];
+    }
+    hipError_t e;
+    DevBuf d;
+    const size_t b64 = sizeof(int64_t) * (kMaxN - 1) * nf, bt = sizeof(int32_t) * kMaxN * nf;
+    if ((e = d.alloc(2 * b64 + bt + sizeof(int32_t) * nf)) != hipSuccess) return e;
+    a.lo = d.as<int64_t>();
+    a.hi = a.lo + (kMaxN - 1) * nf;
+    a.types = reinterpret_cast<int32_t *>(a.hi + (kMaxN - 1) * nf);
+    a.out = a.types + kMaxN * nf;
+    k_mine_rows<<<grid_of(L.nf), kBlock, 0, st>>>(a);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(types, a.types, bt, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(lo, a.lo, b64, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(hi, a.hi, b64, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(counts, a.out, sizeof(int32_t) * nf, hipMemcpyDeviceToHost, st);
+    const hipError_t w = hipStreamSynchronize(st);
+    return e != hipSuccess ? e : w;
+}
 
 hipError_t extend_level1(const Stream &s, Mine &mn, hipStream_t st) {
     if (s.ts_kind == EPI_TS_I64) return level1_t<int64_t>(s, mn, st);
@@ -1461,9 +1532,6 @@ hipError_t extend_host_view(Mine &mn, int level) {
     for (int Lv = 2; Lv <= level; ++Lv) {
         MineLevel &L = mn.levels[Lv - 1];
         if (!L.implicit || L.host_view) continue;
-        std::vector<int64_t> fc;
-        if ((e = to_host(L.d_fcand, L.nf, fc)) != hipSuccess) return e;
-        L.freq = std::move(fc);
         if ((e = to_host(L.d_fpar, L.nf, L.h_fpar)) != hipSuccess) return e;
         if ((e = to_host(L.d_flast, L.nf, L.h_flast)) != hipSuccess) return e;
         if ((e = to_host(L.d_fliv, L.nf, L.h_fliv)) != hipSuccess) return e;
@@ -1476,10 +1544,6 @@ hipError_t extend_host_view(Mine &mn, int level) {
         L.host_view = true;
     }
     return hipSuccess;
-}
-
-void extend_frequent(const Mine &mn, int level, int64_t f, int32_t *types, int *ivs) {
-    frequent_nodes(mn, level, f, types, ivs);
 }
 
 void implicit_candidate(const Mine &mn, int level, int64_t c, int32_t *types, int *ivs) {

@@ -335,7 +335,7 @@ struct MineLevel {
     std::vector<uint8_t> iv;
     std::vector<int32_t> counts;  // [m] (host copy; for device-counted levels made on demand)
     DevBuf dcounts;               // int32 [m] on the device (extension engine)
-    std::vector<int64_t> freq;    // indices with count > threshold (extension engine: host copy on demand)
+    std::vector<int64_t> freq;    // indices with count > threshold (explicit levels)
     double gen_ms = 0, count_ms = 0, kernel_ms = 0;
     int64_t alg_bytes = -1;       // bytes the counting method must read and write (-1: not yet computed)
     int64_t nf = 0;                // frequent episodes
@@ -516,6 +516,9 @@ hipError_t launch_count(const Stream &s, CandSet &c, const CountOptions &opt, in
 hipError_t noalloc_init(int device);
 unsigned char *noalloc_scratch(int device);
 size_t noalloc_scratch_bytes();
+// Whether the wave chains count every episode of set c (its groups are all theirs
+// and no episode is deep).
+bool wave_counts_all(const Stream &s, const CandSet &c, const CountOptions &opt);
 // Segments of a plain count of a group of G episodes on stream s (and the
 // tiles per segment, *S_out), and the bytes of its segment records.
 int64_t plain_segments(const Stream &s, int64_t G, const CountOptions &opt, int64_t *S_out);
@@ -563,10 +566,13 @@ hipError_t extend_level(const Stream &s, Mine &mn, int N, hipStream_t st);
 int64_t extend_level_bytes(const Stream &s, Mine &mn, int level);
 // Host copies of an extension-engine run's levels 2..level, for reading back.
 hipError_t extend_host_view(Mine &mn, int level);
-// Candidate c / frequent episode f of an implicit level (after
-// extend_host_view): types[N], interval ids[N-1].
+// Types, bounds and counts of an implicit level's frequent episodes in the ABI's
+// layout ([nf][8], [nf][7], [nf]), put together on the device; returns when done.
+hipError_t extend_read_frequent(const Mine &mn, int level, int32_t *types, int64_t *lo, int64_t *hi, int32_t *counts,
+                                hipStream_t st);
+// Candidate c of an implicit level (after extend_host_view): types[N], interval
+// ids[N-1].
 void implicit_candidate(const Mine &mn, int level, int64_t c, int32_t *types, int *ivs);
-void extend_frequent(const Mine &mn, int level, int64_t f, int32_t *types, int *ivs);
 // Cost model (epi_mlp.hip).
 int64_t mlp_n_params(int F);
 hipError_t mlp_init(Mlp &net, int F, uint64_t seed);
