@@ -878,6 +878,7 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
                 break;
             }
         }
+        mn->near.reset();
     } else {
         // pair-existence bitmaps of the menu (skipped when they would be too big)
         const double bits_bytes = 2.0 * 8.0 * n_menu * (double)s->K * (double)s->B * (s->T / 64);

@@ -34,6 +34,23 @@
 // all extensions of an episode at once: the work per alpha is |U(alpha)|
 // stream events whatever the number of its extensions.
 //
+// Near rows.  Where an alpha's end events are far apart their extensions need
+// no walk.  Cut its chain list wherever an entry starts after every window of
+// the entries before it: a cluster's occurrences never overlap another's, so
+// its counts add up.  In a cluster whose last start is not after its first end
+// time any two occurrences overlap, so an extension (B, m) of it counts one if
+// some entry x has a type-B event in interval m after t_x.  That depends on
+// the stream position of x alone: a row of 64-bit words per position, made
+// once a run, has a bit for it (k_near).  A wave loads the rows of 64 entries,
+// transposes the words so that a lane holds its type's bits, and counts the
+// clusters with a bit set.  Only the windows of the other clusters are walked.
+// What bounds it: instructions a walked batch (184 vector instructions for 64
+// events, 68 batches an alpha) against some 200 for 64 entries.  788,381
+// alphas of 170 entries, 83.5M candidates: 18.5 ms walked, 2.6 ms so.  A level
+// of 12,096 alphas, lists and all: 6.3 ms by lists of every candidate's end
+// events, 4.7 ms.  The end events of the frequent extensions are then sized by
+// a walk of their own.
+//
 // Level 1 counts distinct timestamps per type.  Level 2 extends a frequent
 // type (its chain list is its own events, s = t).  The chain lists of a
 // level's frequent episodes are written by a second walk over the alphas that
@@ -54,9 +71,11 @@ using Clock = std::chrono::steady_clock;
 double ms_since(Clock::time_point t0) { return std::chrono::duration<double, std::milli>(Clock::now() - t0).count(); }
 
 constexpr int kWave = 64;
+constexpr int kBlock = 256;
 constexpr uint16_t kNoSlot = 0;  // owner-slot entry of a type no lane counts (no intervals)
-// List path: taken for levels with fewer alphas than Mine::list_alphas, whose
-// walks are cut into pieces so that about kListJobs workgroups run.  Chain
+// List path: taken for levels with fewer alphas than Mine::list_alphas that the
+// near rows do not count, whose walks are cut into pieces so that about
+// kListJobs workgroups run.  Chain
 // lists of levels with fewer write jobs than kWritePieced are written by
 // walks cut into pieces likewise (a size walk and a list walk over the
 // frequent extensions, about kWriteJobs workgroups each), so that no long
@@ -65,6 +84,17 @@ constexpr uint16_t kNoSlot = 0;  // owner-slot entry of a type no lane counts (n
 constexpr int64_t kListJobs = 65536;
 constexpr int64_t kWritePieced = 32768;
 constexpr int64_t kWriteJobs = 262144;
+// Near rows: at most this many bytes of them, and only for a level whose chain
+// lists have at least a quarter as many entries (times the words of a row
+// set) as the stream has events: a row costs some 8 lane instructions an event
+// of its window and word, an entry that is walked some 180, so the rows are
+// then at most a fifth of what they save.
+constexpr size_t kNearBytes = size_t(8) << 30;
+constexpr int64_t kNearShare = 4;
+// With fewer alphas the list path is taken instead: one wave an alpha then
+// leaves the GPU idle (levels counted by lists and by near rows, ms: 1599
+// alphas 0.47 and 0.77, 3168 0.61 and 0.46, 12096 6.3 and 4.7).
+constexpr int64_t kNearAlphas = 2048;
 
 // One entry of a chain list: an end event of an episode (time, stream
 // position) and the latest start of an occurrence ending there.
@@ -80,6 +110,9 @@ struct WalkArgs {
     const T *times;           // [n]
     const int32_t *wend;      // [n] first position whose time exceeds times[p] + H
     T H;                      // longest menu interval end
+    // counting pass: the near rows (null: every window is walked), see k_near
+    const unsigned long long *near;
+    int64_t n;                // stream positions
     // the alphas' chain lists: level >= 3, those of the previous level's
     // frequent episodes ([coff[alpha], coff[alpha + 1])); level 2, a frequent
     // type's own events (the per-type index as chain entries, s = t)
@@ -207,6 +240,43 @@ __device__ __forceinline__ int64_t n_extensions(const WalkArgs<T> &a, int64_t jo
     return a.out_off[alpha + 1] - a.out_off[alpha];
 }
 
+// Transpose of a 64 x 64 bit matrix whose row i is lane i's word: lane b gets
+// column b.  The halves are swapped between the wave's halves, then blocks of
+// 16, 8, 4, 2 and 1 with the partner lane (all lanes active).
+__device__ __forceinline__ uint64_t transpose_bits(uint64_t v, int lane) {
+    uint32_t x[2] = {(uint32_t)v, (uint32_t)(v >> 32)};
+    const auto h = __builtin_amdgcn_permlane32_swap(x[0], x[1], false, false);
+    x[0] = h[0];
+    x[1] = h[1];
+    const uint32_t s16 = lane & 16 ? 0x07060302u : 0x05040100u, s8 = lane & 8 ? 0x03070105u : 0x06020400u;
+    const uint32_t r4 = lane & 4 ? 4 : 28, r2 = lane & 2 ? 2 : 30, r1 = lane & 1 ? 1 : 31;
+    const uint32_t m4 = lane & 4 ? 0xF0F0F0F0u : 0x0F0F0F0Fu, m2 = lane & 2 ? 0xCCCCCCCCu : 0x33333333u,
+                   m1 = lane & 1 ? 0xAAAAAAAAu : 0x55555555u;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        uint32_t y = x[k];
+        const auto q = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+        y = __builtin_amdgcn_perm(q[1], q[0], s16);
+        uint32_t p = (uint32_t)__builtin_amdgcn_mov_dpp((int)y, 0x128, 0xF, 0xF, true);  // lane ^ 8
+        y = __builtin_amdgcn_perm(p, y, s8);
+        p = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)y, 0x104, 0xF, 0x5, false);  // lane ^ 4: lane + 4
+        p = (uint32_t)__builtin_amdgcn_update_dpp((int)p, (int)y, 0x114, 0xF, 0xA, false);  // or lane - 4
+        y = (y & m4) | (__builtin_amdgcn_alignbit(p, p, r4) & ~m4);
+        p = (uint32_t)__builtin_amdgcn_mov_dpp((int)y, 0x4E, 0xF, 0xF, true);  // lane ^ 2
+        y = (y & m2) | (__builtin_amdgcn_alignbit(p, p, r2) & ~m2);
+        p = (uint32_t)__builtin_amdgcn_mov_dpp((int)y, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+        x[k] = (y & m1) | (__builtin_amdgcn_alignbit(p, p, r1) & ~m1);
+    }
+    return (uint64_t)x[1] << 32 | x[0];
+}
+
+// Segments of a 64-bit word, the last bit of each marked in `ends`: the ends
+// of the segments in which x has a bit.  (Adding ones below a segment's end
+// carries into the end when a bit is set there, and never past it.)
+__device__ __forceinline__ uint64_t segments_hit(uint64_t x, uint64_t ends) {
+    return (((x & ~ends) + ~ends) | x) & ends;
+}
+
 // A batch event in LDS: its time, its start per menu interval (minimum of
 // the type: no occurrence ends there) and, counting, the next leader event of
 // the same owner.  One record per event, so that a greedy step reads it with
@@ -278,7 +348,8 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
 #pragma unroll
         for (int m = 0; m < MP; ++m) evr[kWave].s[m] = kMin;
     }
-    unsigned long long walked = 0;
+    unsigned long long in_windows = 0;  // stream positions of this lane's runs, all rounds
+    const int64_t rowlen = M + 1;  // words of a near row
     // rounds of up to 64 distinct extension types (one lane each)
     for (int64_t r_start = 0; r_start < R;) {
         gtype[lane] = -1;
@@ -353,15 +424,93 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
             const T t0 = xc[e0].t;
             while (ilo > 0 && xc[ilo - 1].t >= (T)(t0 - a.H)) --ilo;
         }
-        for (int32_t i0 = e0; i0 < e1; i0 += kWave) {  // uniform
+        T et = kMin;         // time of the last entry taken
+        int32_t take;        // entries taken by a step
+        for (int32_t i0 = e0; i0 < e1; i0 += take) {  // uniform
             const int32_t i = i0 + lane;
-            const bool ci = i < e1;
-            const int32_t p = ci ? xc[i].p : 0;
-            const int32_t e = ci ? a.wend[p] : 0;
+            bool ci = i < e1;
+            take = kWave;
+            uint64_t vis = ~0ull;  // entries whose windows are walked
+            bool joined = true;    // the step begins inside a cluster
+            const ChainEntry<T> x = xg[min(i, e1 - 1)];
+            const int32_t p = x.p;
+            int32_t e = 0;
+            if (MODE == kCount && a.near) {  // uniform
+                T tp = __shfl_up(x.t, 1, kWave);
+                if (lane == 0) tp = et;
+                // clusters: an entry whose start comes after every window of
+                // the entries before it begins one
+                uint64_t hd = __ballot(ci & ((i == 0) | (x.s > (T)(tp + a.H))));
+                const int nv = min(e1 - i0, kWave);
+                const bool more = nv < e1 - i0;
+                bool cut = true;  // the step's last cluster ends with the step
+                take = nv;
+                if (more) {
+                    const int lh = hd ? 63 - __builtin_clzll(hd) : 0;
+                    cut = lh > 0;
+                    if (cut) take = lh;
+                }
+                et = read_lane(x.t, take - 1);
+                const uint64_t tm = ~0ull >> (kWave - take);
+                ci = lane < take;
+                hd &= tm;
+                joined = !(hd & 1);
+                const uint64_t ends = hd >> 1 | 1ull << (take - 1);
+                // simple: a cluster whose last start is not after its first
+                // end time.  Any two of its occurrences overlap.
+                const uint64_t upto = hd & (~0ull >> (63 - lane));
+                const int fst = upto ? 63 - __builtin_clzll(upto) : 0;
+                const T ft = __shfl(x.t, fst, kWave);
+                uint64_t bad = __ballot(ci & ((upto == 0) | (x.s > ft)));
+                if (!cut) bad |= 1ull << (take - 1);
+                // the entries of the other clusters: bits from each cluster's
+                // first to its end, by a subtraction in reversed order
+                const uint64_t top = __builtin_bitreverse64((ends << 1 | 1ull) & tm);
+                vis = __builtin_bitreverse64((top - __builtin_bitreverse64(segments_hit(bad, ends))) ^ top);
+                const bool simple = ci & !((vis >> lane) & 1);
+                // a simple cluster gives an extension one occurrence when one
+                // of its entries' near rows has the extension's type
+                const int32_t w0 = __builtin_amdgcn_readfirstlane(myB) >> 6;
+                const int32_t w1 = __builtin_amdgcn_readlane(myB, ng - 1) >> 6;
+                for (int32_t w = w0; w <= w1; ++w) {  // uniform
+                    const bool mine = has && (myB >> 6) == w;
+                    if (!__ballot(mine)) continue;
+                    const unsigned long long *row = a.near + ((int64_t)w * a.n + p) * rowlen;
+                    unsigned long long v[MP];
+#pragma unroll
+                    for (int m = 0; m < MP; ++m) v[m] = kExact || m < M ? row[m] : 0ull;
+                    e = (int32_t)row[M];
+#pragma unroll
+                    for (int m = 0; m < MP; ++m) {
+                        if (!kExact && m >= M) continue;  // uniform
+                        const uint64_t col = transpose_bits(simple ? v[m] : 0ull, lane);
+                        const int32_t c = __popcll(segments_hit(col, ends));
+                        const int32_t cb = __shfl(c, myB & 63, kWave);
+                        cnt[m] += mine ? cb : 0;
+                    }
+                }
+            } else {
+                e = ci ? a.wend[p] : 0;
+            }
             int32_t prev_e = __shfl_up(e, 1, kWave);
             if (lane == 0) prev_e = carry;
             const int32_t beg = max(p + 1, prev_e);
-            const int32_t len = ci ? max(0, e - beg) : 0;
+            int32_t len = ci ? max(0, e - beg) : 0;
+            carry = max(carry, __builtin_amdgcn_readlane(e, 63 - __builtin_clzll(__ballot(ci))));
+            in_windows += (unsigned)len;
+            if (MODE == kCount && a.near) {  // uniform
+                if (vis == 0) continue;
+                if (!((vis >> lane) & 1)) len = 0;
+                // an end event is preceded only by entries of its cluster
+                if (!joined || !(vis & 1)) ilo = max(ilo, i0 + __builtin_ctzll(vis));
+            }
+            // the entry visited after q (all but the simple clusters')
+            auto after = [&](int32_t q) -> int32_t {
+                ++q;
+                if (MODE != kCount || q < i0 || q >= i0 + take) return q;
+                const uint64_t rest = vis >> (q - i0);
+                return rest ? q + __builtin_ctzll(rest) : i0 + take;
+            };
             int32_t S = len;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
@@ -370,8 +519,6 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
             }
             const int32_t X = S - len;
             const int32_t total = __builtin_amdgcn_readlane(S, 63);
-            carry = max(carry, __builtin_amdgcn_readlane(e, 63 - __builtin_clzll(__ballot(ci))));
-            walked += (unsigned long long)total;
             // stream position of this lane in the batch at b: the runs
             // meeting [b, b + 64) are visited in order
             auto position = [&](int32_t b) -> int32_t {
@@ -417,14 +564,14 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
                 const T tf = read_lane(t, 0), tl = read_lane(t, nb - 1);
                 // s_m(y): start of the latest end event x with
                 // t_x < t - lo_m, when t_x >= t - hi_m
-                while (ilo < clen && xc[ilo].t < (T)(tf - a.H)) ++ilo;  // (entries past e1 can precede too)
+                while (ilo < clen && xc[ilo].t < (T)(tf - a.H)) ilo = after(ilo);  // (entries past e1 can precede too)
                 T cx[MP], cxs[MP];
 #pragma unroll
                 for (int m = 0; m < MP; ++m) {
                     cx[m] = kMin;
                     cxs[m] = kMin;
                 }
-                for (int32_t q = ilo; q < clen; ++q) {  // uniform
+                for (int32_t q = ilo; q < clen; q = after(q)) {  // uniform
                     // (t, s) in one load: one wait per entry
                     T qt, qs;
                     load_ts(xc + q, qt, qs);
@@ -459,8 +606,9 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
                 uint64_t vb[MP];  // delivered events that end an occurrence, per interval
                 if (MODE == kCount) {
                     // counted by the events themselves, for the intervals
-                    // their owner counts
-                    const uint32_t dv = dl ? vm & (sl >> 8) : 0u;
+                    // their owner counts (with near rows a walk over the
+                    // frequent extensions counts them)
+                    const uint32_t dv = dl && !a.near ? vm & (sl >> 8) : 0u;
 #pragma unroll
                     for (int m = 0; m < MP; ++m)
                         if ((dv >> m) & 1u) atomicAdd(&cnv[m][ow], 1);
@@ -543,7 +691,7 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
             for (int m = 0; m < MP; ++m) {
                 if (own[m]) {
                     if (MODE == kCount) a.counts[key[m]] = cnt[m];
-                    a.nvalid[key[m]] = nv[m];
+                    if (MODE != kCount || !a.near) a.nvalid[key[m]] = nv[m];
                 }
             }
         }
@@ -551,8 +699,11 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
         __syncthreads();
         r_start = r_next;
     }
-    if ((MODE == kCount || MODE == kSize) && a.walked && lane == 0)
-        atomicAdd(a.walked + (blockIdx.x % kWalkSlots) * kWalkStride, walked);
+    if ((MODE == kCount || MODE == kSize) && a.walked) {
+        unsigned long long w = in_windows;
+        for (int d = 1; d < kWave; d <<= 1) w += __shfl_xor(w, d, kWave);
+        if (lane == 0) atomicAdd(a.walked + (blockIdx.x % kWalkSlots) * kWalkStride, w);
+    }
 }
 
 // Every array a walk of this kind reads or writes must be present.
@@ -565,7 +716,7 @@ bool walk_args_complete(const WalkArgs<T> &a) {
     if (kFreqJob<MODE>) ok = ok && a.job_alpha && a.job_f && a.w_type && a.w_iv;
     else ok = ok && (a.level2 || (a.out_off && a.rlo && a.xlo && a.xhi && a.flast && a.fliv));
     if (MODE == kWrite) ok = ok && a.w_off && a.wchain;
-    if (MODE == kCount) ok = ok && a.counts && a.nvalid;
+    if (MODE == kCount) ok = ok && a.counts && (a.near ? a.n > 0 : a.nvalid != nullptr);
     if (MODE == kSize || MODE == kWSize) ok = ok && a.nvalid;
     if (MODE == kList || MODE == kWList) ok = ok && a.lst_off && a.wchain;
     if (MODE == kWrite || MODE == kCount) ok = ok && a.nseg == 1;
@@ -614,9 +765,48 @@ __global__ void k_walk_prep(const int32_t *__restrict__ types, const T *__restri
     wend[i] = (int32_t)lo;
 }
 
+// Near rows: for each stream position and each 64 types, one word per menu
+// interval with the types that have an event in the interval after the
+// position's time, and a last word with the position's window end.
+template <typename T>
+struct NearArgs {
+    const uint16_t *ty16;
+    const T *times;
+    const int32_t *wend;
+    int64_t n;
+    int32_t M;
+    T lo[kExtMaxMenu], hi[kExtMaxMenu];
+    unsigned long long *out;  // [words][n][M + 1]
+};
+
+template <typename T, int MP>
+__global__ __launch_bounds__(kBlock) void k_near(NearArgs<T> a) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int w = (int)blockIdx.y;
+    if (i >= a.n) return;
+    const T t = a.times[i];
+    const int32_t e = a.wend[i];
+    unsigned long long v[MP];
+#pragma unroll
+    for (int m = 0; m < MP; ++m) v[m] = 0;
+    for (int32_t j = (int32_t)i + 1; j < e; ++j) {
+        const int ty = (int)a.ty16[j];
+        const T d = (T)(a.times[j] - t);
+        const unsigned long long b = (ty >> 6) == w ? 1ull << (ty & 63) : 0ull;
+#pragma unroll
+        for (int m = 0; m < MP; ++m)
+            if ((MP <= 4 || m < a.M) && d > a.lo[m] && d <= a.hi[m]) v[m] |= b;
+    }
+    const int M = MP <= 4 ? MP : a.M;
+    unsigned long long *row = a.out + ((int64_t)w * a.n + i) * (M + 1);
+#pragma unroll
+    for (int m = 0; m < MP; ++m)
+        if (MP <= 4 || m < M) row[m] = v[m];
+    row[M] = (unsigned long long)(uint32_t)e;
+}
+
 // ---- device-side bookkeeping of the levels ----------------------------------
 
-constexpr int kBlock = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kBlock * kScanItems;
 
@@ -751,7 +941,7 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(const int32_t *__restrict_
         if (f) {
             const int64_t o = off + before + __popcll(bal & ((1ull << lane) - 1ull));
             fcand[o] = i;
-            fnv[o] = nvalid[i];
+            if (nvalid) fnv[o] = nvalid[i];
         }
         off += total;
         __syncthreads();
@@ -1023,6 +1213,16 @@ __global__ __launch_bounds__(kBlock) void k_list_begin(const int64_t *__restrict
     if (f < nf) cbeg[f] = lst_off[fcand[f] * nseg];
 }
 
+// The frequent episodes' chain lists from the offsets of their pieces.
+__global__ __launch_bounds__(kBlock) void k_piece_lists(const int64_t *__restrict__ off, int32_t nseg, int64_t nf,
+                                                        int64_t *__restrict__ cbeg, int32_t *__restrict__ fnv) {
+    const int64_t f = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (f > nf) return;
+    const int64_t b = off[f * nseg];
+    cbeg[f] = b;
+    if (f < nf) fnv[f] = (int32_t)(off[(f + 1) * nseg] - b);
+}
+
 unsigned grid_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 template <typename V>
@@ -1050,6 +1250,39 @@ hipError_t order_by_key(const uint16_t *key, const int32_t *idx, int64_t n, int3
     // the temporaries die here: blocks of a cache scope go back for later
     // work of this stream, others are freed after it
     return CacheScope::current() ? hipGetLastError() : hipStreamSynchronize(st);
+}
+
+// The near rows of the stream, made for the first level that counts enough with
+// them; without the memory for them every window is walked.
+template <typename T>
+hipError_t make_near(const Stream &s, Mine &mn, const WalkArgs<T> &w, hipStream_t st) {
+    if (mn.near.p) return hipSuccess;
+    const int64_t words = (s.K + 63) / 64;
+    const size_t bytes = sizeof(unsigned long long) * (size_t)(w.M + 1) * (size_t)s.n * (size_t)words;
+    if (bytes > kNearBytes || mn.near.alloc(bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipSuccess;
+    }
+    NearArgs<T> a{};
+    a.ty16 = w.ty16;
+    a.times = w.times;
+    a.wend = w.wend;
+    a.n = s.n;
+    a.M = w.M;
+    for (int m = 0; m < w.M; ++m) {
+        a.lo[m] = w.menu_lo[m];
+        a.hi[m] = w.menu_hi[m];
+    }
+    a.out = mn.near.as<unsigned long long>();
+    const dim3 grid(grid_of(s.n), (unsigned)words);
+    switch (w.M) {
+        case 1: k_near<T, 1><<<grid, kBlock, 0, st>>>(a); break;
+        case 2: k_near<T, 2><<<grid, kBlock, 0, st>>>(a); break;
+        case 3: k_near<T, 3><<<grid, kBlock, 0, st>>>(a); break;
+        case 4: k_near<T, 4><<<grid, kBlock, 0, st>>>(a); break;
+        default: k_near<T, 8><<<grid, kBlock, 0, st>>>(a); break;
+    }
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -1105,6 +1338,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     a.type_off = s.type_off.as<int32_t>();
     a.M = M;
     a.K = s.K;
+    a.n = s.n;
     a.level2 = N == 2;
     for (int i = 0; i < M; ++i) {
         a.menu_lo[i] = (T)mn.menu_lo[i];
@@ -1141,12 +1375,17 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     if ((e = hipEventCreate(&ev0)) != hipSuccess) return e;
     if ((e = hipEventCreate(&ev1)) != hipSuccess) return e;
     (void)hipEventRecord(ev0, st);
+    if (m > 0 && N > 2 && (nA >= kNearAlphas || nA >= mn.list_alphas) &&
+        P.chain_total >= s.n / kNearShare * ((s.K + 63) / 64)) {
+        if ((e = make_near<T>(s, mn, a, st)) != hipSuccess) return e;
+        a.near = mn.near.as<unsigned long long>();
+    }
     // With few alphas (level 2 has as many as frequent types) one walk per
     // alpha leaves the GPU idle: the walks are cut into pieces and every
     // candidate's end events are listed (list path), when they fit the budget.
     bool listed = false;
     DevBuf lst_off;
-    if (m > 0 && nA < mn.list_alphas) {
+    if (m > 0 && nA < mn.list_alphas && !a.near) {
         const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, (kListJobs + nA - 1) / nA));
         if ((e = lst_off.alloc(sizeof(int64_t) * (m * nseg + 1))) != hipSuccess) return e;
         DevBuf nvseg;
@@ -1219,7 +1458,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     if ((e = L.cbeg.alloc(sizeof(int64_t) * (nf + 1))) != hipSuccess) return e;
     L.chain_total = 0;
     if (nf > 0) {
-        k_sel_write<<<(unsigned)nb, kBlock, 0, st>>>(a.counts, a.nvalid, m, thr, boffs.as<int64_t>(),
+        k_sel_write<<<(unsigned)nb, kBlock, 0, st>>>(a.counts, a.near ? nullptr : a.nvalid, m, thr, boffs.as<int64_t>(),
                                                     L.d_fcand.as<int64_t>(), L.d_fnv.as<int32_t>());
         FreqArgs fa{};
         fa.nf = nf;
@@ -1252,11 +1491,13 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
         // list path keeps every candidate's list; its frequent ones are the
         // chain lists)
         DevBuf tmp2, flag, jidx, job_alpha, job_f, w_order;
-        if ((e = scan64(L.d_fnv.as<int32_t>(), nf, L.cbeg.as<int64_t>(), tmp2, st)) != hipSuccess) return e;
-        // the chain entries in all (pinned slot 2), read at the next synchronisation
-        if ((e = hipMemcpyAsync(&stage[2], L.cbeg.as<int64_t>() + nf, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                st)) != hipSuccess)
-            return e;
+        if (!a.near) {
+            if ((e = scan64(L.d_fnv.as<int32_t>(), nf, L.cbeg.as<int64_t>(), tmp2, st)) != hipSuccess) return e;
+            // the chain entries in all (pinned slot 2), read at the next synchronisation
+            if ((e = hipMemcpyAsync(&stage[2], L.cbeg.as<int64_t>() + nf, sizeof(int64_t), hipMemcpyDeviceToHost,
+                                    st)) != hipSuccess)
+                return e;
+        }
         if (listed) {
             k_list_begin<<<grid_of(nf), kBlock, 0, st>>>(L.d_fcand.as<int64_t>(), lst_off.as<int64_t>(), L.list_seg,
                                                          nf, L.cbeg.as<int64_t>());
@@ -1275,7 +1516,6 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
             hipSuccess)
             return e;
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-        L.chain_total = stage[2];
         const int64_t nj = stage[3];
         if ((e = job_alpha.alloc(sizeof(int32_t) * nj)) != hipSuccess) return e;
         if ((e = job_f.alloc(sizeof(int64_t) * (nj + 1))) != hipSuccess) return e;
@@ -1291,34 +1531,40 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
                                                       lkey.as<uint16_t>());
             if ((e = order_by_key(lkey.as<uint16_t>(), nullptr, nj, 33, w_order, st)) != hipSuccess) return e;
         }
-        const size_t tot = (size_t)L.chain_total;
-        if ((e = L.chain.alloc(sizeof(ChainEntry<T>) * tot)) != hipSuccess) return e;
         a.job_alpha = job_alpha.as<int32_t>();
         a.job_f = job_f.as<int64_t>();
         a.order = N > 2 ? w_order.as<int32_t>() : nullptr;
         a.w_type = L.d_flast.as<uint16_t>();
         a.w_iv = L.d_fliv.as<uint8_t>();
         a.w_off = L.cbeg.as<int64_t>();
-        a.wchain = L.chain.as<ChainEntry<T>>();
+        const bool pieced = mn.list_budget > 0 && nj < kWritePieced;
         DevBuf wseg, woff;
-        if (mn.list_budget > 0 && nj < kWritePieced) {
+        if (pieced || a.near) {
             // few write jobs: walks cut into pieces; the end events of each
             // (frequent episode, piece), scanned in that order, give every
-            // piece its offset in the chain lists (the same layout)
-            const int32_t nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, (kWriteJobs + nj - 1) / nj));
-            if ((e = wseg.alloc(sizeof(int32_t) * (size_t)nf * nseg)) != hipSuccess) return e;
-            if ((e = woff.alloc(sizeof(int64_t) * ((size_t)nf * nseg + 1))) != hipSuccess) return e;
-            a.nseg = nseg;
+            // piece its offset in the chain lists (the same layout).  Counts
+            // by near rows leave the end events to this walk, one piece a job
+            // where the jobs are many.
+            a.nseg = pieced ? (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, (kWriteJobs + nj - 1) / nj)) : 1;
+            if ((e = wseg.alloc(sizeof(int32_t) * (size_t)nf * a.nseg)) != hipSuccess) return e;
+            if ((e = woff.alloc(sizeof(int64_t) * ((size_t)nf * a.nseg + 1))) != hipSuccess) return e;
             a.nvalid = wseg.as<int32_t>();
             a.walked = nullptr;
-            if ((e = launch_walk<T, kWSize>(a, nj * nseg, st)) != hipSuccess) return e;
-            if ((e = scan64(wseg.as<int32_t>(), nf * nseg, woff.as<int64_t>(), tmp, st)) != hipSuccess) return e;
+            if ((e = launch_walk<T, kWSize>(a, nj * a.nseg, st)) != hipSuccess) return e;
+            if ((e = scan64(wseg.as<int32_t>(), nf * a.nseg, woff.as<int64_t>(), tmp, st)) != hipSuccess) return e;
             a.lst_off = woff.as<int64_t>();
-            if ((e = launch_walk<T, kWList>(a, nj * nseg, st)) != hipSuccess) return e;
-        } else {
-            a.nseg = 1;
-            if ((e = launch_walk<T, kWrite>(a, nj, st)) != hipSuccess) return e;
         }
+        if (a.near) {
+            k_piece_lists<<<grid_of(nf + 1), kBlock, 0, st>>>(woff.as<int64_t>(), a.nseg, nf, L.cbeg.as<int64_t>(),
+                                                             L.d_fnv.as<int32_t>());
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            if ((e = read_scalar(woff, nf * a.nseg, &stage[2], st)) != hipSuccess) return e;
+        }
+        L.chain_total = stage[2];
+        if ((e = L.chain.alloc(sizeof(ChainEntry<T>) * (size_t)L.chain_total)) != hipSuccess) return e;
+        a.wchain = L.chain.as<ChainEntry<T>>();
+        e = pieced ? launch_walk<T, kWList>(a, nj * a.nseg, st) : launch_walk<T, kWrite>(a, nj, st);
+        if (e != hipSuccess) return e;
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;  // the job buffers die here
     } else {
         if ((e = hipMemsetAsync(L.cbeg.p, 0, sizeof(int64_t), st)) != hipSuccess) return e;

@@ -384,6 +384,7 @@ struct Mine {
     // p, the first position whose time exceeds time[p] + H (H = the longest
     // menu interval end)
     DevBuf ty16, wend;
+    DevBuf near;    // near rows of the stream (made by the first level counted with them)
     DevBuf chain1;  // the per-type index as chain entries (level 2's alphas)
     // list path: device bytes the end-event lists of every candidate of a
     // level may take (larger: count and write walks)
