@@ -296,8 +296,8 @@ epi_status epi_create(int device, epi_ctx **out) {
     if ((e = hipStreamCreateWithFlags(&ctx->c.stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = ctx->c.flags.alloc(sizeof(int32_t) * kNumFlags)) != hipSuccess ||
         (e = hipMemset(ctx->c.flags.p, 0, sizeof(int32_t) * kNumFlags)) != hipSuccess ||
-        (e = hipHostMalloc((void **)&ctx->c.stage, sizeof(int64_t) * kStageSlots, hipHostMallocDefault)) !=
-            hipSuccess ||
+        (e = hipHostMalloc((void **)&ctx->c.stage, sizeof(int64_t) * kStageSlots + kStageBytes,
+                           hipHostMallocDefault)) != hipSuccess ||
         (e = noalloc_init(device)) != hipSuccess) {
         g_create_err = hipGetErrorString(e);
         delete ctx;
@@ -871,14 +871,14 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
             const MineLevel &prev = mn->levels.back();
             if (prev.nf == 0 || (N == 2 && prev.nf < 2)) break;
             HIPTRY(ctx, extend_level(*s, *mn, N, st), "counting a level");
-            epi_status f = check_flags(ctx);
-            if (f != EPI_OK) return f;
             if (mn->levels.back().m == 0) {
                 mn->levels.pop_back();
                 break;
             }
         }
         mn->near.reset();
+        epi_status f = check_flags(ctx);
+        if (f != EPI_OK) return f;
     } else {
         // pair-existence bitmaps of the menu (skipped when they would be too big)
         const double bits_bytes = 2.0 * 8.0 * n_menu * (double)s->K * (double)s->B * (s->T / 64);

@@ -58,6 +58,7 @@
 // end-event counts (the count / scan / write compaction of Sec. IV-E).
 #include <algorithm>
 #include <chrono>
+#include <cstring>
 #include <numeric>
 #include <thread>
 
@@ -187,13 +188,16 @@ __device__ __forceinline__ void load_ts(const_ptr<ChainEntry<T>> e, T &t, T &s) 
 // summed after: on one counter the atomics of 65,536 workgroups took five times
 // as long as their walks (a size walk of 50k events: 365 us, now 70).
 constexpr int kWalkSlots = 256, kWalkStride = 16;
-__global__ __launch_bounds__(kWalkSlots) void k_sum_walked(unsigned long long *__restrict__ w) {
+// (left at zero for the next level)
+__global__ __launch_bounds__(kWalkSlots) void k_sum_walked(unsigned long long *__restrict__ w,
+                                                           int64_t *__restrict__ sum) {
     __shared__ unsigned long long part[kWalkSlots / 64];
     unsigned long long v = w[threadIdx.x * kWalkStride];
+    w[threadIdx.x * kWalkStride] = 0;
     for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
     if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = v;
     __syncthreads();
-    if (threadIdx.x == 0) w[0] = part[0] + part[1] + part[2] + part[3];
+    if (threadIdx.x == 0) *sum = (int64_t)(part[0] + part[1] + part[2] + part[3]);
 }
 
 // Walk kinds: count (greedy counts and end-event counts per candidate),
@@ -831,10 +835,10 @@ __device__ __forceinline__ int64_t block_scan64(int64_t v, int64_t *total) {
     return off + x - v;
 }
 
-// Exclusive scan of in[len] into int64 out[len + 1] (out[len] = total), in
+// Exclusive scan of in[len] (an array, or anything indexed like one) into int64 out[len + 1] (out[len] = total), in
 // three passes: tile sums, a one-block scan of the tile sums, tile scans.
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_scan_tiles(const V *__restrict__ in, int64_t len,
+template <typename In>
+__global__ __launch_bounds__(kBlock) void k_scan_tiles(const In in, int64_t len,
                                                        int64_t *__restrict__ sums) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     int64_t acc = 0;
@@ -861,10 +865,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_sums64(int64_t *__restrict__ su
     if (threadIdx.x == 0) sums[nb] = carry;
 }
 
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_scan_apply64(const V *__restrict__ in, int64_t len,
+template <typename In>
+__global__ __launch_bounds__(kBlock) void k_scan_apply64(const In in, int64_t len,
                                                          const int64_t *__restrict__ sums, int64_t nb,
-                                                         int64_t *__restrict__ out) {
+                                                         int64_t *__restrict__ out, int64_t *__restrict__ total) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     int64_t v[kScanItems];
     int64_t acc = 0;
@@ -880,18 +884,73 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply64(const V *__restrict__ i
         if (i < len) out[i] = run;
         run += v[k];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[len] = sums[nb];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[len] = sums[nb];
+        if (total) *total = sums[nb];
+    }
 }
 
-// out[len + 1] = exclusive scan of in[len]; the total is left in out[len].
-template <typename V>
-hipError_t scan64(const V *in, int64_t len, int64_t *out, DevBuf &tmp, hipStream_t st) {
-    const int64_t nb = len > 0 ? (len + kScanTile - 1) / kScanTile : 1;
+// The same by one workgroup, kSmallItems elements a thread and step.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = 4;
+
+template <typename In>
+__global__ __launch_bounds__(kSmallBlock) void k_scan_small(const In in, int64_t len,
+                                                            int64_t *__restrict__ out, int64_t *__restrict__ total) {
+    __shared__ int64_t wsum[2][kSmallBlock / kWave];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    int64_t carry = 0;
+    int b = 0;
+    for (int64_t base = 0; base < len; base += kSmallBlock * kSmallItems, b ^= 1) {
+        const int64_t i0 = base + (int64_t)threadIdx.x * kSmallItems;
+        int64_t v[kSmallItems], x = 0;
+#pragma unroll
+        for (int k = 0; k < kSmallItems; ++k) {
+            v[k] = i0 + k < len ? (int64_t)in[i0 + k] : 0;
+            x += v[k];
+        }
+        const int64_t own = x;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int64_t y = __shfl_up(x, d, kWave);
+            if (lane >= d) x += y;
+        }
+        if (lane == kWave - 1) wsum[b][w] = x;
+        __syncthreads();
+        int64_t run = carry + x - own;
+        for (int k = 0; k < kSmallBlock / kWave; ++k) {
+            if (k < w) run += wsum[b][k];
+            carry += wsum[b][k];
+        }
+#pragma unroll
+        for (int k = 0; k < kSmallItems; ++k) {
+            if (i0 + k < len) out[i0 + k] = run;
+            run += v[k];
+        }
+    }
+    if (threadIdx.x == 0) {
+        out[len] = carry;
+        if (total) *total = carry;
+    }
+}
+
+// out[len + 1] = exclusive scan of in[len]; the total is left in out[len] and
+// in *total (null: not wanted), a pinned host slot that the host reads after a
+// synchronisation.  Short inputs take one launch: the three passes cost three
+// launches of 3 to 5 us whatever the length, one workgroup 2 us for every 4096
+// elements.
+constexpr int64_t kScanSmall = 16384;
+template <typename In>
+hipError_t scan64(const In in, int64_t len, int64_t *out, DevBuf &tmp, hipStream_t st, int64_t *total = nullptr) {
+    if (len <= kScanSmall) {
+        k_scan_small<In><<<1, kSmallBlock, 0, st>>>(in, len, out, total);
+        return hipGetLastError();
+    }
+    const int64_t nb = (len + kScanTile - 1) / kScanTile;
     hipError_t e;
     if ((e = tmp.alloc(sizeof(int64_t) * (nb + 1))) != hipSuccess) return e;
-    k_scan_tiles<V><<<(unsigned)nb, kBlock, 0, st>>>(in, len, tmp.as<int64_t>());
+    k_scan_tiles<In><<<(unsigned)nb, kBlock, 0, st>>>(in, len, tmp.as<int64_t>());
     k_scan_sums64<<<1, kBlock, 0, st>>>(tmp.as<int64_t>(), nb);
-    k_scan_apply64<V><<<(unsigned)nb, kBlock, 0, st>>>(in, len, tmp.as<int64_t>(), nb, out);
+    k_scan_apply64<In><<<(unsigned)nb, kBlock, 0, st>>>(in, len, tmp.as<int64_t>(), nb, out, total);
     return hipGetLastError();
 }
 
@@ -951,14 +1010,28 @@ __global__ __launch_bounds__(kBlock) void k_sel_write(const int32_t *__restrict_
 // Level 1: distinct timestamps of each type, one wave per type.
 template <typename T>
 __global__ __launch_bounds__(kWave) void k_level1(const T *__restrict__ ts, const int32_t *__restrict__ type_off,
-                                                  int32_t *__restrict__ counts) {
+                                                  int32_t *__restrict__ counts, int32_t *__restrict__ host) {
     const int k = blockIdx.x;
     const int lane = threadIdx.x;
     const int32_t b = type_off[k], e = type_off[k + 1];
     int32_t c = 0;
     for (int32_t i = b + lane; i < e; i += kWave) c += (i == b || ts[i] != ts[i - 1]) ? 1 : 0;
     for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d, kWave);
-    if (lane == 0) counts[k] = c;
+    if (lane == 0) counts[k] = host[k] = c;
+}
+
+// The frequent types in order, by one wave.
+__global__ __launch_bounds__(kWave) void k_level1_freq(const int32_t *__restrict__ counts, int32_t K, int64_t thr,
+                                                       uint16_t *__restrict__ last, uint16_t *__restrict__ first) {
+    int32_t at = 0;
+    for (int32_t k0 = 0; k0 < K; k0 += kWave) {  // uniform
+        const int32_t k = k0 + (int)threadIdx.x;
+        const bool f = k < K && counts[k] > thr;
+        const uint64_t b = __ballot(f);
+        const int32_t o = at + __popcll(b & ((1ull << threadIdx.x) - 1ull));
+        if (f) last[o] = first[o] = (uint16_t)k;
+        at += __popcll(b);
+    }
 }
 
 // Apriori join on the device.  Every frequent episode of level N-1 >= 2
@@ -1065,14 +1138,12 @@ __global__ __launch_bounds__(kBlock) void k_freq_fields(FreqArgs a) {
 }
 
 // Write jobs: the alphas with frequent extensions (runs of equal fpar).
-__global__ __launch_bounds__(kBlock) void k_job_flags(const int32_t *__restrict__ fpar, int64_t nf,
-                                                      int32_t *__restrict__ flag) {
-    const int64_t f = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (f < nf) flag[f] = (f == 0 || fpar[f] != fpar[f - 1]) ? 1 : 0;
-}
+struct JobStart {
+    const int32_t *fpar;
+    __device__ int32_t operator[](int64_t f) const { return f == 0 || fpar[f] != fpar[f - 1] ? 1 : 0; }
+};
 
-__global__ __launch_bounds__(kBlock) void k_job_write(const int32_t *__restrict__ fpar, const int32_t *__restrict__ flag,
-                                                      const int64_t *__restrict__ jidx, int64_t nf,
+__global__ __launch_bounds__(kBlock) void k_job_write(const int32_t *__restrict__ fpar, const int64_t *__restrict__ jidx, int64_t nf,
                                                       int32_t *__restrict__ job_alpha, int64_t *__restrict__ job_f) {
     const int64_t f = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (f > nf) return;
@@ -1080,53 +1151,49 @@ __global__ __launch_bounds__(kBlock) void k_job_write(const int32_t *__restrict_
         job_f[jidx[nf]] = nf;
         return;
     }
-    if (flag[f]) {
+    if (JobStart{fpar}[f]) {
         job_alpha[jidx[f]] = fpar[f];
         job_f[jidx[f]] = f;
     }
 }
 
-// Length class of each job's alpha: leading zeros of its chain-list length,
-// so that ordering by the key takes the longest walks first.
-__global__ __launch_bounds__(kBlock) void k_len_key(const int32_t *__restrict__ clen, const int32_t *__restrict__ idx,
-                                                    int64_t n, uint16_t *__restrict__ key) {
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n) return;
-    const int32_t a = idx ? idx[j] : (int32_t)j;
-    key[j] = (uint16_t)__clz((uint32_t)clen[a] | 1u);
+// Jobs grouped by length class, the longest walks first (the class: leading
+// zeros of the chain-list length of the job's alpha): a counting sort whose
+// histogram is kept per block in LDS (kKeyItems jobs per block), so that a
+// block adds each class once; the order inside a class is arbitrary.
+constexpr int kLenClasses = 32;
+__device__ __forceinline__ int len_class(const int32_t *__restrict__ clen, const int32_t *__restrict__ idx, int64_t j) {
+    return __clz((uint32_t)clen[idx ? idx[j] : (int32_t)j] | 1u);
 }
 
-// Jobs grouped by a uint16 key (the alphas' last type): a counting sort whose
-// histogram is kept per block in LDS (kKeyItems jobs per block), so that a
-// block adds each key once; the order inside a key is arbitrary.
 constexpr int kKeyItems = 16;
 
-__global__ __launch_bounds__(kBlock) void k_key_count(const uint16_t *__restrict__ key, const int32_t *__restrict__ idx,
-                                                      int64_t n, int32_t K, int32_t *__restrict__ cnt) {
-    extern __shared__ int32_t h[];
-    for (int k = threadIdx.x; k < K; k += kBlock) h[k] = 0;
+__global__ __launch_bounds__(kBlock) void k_key_count(const int32_t *__restrict__ clen, const int32_t *__restrict__ idx,
+                                                      int64_t n, int32_t *__restrict__ cnt) {
+    __shared__ int32_t h[kLenClasses];
+    if (threadIdx.x < kLenClasses) h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kBlock * kKeyItems;
     for (int q = 0; q < kKeyItems; ++q) {
         const int64_t j = base + (int64_t)q * kBlock + threadIdx.x;
-        if (j < n) atomicAdd(&h[key[idx ? idx[j] : j]], 1);
+        if (j < n) atomicAdd(&h[len_class(clen, idx, j)], 1);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < K; k += kBlock) cnt[(int64_t)k * gridDim.x + blockIdx.x] = h[k];
+    if (threadIdx.x < kLenClasses) cnt[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = h[threadIdx.x];
 }
 
-// off: exclusive scan of cnt in key-major order (key, block)
-__global__ __launch_bounds__(kBlock) void k_key_place(const uint16_t *__restrict__ key, const int32_t *__restrict__ idx,
-                                                      int64_t n, int32_t K, const int64_t *__restrict__ off,
+// off: exclusive scan of cnt in class-major order (class, block)
+__global__ __launch_bounds__(kBlock) void k_key_place(const int32_t *__restrict__ clen, const int32_t *__restrict__ idx,
+                                                      int64_t n, const int64_t *__restrict__ off,
                                                       int32_t *__restrict__ order) {
-    extern __shared__ int32_t h[];
-    for (int k = threadIdx.x; k < K; k += kBlock) h[k] = 0;
+    __shared__ int32_t h[kLenClasses];
+    if (threadIdx.x < kLenClasses) h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kBlock * kKeyItems;
     for (int q = 0; q < kKeyItems; ++q) {
         const int64_t j = base + (int64_t)q * kBlock + threadIdx.x;
         if (j < n) {
-            const int32_t k = key[idx ? idx[j] : j];
+            const int k = len_class(clen, idx, j);
             const int32_t r = atomicAdd(&h[k], 1);
             order[off[(int64_t)k * gridDim.x + blockIdx.x] + r] = (int32_t)j;
         }
@@ -1225,27 +1292,18 @@ __global__ __launch_bounds__(kBlock) void k_piece_lists(const int64_t *__restric
 
 unsigned grid_of(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-template <typename V>
-hipError_t read_scalar(const DevBuf &b, int64_t at, V *out, hipStream_t st) {
-    hipError_t e = hipMemcpyAsync(out, b.as<V>() + at, sizeof(V), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    return e;
-}
-
-// jobs j = 0..n-1 ordered by key[idx[j]] (idx null: key[j]), key < K
-hipError_t order_by_key(const uint16_t *key, const int32_t *idx, int64_t n, int32_t K, DevBuf &order,
-                        hipStream_t st) {
+// jobs j = 0..n-1 (of alphas idx[j]; null: j) ordered by length class
+hipError_t order_by_length(const int32_t *clen, const int32_t *idx, int64_t n, DevBuf &order, hipStream_t st) {
     hipError_t e;
     if ((e = order.alloc(sizeof(int32_t) * std::max<int64_t>(1, n))) != hipSuccess) return e;
     if (n == 0) return hipSuccess;
     const int64_t nb = (n + kBlock * kKeyItems - 1) / (kBlock * kKeyItems);
     DevBuf cnt, off, tmp;
-    if ((e = cnt.alloc(sizeof(int32_t) * nb * K)) != hipSuccess) return e;
-    if ((e = off.alloc(sizeof(int64_t) * (nb * K + 1))) != hipSuccess) return e;
-    const size_t lds = sizeof(int32_t) * (size_t)K;
-    k_key_count<<<(unsigned)nb, kBlock, lds, st>>>(key, idx, n, K, cnt.as<int32_t>());
-    if ((e = scan64(cnt.as<int32_t>(), nb * K, off.as<int64_t>(), tmp, st)) != hipSuccess) return e;
-    k_key_place<<<(unsigned)nb, kBlock, lds, st>>>(key, idx, n, K, off.as<int64_t>(), order.as<int32_t>());
+    if ((e = cnt.alloc(sizeof(int32_t) * nb * kLenClasses)) != hipSuccess) return e;
+    if ((e = off.alloc(sizeof(int64_t) * (nb * kLenClasses + 1))) != hipSuccess) return e;
+    k_key_count<<<(unsigned)nb, kBlock, 0, st>>>(clen, idx, n, cnt.as<int32_t>());
+    if ((e = scan64(cnt.as<int32_t>(), nb * kLenClasses, off.as<int64_t>(), tmp, st)) != hipSuccess) return e;
+    k_key_place<<<(unsigned)nb, kBlock, 0, st>>>(clen, idx, n, off.as<int64_t>(), order.as<int32_t>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the temporaries die here: blocks of a cache scope go back for later
     // work of this stream, others are freed after it
@@ -1288,7 +1346,9 @@ hipError_t make_near(const Stream &s, Mine &mn, const WalkArgs<T> &w, hipStream_
 template <typename T>
 hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     hipError_t e;
-    if (!mn.stage) return hipErrorInvalidValue;
+    // pinned host slots that kernels write scalars to, read after a synchronisation
+    int64_t *stage = mn.stage;
+    if (!stage) return hipErrorInvalidValue;
     MineLevel &P = mn.levels.back();  // level N-1
     MineLevel L;
     L.N = N;
@@ -1317,16 +1377,14 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
                                                L.d_rlo.as<int32_t>(), L.d_xlo.as<int32_t>(), L.d_xhi.as<int32_t>(),
                                                cnt.as<int64_t>());
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = scan64(cnt.as<int64_t>(), nA, L.d_out_off.as<int64_t>(), tmp, st)) != hipSuccess) return e;
-        if ((e = read_scalar(L.d_out_off, nA, &m, st)) != hipSuccess) return e;
-        // workgroups take the alphas grouped by their last type: the waves in
-        // flight then walk the neighbourhoods of the same type's events
-        {
-            DevBuf lkey;
-            if ((e = lkey.alloc(sizeof(uint16_t) * std::max<int64_t>(1, nA))) != hipSuccess) return e;
-            k_len_key<<<grid_of(nA), kBlock, 0, st>>>(P.d_fnv.as<int32_t>(), nullptr, nA, lkey.as<uint16_t>());
-            if ((e = order_by_key(lkey.as<uint16_t>(), nullptr, nA, 33, d_order, st)) != hipSuccess) return e;
-        }
+        if ((e = scan64(cnt.as<int64_t>(), nA, L.d_out_off.as<int64_t>(), tmp, st, &stage[0])) != hipSuccess) return e;
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        m = stage[0];
+        // workgroups take the longest walks first, so that none is left alone
+        // at the end (the list path's walks are cut into pieces)
+        if ((nA >= kNearAlphas || nA >= mn.list_alphas) &&
+            (e = order_by_length(P.d_fnv.as<int32_t>(), nullptr, nA, d_order, st)) != hipSuccess)
+            return e;
     }
     L.m = m;
     WalkArgs<T> a{};
@@ -1357,24 +1415,18 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
         a.rlo = L.d_rlo.as<int32_t>();
         a.xlo = L.d_xlo.as<int32_t>();
         a.xhi = L.d_xhi.as<int32_t>();
-        a.order = d_order.as<int32_t>();
+        a.order = d_order.as<int32_t>();  // (null: not ordered)
     }
-    DevBuf d_nval, d_walked;
+    DevBuf d_nval;
     if ((e = L.dcounts.alloc(sizeof(int32_t) * m)) != hipSuccess) return e;
     if ((e = d_nval.alloc(sizeof(int32_t) * m)) != hipSuccess) return e;
-    constexpr size_t kWalkBytes = sizeof(unsigned long long) * kWalkSlots * kWalkStride;
-    if ((e = d_walked.alloc(kWalkBytes)) != hipSuccess) return e;
-    if ((e = hipMemsetAsync(d_walked.p, 0, kWalkBytes, st)) != hipSuccess) return e;
     a.counts = L.dcounts.as<int32_t>();
     a.nvalid = d_nval.as<int32_t>();
-    a.walked = d_walked.as<unsigned long long>();
+    a.walked = mn.walked.as<unsigned long long>();
     L.gen_ms = ms_since(t0);
     auto t1 = Clock::now();
     // ---- count
-    hipEvent_t ev0, ev1;
-    if ((e = hipEventCreate(&ev0)) != hipSuccess) return e;
-    if ((e = hipEventCreate(&ev1)) != hipSuccess) return e;
-    (void)hipEventRecord(ev0, st);
+    (void)hipEventRecord(mn.ev[0], st);
     if (m > 0 && N > 2 && (nA >= kNearAlphas || nA >= mn.list_alphas) &&
         P.chain_total >= s.n / kNearShare * ((s.K + 63) / 64)) {
         if ((e = make_near<T>(s, mn, a, st)) != hipSuccess) return e;
@@ -1394,9 +1446,10 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
         b.nseg = nseg;
         b.nvalid = nvseg.as<int32_t>();
         if ((e = launch_walk<T, kSize>(b, nA * nseg, st)) != hipSuccess) return e;
-        if ((e = scan64(nvseg.as<int32_t>(), m * nseg, lst_off.as<int64_t>(), tmp, st)) != hipSuccess) return e;
-        int64_t total = 0;
-        if ((e = read_scalar(lst_off, m * nseg, &total, st)) != hipSuccess) return e;
+        if ((e = scan64(nvseg.as<int32_t>(), m * nseg, lst_off.as<int64_t>(), tmp, st, &stage[0])) != hipSuccess)
+            return e;
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        const int64_t total = stage[0];
         if (total * (int64_t)sizeof(ChainEntry<T>) <= mn.list_budget) {
             if ((e = L.chain.alloc(sizeof(ChainEntry<T>) * (size_t)total)) != hipSuccess) return e;
             b.lst_off = lst_off.as<int64_t>();
@@ -1414,15 +1467,13 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
         }
     }
     if (m > 0 && !listed && e == hipSuccess) e = launch_walk<T, kCount>(a, nA, st);
-    (void)hipEventRecord(ev1, st);
+    (void)hipEventRecord(mn.ev[1], st);
     // the walked positions and the number of frequent episodes reach the host
-    // at one synchronisation (pinned slots 0 and 1)
-    int64_t *stage = mn.stage;
+    // at one synchronisation (slots 0 and 1)
     if (e == hipSuccess) {
-        k_sum_walked<<<1, kWalkSlots, 0, st>>>(d_walked.as<unsigned long long>());
+        k_sum_walked<<<1, kWalkSlots, 0, st>>>(a.walked, &stage[0]);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(&stage[0], d_walked.p, sizeof(int64_t), hipMemcpyDeviceToHost, st);
     // ---- frequent episodes, selected on the device
     const int64_t nb = m > 0 ? (m + kSelTile - 1) / kSelTile : 0;
     int64_t nf = 0;
@@ -1433,15 +1484,11 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     if (nb > 0 && e == hipSuccess) {
         k_sel_count<<<(unsigned)nb, kBlock, 0, st>>>(a.counts, m, thr, bcnt.as<int32_t>());
         e = hipGetLastError();
-        if (e == hipSuccess) e = scan64(bcnt.as<int32_t>(), nb, boffs.as<int64_t>(), tmp, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&stage[1], boffs.as<int64_t>() + nb, sizeof(int64_t), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = scan64(bcnt.as<int32_t>(), nb, boffs.as<int64_t>(), tmp, st, &stage[1]);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     float kms = 0;
-    if (e == hipSuccess) (void)hipEventElapsedTime(&kms, ev0, ev1);
-    (void)hipEventDestroy(ev0);
-    (void)hipEventDestroy(ev1);
+    if (e == hipSuccess) (void)hipEventElapsedTime(&kms, mn.ev[0], mn.ev[1]);
     if (e != hipSuccess) return e;
     L.kernel_ms = kms;
     L.walked = stage[0];
@@ -1490,14 +1537,11 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
         // chain lists: offsets from the scan of the end-event counts (the
         // list path keeps every candidate's list; its frequent ones are the
         // chain lists)
-        DevBuf tmp2, flag, jidx, job_alpha, job_f, w_order;
-        if (!a.near) {
-            if ((e = scan64(L.d_fnv.as<int32_t>(), nf, L.cbeg.as<int64_t>(), tmp2, st)) != hipSuccess) return e;
-            // the chain entries in all (pinned slot 2), read at the next synchronisation
-            if ((e = hipMemcpyAsync(&stage[2], L.cbeg.as<int64_t>() + nf, sizeof(int64_t), hipMemcpyDeviceToHost,
-                                    st)) != hipSuccess)
-                return e;
-        }
+        DevBuf tmp2, jidx, job_alpha, job_f, w_order;
+        // (the chain entries in all: slot 2, read after the next synchronisation)
+        if (!a.near &&
+            (e = scan64(L.d_fnv.as<int32_t>(), nf, L.cbeg.as<int64_t>(), tmp2, st, &stage[2])) != hipSuccess)
+            return e;
         if (listed) {
             k_list_begin<<<grid_of(nf), kBlock, 0, st>>>(L.d_fcand.as<int64_t>(), lst_off.as<int64_t>(), L.list_seg,
                                                          nf, L.cbeg.as<int64_t>());
@@ -1508,29 +1552,20 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
             goto done;
         }
         // write jobs: the alphas with frequent extensions
-        if ((e = flag.alloc(sizeof(int32_t) * nf)) != hipSuccess) return e;
         if ((e = jidx.alloc(sizeof(int64_t) * (nf + 1))) != hipSuccess) return e;
-        k_job_flags<<<grid_of(nf), kBlock, 0, st>>>(L.d_fpar.as<int32_t>(), nf, flag.as<int32_t>());
-        if ((e = scan64(flag.as<int32_t>(), nf, jidx.as<int64_t>(), tmp, st)) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(&stage[3], jidx.as<int64_t>() + nf, sizeof(int64_t), hipMemcpyDeviceToHost, st)) !=
-            hipSuccess)
+        if ((e = scan64(JobStart{L.d_fpar.as<int32_t>()}, nf, jidx.as<int64_t>(), tmp, st, &stage[3])) != hipSuccess)
             return e;
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         const int64_t nj = stage[3];
+        L.chain_total = stage[2];
         if ((e = job_alpha.alloc(sizeof(int32_t) * nj)) != hipSuccess) return e;
         if ((e = job_f.alloc(sizeof(int64_t) * (nj + 1))) != hipSuccess) return e;
-        k_job_write<<<grid_of(nf + 1), kBlock, 0, st>>>(L.d_fpar.as<int32_t>(), flag.as<int32_t>(),
-                                                       jidx.as<int64_t>(), nf, job_alpha.as<int32_t>(),
+        k_job_write<<<grid_of(nf + 1), kBlock, 0, st>>>(L.d_fpar.as<int32_t>(), jidx.as<int64_t>(), nf, job_alpha.as<int32_t>(),
                                                        job_f.as<int64_t>());
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (N > 2) {
-            // few jobs: the longest walks first, so that none is left alone at the end
-            DevBuf lkey;
-            if ((e = lkey.alloc(sizeof(uint16_t) * std::max<int64_t>(1, nj))) != hipSuccess) return e;
-            k_len_key<<<grid_of(nj), kBlock, 0, st>>>(P.d_fnv.as<int32_t>(), job_alpha.as<int32_t>(), nj,
-                                                      lkey.as<uint16_t>());
-            if ((e = order_by_key(lkey.as<uint16_t>(), nullptr, nj, 33, w_order, st)) != hipSuccess) return e;
-        }
+        // few jobs: the longest walks first, so that none is left alone at the end
+        if (N > 2 && (e = order_by_length(P.d_fnv.as<int32_t>(), job_alpha.as<int32_t>(), nj, w_order, st)) != hipSuccess)
+            return e;
         a.job_alpha = job_alpha.as<int32_t>();
         a.job_f = job_f.as<int64_t>();
         a.order = N > 2 ? w_order.as<int32_t>() : nullptr;
@@ -1551,16 +1586,17 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
             a.nvalid = wseg.as<int32_t>();
             a.walked = nullptr;
             if ((e = launch_walk<T, kWSize>(a, nj * a.nseg, st)) != hipSuccess) return e;
-            if ((e = scan64(wseg.as<int32_t>(), nf * a.nseg, woff.as<int64_t>(), tmp, st)) != hipSuccess) return e;
+            if ((e = scan64(wseg.as<int32_t>(), nf * a.nseg, woff.as<int64_t>(), tmp, st, &stage[2])) != hipSuccess)
+                return e;
             a.lst_off = woff.as<int64_t>();
         }
         if (a.near) {
             k_piece_lists<<<grid_of(nf + 1), kBlock, 0, st>>>(woff.as<int64_t>(), a.nseg, nf, L.cbeg.as<int64_t>(),
                                                              L.d_fnv.as<int32_t>());
             if ((e = hipGetLastError()) != hipSuccess) return e;
-            if ((e = read_scalar(woff, nf * a.nseg, &stage[2], st)) != hipSuccess) return e;
+            if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         }
-        L.chain_total = stage[2];
+        if (a.near) L.chain_total = stage[2];
         if ((e = L.chain.alloc(sizeof(ChainEntry<T>) * (size_t)L.chain_total)) != hipSuccess) return e;
         a.wchain = L.chain.as<ChainEntry<T>>();
         e = pieced ? launch_walk<T, kWList>(a, nj * a.nseg, st) : launch_walk<T, kWrite>(a, nj, st);
@@ -1591,35 +1627,22 @@ hipError_t level1_t(const Stream &s, Mine &mn, hipStream_t st) {
     L.implicit = false;
     auto t1 = Clock::now();
     if ((e = L.dcounts.alloc(sizeof(int32_t) * s.K)) != hipSuccess) return e;
-    k_level1<T><<<s.K, kWave, 0, st>>>(s.ts_by_type.as<T>(), s.type_off.as<int32_t>(), L.dcounts.as<int32_t>());
+    // a 1-node episode's first and last node is its type
+    if ((e = L.d_flast.alloc(sizeof(uint16_t) * (size_t)s.K)) != hipSuccess) return e;
+    if ((e = L.d_ffirst.alloc(sizeof(uint16_t) * (size_t)s.K)) != hipSuccess) return e;
+    int32_t *host = reinterpret_cast<int32_t *>(mn.stage + kStageSlots);
+    k_level1<T><<<s.K, kWave, 0, st>>>(s.ts_by_type.as<T>(), s.type_off.as<int32_t>(), L.dcounts.as<int32_t>(), host);
+    k_level1_freq<<<1, kWave, 0, st>>>(L.dcounts.as<int32_t>(), s.K, mn.threshold, L.d_flast.as<uint16_t>(),
+                                       L.d_ffirst.as<uint16_t>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    L.counts.resize(s.K);
-    if ((e = hipMemcpyAsync(L.counts.data(), L.dcounts.p, sizeof(int32_t) * s.K, hipMemcpyDeviceToHost, st)) !=
-        hipSuccess)
-        return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    L.counts.assign(host, host + s.K);
     L.types.resize(s.K);
-    for (int32_t k = 0; k < s.K; ++k) L.types[k] = (uint16_t)k;
-    std::vector<uint16_t> f1;
     for (int32_t k = 0; k < s.K; ++k) {
-        if (L.counts[k] > mn.threshold) {
-            L.freq.push_back(k);
-            f1.push_back((uint16_t)k);
-        }
+        L.types[k] = (uint16_t)k;
+        if (L.counts[k] > mn.threshold) L.freq.push_back(k);
     }
     L.nf = (int64_t)L.freq.size();
-    // a 1-node episode's first and last node is its type
-    if ((e = L.d_flast.alloc(sizeof(uint16_t) * std::max<size_t>(1, f1.size()))) != hipSuccess) return e;
-    if ((e = L.d_ffirst.alloc(sizeof(uint16_t) * std::max<size_t>(1, f1.size()))) != hipSuccess) return e;
-    if (!f1.empty()) {
-        if ((e = hipMemcpyAsync(L.d_flast.p, f1.data(), sizeof(uint16_t) * f1.size(), hipMemcpyHostToDevice, st)) !=
-            hipSuccess)
-            return e;
-        if ((e = hipMemcpyAsync(L.d_ffirst.p, f1.data(), sizeof(uint16_t) * f1.size(), hipMemcpyHostToDevice,
-                                st)) != hipSuccess)
-            return e;
-    }
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     L.count_ms = ms_since(t1);
     L.alg_bytes = s.n * (int64_t)s.ts_bytes() + 4 * (int64_t)s.K;
     mn.levels.push_back(std::move(L));
@@ -1712,6 +1735,19 @@ hipError_t extend_read_frequent(const Mine &mn, int level, int32_t *types, int64
     a.out = a.types + kMaxN * nf;
     k_mine_rows<<<grid_of(L.nf), kBlock, 0, st>>>(a);
     e = hipGetLastError();
+    // few rows come with one copy to pinned memory
+    const size_t all = 2 * b64 + bt + sizeof(int32_t) * nf;
+    if (all <= kStageBytes) {
+        char *h = reinterpret_cast<char *>(mn.stage + kStageSlots);
+        if (e == hipSuccess) e = hipMemcpyAsync(h, d.p, all, hipMemcpyDeviceToHost, st);
+        const hipError_t w = hipStreamSynchronize(st);
+        if (e != hipSuccess || w != hipSuccess) return e != hipSuccess ? e : w;
+        std::memcpy(lo, h, b64);
+        std::memcpy(hi, h + b64, b64);
+        std::memcpy(types, h + 2 * b64, bt);
+        std::memcpy(counts, h + 2 * b64 + bt, sizeof(int32_t) * nf);
+        return hipSuccess;
+    }
     if (e == hipSuccess) e = hipMemcpyAsync(types, a.types, bt, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipMemcpyAsync(lo, a.lo, b64, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipMemcpyAsync(hi, a.hi, b64, hipMemcpyDeviceToHost, st);
@@ -1753,6 +1789,11 @@ hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st) {
     hipError_t e;
     if ((e = mn.ty16.alloc(sizeof(uint16_t) * (size_t)s.n)) != hipSuccess) return e;
     if ((e = mn.wend.alloc(sizeof(int32_t) * (size_t)s.n)) != hipSuccess) return e;
+    constexpr size_t kWalkBytes = sizeof(unsigned long long) * kWalkSlots * kWalkStride;
+    if ((e = mn.walked.alloc(kWalkBytes)) != hipSuccess) return e;
+    if ((e = hipMemsetAsync(mn.walked.p, 0, kWalkBytes, st)) != hipSuccess) return e;
+    for (hipEvent_t &ev : mn.ev)
+        if ((e = hipEventCreate(&ev)) != hipSuccess) return e;
     if (s.n == 0) return hipSuccess;
     const int64_t H = *std::max_element(mn.menu_hi.begin(), mn.menu_hi.end());
     const unsigned blocks = (unsigned)((s.n + 255) / 256);

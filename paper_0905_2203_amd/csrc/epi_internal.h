@@ -394,6 +394,12 @@ struct Mine {
     // pinned host slots (the context's) that device scalars are copied to,
     // several per synchronisation
     int64_t *stage = nullptr;
+    DevBuf walked;  // counters of the positions in the walked windows
+    hipEvent_t ev[2] = {nullptr, nullptr};  // around a level's counting kernels
+    ~Mine() {
+        for (hipEvent_t x : ev)
+            if (x) (void)hipEventDestroy(x);
+    }
 };
 
 // Cost model (epi_mlp.hip): parameters, Adam moments, gradient, activations.
@@ -558,7 +564,8 @@ int queue_class_of(int64_t bound);
 // then count level N (>= 2) from level N-1's frequent episodes and chain lists,
 // select its frequent episodes and write their chain lists.  Menus of up to
 // kExtMaxMenu intervals.
-constexpr int kStageSlots = 8;     // pinned host slots of a mining run
+constexpr int kStageSlots = 8;     // pinned host slots of a mining run, and room after them
+constexpr size_t kStageBytes = size_t(1) << 20;
 constexpr int kExtMaxMenu = 8;
 hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st);
 hipError_t extend_level1(const Stream &s, Mine &mn, hipStream_t st);
