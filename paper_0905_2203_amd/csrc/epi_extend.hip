@@ -84,7 +84,7 @@ constexpr uint16_t kNoSlot = 0;  // owner-slot entry of a type no lane counts (n
 // costs half the work.
 constexpr int64_t kListJobs = 65536;
 constexpr int64_t kWritePieced = 32768;
-constexpr int64_t kWriteJobs = 262144;
+constexpr int64_t kWriteJobs = 65536;
 // Near rows: at most this many bytes of them, and only for a level whose chain
 // lists have at least a quarter as many entries (times the words of a row
 // set) as the stream has events: a row costs some 8 lane instructions an event
