@@ -169,6 +169,9 @@ hipError_t wave_launch_append(const CountArgs<T> &a, T B, hipStream_t st);
 // slots; segmented: some unit has P > 1.
 template <typename T>
 hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WorkItem *items,
-                                  int64_t n_items, unsigned long long *queue, bool segmented);
+                                  int64_t n_items, unsigned long long *queue, bool segmented, void *list, int64_t cap);
+// Bytes of `list` (null: every slot of the items is queued) for at most cap
+// slots at work.
+size_t wave_list_bytes(int64_t n_items, int64_t cap);
 
 }  // namespace epi

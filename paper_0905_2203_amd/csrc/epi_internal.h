@@ -426,7 +426,7 @@ struct BatchPlan {
     uint64_t id = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    DevBuf units, tmpl, items, queue, rec, cycles;
+    DevBuf units, tmpl, items, queue, rec, cycles, wave_list;
     DevBuf ssets, sgroups, gid, sunits, X, y, k0, k1, v0, v1, ik0, ik1, iv0, iv1, hist;
     int64_t n_items = 0;
     int64_t launches = 0;

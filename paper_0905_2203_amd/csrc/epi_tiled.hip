@@ -985,20 +985,27 @@ void candidate_costs(const Stream &s, CandSet &c) {
 }
 
 // Segments of episodes counted by the wave chains (and the tiles per segment,
-// *S_out): the costliest (episode, segment) takes about a third of what each
+// *S_out): the costliest (episode, segment) takes 1 / share of what each
 // resident wave has to do of the whole launch, so that no wave is left running
-// alone at its end; a segment holds at least kWaveMinEvents of the costliest
+// alone at its end (plain launches 3: 5k episodes of 1-6 nodes 508 us, 521 at
+// 4.5, 530 at 6; batched ones 4.5: 12.5k episodes over skewed rates 4.63 ms,
+// 5.00 at 3, 4.52 at 6, 7k in five sets 805 us, 822 and 895); a segment holds at least kWaveMinEvents of the costliest
 // episode's events, below which its start and reconciliation cost more than
 // they spread.  EPI_OPT_TARGET_LANES scales the resident waves aimed at.
+// At most kWaveSlots slots in all: the light episodes' empty ones cost a
+// workgroup's or a list kernel's time each.
 constexpr double kWaveMinEvents = 4096;
-int64_t wave_segments(const Stream &s, double cost_max, double cost_all, const CountOptions &opt, int waves,
-                      int64_t *S_out) {
+constexpr int64_t kWaveSlots = int64_t(1) << 21;
+constexpr double kWaveSharePlain = 3.0, kWaveShareBatched = 4.5;
+int64_t wave_segments(const Stream &s, int64_t G, double cost_max, double cost_all, double share,
+                      const CountOptions &opt, int waves, int64_t *S_out) {
     int64_t P = 1;
     if (opt.segments > 0) {
         P = opt.segments;
     } else if (cost_all > 0) {
-        const double aim = 3.0 * (double)waves * ((double)opt.target_lanes / 262144.0);
+        const double aim = share * (double)waves * ((double)opt.target_lanes / 262144.0);
         P = (int64_t)std::min(std::ceil(aim * cost_max / cost_all), cost_max / kWaveMinEvents);
+        P = std::min(P, kWaveSlots / G);
     }
     P = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(P, s.B), 65535));
     const int64_t S = (std::max<int64_t>(s.B, 1) + P - 1) / P;
@@ -1054,7 +1061,7 @@ hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end,
     int waves = 0;
     if ((e = wave_resident(&waves)) != hipSuccess) return e;
     CountArgs<T> a = wave_args<T>(s, c, d_flags);
-    const int64_t P = wave_segments(s, cost_max, cost_all, opt, waves, &a.S);
+    const int64_t P = wave_segments(s, end - begin, cost_max, cost_all, kWaveSharePlain, opt, waves, &a.S);
     a.P = (int32_t)P;
     a.seg_cost = wave_seg_cost(opt, cost_max, P);
     int64_t step = end - begin;
@@ -1527,7 +1534,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             u.cost_max = g.cost_max;
             u.wave = wave_group_ok(s, c, g, opt);
             if (u.wave) {
-                u.P = wave_segments(s, u.cost_max, wave_cost, opt, waves, &u.S);
+                u.P = wave_segments(s, G, u.cost_max, wave_cost, kWaveShareBatched, opt, waves, &u.S);
                 units.push_back(u);
                 continue;
             }
@@ -1753,6 +1760,20 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             return e;
     }
 
+    // the wave chains' slots at work: an episode of c events has at most
+    // c / seg_cost + 1 segments
+    int64_t wave_cap = 0, wave_slots = 0;
+    for (size_t ui = 0; ui < units.size(); ++ui) {
+        const UnitH &u = units[ui];
+        if (!u.wave) continue;
+        const int64_t all = (u.G + 63) / 64 * 64 * u.P;
+        wave_slots += all;
+        wave_cap += ua[ui].seg_cost > 0 ? std::min(all, (int64_t)(u.cost_sum / (double)ua[ui].seg_cost) + u.G) : all;
+    }
+    const bool wave_listed = wave_cap < wave_slots / 2;
+    const int64_t wave_items = ioff[kWaveClass + 1] - ioff[kWaveClass];
+    if (wave_listed && (e = plan.wave_list.alloc(wave_list_bytes(wave_items, wave_cap))) != hipSuccess) return e;
+
     // 5. capture: scheduler, queue clear, persistent launches on parallel
     // branches (costliest classes first, each onto the least loaded branch),
     // join, reconciliation
@@ -1835,7 +1856,8 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ncl * 64, waves));
             e = wave_launch_persistent<T>((unsigned)grid, cache.br[bi], plan.units.as<CountArgs<T>>(),
                                           plan.items.as<WorkItem>() + ioff[cl], ncl,
-                                          plan.queue.as<unsigned long long>() + cl, wave_segmented);
+                                          plan.queue.as<unsigned long long>() + cl, wave_segmented,
+                                          wave_listed ? plan.wave_list.p : nullptr, wave_cap);
             continue;
         }
         if (laneN[cl]) {

@@ -124,3 +124,28 @@ def test_appended_events():
             ctx.epi_count([cid], epi.EPI_MODE_INCREMENTAL)
             part = dict(s, types=s["types"][:b], times=s["times"][:b])
             assert np.array_equal(ctx.epi_read_counts(cid, c["N"].size), oracle.count(part, c)), f"events 0..{b}"
+
+
+@pytest.mark.parametrize("m,kind", [(64, 0), (65, 1), (300, 0)])
+def test_skewed_episodes_in_listed_slots(m, kind):
+    """Batched: few episodes have many segments and most have one, so the queue runs over a list of the slots at work;
+    two sets of different streams, every schedule twice (the second from the kept plan)."""
+    rng = np.random.Generator(np.random.PCG64(70 + m))
+    sets, ctx = [], epi.Context(0)
+    with ctx:
+        for busy in (60000, 23000):
+            types, times = per_type(rng, [busy] + [200] * 9, 50)
+            s = stream(types, times, kind)
+            eps = [(np.arange(1, 10)[rng.permutation(9)[:n]], np.zeros(n - 1, int), rng.integers(2000, 40000, size=n - 1))
+                   for n in rng.integers(1, 5, size=m)]
+            for i in rng.permutation(m)[:5]:  # with the busy type
+                eps[i] = (np.concatenate([[0], eps[i][0]]), np.zeros(eps[i][0].size, int),
+                          rng.integers(200, 40000, size=eps[i][0].size))
+            c = sg.candidates_from_list(eps)
+            sid = ctx.epi_load_stream(s["types"], s["times"], s["K"])
+            sets.append((ctx.epi_submit_candidates(sid, c), c["N"].size, oracle.count(s, c)))
+        for sched in (epi.EPI_SCHED_RR, epi.EPI_SCHED_HEURISTIC):
+            for _ in range(2):
+                ctx.epi_count([cid for cid, _, _ in sets], epi.EPI_MODE_BATCHED, sched)
+                for cid, k, want in sets:
+                    assert np.array_equal(ctx.epi_read_counts(cid, k), want)
