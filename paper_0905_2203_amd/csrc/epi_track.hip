@@ -323,11 +323,19 @@ __global__ __launch_bounds__(kTB) void k_track_final(const GreedyJob<T> *__restr
     if (tau) tau[j.slot] = n > 0 ? j.t[h0.last] : TsLimits<T>::lo();
 }
 
-// stream positions of a type's events, widened to the time type
+// Stream positions of the events of each job's first type, widened to the time
+// type (one launch: a launch a job took 3 us each, a third of a short call).
 template <typename T>
-__global__ __launch_bounds__(kTB) void k_track_pos(const int32_t *__restrict__ pos, int32_t n, T *__restrict__ out) {
+struct PosJob {
+    const int32_t *pos;
+    T *out;
+    int32_t n;
+};
+template <typename T>
+__global__ __launch_bounds__(kTB) void k_track_pos(const PosJob<T> *__restrict__ jobs) {
+    const PosJob<T> j = jobs[blockIdx.y];
     const int64_t i = (int64_t)blockIdx.x * kTB + threadIdx.x;
-    if (i < n) out[i] = (T)pos[i];
+    if (i < j.n) j.out[i] = (T)j.pos[i];
 }
 
 size_t round_up(size_t b) { return (b + 255) & ~size_t(255); }
@@ -367,7 +375,8 @@ hipError_t count_tracking_t(const Stream &s, CandSet &c, hipStream_t st) {
         if (work.bytes < total && (e = work.alloc(total)) != hipSuccess) return e;
         std::vector<std::vector<TrackJob<T>>> lv(kMaxN + 1);
         std::vector<GreedyJob<T>> gj;
-        int32_t max_bound = 1;
+        std::vector<PosJob<T>> pj;
+        int32_t max_bound = 1, max_first = 0;
         char *p = work.as<char>();
         for (int64_t q = q0; q < q1; ++q) {
             const int N = c.h_N[q];
@@ -396,9 +405,8 @@ hipError_t count_tracking_t(const Stream &s, CandSet &c, hipStream_t st) {
             // node 1: the type's events, each its own start (its time, or its stream position)
             const T *pt = tsb + s.h_off[ty[0]], *pL = pt, *pK = pt;
             if (so) {
-                if (nt(ty[0]) > 0)
-                    k_track_pos<T><<<(unsigned)((nt(ty[0]) + kTB - 1) / kTB), kTB, 0, st>>>(
-                        s.pos_by_type.as<int32_t>() + s.h_off[ty[0]], nt(ty[0]), l1);
+                pj.push_back(PosJob<T>{s.pos_by_type.as<int32_t>() + s.h_off[ty[0]], l1, nt(ty[0])});
+                max_first = std::max(max_first, nt(ty[0]));
                 pL = pK = l1;
             }
             const int32_t *pn = nullptr;
@@ -448,13 +456,19 @@ hipError_t count_tracking_t(const Stream &s, CandSet &c, hipStream_t st) {
         }
         const size_t goff = db;
         db += round_up(sizeof(GreedyJob<T>) * gj.size());
+        const size_t poff = db;
+        db += round_up(sizeof(PosJob<T>) * pj.size());
         std::vector<char> hd(db);
         for (int k = 1; k < kMaxN; ++k)
             if (!lv[k].empty()) std::copy_n((const char *)lv[k].data(), sizeof(TrackJob<T>) * lv[k].size(), &hd[loff[k]]);
         std::copy_n((const char *)gj.data(), sizeof(GreedyJob<T>) * gj.size(), &hd[goff]);
+        if (!pj.empty()) std::copy_n((const char *)pj.data(), sizeof(PosJob<T>) * pj.size(), &hd[poff]);
         DevBuf &desc = c.track_desc;
         if (desc.bytes < db && (e = desc.alloc(db)) != hipSuccess) return e;
         if ((e = hipMemcpyAsync(desc.p, hd.data(), db, hipMemcpyHostToDevice, st)) != hipSuccess) return e;
+        if (max_first > 0)
+            k_track_pos<T><<<dim3((unsigned)((max_first + kTB - 1) / kTB), (unsigned)pj.size()), kTB, 0, st>>>(
+                (const PosJob<T> *)(desc.as<char>() + poff));
         for (int k = 1; k < kMaxN; ++k) {
             if (lv[k].empty()) continue;
             int32_t gx = 1;
