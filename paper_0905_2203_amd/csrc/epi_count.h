@@ -151,25 +151,31 @@ hipError_t lane_launch_persistent(int N, bool pk, bool wl, unsigned grid, int W,
 // One wave counts one (candidate, segment), of any size.  A launch takes slots
 // [begin, begin + G) of a set and, for P > 1, reconciles the segments.
 constexpr int kWaveChunks = 4;   // events per node and window, in 64s
-constexpr int kWaveGap = 63;     // Stream::gap is the least t[i + kWaveGap] - t[i] of one type
+constexpr int kWaveHands = 2;    // chain lists hand on up to 64 or 128 entries
+constexpr int kWaveGap[kWaveHands] = {63, 127};  // Stream::gap[h]: the least t[i + kWaveGap[h]] - t[i] of one type
 
-// Whether the chains' bounds hold for episodes of the given longest span and
-// largest lower bound on a stream of the given gap: fewer than 64 events of a
-// type within any lower bound (the entries a list hands on fit a wave), fewer
-// than 64 at one time (a window always advances), spans below 2^29.
-inline bool wave_ok(int64_t gap, int64_t hspan, int64_t lomax) {
-    return gap >= 1 && gap >= lomax && hspan >= 0 && hspan < (int64_t(1) << 29);
+// How many entries, in 64s, the chains' lists hand on at most for episodes of
+// the given longest span and largest lower bound on a stream of the given gaps;
+// 0: the chains' bounds do not hold.  Within any lower bound and at any one time
+// a type then has fewer events than that (so a window always advances); spans
+// are below 2^29.
+inline int wave_hand(const int64_t *gap, int64_t hspan, int64_t lomax) {
+    if (hspan < 0 || hspan >= (int64_t(1) << 29)) return 0;
+    for (int h = 0; h < kWaveHands; ++h)
+        if (gap[h] >= 1 && gap[h] >= lomax) return h + 1;
+    return 0;
 }
-int wave_waves_per_cu();
+int wave_waves_per_cu(int hand);
 template <typename T>
-hipError_t wave_launch(const CountArgs<T> &a, hipStream_t st);
+hipError_t wave_launch(const CountArgs<T> &a, int hand, hipStream_t st);
 template <typename T>
-hipError_t wave_launch_append(const CountArgs<T> &a, T B, hipStream_t st);
-// units, items, queue: as lane_launch_persistent, an item's block being 64
-// slots; segmented: some unit has P > 1.
+hipError_t wave_launch_append(const CountArgs<T> &a, int hand, T B, hipStream_t st);
+// The batched form over work items (blocks of 64 slots): a persistent grid and,
+// if segmented, the reconciliation of the units cut into segments.
 template <typename T>
-hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WorkItem *items,
-                                  int64_t n_items, unsigned long long *queue, bool segmented, void *list, int64_t cap);
+hipError_t wave_launch_persistent(unsigned grid, int hand, hipStream_t st, const CountArgs<T> *units,
+                                  const WorkItem *items, int64_t n_items, unsigned long long *queue, bool segmented,
+                                  void *list, int64_t cap);
 // Bytes of `list` (null: every slot of the items is queued) for at most cap
 // slots at work.
 size_t wave_list_bytes(int64_t n_items, int64_t cap);

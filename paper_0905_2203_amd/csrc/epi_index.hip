@@ -257,8 +257,8 @@ __global__ __launch_bounds__(kIdxBlock) void k_scatter(const int32_t *__restrict
     }
 }
 
-// out = min over events i with an event i + kWaveGap of the same type of the
-// time between them (out holds the type's maximum before).
+// out[h] = min over events i with an event i + kWaveGap[h] of the same type of
+// the time between them (out holds the type's maximum before).
 constexpr int kGapBlock = 256, kGapItems = 16;
 template <typename T>
 __global__ __launch_bounds__(kGapBlock) void k_gap(const T *__restrict__ ts, int64_t n,
@@ -272,32 +272,40 @@ __global__ __launch_bounds__(kGapBlock) void k_gap(const T *__restrict__ ts, int
         if (off[mid] <= b0) lo = mid; else hi = mid - 1;
     }
     int ty = lo;
-    unsigned long long best = INT64_MAX;
+    unsigned long long best[kWaveHands];
+    for (int h = 0; h < kWaveHands; ++h) best[h] = INT64_MAX;
     for (int q = 0; q < kGapItems; ++q) {
         const int64_t i = b0 + q * kGapBlock + threadIdx.x;
-        if (i + kWaveGap >= n) break;
+        if (i + kWaveGap[0] >= n) break;
         while (off[ty + 1] <= i) ++ty;
-        if (i + kWaveGap < off[ty + 1]) {
-            const unsigned long long d = (unsigned long long)ts[i + kWaveGap] - (unsigned long long)ts[i];
-            best = d < best ? d : best;
+#pragma unroll
+        for (int h = 0; h < kWaveHands; ++h) {
+            if (i + kWaveGap[h] < off[ty + 1]) {
+                const unsigned long long d = (unsigned long long)ts[i + kWaveGap[h]] - (unsigned long long)ts[i];
+                best[h] = d < best[h] ? d : best[h];
+            }
         }
-    }
-    for (int d = 1; d < kWave; d <<= 1) {
-        const unsigned long long o = __shfl_xor(best, d, kWave);
-        best = o < best ? o : best;
     }
     // one atomic a block, and only where it lowers the minimum (a stale read
     // only costs an atomic): thousands on one address would serialise
-    __shared__ unsigned long long part[kGapBlock / kWave];
-    if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = best;
+    __shared__ unsigned long long part[kWaveHands][kGapBlock / kWave];
+#pragma unroll
+    for (int h = 0; h < kWaveHands; ++h) {
+        for (int d = 1; d < kWave; d <<= 1) {
+            const unsigned long long o = __shfl_xor(best[h], d, kWave);
+            best[h] = o < best[h] ? o : best[h];
+        }
+        if (threadIdx.x % kWave == 0) part[h][threadIdx.x / kWave] = best[h];
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kGapBlock / kWave; ++q) best = part[q] < best ? part[q] : best;
-        if (best < *(volatile unsigned long long *)out) atomicMin(out, best);
+    if (threadIdx.x < kWaveHands) {
+        unsigned long long b = part[threadIdx.x][0];
+        for (int q = 1; q < kGapBlock / kWave; ++q) b = part[threadIdx.x][q] < b ? part[threadIdx.x][q] : b;
+        if (b < *(volatile unsigned long long *)(out + threadIdx.x)) atomicMin(out + threadIdx.x, b);
     }
 }
 
-__global__ void k_gap_init(unsigned long long *out) { *out = INT64_MAX; }
+__global__ void k_gap_init(unsigned long long *out) { out[threadIdx.x] = INT64_MAX; }
 
 // Tile sizes a stream may pick: kMinTile << q.
 constexpr int kTileSizes = 5;
@@ -430,7 +438,7 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
     const int64_t B = n > 0 ? (n + TT - 1) / TT : 0;
     s.B = B;
     s.max_tile_span = n > 0 ? longest_tile(s, TT) : 0;
-    s.gap = INT64_MAX;
+    for (int64_t &g : s.gap) g = INT64_MAX;
     if ((e = s.type_off.alloc(sizeof(int32_t) * (K + 1))) != hipSuccess) return e;
     // (padded: the wave chains load whole windows)
     if ((e = s.ts_by_type.alloc(s.ts_bytes() * ((size_t)n + kWaveChunks * kWave))) != hipSuccess) return e;
@@ -448,7 +456,7 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
     if ((e = cnt.alloc(sizeof(int32_t) * (size_t)B * K)) != hipSuccess) return e;
     if ((e = sums.alloc(sizeof(int32_t) * (size_t)nc * K)) != hipSuccess) return e;
     if ((e = tot.alloc(sizeof(int32_t) * (size_t)K)) != hipSuccess) return e;
-    if ((e = gap.alloc(sizeof(unsigned long long))) != hipSuccess) return e;
+    if ((e = gap.alloc(sizeof(s.gap))) != hipSuccess) return e;
     k_hist<<<tile_grid(B), kIdxBlock, sizeof(int32_t) * (size_t)K, st>>>(s.types.as<int32_t>(), n, K, TT, B,
                                                                        cnt.as<int32_t>());
     const dim3 cols((unsigned)nc, (unsigned)((K + kIdxBlock - 1) / kIdxBlock));
@@ -470,14 +478,14 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
         k_scatter<T><<<tile_grid(B), kIdxBlock, lds, st>>>(
             s.types.as<int32_t>(), s.times.as<T>(), n, K, bits, B, cnt.as<int32_t>(), s.ts_by_type.as<T>(),
             s.pos_by_type.as<int32_t>(), s.tiled_ts.as<T>(), s.tile_loff.as<uint16_t>(), s.tile_t0.as<T>(), TT);
-        k_gap_init<<<1, 1, 0, st>>>(gap.as<unsigned long long>());
-        if (n > kWaveGap)
+        k_gap_init<<<1, kWaveHands, 0, st>>>(gap.as<unsigned long long>());
+        if (n > kWaveGap[0])
             k_gap<T><<<(unsigned)((n + kGapBlock * kGapItems - 1) / (kGapBlock * kGapItems)), kGapBlock, 0, st>>>(
                 s.ts_by_type.as<T>(), n, s.type_off.as<int32_t>(), K, gap.as<unsigned long long>());
         return hipGetLastError();
     };
     if ((e = s.ts_kind == EPI_TS_I64 ? scatter(int64_t()) : scatter(int32_t())) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(&s.gap, gap.p, sizeof(int64_t), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(s.gap, gap.p, sizeof(s.gap), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(s.h_off.data(), s.type_off.p, sizeof(int32_t) * (K + 1), hipMemcpyDeviceToHost, st)) !=
         hipSuccess)
         return e;

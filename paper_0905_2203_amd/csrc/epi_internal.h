@@ -216,7 +216,8 @@ struct Stream {
     std::vector<int32_t> h_off;  // host copy of type_off
     int64_t tile_span[5] = {};       // longest tile of 256, 512, ... 4096 events (ingest_stream)
     int64_t max_tile_span = -1;      // longest time from a tile's first event to the next tile's (or the last event)
-    int64_t gap = 0;                 // least time from one event to the 63rd after it of the same type (INT64_MAX: no type has 64)
+    // least time from one event to the 63rd, 127th after it of the same type (INT64_MAX: no type has as many)
+    int64_t gap[2] = {};
     size_t ts_bytes() const { return ts_kind == EPI_TS_I64 ? 8 : 4; }
 };
 

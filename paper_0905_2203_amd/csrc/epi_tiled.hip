@@ -960,9 +960,11 @@ bool lane_group_ok(const Stream &s, const CandSet &c, const Group &g, const Coun
            lane_rel_ok(s.max_tile_span, g.hspan);
 }
 
-// Whether the wave chains count group g of stream s.
-bool wave_group_ok(const Stream &s, const CandSet &c, const Group &g, const CountOptions &opt) {
-    return opt.lane_engine && !opt.worklog && !c.compact && c.cN.p && s.n > 0 && wave_ok(s.gap, g.hspan, g.lomax);
+// Whether the wave chains count group g of stream s, and by which kernels (0: no;
+// else the 64s of entries their lists hand on).
+int wave_group_hand(const Stream &s, const CandSet &c, const Group &g, const CountOptions &opt) {
+    if (!opt.lane_engine || opt.worklog || c.compact || !c.cN.p || s.n <= 0) return 0;
+    return wave_hand(s.gap, g.hspan, g.lomax);
 }
 
 // Summed event counts of the types of a set's episodes, per group (the events
@@ -1019,13 +1021,13 @@ int64_t wave_seg_cost(const CountOptions &opt, double cost_max, int64_t P) {
     return opt.segments > 0 || P < 2 ? 0 : std::max<int64_t>(1, (int64_t)(cost_max / (double)P));
 }
 
-hipError_t wave_resident(int *waves) {
+hipError_t wave_resident(int hand, int *waves) {
     int dev = 0, ncu = 0;
     hipError_t e;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    static const int per = wave_waves_per_cu();  // a property of the kernel
-    *waves = ncu * per;
+    static const int per[kWaveHands] = {wave_waves_per_cu(1), wave_waves_per_cu(2)};  // properties of the kernels
+    *waves = ncu * per[hand - 1];
     return hipSuccess;
 }
 
@@ -1054,12 +1056,12 @@ CountArgs<T> wave_args(const Stream &s, const CandSet &c, int32_t *d_flags) {
 
 // Plain count of slots [begin, end) of set c by the wave chains.
 template <typename T>
-hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end, double cost_max, double cost_all,
+hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end, int hand, double cost_max, double cost_all,
                         const CountOptions &opt, int32_t *d_flags, hipStream_t st, unsigned char *ext_scratch,
                         size_t ext_bytes) {
     hipError_t e;
     int waves = 0;
-    if ((e = wave_resident(&waves)) != hipSuccess) return e;
+    if ((e = wave_resident(hand, &waves)) != hipSuccess) return e;
     CountArgs<T> a = wave_args<T>(s, c, d_flags);
     const int64_t P = wave_segments(s, end - begin, cost_max, cost_all, kWaveSharePlain, opt, waves, &a.S);
     a.P = (int32_t)P;
@@ -1078,7 +1080,7 @@ hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end,
         a.begin = b;
         a.G = std::min(step, end - b);
         if (P > 1) set_records<T>(a, ext_scratch ? ext_scratch : c.scratch.as<unsigned char>(), P, a.G);
-        if ((e = wave_launch<T>(a, st)) != hipSuccess) return e;
+        if ((e = wave_launch<T>(a, hand, st)) != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -1092,18 +1094,19 @@ hipError_t count_t(const Stream &s, CandSet &c, const CountOptions &opt, int32_t
         const Group &g = c.groups[gi];
         const int64_t G = g.end - g.begin;
         if (G <= 0) continue;
-        if (wave_group_ok(s, c, g, opt)) {
+        if (int hand = wave_group_hand(s, c, g, opt)) {
             // adjacent groups in one launch (a wave takes an episode of any size)
             int64_t end = g.end;
             double cmax = g.cost_max, call = g.cost_sum;
             while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end &&
-                   wave_group_ok(s, c, c.groups[gi + 1], opt)) {
+                   wave_group_hand(s, c, c.groups[gi + 1], opt)) {
                 const Group &h = c.groups[++gi];
                 end = h.end;
+                hand = std::max(hand, wave_group_hand(s, c, h, opt));
                 cmax = std::max(cmax, h.cost_max);
                 call += h.cost_sum;
             }
-            if ((e = wave_count_t<T>(s, c, g.begin, end, cmax, call, opt, d_flags, st, ext_scratch, ext_bytes)) !=
+            if ((e = wave_count_t<T>(s, c, g.begin, end, hand, cmax, call, opt, d_flags, st, ext_scratch, ext_bytes)) !=
                 hipSuccess)
                 return e;
             continue;
@@ -1219,15 +1222,17 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOpt
         const Group &g = c.groups[gi];
         const int64_t G = g.end - g.begin;
         if (G <= 0) continue;
-        if (wave_group_ok(s, c, g, opt)) {
+        if (int hand = wave_group_hand(s, c, g, opt)) {
             CountArgs<T> a = wave_args<T>(s, c, d_flags);
             a.begin = g.begin;
             int64_t end = g.end;
             while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end &&
-                   wave_group_ok(s, c, c.groups[gi + 1], opt))
+                   wave_group_hand(s, c, c.groups[gi + 1], opt)) {
                 end = c.groups[++gi].end;
+                hand = std::max(hand, wave_group_hand(s, c, c.groups[gi], opt));
+            }
             a.G = end - a.begin;
-            if ((e = wave_launch_append<T>(a, (T)B, st)) != hipSuccess) return e;
+            if ((e = wave_launch_append<T>(a, hand, (T)B, st)) != hipSuccess) return e;
             continue;
         }
         AFn<T> fn = pick_append<T>(g.N);
@@ -1266,7 +1271,7 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOpt
 bool wave_counts_all(const Stream &s, const CandSet &c, const CountOptions &opt) {
     if (c.deep || c.groups.empty()) return false;
     for (const Group &g : c.groups)
-        if (!wave_group_ok(s, c, g, opt)) return false;
+        if (!wave_group_hand(s, c, g, opt)) return false;
     return true;
 }
 
@@ -1377,7 +1382,7 @@ std::vector<int64_t> plan_key(const std::vector<BatchRef> &sets, const std::vect
         k.push_back(s.B);
         k.push_back(s.T);
         k.push_back(s.max_tile_span);
-        k.push_back(s.gap);
+        for (int64_t g : s.gap) k.push_back(g);
         P(s.tiled_ts.p);
         P(s.tile_loff.p);
         P(s.tile_t0.p);
@@ -1506,12 +1511,16 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
         double cost_sum, cost_max;
     };
     std::vector<UnitH> units;
-    int waves = 0;
-    if ((e = wave_resident(&waves)) != hipSuccess) return e;
+    int waves = 0, hand = 1;
     double wave_cost = 0;  // of all groups the wave chains count
-    for (size_t si = 0; si < sets.size(); ++si)
-        for (const Group &g : mg[si])
-            if (wave_group_ok(*sets[si].s, *sets[si].c, g, opt)) wave_cost += g.cost_sum;
+    for (size_t si = 0; si < sets.size(); ++si) {
+        for (const Group &g : mg[si]) {
+            const int h = wave_group_hand(*sets[si].s, *sets[si].c, g, opt);
+            if (h) wave_cost += g.cost_sum;
+            hand = std::max(hand, h);
+        }
+    }
+    if ((e = wave_resident(hand, &waves)) != hipSuccess) return e;
     std::vector<std::pair<size_t, Group>> empty_groups;  // groups of sets on streams without events
     for (size_t si = 0; si < sets.size(); ++si) {
         const Stream &s = *sets[si].s;
@@ -1532,7 +1541,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             u.filt = c.compact && c.pred_bits && c.succ_bits;
             u.cost_sum = c.compact ? (double)G * (double)g.N * (double)s.n / std::max(1.0, (double)s.K) : g.cost_sum;
             u.cost_max = g.cost_max;
-            u.wave = wave_group_ok(s, c, g, opt);
+            u.wave = wave_group_hand(s, c, g, opt) > 0;
             if (u.wave) {
                 u.P = wave_segments(s, G, u.cost_max, wave_cost, kWaveShareBatched, opt, waves, &u.S);
                 units.push_back(u);
@@ -1854,7 +1863,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
         int per = 0;
         if (cl == kWaveClass) {
             const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(ncl * 64, waves));
-            e = wave_launch_persistent<T>((unsigned)grid, cache.br[bi], plan.units.as<CountArgs<T>>(),
+            e = wave_launch_persistent<T>((unsigned)grid, hand, cache.br[bi], plan.units.as<CountArgs<T>>(),
                                           plan.items.as<WorkItem>() + ioff[cl], ncl,
                                           plan.queue.as<unsigned long long>() + cl, wave_segmented,
                                           wave_listed ? plan.wave_list.p : nullptr, wave_cap);

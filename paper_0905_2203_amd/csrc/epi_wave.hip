@@ -21,8 +21,11 @@
 // lockstep), and append the hits in time order.  From one window to the next a
 // list hands on the entries a later event can still reach: those less than lo
 // before the window's end, and the latest one before them (any other is
-// dominated); that is at most 64 when the type has no 64 events within lo
-// (wave_ok, a property of the stream that the host checks).
+// dominated); that is at most 64 when the type has no 64 events within lo, at
+// most 128 when it has no 128 (wave_hand, properties of the stream that the host
+// checks).  The kernels that hand on 128 (HC = 2, in 64s) take 13.3 KB of LDS a
+// wave instead of 8.7, so 12 waves a CU instead of 18: they count streams with
+// such busy types alone (skewed rates, some 6 kHz in all and more).
 //
 // What bounds it: instruction issue and LDS latency.  A state machine lane
 // takes its events one at a time (135 VALU instructions over the loop's paths,
@@ -46,7 +49,6 @@ constexpr int kW = 64;
 constexpr int kR = kWaveChunks;
 constexpr int kCap = kR * kW;
 constexpr int kRunMin = 6;            // hits of 64 from which the greedy takes runs at a time
-constexpr int kList = 1 + kCap + kW;   // a sentinel, handed-on entries, a window's events
 
 // Chain lists.  An entry is one 64-bit word, a time above the latest start of an
 // occurrence ending there, so that one LDS access moves both.  int32 times: the
@@ -82,9 +84,11 @@ struct Entry {
         else return (T)bits;
     }
 };
+template <int HC>
 struct WaveLds {
-    int64_t e[2][kList];
-    int64_t c[kMaxN - 1][kW];  // handed on per node
+    static constexpr int kHand = HC * kW;
+    int64_t e[2][1 + kCap + kHand];  // a sentinel, handed-on entries, a window's events
+    int64_t c[kMaxN - 1][kHand];     // handed on per node
 };
 
 // One candidate's episode as the wave holds it: lane k keeps node k's next
@@ -242,8 +246,8 @@ struct WaveRec {
 // from the positions on is after e0.  SYNC: a re-run that stops where it meets
 // the speculative record (see rerun_segment in epi_tiled.hip); out.cnt then
 // includes the record's remaining completions.
-template <typename T, bool SYNC>
-__device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep, T e0, T Bp, T Ep,
+template <typename T, bool SYNC, int HC>
+__device__ __forceinline__ void wave_run(Times<T> ts, WaveLds<HC> &w, WaveEp<T> &ep, T e0, T Bp, T Ep,
                                          int lane, T *__restrict__ first_out, int64_t first_stride,
                                          const WaveRec<T> *rec, WaveOut<T> &out) {
     using U = std::make_unsigned_t<T>;  // differences of ordered times: exact in it
@@ -358,7 +362,11 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
             if (k + 1 < N) {
                 // this node's list: what it handed on, then the hits in order
                 n = rdlane(nc, k);
-                if (lane < n) w.e[qb][1 + lane] = (int64_t)((uint64_t)w.c[k][lane] - (uint64_t)shift);
+#pragma unroll
+                for (int j = 0; j < HC; ++j) {
+                    const int i = j * kW + lane;
+                    if (i < n) w.e[qb][1 + i] = (int64_t)((uint64_t)w.c[k][i] - (uint64_t)shift);
+                }
 #pragma unroll
                 for (int r = 0; r < kR; ++r) {
                     const int o = below(ok[r], n + 1);
@@ -368,17 +376,26 @@ __device__ __forceinline__ void wave_run(Times<T> ts, WaveLds &w, WaveEp<T> &ep,
                 lds_order();
                 // what later windows can reach
                 const UKey lo = E::len(rdlane(ep.lo, k)), hi = E::len(rdlane(ep.hi, k));
-                const int i = n - kW + lane;
-                int64_t y = 0;
-                UKey d = ~UKey(0);  // from the entry to the window's end
-                if (i >= 0) {
-                    y = w.e[qb][1 + i];
-                    d = (UKey)te_k - E::key_of(y);
+                int64_t y[HC];
+                int fut = 0, live = 0;
+#pragma unroll
+                for (int j = 0; j < HC; ++j) {
+                    const int i = n - HC * kW + j * kW + lane;
+                    y[j] = 0;
+                    UKey d = ~UKey(0);  // from the entry to the window's end
+                    if (i >= 0) {
+                        y[j] = w.e[qb][1 + i];
+                        d = (UKey)te_k - E::key_of(y[j]);
+                    }
+                    fut += __popcll(__ballot(d <= lo));
+                    live += __popcll(__ballot(d <= hi));
                 }
-                const int fut = __popcll(__ballot(d <= lo));
-                const int live = __popcll(__ballot(d <= hi));
                 const int keep = fut + 1 < live ? fut + 1 : live;
-                if (lane >= kW - keep) w.c[k][lane - (kW - keep)] = y;
+#pragma unroll
+                for (int j = 0; j < HC; ++j) {
+                    const int o = j * kW + lane - (HC * kW - keep);
+                    if (o >= 0) w.c[k][o] = y[j];
+                }
                 if (lane == k) nc = keep;
                 lds_order();
             } else {
@@ -457,8 +474,8 @@ __device__ __forceinline__ void seg_bounds(const CountArgs<T> &a, const WaveEp<T
 
 // Candidate s of unit a over segment p: the whole count (P = 1) or the
 // segment's speculative record.
-template <typename T>
-__device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int p, WaveLds &w, int lane) {
+template <typename T, int HC>
+__device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int p, WaveLds<HC> &w, int lane) {
     constexpr T kMin = TsLimits<T>::lo();
     const int64_t slot = slot_of(a, s);
     WaveEp<T> ep = load_episode(a, slot, lane);
@@ -491,8 +508,8 @@ __device__ __forceinline__ void wave_item(const CountArgs<T> &a, int64_t s, int 
 
 // Segment p's completions and last completion given the last completion tau
 // before it (see rerun_segment in epi_tiled.hip).
-template <typename T>
-__device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds &w,
+template <typename T, int HC>
+__device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64_t s, int p, T &tau, WaveLds<HC> &w,
                                                     int lane, const WaveEp<T> &ep0) {
     T Bp, Ep;
     seg_bounds(a, ep0, p, Bp, Ep);
@@ -524,8 +541,8 @@ __device__ __forceinline__ int32_t wave_fix_segment(const CountArgs<T> &a, int64
 
 // Pre-pass of candidate s, segment p >= 1: its true completions if the earlier
 // records' last completion is the true one.
-template <typename T>
-__device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds &w, int lane) {
+template <typename T, int HC>
+__device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p, WaveLds<HC> &w, int lane) {
     const WaveEp<T> ep = load_episode(a, slot_of(a, s), lane);
     if (p >= ep.P) return;
     T tau = TsLimits<T>::lo();
@@ -549,8 +566,8 @@ __device__ __forceinline__ void wave_pre(const CountArgs<T> &a, int64_t s, int p
 // The count of candidate s from its segments: the pre-pass's results where the
 // last completion they assumed is the true one (all lanes test 64 segments at
 // once), a re-run elsewhere.
-template <typename T>
-__device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds &w, int lane) {
+template <typename T, int HC>
+__device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveLds<HC> &w, int lane) {
     const int64_t slot = slot_of(a, s);
     const WaveEp<T> ep = load_episode(a, slot, lane);
     if (ep.P == 1) return;  // counted whole
@@ -591,29 +608,29 @@ __device__ __forceinline__ void wave_sum(const CountArgs<T> &a, int64_t s, WaveL
     rejoin();
 }
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_count(CountArgs<T> a) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     wave_item<T>(a, blockIdx.x, blockIdx.y, w, threadIdx.x);
 }
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_pre(CountArgs<T> a) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     wave_pre<T>(a, blockIdx.x, blockIdx.y + 1, w, threadIdx.x);
 }
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_sum(CountArgs<T> a) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     wave_sum<T>(a, blockIdx.x, w, threadIdx.x);
 }
 
 // Appended events (see k_count_append in epi_tiled.hip): the run resumes right
 // after max(tau, B - H - 1); every completion it finds is at or after B.
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_append(CountArgs<T> a, T B) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     const int lane = threadIdx.x;
     const int64_t s = blockIdx.x;
     const int64_t slot = slot_of(a, s);
@@ -716,10 +733,10 @@ struct WaveSlots {
     __device__ __forceinline__ int64_t at(int64_t q) const { return list ? bcast(list[q]) : q; }
 };
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__restrict__ units, WaveSlots slots,
                                                         unsigned long long *__restrict__ queue) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     const int lane = threadIdx.x;
     const int64_t n = slots.count();
     while (true) {
@@ -738,9 +755,9 @@ __global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__re
     }
 }
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_pre_all(const CountArgs<T> *__restrict__ units, WaveSlots slots) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     const int64_t n = slots.count();
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
         const int64_t q = slots.at(i);
@@ -751,9 +768,9 @@ __global__ __launch_bounds__(kW) void k_wave_pre_all(const CountArgs<T> *__restr
     }
 }
 
-template <typename T>
+template <typename T, int HC>
 __global__ __launch_bounds__(kW) void k_wave_sum_all(const CountArgs<T> *__restrict__ units, WaveSlots slots) {
-    __shared__ WaveLds w;
+    __shared__ WaveLds<HC> w;
     const int64_t n = slots.count();
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
         const int64_t q = slots.at(i);
@@ -768,33 +785,56 @@ unsigned grid_of(int64_t n) { return (unsigned)std::min<int64_t>(std::max<int64_
 
 }  // namespace
 
-int wave_waves_per_cu() {
+int wave_waves_per_cu(int hand) {
     int per = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wave_persistent<int64_t>, kW, 0) != hipSuccess || per < 1) {
+    const void *fn = hand == 1 ? (const void *)k_wave_persistent<int64_t, 1> : (const void *)k_wave_persistent<int64_t, 2>;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kW, 0) != hipSuccess || per < 1) {
         (void)hipGetLastError();
         per = 8;
     }
     return per;
 }
 
-template <typename T>
-hipError_t wave_launch(const CountArgs<T> &a, hipStream_t st) {
-    if (a.G <= 0) return hipSuccess;
-    if (a.P < 1 || a.P > 65535 || !a.cN || !a.orig || a.G > INT32_MAX) return hipErrorInvalidValue;
-    k_wave_count<T><<<dim3((unsigned)a.G, (unsigned)a.P), kW, 0, st>>>(a);
+namespace {
+
+template <typename T, int HC>
+hipError_t launch_hand(const CountArgs<T> &a, hipStream_t st) {
+    k_wave_count<T, HC><<<dim3((unsigned)a.G, (unsigned)a.P), kW, 0, st>>>(a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.P == 1) return e;
-    k_wave_pre<T><<<dim3((unsigned)a.G, (unsigned)(a.P - 1)), kW, 0, st>>>(a);
+    k_wave_pre<T, HC><<<dim3((unsigned)a.G, (unsigned)(a.P - 1)), kW, 0, st>>>(a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_wave_sum<T><<<(unsigned)a.G, kW, 0, st>>>(a);
+    k_wave_sum<T, HC><<<(unsigned)a.G, kW, 0, st>>>(a);
     return hipGetLastError();
 }
 
+template <typename T, int HC>
+hipError_t persistent_hand(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WaveSlots &slots,
+                           unsigned long long *queue, bool segmented, unsigned all) {
+    k_wave_persistent<T, HC><<<grid, kW, 0, st>>>(units, slots, queue);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !segmented) return e;
+    k_wave_pre_all<T, HC><<<all, kW, 0, st>>>(units, slots);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    k_wave_sum_all<T, HC><<<all, kW, 0, st>>>(units, slots);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 template <typename T>
-hipError_t wave_launch_append(const CountArgs<T> &a, T B, hipStream_t st) {
+hipError_t wave_launch(const CountArgs<T> &a, int hand, hipStream_t st) {
+    if (a.G <= 0) return hipSuccess;
+    if (a.P < 1 || a.P > 65535 || !a.cN || !a.orig || a.G > INT32_MAX) return hipErrorInvalidValue;
+    return hand == 1 ? launch_hand<T, 1>(a, st) : launch_hand<T, 2>(a, st);
+}
+
+template <typename T>
+hipError_t wave_launch_append(const CountArgs<T> &a, int hand, T B, hipStream_t st) {
     if (a.G <= 0) return hipSuccess;
     if (!a.cN || !a.orig || !a.tau || a.G > INT32_MAX) return hipErrorInvalidValue;
-    k_wave_append<T><<<(unsigned)a.G, kW, 0, st>>>(a, B);
+    if (hand == 1) k_wave_append<T, 1><<<(unsigned)a.G, kW, 0, st>>>(a, B);
+    else k_wave_append<T, 2><<<(unsigned)a.G, kW, 0, st>>>(a, B);
     return hipGetLastError();
 }
 
@@ -803,8 +843,9 @@ size_t wave_list_bytes(int64_t n_items, int64_t cap) {
 }
 
 template <typename T>
-hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs<T> *units, const WorkItem *items,
-                                  int64_t n_items, unsigned long long *queue, bool segmented, void *list, int64_t cap) {
+hipError_t wave_launch_persistent(unsigned grid, int hand, hipStream_t st, const CountArgs<T> *units,
+                                  const WorkItem *items, int64_t n_items, unsigned long long *queue, bool segmented,
+                                  void *list, int64_t cap) {
     WaveSlots slots{items, n_items, nullptr, nullptr, cap};
     if (list) {
         if (n_items > INT32_MAX) return hipErrorInvalidValue;
@@ -816,23 +857,18 @@ hipError_t wave_launch_persistent(unsigned grid, hipStream_t st, const CountArgs
         slots.list = out;
         slots.total = off + n_items;
     }
-    k_wave_persistent<T><<<grid, kW, 0, st>>>(units, slots, queue);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !segmented) return e;
     const unsigned all = grid_of(list ? cap : n_items * kW);
-    k_wave_pre_all<T><<<all, kW, 0, st>>>(units, slots);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    k_wave_sum_all<T><<<all, kW, 0, st>>>(units, slots);
-    return hipGetLastError();
+    return hand == 1 ? persistent_hand<T, 1>(grid, st, units, slots, queue, segmented, all)
+                     : persistent_hand<T, 2>(grid, st, units, slots, queue, segmented, all);
 }
 
-template hipError_t wave_launch<int32_t>(const CountArgs<int32_t> &, hipStream_t);
-template hipError_t wave_launch<int64_t>(const CountArgs<int64_t> &, hipStream_t);
-template hipError_t wave_launch_append<int32_t>(const CountArgs<int32_t> &, int32_t, hipStream_t);
-template hipError_t wave_launch_append<int64_t>(const CountArgs<int64_t> &, int64_t, hipStream_t);
-template hipError_t wave_launch_persistent<int32_t>(unsigned, hipStream_t, const CountArgs<int32_t> *, const WorkItem *,
-                                                    int64_t, unsigned long long *, bool, void *, int64_t);
-template hipError_t wave_launch_persistent<int64_t>(unsigned, hipStream_t, const CountArgs<int64_t> *, const WorkItem *,
-                                                    int64_t, unsigned long long *, bool, void *, int64_t);
+template hipError_t wave_launch<int32_t>(const CountArgs<int32_t> &, int, hipStream_t);
+template hipError_t wave_launch<int64_t>(const CountArgs<int64_t> &, int, hipStream_t);
+template hipError_t wave_launch_append<int32_t>(const CountArgs<int32_t> &, int, int32_t, hipStream_t);
+template hipError_t wave_launch_append<int64_t>(const CountArgs<int64_t> &, int, int64_t, hipStream_t);
+template hipError_t wave_launch_persistent<int32_t>(unsigned, int, hipStream_t, const CountArgs<int32_t> *,
+                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t);
+template hipError_t wave_launch_persistent<int64_t>(unsigned, int, hipStream_t, const CountArgs<int64_t> *,
+                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t);
 
 }  // namespace epi

@@ -149,3 +149,27 @@ def test_skewed_episodes_in_listed_slots(m, kind):
                 ctx.epi_count([cid for cid, _, _ in sets], epi.EPI_MODE_BATCHED, sched)
                 for cid, k, want in sets:
                     assert np.array_equal(ctx.epi_read_counts(cid, k), want)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("over", [0, 1])
+def test_lower_bound_of_127_events(kind, over):
+    """Lists that hand on up to 128 entries: a type's 128 events just fit the largest lower bound, or do not by one unit
+    (the lane machines then count); plain, batched, in segments, and appended to."""
+    rng = np.random.default_rng(80 + kind)
+    s = stream(*per_type(rng, [9000, 8700, 9000, 3000], 40), kind)
+    times = [s["times"][s["types"] == k].astype(np.int64) for k in range(s["K"])]
+    lo = min(int((t[127:] - t[:-127]).min()) for t in times) + over
+    eps = [(rng.permutation(4)[:n], [lo] * (n - 1), [lo + w] * (n - 1)) for n in (2, 3, 4) for w in (333, 700, 5000)]
+    eps = [e for e in eps if 1 + e[2][0] // (e[2][0] - e[1][0] + 1) <= 15]
+    c = sg.candidates_from_list(eps)
+    assert check(s, c).max() > 20
+    n = s["types"].size
+    with epi.Context(0) as ctx:
+        sid = ctx.epi_load_stream(s["types"][: n - 700], s["times"][: n - 700], s["K"])
+        cid = ctx.epi_submit_candidates(sid, c)
+        ctx.epi_count([cid])
+        for a, b in ((n - 700, n - 699), (n - 699, n)):
+            ctx.epi_append_stream(sid, s["types"][a:b], s["times"][a:b])
+            ctx.epi_count([cid], epi.EPI_MODE_INCREMENTAL)
+        assert np.array_equal(ctx.epi_read_counts(cid, c["N"].size), oracle.count(s, c))
