@@ -19,6 +19,7 @@
 //   raw base feature (the network predicts the correction to it).
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "epi_internal.h"
@@ -38,6 +39,13 @@ __host__ __device__ inline int64_t n_params_of(int F) { return (int64_t)F * kH +
 // host took 262 us a step; a wave a tile spreads the batch over 128 waves and
 // leaves sums of at most kParts / 4 a thread: 14 + 4 us a step (an epoch of 16
 // steps of 512 and 50k predictions, host copies included: 4.2 -> 0.69 ms).
+//
+// A training step's sums are FP64 (the parameters, moments and inputs FP32): Adam
+// divides a gradient by its own size, so where a parameter's gradient all but
+// cancels, the sums' rounding moves it by up to the learning rate.  With other
+// FP32 sums than a serial run's, the predictions of 1 epoch in some 10 were
+// further from exact ones than that run's; so they are as near or nearer in all
+// of 24 (0.63 -> 0.69 ms).
 constexpr int kMlpWaves = 4;     // waves per workgroup, sharing the staged W2
 constexpr int kParts = 256;      // most gradient parts (waves of a training launch)
 constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of bank conflicts
@@ -47,16 +55,18 @@ constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of ba
 template <bool TRAIN, int S>
 __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__restrict__ p, int F,
                                                              const float *__restrict__ X, const float *__restrict__ t,
-                                                             int64_t B, float *__restrict__ y, float *__restrict__ part,
+                                                             int64_t B, float *__restrict__ y, double *__restrict__ part,
                                                              float *__restrict__ sqerr) {
+    using A = std::conditional_t<TRAIN, double, float>;
     __shared__ float W2[kH * kRow];
     __shared__ __align__(16) float W1s[kH * kH];  // W1, for up to 64 inputs
     __shared__ __align__(16) float xb[kMlpWaves][kH][S];  // 64 inputs of the tile's samples
-    __shared__ __align__(16) float hb[kMlpWaves][kH][S];  // h1
-    __shared__ __align__(16) float db[kMlpWaves][kH][S];  // dz2
+    __shared__ __align__(16) A hb[kMlpWaves][kH][S];      // h1
+    __shared__ __align__(16) A db[TRAIN ? kMlpWaves : 1][kH][S];  // dz2
     const int j = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const float *W1 = p, *b1 = p + (int64_t)F * kH, *pW2 = b1 + kH, *b2 = pW2 + kH * kH, *w3 = b2 + kH, *b3 = w3 + kH;
-    float(*x)[S] = xb[wv], (*h)[S] = hb[wv], (*d)[S] = db[wv];
+    float(*x)[S] = xb[wv];
+    A(*h)[S] = hb[wv], (*d)[S] = db[TRAIN ? wv : 0];
     const float vb1 = b1[j], vb2 = b2[j], vw3 = w3[j], vb3 = b3[0];
     const bool staged = F <= kH;
     {
@@ -83,7 +93,7 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
     }
     __syncthreads();  // (the only barrier: from here on the waves work alone)
     const int64_t wave = (int64_t)blockIdx.x * kMlpWaves + wv, waves = (int64_t)gridDim.x * kMlpWaves;
-    float *g = TRAIN ? part + wave * n_params_of(F) : nullptr;
+    double *g = TRAIN ? part + wave * n_params_of(F) : nullptr;
     bool first = true;
     for (int64_t s0 = wave * S; s0 < B; s0 += waves * S) {
         const int ns = B - s0 < S ? (int)(B - s0) : S;
@@ -99,7 +109,8 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
         };
-        float h1[S], z2[S], out[S], tq[S];
+        A h1[S], z2[S], out[S];
+        float tq[S];
 #pragma unroll
         for (int q = 0; q < S; ++q) {
             h1[q] = vb1;
@@ -111,9 +122,9 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
             auto column = [&](const float *w1) {
 #pragma unroll 8
                 for (int f = 0; f < nf; ++f) {
-                    const float wt = w1[f * kH + j];
+                    const A wt = w1[f * kH + j];
 #pragma unroll
-                    for (int q = 0; q < S; ++q) h1[q] = fmaf(x[f][q], wt, h1[q]);
+                    for (int q = 0; q < S; ++q) h1[q] = fma((A)x[f][q], wt, h1[q]);
                 }
             };
             if (staged) column(W1s);
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
         }
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            h1[q] = h1[q] > 0.f ? h1[q] : 0.f;  // z1 > 0 <=> h1 > 0
+            h1[q] = h1[q] > 0 ? h1[q] : 0;  // z1 > 0 <=> h1 > 0
             h[j][q] = h1[q];
             z2[q] = vb2;
         }
@@ -129,55 +140,55 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
         __builtin_amdgcn_wave_barrier();
 #pragma unroll 8
         for (int a = 0; a < kH; ++a) {
-            const float wt = W2[a * kRow + j];
+            const A wt = W2[a * kRow + j];
 #pragma unroll
-            for (int q = 0; q < S; ++q) z2[q] = fmaf(h[a][q], wt, z2[q]);
+            for (int q = 0; q < S; ++q) z2[q] = fma(h[a][q], wt, z2[q]);
         }
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            float v = z2[q] > 0.f ? z2[q] * vw3 : 0.f;
+            A v = z2[q] > 0 ? z2[q] * (A)vw3 : 0;
             for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
             out[q] = v + vb3;
-            if (j == q && q < ns) y[s0 + q] = out[q];
+            if (j == q && q < ns) y[s0 + q] = (float)out[q];
         }
         if constexpr (TRAIN) {
             // dz2 = dy * w3 * [z2 > 0];  dz1 = (dz2 W2^T) * [z1 > 0]
-            float gb1 = 0.f, gb2 = 0.f, gw3 = 0.f, gb3 = 0.f, dz1[S], dz2[S];
+            A gb1 = 0, gb2 = 0, gw3 = 0, gb3 = 0, dz1[S], dz2[S];
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                const float r = q < ns ? out[q] - tq[q] : 0.f;
-                if (j == q && q < ns) sqerr[s0 + q] = r * r;
-                const float dy = 2.f * r / (float)B;
-                dz2[q] = z2[q] > 0.f ? dy * vw3 : 0.f;
-                gw3 = fmaf(z2[q] > 0.f ? z2[q] : 0.f, dy, gw3);
+                const A r = q < ns ? out[q] - (A)tq[q] : 0;
+                if (j == q && q < ns) sqerr[s0 + q] = (float)(r * r);
+                const A dy = 2 * r / (A)B;
+                dz2[q] = z2[q] > 0 ? dy * (A)vw3 : 0;
+                gw3 = fma(z2[q] > 0 ? z2[q] : 0, dy, gw3);
                 gb2 += dz2[q];
                 gb3 += dy;
                 d[j][q] = dz2[q];
-                dz1[q] = 0.f;
+                dz1[q] = 0;
             }
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
 #pragma unroll 8
             for (int k = 0; k < kH; ++k) {  // lane j = unit j of the first layer
-                const float wt = W2[j * kRow + k];
+                const A wt = W2[j * kRow + k];
 #pragma unroll
-                for (int q = 0; q < S; ++q) dz1[q] = fmaf(d[k][q], wt, dz1[q]);
+                for (int q = 0; q < S; ++q) dz1[q] = fma(d[k][q], wt, dz1[q]);
             }
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                dz1[q] = h1[q] > 0.f ? dz1[q] : 0.f;
+                dz1[q] = h1[q] > 0 ? dz1[q] : 0;
                 gb1 += dz1[q];
             }
             // the tile's gradient onto the wave's part (each lane its own parameters)
-            auto put = [&](int64_t o, float v) { g[o] = first ? v : g[o] + v; };
+            auto put = [&](int64_t o, A v) { g[o] = first ? v : g[o] + v; };
             for (int f0 = 0; f0 < F; f0 += kH) {
                 if (F > kH) stage(f0);  // (else the inputs are still there)
                 const int nf = F - f0 < kH ? F - f0 : kH;
 #pragma unroll 4
                 for (int f = 0; f < nf; ++f) {  // W1[f][j]: x_f dz1_j
-                    float v = 0.f;
+                    A v = 0;
 #pragma unroll
-                    for (int q = 0; q < S; ++q) v = fmaf(x[f][q], dz1[q], v);
+                    for (int q = 0; q < S; ++q) v = fma((A)x[f][q], dz1[q], v);
                     put((int64_t)(f0 + f) * kH + j, v);
                 }
             }
@@ -185,9 +196,9 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
             put(o1 + j, gb1);
 #pragma unroll 4
             for (int a = 0; a < kH; ++a) {  // W2[a][j]: h1_a dz2_j
-                float v = 0.f;
+                A v = 0;
 #pragma unroll
-                for (int q = 0; q < S; ++q) v = fmaf(h[a][q], dz2[q], v);
+                for (int q = 0; q < S; ++q) v = fma(h[a][q], dz2[q], v);
                 put(o1 + kH + a * kH + j, v);
             }
             const int64_t o2 = o1 + kH + kH * kH;
@@ -212,14 +223,14 @@ __device__ __forceinline__ void adam(float *__restrict__ p, float *__restrict__ 
 // g = the sum of the parts, four threads a parameter, each over every fourth
 // part; ADAM: and the step with it.
 template <bool ADAM>
-__global__ __launch_bounds__(256) void k_mlp_sum(const float *__restrict__ part, int parts, int64_t n,
+__global__ __launch_bounds__(256) void k_mlp_sum(const double *__restrict__ part, int parts, int64_t n,
                                                  float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
                                                  float *__restrict__ v, float lr, float b1, float b2, float eps,
                                                  float c1, float c2) {
-    __shared__ float sum[4][64];
+    __shared__ double sum[4][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t q = (int64_t)blockIdx.x * 64 + l;
-    float acc = 0.f;
+    double acc = 0;
     if (q < n) {
 #pragma unroll 16
         for (int i = w; i < parts; i += 4) acc += part[i * n + q];
@@ -228,8 +239,8 @@ __global__ __launch_bounds__(256) void k_mlp_sum(const float *__restrict__ part,
     __syncthreads();
     if (w != 0 || q >= n) return;
     acc = (sum[0][l] + sum[1][l]) + (sum[2][l] + sum[3][l]);
-    g[q] = acc;
-    if constexpr (ADAM) adam(p, m, v, q, acc, lr, b1, b2, eps, c1, c2);
+    g[q] = (float)acc;
+    if constexpr (ADAM) adam(p, m, v, q, (float)acc, lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void k_mlp_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -314,12 +325,13 @@ static hipError_t grad_launch(Mlp &net, const float *dX, const float *dt, int64_
     if (!mlp_fits(net)) return hipErrorInvalidValue;
     constexpr int S = 4;
     const int64_t np = n_params_of(net.F);
-    const size_t need = sizeof(float) * ((size_t)kParts * np + (size_t)B);
+    const size_t need = sizeof(double) * (size_t)kParts * np + sizeof(float) * (size_t)B;
     if (net.act.bytes < need) {
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         if ((e = net.act.alloc(need)) != hipSuccess) return e;
     }
-    float *part = net.act.as<float>(), *ys = part + (size_t)kParts * np;
+    double *part = net.act.as<double>();
+    float *ys = reinterpret_cast<float *>(part + (size_t)kParts * np);
     const int64_t tiles = (B + S - 1) / S;
     const unsigned blocks = (unsigned)std::min<int64_t>((tiles + kMlpWaves - 1) / kMlpWaves, kParts / kMlpWaves);
     // (a wave without a tile writes no part)
