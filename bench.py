@@ -6,7 +6,7 @@ planted cascades of 3-8 types), 200k candidate episodes of sizes 2-8 (every
 sub-episode of the planted cascades, the rest random over the interval menu
 {0,5,10,20} ms offset x {5,10,20} ms width).  One step = one exact count of
 all 200k candidates over the whole stream, inputs resident in HBM: the batched
-engine (segment-parallel lane machines in persistent launches, one kept
+engine (segment-parallel wave chains in one persistent launch, one kept
 hipGraph) ordered by the learned cost model (features -> MLP -> device sort ->
 longest-first work items, all inside the graph).  The plain engine, round
 robin and the event-count heuristic are timed beside it on the same inputs.
@@ -515,7 +515,7 @@ def large_bench(args):
     alg = alg_bytes(s, c)
     t_step = res["batched_learned"] / 1e3
     achieved = alg / t_step / 1e9
-    kname = "batched count graph (k_lane_persistent per launch class on parallel branches, scheduler, reconcile)"
+    kname = "batched count graph (k_wave_persistent, scheduler, reconcile)"
     traffic = profiled("batched_learned_graph", "traffic_bytes_per_launch", "bytes", LARGE_PROFILE, LARGE_SOURCES)
     traffic_setting = profiled("batched_learned_graph", "traffic_bytes_per_launch", "setting", LARGE_PROFILE,
                                LARGE_SOURCES)
@@ -543,7 +543,7 @@ def large_bench(args):
         "config": {
             "workload": "Large: 256 types, 50M events over 3600 s, int64 ns, Poisson background + 32 planted "
                         "cascades (3-8 types); 200k candidates of sizes 2-8; batched persistent graph, "
-                        "segment-parallel lane machines, learned cost-model schedule",
+                        "segment-parallel wave chains, learned cost-model schedule",
             "scale": args.scale, "events": n, "candidates": m,
             "mode": "batched + learned schedule",
         },

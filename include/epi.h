@@ -150,13 +150,14 @@ epi_status epi_release_set(epi_ctx *ctx, int32_t set_id);
 
 /* Enqueue the count of k candidate sets on `hip_stream` (null = the
  * context's stream).  mode:
- *   EPI_MODE_PLAIN    one launch per set and episode-size class, candidates
- *                     in submission order (asynchronous);
+ *   EPI_MODE_PLAIN    one launch per set (state machines: per episode-size
+ *                     class), candidates in submission order (asynchronous);
  *   EPI_MODE_BATCHED  all sets (possibly on different streams of one
  *                     timestamp kind) in one captured graph: one persistent
- *                     kernel per launch class (episode size, ring class,
- *                     machine time type) pulls (set, lane block, segment)
- *                     work items from a device queue, then the segmented
+ *                     kernel per launch class (all sizes in one; state
+ *                     machines: episode size, ring class, machine time
+ *                     type) pulls (set, block of episodes, segment) work
+ *                     items from a device queue, then the segmented
  *                     ones are reconciled.  The graph is kept per (sets,
  *                     schedule, options, cost model) and replayed by later
  *                     calls, which are asynchronous; a call that plans a
@@ -173,7 +174,9 @@ epi_status epi_release_set(epi_ctx *ctx, int32_t set_id);
  *                     chain ending at it, the events with a chain are
  *                     compacted in time order (Sec. IV-D/E), and the count
  *                     is the greedy over the (latest start, end) intervals,
- *                     ranked by pointer jumping.  Working memory about
+ *                     ranked by pointer jumping.  Sets that one wave per
+ *                     episode and time segment counts (EPI_OPT_LANE_ENGINE)
+ *                     are counted so in this mode too.  Working memory about
  *                     5*ts + 32 bytes (8*ts + 32 under
  *                     EPI_OPT_STREAM_ORDER) per event of an episode's most
  *                     frequent type, in groups of at most 2 GiB, kept with
@@ -218,11 +221,13 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *   EPI_OPT_SEGMENTS      0 = automatic (default); k >= 1 = cut the stream
  *                         into k time segments counted in parallel and
  *                         reconciled exactly (1 = no segmentation)
- *   EPI_OPT_LANES         0 = automatic (default); else the largest number
- *                         of episodes per workgroup (64, 128 or 256); the
- *                         engine uses the widest one whose state fits LDS
+ *   EPI_OPT_LANES         state machines: 0 = automatic (default); else the
+ *                         largest number of episodes per workgroup (64, 128
+ *                         or 256); the engine uses the widest one whose
+ *                         state fits LDS
  *   EPI_OPT_TARGET_LANES  automatic segmentation aims at this many
- *                         (episode, segment) work lanes (default 262144)
+ *                         (episode, segment) work lanes (default 262144);
+ *                         one-wave counts at that share of their own target
  *   EPI_OPT_PAIR_FILTER   1 (default) / 0: in level-wise discovery with the
  *                         state-machine engine, precompute for each event,
  *                         event type and menu interval whether a constrained
@@ -240,7 +245,8 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         kWork = 5 int32 counters (events visited, partial
  *                         occurrences recorded, predecessor queries,
  *                         completions, deepest interval ring) and, in batched
- *                         mode, a wall-clock start/end per work item
+ *                         mode, a wall-clock start/end per work item (such
+ *                         counts run on the state machines)
  *   EPI_OPT_TARGET_ITEMS  accepted for compatibility; the batched scheduler
  *                         cuts every lane block of a launch group into the
  *                         same segments (EPI_OPT_TARGET_LANES) and orders
@@ -252,7 +258,10 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         lists, listed by walks cut into pieces, when they
  *                         fit; else one walk per parent counts it and a
  *                         second writes its chain lists (0 = always the
- *                         latter)
+ *                         latter).  Levels of 2048 and more parents are
+ *                         counted by one wave per parent that walks only
+ *                         what per-position rows of near types do not
+ *                         settle, whatever the lists would take
  *   EPI_OPT_MINE_LIST_ALPHAS  level-wise discovery, extension engine: levels
  *                         with fewer frequent parent episodes than this
  *                         (default 65536) take the list path when it fits;
@@ -282,7 +291,12 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         on streams without equal timestamps.  Such sets
  *                         are counted by EPI_MODE_TRACKING only (other
  *                         modes: EPI_EINVAL).
- *   EPI_OPT_LANE_ENGINE   1 (default) / 0: the state machines keep their
+ *   EPI_OPT_LANE_ENGINE   1 (default) / 0: episodes are counted by one wave
+ *                         per (episode, time segment), parallel over events,
+ *                         where no type of the stream has 128 events within
+ *                         the set's largest lower bound, spans are below
+ *                         2^29 time units and no work log is kept; else the
+ *                         state machines keep their
  *                         bookkeeping in registers and, per node, a ring of
  *                         exactly that interval's bound in LDS (lane
  *                         machines), wherever the stream's tiles allow int32

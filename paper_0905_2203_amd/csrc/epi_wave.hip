@@ -32,10 +32,10 @@
 // nearly all issued by a diverged wave, 64 events a pass); here a wave spends
 // about 46 VALU and 36 SALU instructions on 64 events of a node, whatever the
 // events do, and needs no tile staging, rings or rebasing.  80k episodes of 2-8
-// nodes over 20M events of 256 types: 199 -> 52 ms (VALU issue 0.71; the index
+// nodes over 20M events of 256 types: 198 -> 50 ms (VALU issue 0.73; the index
 // comes at 5 TB/s from beyond L2: cutting time so that a stretch stays in L2 gained
-// nothing); 5k episodes of 1-6 nodes over 1.5M events: 24.5 -> 0.54 ms; 992 pairs
-// over 10k events: 2.6 ms -> 52 us (a lane each had left the chip idle).
+// nothing); 5k episodes of 1-6 nodes over 1.5M events: 24.8 -> 0.50 ms; 992 pairs
+// over 10k events: 2.7 ms -> 53 us (a lane each had left the chip idle).
 #include <algorithm>
 #include <type_traits>
 
