@@ -258,10 +258,10 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         lists, listed by walks cut into pieces, when they
  *                         fit; else one walk per parent counts it and a
  *                         second writes its chain lists (0 = always the
- *                         latter).  Levels of 2048 and more parents are
- *                         counted by one wave per parent that walks only
- *                         what per-position rows of near types do not
- *                         settle, whatever the lists would take
+ *                         latter).  Levels of 512 and more parents are
+ *                         counted by waves that walk only what
+ *                         per-position rows of near types do not settle,
+ *                         whatever the lists would take
  *   EPI_OPT_MINE_LIST_ALPHAS  level-wise discovery, extension engine: levels
  *                         with fewer frequent parent episodes than this
  *                         (default 65536) take the list path when it fits;

@@ -48,7 +48,7 @@
 // events, 68 batches an alpha) against some 200 for 64 entries.  788,381
 // alphas of 170 entries, 83.5M candidates: 18.5 ms walked, 2.6 ms so.  A level
 // of 12,096 alphas, lists and all: 6.3 ms by lists of every candidate's end
-// events, 4.7 ms.  The end events of the frequent extensions are then sized by
+// events, 3.6 ms.  The end events of the frequent extensions are then sized by
 // a walk of their own.
 //
 // Level 1 counts distinct timestamps per type.  Level 2 extends a frequent
@@ -92,10 +92,15 @@ constexpr int64_t kWriteJobs = 65536;
 // then at most a fifth of what they save.
 constexpr size_t kNearBytes = size_t(8) << 30;
 constexpr int64_t kNearShare = 4;
-// With fewer alphas the list path is taken instead: one wave an alpha then
-// leaves the GPU idle (levels counted by lists and by near rows, ms: 1599
-// alphas 0.47 and 0.77, 3168 0.61 and 0.46, 12096 6.3 and 4.7).
-constexpr int64_t kNearAlphas = 2048;
+// A count by near rows cuts the chain lists of few alphas into pieces of whole
+// clusters, about kNearJobs workgroups of at least kNearPiece entries on average,
+// whose counts are added up (a level of 11,718 alphas, ms: one wave each 1.18,
+// 32,768 pieces 0.78, 65,536 0.65, 131,072 0.72; pieces of 128 entries and more
+// 0.44 for one of 1599 alphas, of 64 and more 0.26, of 32 and more 0.23 but 0.33
+// instead of 0.30 for others).  With fewer than kNearAlphas alphas the list path
+// is as fast (311 alphas: 0.24 both) and writes the chain lists besides.
+constexpr int64_t kNearAlphas = 512;
+constexpr int64_t kNearJobs = 65536, kNearPiece = 64;
 
 // One entry of a chain list: an end event of an episode (time, stream
 // position) and the latest start of an occurrence ending there.
@@ -334,8 +339,22 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
     const_ptr<ChainEntry<T>> xc = (const_ptr<ChainEntry<T>>)(a.chain + c0);
     const ChainEntry<T> *xg = a.chain + c0;  // the same entries, read per lane
     // this job's piece of the chain list
-    const int32_t e0 = (int32_t)((int64_t)clen * seg / a.nseg);
-    const int32_t e1 = (int32_t)((int64_t)clen * (seg + 1) / a.nseg);
+    int32_t e0 = (int32_t)((int64_t)clen * seg / a.nseg);
+    int32_t e1 = (int32_t)((int64_t)clen * (seg + 1) / a.nseg);
+    if (MODE == kCount && a.nseg > 1) {
+        // pieces of whole clusters: from a cluster's first entry to another's
+        auto to_head = [&](int32_t i) -> int32_t {
+            if (i == 0) return 0;
+            for (; i < clen; i += kWave) {  // uniform
+                const int32_t j = min(i + lane, clen - 1);
+                const uint64_t b = __ballot((i + lane < clen) & (xg[j].s > (T)(xg[j - 1].t + a.H)));
+                if (b) return i + __builtin_ctzll(b);
+            }
+            return clen;
+        };
+        e0 = to_head(e0);
+        e1 = to_head(e1);
+    }
     // the menu, uniform
     T mlo[MP], mhi[MP];
 #pragma unroll
@@ -444,7 +463,7 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
                 if (lane == 0) tp = et;
                 // clusters: an entry whose start comes after every window of
                 // the entries before it begins one
-                uint64_t hd = __ballot(ci & ((i == 0) | (x.s > (T)(tp + a.H))));
+                uint64_t hd = __ballot(ci & ((i == e0) | (x.s > (T)(tp + a.H))));
                 const int nv = min(e1 - i0, kWave);
                 const bool more = nv < e1 - i0;
                 bool cut = true;  // the step's last cluster ends with the step
@@ -694,7 +713,11 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
 #pragma unroll
             for (int m = 0; m < MP; ++m) {
                 if (own[m]) {
-                    if (MODE == kCount) a.counts[key[m]] = cnt[m];
+                    if (MODE == kCount && a.nseg > 1) {
+                        if (cnt[m]) atomicAdd(&a.counts[key[m]], cnt[m]);
+                    } else if (MODE == kCount) {
+                        a.counts[key[m]] = cnt[m];
+                    }
                     if (MODE != kCount || !a.near) a.nvalid[key[m]] = nv[m];
                 }
             }
@@ -723,7 +746,7 @@ bool walk_args_complete(const WalkArgs<T> &a) {
     if (MODE == kCount) ok = ok && a.counts && (a.near ? a.n > 0 : a.nvalid != nullptr);
     if (MODE == kSize || MODE == kWSize) ok = ok && a.nvalid;
     if (MODE == kList || MODE == kWList) ok = ok && a.lst_off && a.wchain;
-    if (MODE == kWrite || MODE == kCount) ok = ok && a.nseg == 1;
+    if (MODE == kWrite || (MODE == kCount && !a.near)) ok = ok && a.nseg == 1;
     return ok;
 }
 
@@ -1466,7 +1489,16 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
             L.list_seg = nseg;
         }
     }
-    if (m > 0 && !listed && e == hipSuccess) e = launch_walk<T, kCount>(a, nA, st);
+    if (m > 0 && !listed && e == hipSuccess) {
+        if (a.near) {
+            // few alphas: pieces of their lists, of at least kNearPiece entries, add their counts up
+            const int64_t most = std::min<int64_t>((kNearJobs + nA - 1) / nA, P.chain_total / nA / kNearPiece);
+            a.nseg = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, most));
+            if (a.nseg > 1) e = hipMemsetAsync(a.counts, 0, sizeof(int32_t) * m, st);
+        }
+        if (e == hipSuccess) e = launch_walk<T, kCount>(a, nA * a.nseg, st);
+        a.nseg = 1;
+    }
     (void)hipEventRecord(mn.ev[1], st);
     // the walked positions and the number of frequent episodes reach the host
     // at one synchronisation (slots 0 and 1)
