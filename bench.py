@@ -38,8 +38,8 @@ PEAK_HBM_GBS = 8000.0
 PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12  # vector-ALU lane operations per second (T)
 PROFILE = "k_ext_walk_mining.md"
 KERNEL_SOURCES = ("epi_extend.hip",)
-LARGE_PROFILE = "k_lane_persistent_large.md"
-LARGE_SOURCES = ("epi_lane.hip", "epi_tiled.hip", "epi_sched.hip", "epi_sort.hip", "epi_count.h")
+LARGE_PROFILE = "k_wave_persistent_large.md"
+LARGE_SOURCES = ("epi_wave.hip", "epi_lane.hip", "epi_tiled.hip", "epi_sched.hip", "epi_sort.hip", "epi_count.h")
 THRESHOLD = 100
 MAX_SIZE = 6
 
