@@ -296,8 +296,8 @@ epi_status epi_create(int device, epi_ctx **out) {
     if ((e = hipStreamCreateWithFlags(&ctx->c.stream, hipStreamNonBlocking)) != hipSuccess ||
         (e = ctx->c.flags.alloc(sizeof(int32_t) * kNumFlags)) != hipSuccess ||
         (e = hipMemset(ctx->c.flags.p, 0, sizeof(int32_t) * kNumFlags)) != hipSuccess ||
-        (e = hipHostMalloc((void **)&ctx->c.stage, sizeof(int64_t) * kStageSlots + kStageBytes,
-                           hipHostMallocDefault)) != hipSuccess ||
+        (e = hipHostMalloc((void **)&ctx->c.stage, sizeof(int64_t) * kStageSlots, hipHostMallocDefault)) !=
+            hipSuccess ||
         (e = noalloc_init(device)) != hipSuccess) {
         g_create_err = hipGetErrorString(e);
         delete ctx;
@@ -319,6 +319,7 @@ void epi_destroy(epi_ctx *ctx) {
     ctx->c.cache.release();
     ctx->c.idle.release();
     if (ctx->c.stage) (void)hipHostFree(ctx->c.stage);
+    if (ctx->c.rows) (void)hipHostFree(ctx->c.rows);
     if (ctx->c.stream) (void)hipStreamDestroy(ctx->c.stream);
     delete ctx;
 }
@@ -851,6 +852,9 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
     mn->stream_id = stream_id;
     mn->max_span = span;
     mn->stage = ctx->c.stage;
+    // (150 us: by the first run, not by every context)
+    if (!ctx->c.rows) HIPTRY(ctx, hipHostMalloc(&ctx->c.rows, kStageBytes, hipHostMallocDefault), "pinned memory");
+    mn->rows = ctx->c.rows;
     mn->menu_lo.assign(menu_lo, menu_lo + n_menu);
     mn->menu_hi.assign(menu_hi, menu_hi + n_menu);
     mn->threshold = threshold;

@@ -1371,7 +1371,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     hipError_t e;
     // pinned host slots that kernels write scalars to, read after a synchronisation
     int64_t *stage = mn.stage;
-    if (!stage) return hipErrorInvalidValue;
+    if (!stage || !mn.rows) return hipErrorInvalidValue;
     MineLevel &P = mn.levels.back();  // level N-1
     MineLevel L;
     L.N = N;
@@ -1662,7 +1662,7 @@ hipError_t level1_t(const Stream &s, Mine &mn, hipStream_t st) {
     // a 1-node episode's first and last node is its type
     if ((e = L.d_flast.alloc(sizeof(uint16_t) * (size_t)s.K)) != hipSuccess) return e;
     if ((e = L.d_ffirst.alloc(sizeof(uint16_t) * (size_t)s.K)) != hipSuccess) return e;
-    int32_t *host = reinterpret_cast<int32_t *>(mn.stage + kStageSlots);
+    int32_t *host = static_cast<int32_t *>(mn.rows);
     k_level1<T><<<s.K, kWave, 0, st>>>(s.ts_by_type.as<T>(), s.type_off.as<int32_t>(), L.dcounts.as<int32_t>(), host);
     k_level1_freq<<<1, kWave, 0, st>>>(L.dcounts.as<int32_t>(), s.K, mn.threshold, L.d_flast.as<uint16_t>(),
                                        L.d_ffirst.as<uint16_t>());
@@ -1770,7 +1770,7 @@ hipError_t extend_read_frequent(const Mine &mn, int level, int32_t *types, int64
     // few rows come with one copy to pinned memory
     const size_t all = 2 * b64 + bt + sizeof(int32_t) * nf;
     if (all <= kStageBytes) {
-        char *h = reinterpret_cast<char *>(mn.stage + kStageSlots);
+        char *h = static_cast<char *>(mn.rows);
         if (e == hipSuccess) e = hipMemcpyAsync(h, d.p, all, hipMemcpyDeviceToHost, st);
         const hipError_t w = hipStreamSynchronize(st);
         if (e != hipSuccess || w != hipSuccess) return e != hipSuccess ? e : w;

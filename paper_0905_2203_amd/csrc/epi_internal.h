@@ -395,6 +395,7 @@ struct Mine {
     // pinned host slots (the context's) that device scalars are copied to,
     // several per synchronisation
     int64_t *stage = nullptr;
+    void *rows = nullptr;  // pinned room of kStageBytes (the context's): level 1's counts, few patterns read back
     DevBuf walked;  // counters of the positions in the walked windows
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a level's counting kernels
     ~Mine() {
@@ -488,6 +489,7 @@ struct Ctx {
     static constexpr size_t kIdleLimit = size_t(4) << 30;
     BlockCache idle{kIdleLimit};
     int64_t *stage = nullptr;  // pinned host slots of the mining runs (kStageSlots)
+    void *rows = nullptr;      // pinned room of the mining runs (kStageBytes; made by the first)
     std::string err;
     std::map<int32_t, std::unique_ptr<Stream>> streams;
     std::map<int32_t, std::unique_ptr<CandSet>> sets;
@@ -565,7 +567,7 @@ int queue_class_of(int64_t bound);
 // then count level N (>= 2) from level N-1's frequent episodes and chain lists,
 // select its frequent episodes and write their chain lists.  Menus of up to
 // kExtMaxMenu intervals.
-constexpr int kStageSlots = 8;     // pinned host slots of a mining run, and room after them
+constexpr int kStageSlots = 8;     // pinned host slots of a mining run
 constexpr size_t kStageBytes = size_t(1) << 20;
 constexpr int kExtMaxMenu = 8;
 hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st);
