@@ -9,17 +9,16 @@
 // w3[64], b3[1].
 //
 // k_mlp_rows:   one wave per tile of 4 or 8 samples, lane j = hidden unit j: the
-//   forward pass and, when training, the back-propagated terms and the tile's
-//   gradient, added up over the wave's tiles in a part of its own.
-// k_mlp_sum:    sums the parts of each parameter's gradient in a fixed order
-//   (deterministic) and, in a training step, applies Adam step k.
+//   forward pass and, when training, the back-propagated terms of every sample
+//   (dz1, dz2, dy) beside its activations.
+// k_mlp_reduce: one wave per 64 parameters: their gradients, each summed over the
+//   batch in sample order, and, in a training step, Adam step k.
 // k_mlp_adam:   one thread per parameter; Adam step k with a given gradient.
 // k_standardize, k_affine_base: the cost model's input and output scaling
 //   around the network, (x - mu) * isd per feature and y * sd + mu, plus the
 //   raw base feature (the network predicts the correction to it).
 #include <algorithm>
 #include <cmath>
-#include <type_traits>
 #include <vector>
 
 #include "epi_internal.h"
@@ -35,38 +34,41 @@ __host__ __device__ inline int64_t n_params_of(int F) { return (int64_t)F * kH +
 // What bounds a training step is latency: 512 samples are 9 million multiply-adds,
 // nothing for the chip, in a chain of forward, backward, gradient and update.  One
 // thread a sample with all weights broadcast from LDS (79 us), then one thread a
-// parameter summing 512 samples in a row (134 us), then the loss fetched by the
-// host took 262 us a step; a wave a tile spreads the batch over 128 waves and
-// leaves sums of at most kParts / 4 a thread: 14 + 4 us a step (an epoch of 16
-// steps of 512 and 50k predictions, host copies included: 4.2 -> 0.69 ms).
+// parameter with a load to wait for at each of 512 samples (134 us), then the loss
+// fetched by the host took 262 us a step; a wave a tile spreads the batch over 128
+// waves, and the sums over the batch keep 64 loads in flight (an epoch of 16 steps of
+// 512 and 50k predictions, host copies included: 4.3 -> 0.96 ms).
 //
-// A training step's sums are FP64 (the parameters, moments and inputs FP32): Adam
-// divides a gradient by its own size, so where a parameter's gradient all but
-// cancels, the sums' rounding moves it by up to the learning rate.  With other
-// FP32 sums than a serial run's, the predictions of 1 epoch in some 10 were
-// further from exact ones than that run's; so they are as near or nearer in all
-// of 24 (0.63 -> 0.69 ms).
+// Every sum is one chain of FP32 fused multiply-adds in a fixed order: over the inputs,
+// over the units, over the samples.  Adam divides a gradient by its own size, and a
+// ReLU decides on the sign of a sum, so another order (or other bits: FP64 sums moved
+// the parameters of some sample sets by up to the learning rate) is another training
+// run: the order is part of what the calls return.
 constexpr int kMlpWaves = 4;     // waves per workgroup, sharing the staged W2
-constexpr int kParts = 256;      // most gradient parts (waves of a training launch)
 constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of bank conflicts
+constexpr int kRowT = kH + 4;    // h2's row in LDS (16-byte aligned)
 
-// y[s] for every sample; TRAIN also the gradient parts part[wave][n_params] of
-// the loss over B samples, and the squared errors.  S samples a tile.
+// What a training step keeps of every sample, for the sums over the batch: [B][64]
+// activations and terms, [B] dy and squared errors.
+struct MlpRows {
+    float *h1, *dz1, *dz2, *h2, *dy, *sqerr;
+};
+
+// y[s] for every sample; TRAIN also its terms of the gradient of the loss over B
+// samples.  S samples a tile.
 template <bool TRAIN, int S>
 __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__restrict__ p, int F,
                                                              const float *__restrict__ X, const float *__restrict__ t,
-                                                             int64_t B, float *__restrict__ y, double *__restrict__ part,
-                                                             float *__restrict__ sqerr) {
-    using A = std::conditional_t<TRAIN, double, float>;
+                                                             int64_t B, float *__restrict__ y, MlpRows rows) {
     __shared__ float W2[kH * kRow];
     __shared__ __align__(16) float W1s[kH * kH];  // W1, for up to 64 inputs
-    __shared__ __align__(16) float xb[kMlpWaves][kH][S];  // 64 inputs of the tile's samples
-    __shared__ __align__(16) A hb[kMlpWaves][kH][S];      // h1
-    __shared__ __align__(16) A db[TRAIN ? kMlpWaves : 1][kH][S];  // dz2
+    __shared__ __align__(16) float w3s[kH];
+    __shared__ __align__(16) float xb[kMlpWaves][kH][S];      // 64 inputs of the tile's samples
+    __shared__ __align__(16) float hb[kMlpWaves][kH][S];      // h1, then dz2
+    __shared__ __align__(16) float tb[kMlpWaves][S][kRowT];   // h2
     const int j = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const float *W1 = p, *b1 = p + (int64_t)F * kH, *pW2 = b1 + kH, *b2 = pW2 + kH * kH, *w3 = b2 + kH, *b3 = w3 + kH;
-    float(*x)[S] = xb[wv];
-    A(*h)[S] = hb[wv], (*d)[S] = db[TRAIN ? wv : 0];
+    float(*x)[S] = xb[wv], (*h)[S] = hb[wv], (*h2)[kRowT] = tb[wv];
     const float vb1 = b1[j], vb2 = b2[j], vw3 = w3[j], vb3 = b3[0];
     const bool staged = F <= kH;
     {
@@ -90,41 +92,36 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
             o[3] = a[r].w;
             reinterpret_cast<float4 *>(W1s)[i] = b[r];
         }
+        if (wv == 0) w3s[j] = vw3;
     }
     __syncthreads();  // (the only barrier: from here on the waves work alone)
+    auto lds_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     const int64_t wave = (int64_t)blockIdx.x * kMlpWaves + wv, waves = (int64_t)gridDim.x * kMlpWaves;
-    double *g = TRAIN ? part + wave * n_params_of(F) : nullptr;
-    bool first = true;
     for (int64_t s0 = wave * S; s0 < B; s0 += waves * S) {
         const int ns = B - s0 < S ? (int)(B - s0) : S;
-        // inputs f0 .. f0+63 of the tile (zero for the samples past the batch)
-        auto stage = [&](int f0) {
+        float h1[S], z2[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) h1[q] = vb1;
+        for (int f0 = 0; f0 < F; f0 += kH) {
+            // inputs f0 .. f0+63 of the tile (zero for the samples past the batch)
             __builtin_amdgcn_wave_barrier();
             float v[S];
-            const int f = f0 + j < F ? f0 + j : F - 1;
+            const int fi = f0 + j < F ? f0 + j : F - 1;
 #pragma unroll
-            for (int q = 0; q < S; ++q) v[q] = X[(s0 + (q < ns ? q : 0)) * F + f];
+            for (int q = 0; q < S; ++q) v[q] = X[(s0 + (q < ns ? q : 0)) * F + fi];
 #pragma unroll
             for (int q = 0; q < S; ++q) x[j][q] = q < ns && f0 + j < F ? v[q] : 0.f;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        };
-        A h1[S], z2[S], out[S];
-        float tq[S];
-#pragma unroll
-        for (int q = 0; q < S; ++q) {
-            h1[q] = vb1;
-            tq[q] = TRAIN && q < ns ? t[s0 + q] : 0.f;
-        }
-        for (int f0 = 0; f0 < F; f0 += kH) {
-            stage(f0);
+            lds_order();
             const int nf = F - f0 < kH ? F - f0 : kH;
             auto column = [&](const float *w1) {
 #pragma unroll 8
                 for (int f = 0; f < nf; ++f) {
-                    const A wt = w1[f * kH + j];
+                    const float wt = w1[f * kH + j];
 #pragma unroll
-                    for (int q = 0; q < S; ++q) h1[q] = fma((A)x[f][q], wt, h1[q]);
+                    for (int q = 0; q < S; ++q) h1[q] = fmaf(x[f][q], wt, h1[q]);
                 }
             };
             if (staged) column(W1s);
@@ -132,115 +129,155 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
         }
 #pragma unroll
         for (int q = 0; q < S; ++q) {
-            h1[q] = h1[q] > 0 ? h1[q] : 0;  // z1 > 0 <=> h1 > 0
+            h1[q] = h1[q] > 0.f ? h1[q] : 0.f;  // z1 > 0 <=> h1 > 0
             h[j][q] = h1[q];
             z2[q] = vb2;
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        lds_order();
 #pragma unroll 8
         for (int a = 0; a < kH; ++a) {
-            const A wt = W2[a * kRow + j];
+            const float wt = W2[a * kRow + j];
 #pragma unroll
-            for (int q = 0; q < S; ++q) z2[q] = fma(h[a][q], wt, z2[q]);
+            for (int q = 0; q < S; ++q) z2[q] = fmaf(h[a][q], wt, z2[q]);
         }
+        // the output is one chain over the units: a lane per sample takes it
 #pragma unroll
-        for (int q = 0; q < S; ++q) {
-            A v = z2[q] > 0 ? z2[q] * (A)vw3 : 0;
-            for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-            out[q] = v + vb3;
-            if (j == q && q < ns) y[s0 + q] = (float)out[q];
+        for (int q = 0; q < S; ++q) h2[q][j] = z2[q] > 0.f ? z2[q] : 0.f;
+        lds_order();
+        float out = vb3;
+        const int mine = j % S;
+#pragma unroll 4
+        for (int a = 0; a < kH; a += 4) {
+            const float4 u = *reinterpret_cast<const float4 *>(&h2[mine][a]);
+            const float4 w = *reinterpret_cast<const float4 *>(&w3s[a]);
+            out = fmaf(u.x, w.x, out);
+            out = fmaf(u.y, w.y, out);
+            out = fmaf(u.z, w.z, out);
+            out = fmaf(u.w, w.w, out);
         }
+        if (j < ns) y[s0 + j] = out;
         if constexpr (TRAIN) {
             // dz2 = dy * w3 * [z2 > 0];  dz1 = (dz2 W2^T) * [z1 > 0]
-            A gb1 = 0, gb2 = 0, gw3 = 0, gb3 = 0, dz1[S], dz2[S];
+            const float r = mine < ns ? out - t[s0 + mine] : 0.f;
+            const float dy1 = 2.f * r / (float)B;
+            if (j < ns) {
+                rows.sqerr[s0 + j] = r * r;
+                rows.dy[s0 + j] = dy1;
+            }
+            float dz1[S];
 #pragma unroll
             for (int q = 0; q < S; ++q) {
-                const A r = q < ns ? out[q] - (A)tq[q] : 0;
-                if (j == q && q < ns) sqerr[s0 + q] = (float)(r * r);
-                const A dy = 2 * r / (A)B;
-                dz2[q] = z2[q] > 0 ? dy * (A)vw3 : 0;
-                gw3 = fma(z2[q] > 0 ? z2[q] : 0, dy, gw3);
-                gb2 += dz2[q];
-                gb3 += dy;
-                d[j][q] = dz2[q];
-                dz1[q] = 0;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll 8
-            for (int k = 0; k < kH; ++k) {  // lane j = unit j of the first layer
-                const A wt = W2[j * kRow + k];
-#pragma unroll
-                for (int q = 0; q < S; ++q) dz1[q] = fma(d[k][q], wt, dz1[q]);
-            }
-#pragma unroll
-            for (int q = 0; q < S; ++q) {
-                dz1[q] = h1[q] > 0 ? dz1[q] : 0;
-                gb1 += dz1[q];
-            }
-            // the tile's gradient onto the wave's part (each lane its own parameters)
-            auto put = [&](int64_t o, A v) { g[o] = first ? v : g[o] + v; };
-            for (int f0 = 0; f0 < F; f0 += kH) {
-                if (F > kH) stage(f0);  // (else the inputs are still there)
-                const int nf = F - f0 < kH ? F - f0 : kH;
-#pragma unroll 4
-                for (int f = 0; f < nf; ++f) {  // W1[f][j]: x_f dz1_j
-                    A v = 0;
-#pragma unroll
-                    for (int q = 0; q < S; ++q) v = fma((A)x[f][q], dz1[q], v);
-                    put((int64_t)(f0 + f) * kH + j, v);
+                const float dy = __shfl(dy1, q, 64);
+                const float h2q = z2[q] > 0.f ? z2[q] : 0.f, dz2 = z2[q] > 0.f ? dy * vw3 : 0.f;
+                h[j][q] = dz2;
+                dz1[q] = 0.f;
+                if (q < ns) {  // uniform
+                    const int64_t o = (s0 + q) * kH + j;
+                    rows.h1[o] = h1[q];
+                    rows.h2[o] = h2q;
+                    rows.dz2[o] = dz2;
                 }
             }
-            const int64_t o1 = (int64_t)F * kH;
-            put(o1 + j, gb1);
-#pragma unroll 4
-            for (int a = 0; a < kH; ++a) {  // W2[a][j]: h1_a dz2_j
-                A v = 0;
+            lds_order();
+#pragma unroll 8
+            for (int k = 0; k < kH; ++k) {  // lane j = unit j of the first layer
+                const float wt = W2[j * kRow + k];
 #pragma unroll
-                for (int q = 0; q < S; ++q) v = fma(h[a][q], dz2[q], v);
-                put(o1 + kH + a * kH + j, v);
+                for (int q = 0; q < S; ++q) dz1[q] = fmaf(h[k][q], wt, dz1[q]);
             }
-            const int64_t o2 = o1 + kH + kH * kH;
-            put(o2 + j, gb2);
-            put(o2 + kH + j, gw3);
-            if (j == 0) put(o2 + 2 * kH, gb3);
-            first = false;
+#pragma unroll
+            for (int q = 0; q < S; ++q)
+                if (q < ns) rows.dz1[(s0 + q) * kH + j] = h1[q] > 0.f ? dz1[q] : 0.f;  // uniform
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
+// (every product that is added is a fused multiply-add, whatever the kernel)
 __device__ __forceinline__ void adam(float *__restrict__ p, float *__restrict__ m, float *__restrict__ v, int64_t q,
                                      float gq, float lr, float b1, float b2, float eps, float c1, float c2) {
-    const float mq = b1 * m[q] + (1.f - b1) * gq;
-    const float vq = b2 * v[q] + (1.f - b2) * gq * gq;
+#pragma clang fp contract(off)
+    const float mq = fmaf(1.f - b1, gq, b1 * m[q]);
+    const float vq = fmaf((1.f - b2) * gq, gq, b2 * v[q]);
     m[q] = mq;
     v[q] = vq;
-    p[q] -= lr * (mq / c1) / (sqrtf(vq / c2) + eps);
+    p[q] = p[q] - lr * (mq / c1) / (sqrtf(vq / c2) + eps);
 }
 
-// g = the sum of the parts, four threads a parameter, each over every fourth
-// part; ADAM: and the step with it.
+// Gradients of parameters 64 row .. 64 row + 63, each the chain acc = u_i v_i + acc
+// over the samples i in order (a bias: u = 1); ADAM: and the step with them.
+// Lane j: parameter j of the row.  u is the same for all lanes (the last row, the
+// output's bias, has one parameter).  Chunks of 64 samples, the next one's loads in
+// flight under this one's chain.
 template <bool ADAM>
-__global__ __launch_bounds__(256) void k_mlp_sum(const double *__restrict__ part, int parts, int64_t n,
-                                                 float *__restrict__ g, float *__restrict__ p, float *__restrict__ m,
-                                                 float *__restrict__ v, float lr, float b1, float b2, float eps,
-                                                 float c1, float c2) {
-    __shared__ double sum[4][64];
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 64 + l;
-    double acc = 0;
-    if (q < n) {
-#pragma unroll 16
-        for (int i = w; i < parts; i += 4) acc += part[i * n + q];
+__global__ __launch_bounds__(64) void k_mlp_reduce(int F, const float *__restrict__ X, int64_t B, MlpRows rows,
+                                                   float *__restrict__ g, float *__restrict__ p,
+                                                   float *__restrict__ m, float *__restrict__ v, float lr, float b1,
+                                                   float b2, float eps, float c1, float c2) {
+    const int row = blockIdx.x, j = threadIdx.x;
+    const float *u = nullptr, *e = rows.dz1 + j;
+    int64_t us = 0, es = kH;
+    int r = row;
+    if (r < F) {  // W1[f][j]: x_f dz1_j
+        u = X + r;
+        us = F;
+    } else if ((r -= F) == 0) {  // b1
+    } else if ((r -= 1) < kH) {  // W2[a][j]: h1_a dz2_j
+        u = rows.h1 + r;
+        us = kH;
+        e = rows.dz2 + j;
+    } else if ((r -= kH) == 0) {  // b2
+        e = rows.dz2 + j;
+    } else if (r == 1) {  // w3[j]: h2_j dy
+        u = rows.dy;
+        us = 1;
+        e = rows.h2 + j;
+    } else {  // b3
+        e = rows.dy;
+        es = 1;
     }
-    sum[w][l] = acc;
-    __syncthreads();
-    if (w != 0 || q >= n) return;
-    acc = (sum[0][l] + sum[1][l]) + (sum[2][l] + sum[3][l]);
-    g[q] = (float)acc;
-    if constexpr (ADAM) adam(p, m, v, q, (float)acc, lr, b1, b2, eps, c1, c2);
+    struct Chunk {
+        float e[kH], u;
+    };
+    auto load = [&](Chunk &c, int64_t i0) __attribute__((always_inline)) {
+        const int64_t last = B - 1;
+        const int64_t iu = i0 + j < last ? i0 + j : last;
+        c.u = u ? u[iu * us] : 1.f;
+#pragma unroll
+        for (int k = 0; k < kH; ++k) {
+            const int64_t i = i0 + k < last ? i0 + k : last;
+            c.e[k] = e[i * es];
+        }
+    };
+    float acc = 0.f;
+    auto chain = [&](const Chunk &c, int64_t i0) __attribute__((always_inline)) {
+        auto term = [&](int k) __attribute__((always_inline)) {
+            const float uk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.u), k));
+            acc = fmaf(uk, c.e[k], acc);
+        };
+        if (B - i0 >= kH) {  // uniform
+#pragma unroll
+            for (int k = 0; k < kH; ++k) term(k);
+        } else {
+            const int n = (int)(B - i0);
+#pragma unroll
+            for (int k = 0; k < kH; ++k)
+                if (k < n) term(k);  // uniform
+        }
+    };
+    Chunk c0, c1b;
+    load(c0, 0);
+    for (int64_t i0 = 0; i0 < B; i0 += 2 * kH) {
+        if (i0 + kH < B) load(c1b, i0 + kH);
+        chain(c0, i0);
+        if (i0 + kH >= B) break;
+        if (i0 + 2 * kH < B) load(c0, i0 + 2 * kH);
+        chain(c1b, i0 + kH);
+    }
+    const int64_t q = (int64_t)row * kH + j;
+    if (q >= n_params_of(F)) return;
+    g[q] = acc;
+    if constexpr (ADAM) adam(p, m, v, q, acc, lr, b1, b2, eps, c1, c2);
 }
 
 __global__ void k_mlp_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -313,7 +350,7 @@ hipError_t mlp_forward_device(Mlp &net, const float *dX, int64_t B, float *dy, h
     const int64_t tiles = (B + S - 1) / S, blocks = (tiles + kMlpWaves - 1) / kMlpWaves;
     // (staging W2 is amortised over a wave's tiles: no more workgroups than the chip holds)
     k_mlp_rows<false, S><<<(unsigned)std::min<int64_t>(blocks, 1024), 64 * kMlpWaves, 0, st>>>(
-        net.p.as<float>(), net.F, dX, nullptr, B, dy, nullptr, nullptr);
+        net.p.as<float>(), net.F, dX, nullptr, B, dy, MlpRows{});
     return hipGetLastError();
 }
 
@@ -325,29 +362,29 @@ static hipError_t grad_launch(Mlp &net, const float *dX, const float *dt, int64_
     if (!mlp_fits(net)) return hipErrorInvalidValue;
     constexpr int S = 4;
     const int64_t np = n_params_of(net.F);
-    const size_t need = sizeof(double) * (size_t)kParts * np + sizeof(float) * (size_t)B;
+    const size_t need = sizeof(float) * (size_t)B * (4 * kH + 2);
     if (net.act.bytes < need) {
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         if ((e = net.act.alloc(need)) != hipSuccess) return e;
     }
-    double *part = net.act.as<double>();
-    float *ys = reinterpret_cast<float *>(part + (size_t)kParts * np);
-    const int64_t tiles = (B + S - 1) / S;
-    const unsigned blocks = (unsigned)std::min<int64_t>((tiles + kMlpWaves - 1) / kMlpWaves, kParts / kMlpWaves);
-    // (a wave without a tile writes no part)
-    const int parts = (int)std::min<int64_t>(tiles, (int64_t)blocks * kMlpWaves);
-    k_mlp_rows<true, S><<<blocks, 64 * kMlpWaves, 0, st>>>(net.p.as<float>(), net.F, dX, dt, B, ys, part, sq);
+    const size_t w = (size_t)B * kH;
+    float *base = net.act.as<float>();
+    MlpRows rows{base, base + w, base + 2 * w, base + 3 * w, base + 4 * w, sq};
+    float *ys = rows.dy + B;
+    const int64_t blocks = ((B + S - 1) / S + kMlpWaves - 1) / kMlpWaves;
+    k_mlp_rows<true, S><<<(unsigned)std::min<int64_t>(blocks, 1024), 64 * kMlpWaves, 0, st>>>(
+        net.p.as<float>(), net.F, dX, dt, B, ys, rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const unsigned sb = (unsigned)((np + 63) / 64);
+    const unsigned nr = (unsigned)((np + kH - 1) / kH);
     if (step) {
         net.step += 1;
         const float c1 = 1.f - std::pow(net.b1, (float)net.step);
         const float c2 = 1.f - std::pow(net.b2, (float)net.step);
-        k_mlp_sum<true><<<sb, 256, 0, st>>>(part, parts, np, dg, net.p.as<float>(), net.m.as<float>(),
-                                            net.v.as<float>(), net.lr, net.b1, net.b2, net.eps, c1, c2);
+        k_mlp_reduce<true><<<nr, kH, 0, st>>>(net.F, dX, B, rows, dg, net.p.as<float>(), net.m.as<float>(),
+                                              net.v.as<float>(), net.lr, net.b1, net.b2, net.eps, c1, c2);
     } else {
-        k_mlp_sum<false><<<sb, 256, 0, st>>>(part, parts, np, dg, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f, 0.f,
-                                             0.f);
+        k_mlp_reduce<false><<<nr, kH, 0, st>>>(net.F, dX, B, rows, dg, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f, 0.f,
+                                               0.f, 0.f);
     }
     return hipGetLastError();
 }
