@@ -239,13 +239,19 @@ hipError_t upload_candidates(CandSet &cs, int64_t m, const uint8_t *N, const int
 epi_status check_flags(epi_ctx *ctx) {
     int32_t f[kNumFlags];
     HIPTRY(ctx, hipMemcpy(f, ctx->c.flags.p, sizeof(f), hipMemcpyDeviceToHost), "reading device flags");
-    if (f[kFlagQueueOverflow] | f[kFlagUnsorted] | f[kFlagBadType] | f[kFlagBadTime]) {
+    if (f[kFlagQueueOverflow]) {
         HIPTRY(ctx, hipMemset(ctx->c.flags.p, 0, sizeof(f)), "clearing device flags");
-        if (f[kFlagUnsorted]) return fail(ctx, EPI_EUNSORTED, "device check: stream times decrease");
-        if (f[kFlagBadType]) return fail(ctx, EPI_ETYPE, "device check: event type outside [0, K)");
-        if (f[kFlagBadTime]) return fail(ctx, EPI_EOVERFLOW, "device check: reserved timestamp value in stream");
         return fail(ctx, EPI_EDEVICE, "device check: interval queue overflow (%d)", f[kFlagQueueOverflow]);
     }
+    return EPI_OK;
+}
+
+// The status of a load whose events are `bad` (IngestBad bits; the flags of
+// counts are theirs, and stay).
+epi_status check_ingest(epi_ctx *ctx, uint32_t bad) {
+    if (bad & kUnsorted) return fail(ctx, EPI_EUNSORTED, "device check: stream times decrease");
+    if (bad & kBadType) return fail(ctx, EPI_ETYPE, "device check: event type outside [0, K)");
+    if (bad & kBadTime) return fail(ctx, EPI_EOVERFLOW, "device check: reserved timestamp value in stream");
     return EPI_OK;
 }
 
@@ -373,10 +379,11 @@ epi_status epi_load_stream(epi_ctx *ctx, const int32_t *types, const void *times
     if (n > 0) {
         hipError_t e = hipMemcpyAsync(s->types.p, types, sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(s->times.p, times, s->ts_bytes() * n, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = ingest_stream(*s, nullptr, nullptr, true, ctx->c.flags.as<int32_t>(), st);
+        uint32_t bad = 0;
+        if (e == hipSuccess) e = ingest_stream(*s, nullptr, nullptr, true, &bad, st);
         if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
         HIPTRY(ctx, e, "copying the stream");
-        epi_status f = check_flags(ctx);
+        epi_status f = check_ingest(ctx, bad);
         if (f != EPI_OK) {
             // the first violation in stream order, and its message
             v = check_stream(types, times, n, ts_kind, K, &msg);
@@ -405,10 +412,11 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     HIPTRY(ctx, s->types.alloc(sizeof(int32_t) * n), "allocating stream types");
     HIPTRY(ctx, s->times.alloc(s->ts_bytes() * n), "allocating stream times");
     if (n > 0) {
-        const hipError_t e = ingest_stream(*s, d_types, d_times, true, ctx->c.flags.as<int32_t>(), st);
+        uint32_t bad = 0;
+        const hipError_t e = ingest_stream(*s, d_types, d_times, true, &bad, st);
         if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
         HIPTRY(ctx, e, "validating the stream");
-        epi_status f = check_flags(ctx);
+        epi_status f = check_ingest(ctx, bad);
         if (f != EPI_OK) return f;
     }
     return finish_load(ctx, std::move(s), st, stream_id);
@@ -722,7 +730,8 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     if (s->n == 0) s->tmin = first;
     s->tmax = last;
     s->n += n;
-    HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, ctx->c.flags.as<int32_t>(), ctx->c.stream), "ingesting the stream");
+    uint32_t bad = 0;  // (checked on the host)
+    HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, &bad, ctx->c.stream), "ingesting the stream");
     HIPTRY(ctx, build_type_index(*s, ctx->c.stream), "building the per-type index");
     HIPTRY(ctx, hipStreamSynchronize(ctx->c.stream), "sync");
     return EPI_OK;

@@ -311,10 +311,12 @@ __global__ void k_gap_init(unsigned long long *out) { out[threadIdx.x] = INT64_M
 constexpr int kTileSizes = 5;
 static_assert(kMinTile << (kTileSizes - 1) == kTile, "tile sizes");
 // What k_ingest finds out: the longest tile of each size (its first time to the
-// next tile's first, or to the last event), a cache line each.
+// next tile's first, or to the last event), a cache line each, and what is wrong
+// with the events (IngestBad).
 struct IngestInfo {
     static constexpr int kStride = 16;
     unsigned long long span[kTileSizes * kStride];
+    uint32_t bad;
 };
 
 // Copies the events (src null: they are in place already), checks them and takes
@@ -323,13 +325,13 @@ template <typename T>
 __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict__ src_types,
                                                       const T *__restrict__ src_times, int32_t *__restrict__ types,
                                                       T *__restrict__ times, int64_t n, int32_t K, bool check,
-                                                      int32_t *__restrict__ flags, IngestInfo *__restrict__ info) {
+                                                      IngestInfo *__restrict__ info) {
     // a workgroup takes kTile events: few workgroups meet at the maxima
     const int64_t beg = (int64_t)blockIdx.x * kTile, end = beg + kTile < n ? beg + kTile : n;
     const T *tm = src_times ? src_times : times;
     const int32_t *ty = src_types ? src_types : types;
     if (src_types || check) {
-        int bad = 0;
+        uint32_t bad = 0;
 #pragma unroll 4
         for (int64_t i = beg + threadIdx.x; i < end; i += kIdxBlock) {
             const int32_t y = ty[i];
@@ -340,13 +342,12 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
             }
             if (check) {
                 const T next = tm[i + 1 < n ? i + 1 : i];
-                bad |= (y < 0 || y >= K ? 1 : 0) | (t == TsLimits<T>::lo() || t == TsLimits<T>::hi() ? 2 : 0) |
-                       (next < t ? 4 : 0);
+                bad |= (y < 0 || y >= K ? kBadType : 0) |
+                       (t == TsLimits<T>::lo() || t == TsLimits<T>::hi() ? kBadTime : 0) |
+                       (next < t ? kUnsorted : 0);
             }
         }
-        if (bad & 1) atomicOr(&flags[kFlagBadType], 1);
-        if (bad & 2) atomicOr(&flags[kFlagBadTime], 1);
-        if (bad & 4) atomicOr(&flags[kFlagUnsorted], 1);
+        if (bad) atomicOr(&info->bad, bad);
     }
     // one wave: lane q of 16 the smallest tile q of the stretch, and from their
     // ends the larger tiles
@@ -369,18 +370,19 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
 }
 
 __global__ void k_ingest_init(IngestInfo *info) {
+    info->bad = 0;
     for (int q = 0; q < kTileSizes; ++q) info->span[q * IngestInfo::kStride] = 0;
 }
 
 template <typename T>
-hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, bool check, int32_t *d_flags,
+hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, bool check, uint32_t *bad,
                     hipStream_t st) {
     hipError_t e;
     DevBuf info;
     if ((e = info.alloc(sizeof(IngestInfo))) != hipSuccess) return e;
     k_ingest_init<<<1, 1, 0, st>>>(info.as<IngestInfo>());
     k_ingest<T><<<(unsigned)((s.n + kTile - 1) / kTile), kIdxBlock, 0, st>>>(
-        src_types, src_times, s.types.as<int32_t>(), s.times.as<T>(), s.n, s.K, check, d_flags, info.as<IngestInfo>());
+        src_types, src_times, s.types.as<int32_t>(), s.times.as<T>(), s.n, s.K, check, info.as<IngestInfo>());
     if ((e = hipGetLastError()) != hipSuccess) return e;
     IngestInfo h;
     if ((e = hipMemcpyAsync(&h, info.p, sizeof(h), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
@@ -389,6 +391,7 @@ hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, boo
     if ((e = hipMemcpyAsync(&ends[1], s.times.as<T>() + (s.n - 1), sizeof(T), hipMemcpyDeviceToHost, st)) != hipSuccess)
         return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    *bad = h.bad;
     s.tmin = ends[0];
     s.tmax = ends[1];
     for (int q = 0; q < kTileSizes; ++q) {
@@ -422,11 +425,12 @@ void pick_tile(Stream &s) {
 
 }  // namespace
 
-hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, int32_t *d_flags,
+hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, uint32_t *bad,
                          hipStream_t st) {
+    *bad = 0;
     if (s.n == 0) return hipSuccess;
-    if (s.ts_kind == EPI_TS_I64) return ingest_t<int64_t>(s, src_types, (const int64_t *)src_times, check, d_flags, st);
-    return ingest_t<int32_t>(s, src_types, (const int32_t *)src_times, check, d_flags, st);
+    if (s.ts_kind == EPI_TS_I64) return ingest_t<int64_t>(s, src_types, (const int64_t *)src_times, check, bad, st);
+    return ingest_t<int32_t>(s, src_types, (const int32_t *)src_times, check, bad, st);
 }
 
 hipError_t build_type_index(Stream &s, hipStream_t st) {

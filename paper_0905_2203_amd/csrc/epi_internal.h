@@ -25,8 +25,10 @@ constexpr int kFeatures = 24;      // cost-model features per candidate
 constexpr int kBaseFeature = 23;   // the cost model predicts log work as this feature + the network's correction
 constexpr int kWork = 5;           // work-log counters per candidate
 
-// Device error flags (int32 each), set by kernels with atomicOr / atomicAdd.
-enum DevFlag { kFlagQueueOverflow = 0, kFlagUnsorted = 1, kFlagBadType = 2, kFlagBadTime = 3, kNumFlags = 4 };
+// Device error flags (int32 each), set by counting kernels with atomicAdd.
+enum DevFlag { kFlagQueueOverflow = 0, kNumFlags = 1 };
+// What a load finds wrong with a stream's events (ingest_stream).
+enum IngestBad : uint32_t { kUnsorted = 1, kBadType = 2, kBadTime = 4 };
 
 template <typename T>
 struct TsLimits {
@@ -511,9 +513,9 @@ inline int64_t queue_bound(int64_t lo, int64_t hi) {
 // ---- launchers -------------------------------------------------------------
 hipError_t build_type_index(Stream &s, hipStream_t st);
 // Copy a stream's events from device buffers (null: they are in s.types and
-// s.times already), check them on the device (flags) when asked to, and set s's
-// first and last time and longest tiles; before build_type_index.
-hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, int32_t *d_flags,
+// s.times already), check them on the device when asked to (*bad: IngestBad bits),
+// and set s's first and last time and longest tiles; before build_type_index.
+hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, uint32_t *bad,
                          hipStream_t st);
 // ext_scratch (optional): device memory of ext_bytes for the segment records,
 // used instead of the set's own (then nothing is allocated and nothing waits

@@ -1,0 +1,73 @@
+"""The library's host side on the CPU, over a HIP runtime without a device (hip_stub.cpp): what stays queued and what
+is kept when a call fails, launches within the limits of a dispatch, memory that runs out.  Each case runs in a
+process of its own, which loads the stub before the library (and no torch)."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PRELUDE = """
+import ctypes, os, sys
+import numpy as np
+sys.path.insert(0, {root!r})
+stub = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
+for f in ("stub_queued", "stub_used", "stub_most", "stub_launches", "stub_launch_grid"):
+    getattr(stub, f).restype = ctypes.c_int64
+stub.stub_launch_name.restype = ctypes.c_char_p
+for f in ("stub_first_block", "stub_device_block", "stub_launch_arg"):
+    getattr(stub, f).restype = ctypes.c_void_p
+for f in ("stub_limit", "stub_total", "stub_launch_name", "stub_launch_grid", "stub_launch_arg"):
+    getattr(stub, f).argtypes = [ctypes.c_int64]
+stub.stub_device_block.argtypes = [ctypes.c_int64, ctypes.c_int]
+from paper_0905_2203_amd import epi
+
+def launches(part):
+    return [i for i in range(stub.stub_launches()) if part in stub.stub_launch_name(i).decode()]
+
+def code(f, *a, **k):
+    try:
+        f(*a, **k)
+    except epi.EpiError as e:
+        return e.code
+    return epi.EPI_OK
+
+def events(n, K=4):
+    return np.arange(n, dtype=np.int32) % K, np.arange(n, dtype=np.int64) * 1000
+
+def pairs(m, K=4):
+    ty = np.full((m, 8), -1, np.int32)
+    ty[:, 0], ty[:, 1] = np.arange(m) % K, (np.arange(m) + 1) % K
+    lo, hi = np.zeros((m, 7), np.int64), np.zeros((m, 7), np.int64)
+    hi[:, 0] = 5000
+    return dict(N=np.full(m, 2, np.uint8), types=ty, lo=lo, hi=hi)
+
+ctx = epi.Context(0)
+"""
+
+
+@pytest.fixture(scope="session")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "hip_stub.cpp")], check=True)
+    return out
+
+
+def run(stub, body):
+    text = PRELUDE.format(root=os.path.dirname(HERE), stub=stub) + body
+    r = subprocess.run([sys.executable, "-c", text], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_a_load_leaves_other_calls_flags_alone(stub):
+    """The flag of a count whose rings overflowed is that count's: loading another stream neither fails nor clears it."""
+    run(stub, """
+flag = ctypes.c_int32.from_address(stub.stub_first_block())  # (the context's first device memory)
+flag.value = 1
+assert code(ctx.epi_load_stream, *events(1000), 4) == epi.EPI_OK
+assert flag.value == 1
+assert code(ctx.epi_sync) == epi.EPI_EDEVICE
+assert flag.value == 0
+""")
