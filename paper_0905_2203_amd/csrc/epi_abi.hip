@@ -32,6 +32,7 @@ epi_status fail(epi_ctx *ctx, epi_status code, const char *fmt, ...) {
 }
 
 epi_status hipfail(epi_ctx *ctx, hipError_t e, const char *what) {
+    (void)hipGetLastError();  // (reported here: the next call's launches would report it again)
     if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
         return fail(ctx, EPI_ENOMEM, "%s: %s", what, hipGetErrorString(e));
     return fail(ctx, EPI_EDEVICE, "%s: %s", what, hipGetErrorString(e));
@@ -708,32 +709,35 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     const size_t tb = s->ts_bytes();
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
-    DevBuf ty, tm;
-    HIPTRY(ctx, ty.alloc(sizeof(int32_t) * (size_t)(s->n + n)), "allocating stream types");
-    HIPTRY(ctx, tm.alloc(tb * (size_t)(s->n + n)), "allocating stream times");
-    {
-        hipError_t e = hipSuccess;
+    // the longer stream is made beside the old one, which stays as it is when that fails
+    Stream longer;
+    longer.n = s->n + n;
+    longer.K = s->K;
+    longer.ts_kind = s->ts_kind;
+    longer.tile_cap = s->tile_cap;
+    auto make = [&]() -> hipError_t {
+        hipError_t e;
+        if ((e = longer.types.alloc(sizeof(int32_t) * (size_t)longer.n)) != hipSuccess) return e;
+        if ((e = longer.times.alloc(tb * (size_t)longer.n)) != hipSuccess) return e;
         if (s->n > 0) {
-            e = hipMemcpyAsync(ty.p, s->types.p, sizeof(int32_t) * s->n, hipMemcpyDeviceToDevice, st);
-            if (e == hipSuccess) e = hipMemcpyAsync(tm.p, s->times.p, tb * s->n, hipMemcpyDeviceToDevice, st);
+            e = hipMemcpyAsync(longer.types.p, s->types.p, sizeof(int32_t) * s->n, hipMemcpyDeviceToDevice, st);
+            if (e != hipSuccess) return e;
+            e = hipMemcpyAsync(longer.times.p, s->times.p, tb * s->n, hipMemcpyDeviceToDevice, st);
+            if (e != hipSuccess) return e;
         }
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(ty.as<int32_t>() + s->n, types, sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(tm.as<unsigned char>() + tb * s->n, times, tb * n, hipMemcpyHostToDevice, st);
-        // the old buffers go back idle
-        const hipError_t w = hipStreamSynchronize(st);
-        HIPTRY(ctx, e != hipSuccess ? e : w, "copying the events");
-    }
-    s->types = std::move(ty);
-    s->times = std::move(tm);
-    if (s->n == 0) s->tmin = first;
-    s->tmax = last;
-    s->n += n;
-    uint32_t bad = 0;  // (checked on the host)
-    HIPTRY(ctx, ingest_stream(*s, nullptr, nullptr, false, &bad, ctx->c.stream), "ingesting the stream");
-    HIPTRY(ctx, build_type_index(*s, ctx->c.stream), "building the per-type index");
-    HIPTRY(ctx, hipStreamSynchronize(ctx->c.stream), "sync");
+        e = hipMemcpyAsync(longer.types.as<int32_t>() + s->n, types, sizeof(int32_t) * n, hipMemcpyHostToDevice, st);
+        if (e != hipSuccess) return e;
+        e = hipMemcpyAsync(longer.times.as<unsigned char>() + tb * s->n, times, tb * n, hipMemcpyHostToDevice, st);
+        if (e != hipSuccess) return e;
+        uint32_t bad = 0;  // (checked on the host)
+        if ((e = ingest_stream(longer, nullptr, nullptr, false, &bad, st)) != hipSuccess) return e;
+        if ((e = build_type_index(longer, st)) != hipSuccess) return e;
+        return hipStreamSynchronize(st);
+    };
+    const hipError_t e = make();
+    if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
+    HIPTRY(ctx, e, "appending to the stream");
+    *s = std::move(longer);
     return EPI_OK;
 }
 

@@ -71,3 +71,38 @@ assert flag.value == 1
 assert code(ctx.epi_sync) == epi.EPI_EDEVICE
 assert flag.value == 0
 """)
+
+
+@pytest.mark.parametrize("kernel", ["k_ingest", "k_hist", "k_scatter"])
+def test_a_failed_append_leaves_nothing_queued_and_the_stream_as_it_was(stub, kernel):
+    """Its temporaries go back to the context's cache, so no queued work may still use them; the events before it stay."""
+    run(stub, f"""
+ty, t = events(3000)
+sid = ctx.epi_load_stream(ty[:2000], t[:2000], 4)
+cid = ctx.epi_submit_candidates(sid, pairs(4))
+ctx.epi_count([cid])
+ctx.epi_sync()
+stub.stub_fail_kernel(b"{kernel}")
+assert code(ctx.epi_append_stream, sid, ty[2000:], t[2000:]) == epi.EPI_EDEVICE
+assert stub.stub_queued() == 0
+assert ctx.epi_stream_info(sid)[0] == 2000
+off, by = ctx.epi_read_type_index(sid)
+assert by.size == 2000
+stub.stub_fail_kernel(b"no kernel")
+assert code(ctx.epi_append_stream, sid, ty[2000:], t[2000:]) == epi.EPI_OK
+assert ctx.epi_stream_info(sid)[0] == 3000
+""")
+
+
+def test_an_append_out_of_memory_leaves_the_stream_as_it_was(stub):
+    run(stub, """
+n = 1 << 20
+ty, t = events(n + 1000)
+sid = ctx.epi_load_stream(ty[:n], t[:n], 4)
+stub.stub_limit(stub.stub_used() + (14 << 20))  # room for the events, not for their index
+assert code(ctx.epi_append_stream, sid, ty[n:], t[n:]) == epi.EPI_ENOMEM
+assert ctx.epi_stream_info(sid)[0] == n and stub.stub_queued() == 0
+stub.stub_limit(1 << 40)
+assert code(ctx.epi_append_stream, sid, ty[n:], t[n:]) == epi.EPI_OK
+assert ctx.epi_stream_info(sid)[0] == n + 1000
+""")
