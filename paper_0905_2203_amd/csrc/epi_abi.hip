@@ -266,6 +266,21 @@ CandSet *find_set(epi_ctx *ctx, int32_t id) {
     return it == ctx->c.sets.end() ? nullptr : it->second.get();
 }
 
+// Whether kernels may read `bytes` at a caller's pointer: memory of this device
+// that holds them all.
+bool device_holds(const void *p, size_t bytes, int device) {
+    hipPointerAttribute_t a{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != device ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t at = (size_t)(static_cast<const char *>(p) - static_cast<const char *>(base));
+    return at <= size && bytes <= size - at;
+}
+
 hipStream_t pick_stream(epi_ctx *ctx, void *s) { return s ? (hipStream_t)s : ctx->c.stream; }
 
 // Index an ingested stream and hand out its id.
@@ -414,7 +429,17 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     HIPTRY(ctx, s->times.alloc(s->ts_bytes() * n), "allocating stream times");
     if (n > 0) {
         uint32_t bad = 0;
-        const hipError_t e = ingest_stream(*s, d_types, d_times, true, &bad, st);
+        hipError_t e = hipSuccess;
+        // memory that kernels can't be trusted to read (another device's, the host's, or less than n events) goes
+        // through a copy, which takes it or says what is wrong
+        const bool direct = device_holds(d_types, sizeof(int32_t) * n, ctx->c.device) &&
+                            device_holds(d_times, s->ts_bytes() * n, ctx->c.device);
+        if (!direct) {
+            e = hipMemcpyAsync(s->types.p, d_types, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st);
+            if (e == hipSuccess) e = hipMemcpyAsync(s->times.p, d_times, s->ts_bytes() * n, hipMemcpyDeviceToDevice, st);
+        }
+        if (e == hipSuccess)
+            e = ingest_stream(*s, direct ? d_types : nullptr, direct ? d_times : nullptr, true, &bad, st);
         if (e != hipSuccess) (void)hipDeviceSynchronize();  // (the buffers go back idle)
         HIPTRY(ctx, e, "validating the stream");
         epi_status f = check_ingest(ctx, bad);

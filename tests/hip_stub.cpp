@@ -97,7 +97,15 @@ int hipPointerGetAttributes(void *out, const void *p) {
 int hipHostMalloc(void **p, size_t n, unsigned) { return (*p = std::calloc(1, n)) ? 0 : set(kNoMemory); }
 int hipHostFree(void *p) { std::free(p); return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int) { std::memmove(d, s, n); queued = 0; return 0; }
-int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) { std::memmove(d, s, n); ++queued; return 0; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int, void *) {
+    for (const char *p : {(const char *)s, (const char *)d}) {  // (a range that leaves its block is refused)
+        auto it = blocks.upper_bound((char *)p);
+        if (it != blocks.begin() && p < (--it)->first + it->second && p + n > it->first + it->second) return set(kInvalid);
+    }
+    std::memmove(d, s, n);
+    ++queued;
+    return 0;
+}
 int hipMemset(void *d, int v, size_t n) { std::memset(d, v, n); queued = 0; return 0; }
 int hipMemsetAsync(void *d, int v, size_t n, void *) { std::memset(d, v, n); ++queued; return 0; }
 int hipDeviceSynchronize() { queued = 0; return 0; }

@@ -106,3 +106,31 @@ stub.stub_limit(1 << 40)
 assert code(ctx.epi_append_stream, sid, ty[n:], t[n:]) == epi.EPI_OK
 assert ctx.epi_stream_info(sid)[0] == n + 1000
 """)
+
+
+def test_device_loads_read_in_kernels_only_what_the_device_holds(stub):
+    """Borrowed arrays that are whole in this device's memory are read in place.  Others (host arrays, arrays shorter
+    than the count) go through a copy, which accepts or refuses them as it always did."""
+    run(stub, """
+def load(ty, t, n):
+    before = len(launches("k_ingestI"))
+    sid = ctypes.c_int32()
+    r = epi.lib().epi_load_stream_device(ctx.h, ty, t, n, epi.EPI_TS_I64, 4, None, ctypes.byref(sid))
+    at = launches("k_ingestI")[before:]
+    return r, [stub.stub_launch_arg(i) for i in at]
+
+n = 5000
+dty, dt = stub.stub_device_block(4 * n, 0), stub.stub_device_block(8 * n, 0)
+r, src = load(dty, dt, n)
+assert r == epi.EPI_OK and src == [dty]
+ty, t = events(n)
+r, src = load(ty.ctypes.data, t.ctypes.data, n)
+assert r == epi.EPI_OK and src == [None]
+r, src = load(dty, t.ctypes.data, n)
+assert r == epi.EPI_OK and src == [None]
+short = stub.stub_device_block(8 * n - 8, 0)
+r, src = load(dty, short, n)
+assert r == epi.EPI_EDEVICE and src == []
+r, src = load(dty + 4 * 100, dt + 8 * 100, n - 100)
+assert r == epi.EPI_OK and src == [dty + 400]
+""")
