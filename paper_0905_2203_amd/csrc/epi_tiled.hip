@@ -1031,6 +1031,10 @@ hipError_t wave_resident(int hand, int *waves) {
     return hipSuccess;
 }
 
+// Episodes of one launch: a workgroup of 64 lanes each, and a grid has fewer than
+// 2^32 lanes (a launch's own time is nothing beside a million episodes').
+constexpr int64_t kWaveGrid = int64_t(1) << 20;
+
 // What the wave chains read of a stream and a set.
 template <typename T>
 CountArgs<T> wave_args(const Stream &s, const CandSet &c, int32_t *d_flags) {
@@ -1066,7 +1070,7 @@ hipError_t wave_count_t(const Stream &s, CandSet &c, int64_t begin, int64_t end,
     const int64_t P = wave_segments(s, end - begin, cost_max, cost_all, kWaveSharePlain, opt, waves, &a.S);
     a.P = (int32_t)P;
     a.seg_cost = wave_seg_cost(opt, cost_max, P);
-    int64_t step = end - begin;
+    int64_t step = std::min(end - begin, kWaveGrid);
     if (P > 1 && ext_scratch) {
         // the caller's scratch: as many episodes at a time as it holds records for
         step = std::min<int64_t>(step, (int64_t)(ext_bytes / record_bytes<T>(P, 1)));
@@ -1231,8 +1235,10 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOpt
                 end = c.groups[++gi].end;
                 hand = std::max(hand, wave_group_hand(s, c, c.groups[gi], opt));
             }
-            a.G = end - a.begin;
-            if ((e = wave_launch_append<T>(a, hand, (T)B, st)) != hipSuccess) return e;
+            for (; a.begin < end; a.begin += a.G) {
+                a.G = std::min(end - a.begin, kWaveGrid);
+                if ((e = wave_launch_append<T>(a, hand, (T)B, st)) != hipSuccess) return e;
+            }
             continue;
         }
         AFn<T> fn = pick_append<T>(g.N);

@@ -781,6 +781,8 @@ __global__ __launch_bounds__(kW) void k_wave_sum_all(const CountArgs<T> *__restr
     }
 }
 
+constexpr int64_t kMostWaves = (int64_t(1) << 32) / kW - 1;  // of a grid's first dimension
+
 unsigned grid_of(int64_t n) { return (unsigned)std::min<int64_t>(std::max<int64_t>(n, 1), int64_t(1) << 16); }
 
 }  // namespace
@@ -825,14 +827,14 @@ hipError_t persistent_hand(unsigned grid, hipStream_t st, const CountArgs<T> *un
 template <typename T>
 hipError_t wave_launch(const CountArgs<T> &a, int hand, hipStream_t st) {
     if (a.G <= 0) return hipSuccess;
-    if (a.P < 1 || a.P > 65535 || !a.cN || !a.orig || a.G > INT32_MAX) return hipErrorInvalidValue;
+    if (a.P < 1 || a.P > 65535 || !a.cN || !a.orig || a.G > kMostWaves) return hipErrorInvalidValue;
     return hand == 1 ? launch_hand<T, 1>(a, st) : launch_hand<T, 2>(a, st);
 }
 
 template <typename T>
 hipError_t wave_launch_append(const CountArgs<T> &a, int hand, T B, hipStream_t st) {
     if (a.G <= 0) return hipSuccess;
-    if (!a.cN || !a.orig || !a.tau || a.G > INT32_MAX) return hipErrorInvalidValue;
+    if (!a.cN || !a.orig || !a.tau || a.G > kMostWaves) return hipErrorInvalidValue;
     if (hand == 1) k_wave_append<T, 1><<<(unsigned)a.G, kW, 0, st>>>(a, B);
     else k_wave_append<T, 2><<<(unsigned)a.G, kW, 0, st>>>(a, B);
     return hipGetLastError();
@@ -848,7 +850,7 @@ hipError_t wave_launch_persistent(unsigned grid, int hand, hipStream_t st, const
                                   void *list, int64_t cap) {
     WaveSlots slots{items, n_items, nullptr, nullptr, cap};
     if (list) {
-        if (n_items > INT32_MAX) return hipErrorInvalidValue;
+        if (n_items > kMostWaves) return hipErrorInvalidValue;
         int64_t *off = static_cast<int64_t *>(list), *out = off + n_items + 1;
         auto *masks = reinterpret_cast<unsigned long long *>(out + cap);
         k_wave_live<T><<<(unsigned)n_items, kW, 0, st>>>(units, items, masks);

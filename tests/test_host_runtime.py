@@ -134,3 +134,20 @@ assert r == epi.EPI_EDEVICE and src == []
 r, src = load(dty + 4 * 100, dt + 8 * 100, n - 100)
 assert r == epi.EPI_OK and src == [dty + 400]
 """)
+
+
+def test_sets_of_more_episodes_than_one_grid(stub):
+    """A launch takes at most 2^20 episodes, a workgroup each: a grid of 2^32 lanes (2^26 episodes) is refused."""
+    run(stub, """
+ty, t = events(4000)
+m = (1 << 21) + 5
+sid = ctx.epi_load_stream(ty[:3000], t[:3000], 4)
+cid = ctx.epi_submit_candidates(sid, pairs(m))
+ctx.epi_count([cid])
+at = launches("k_wave_count")
+assert [stub.stub_launch_grid(i) for i in at] == [1 << 20, 1 << 20, 5]
+ctx.epi_append_stream(sid, ty[3000:], t[3000:])
+ctx.epi_count([cid], epi.EPI_MODE_INCREMENTAL)
+at = launches("k_wave_append")
+assert [stub.stub_launch_grid(i) for i in at] == [1 << 20, 1 << 20, 5]
+""")
