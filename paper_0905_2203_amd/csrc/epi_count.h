@@ -170,12 +170,13 @@ template <typename T>
 hipError_t wave_launch(const CountArgs<T> &a, int hand, hipStream_t st);
 template <typename T>
 hipError_t wave_launch_append(const CountArgs<T> &a, int hand, T B, hipStream_t st);
-// The batched form over work items (blocks of 64 slots): a persistent grid and,
-// if segmented, the reconciliation of the units cut into segments.
+// The batched form over work items (blocks of 64 slots): a persistent grid, whose
+// waves take `take` slots at a time, and, if segmented, the reconciliation of the
+// units cut into segments.
 template <typename T>
 hipError_t wave_launch_persistent(unsigned grid, int hand, hipStream_t st, const CountArgs<T> *units,
                                   const WorkItem *items, int64_t n_items, unsigned long long *queue, bool segmented,
-                                  void *list, int64_t cap);
+                                  void *list, int64_t cap, int take);
 // Bytes of `list` (null: every slot of the items is queued) for at most cap
 // slots at work.
 size_t wave_list_bytes(int64_t n_items, int64_t cap);

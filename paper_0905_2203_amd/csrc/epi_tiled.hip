@@ -1021,6 +1021,20 @@ int64_t wave_seg_cost(const CountOptions &opt, double cost_max, int64_t P) {
     return opt.segments > 0 || P < 2 ? 0 : std::max<int64_t>(1, (int64_t)(cost_max / (double)P));
 }
 
+// How many light slots a wave of a batched count takes from the queue at a time, of
+// `slots` whose counting takes all of `cost_all` events, none more than cost_max.  A
+// turn at the queue's counter takes 12 ns, whoever takes it, a light episode 5 us of a
+// wave (7 ns an event): runs are as long as keep the turns to a quarter of the counting,
+// but none takes more than half of what each wave has to do.  1 where slots have 15,000
+// events.  (A million pairs of 8 events a type: 12.4 ms one at a time, 1.4 so.)
+constexpr double kSlotNs = 1000, kSlotEventNs = 7.4, kTurnNs = 12;
+int wave_take(int64_t slots, double cost_all, double cost_max, int waves) {
+    const double one = kSlotNs + kSlotEventNs * cost_all / (double)std::max<int64_t>(slots, 1);
+    double t = 4 * kTurnNs * (double)waves / one;
+    t = std::min(t, one * (double)slots / (double)waves / 2 / (kSlotNs + kSlotEventNs * cost_max));
+    return (int)std::max(1.0, std::min(t, 64.0));
+}
+
 hipError_t wave_resident(int hand, int *waves) {
     int dev = 0, ncu = 0;
     hipError_t e;
@@ -1778,11 +1792,13 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     // the wave chains' slots at work: an episode of c events has at most
     // c / seg_cost + 1 segments
     int64_t wave_cap = 0, wave_slots = 0;
+    double wave_most = 0;  // events of the costliest slot
     for (size_t ui = 0; ui < units.size(); ++ui) {
         const UnitH &u = units[ui];
         if (!u.wave) continue;
         const int64_t all = (u.G + 63) / 64 * 64 * u.P;
         wave_slots += all;
+        wave_most = std::max(wave_most, u.cost_max / (double)u.P);
         wave_cap += ua[ui].seg_cost > 0 ? std::min(all, (int64_t)(u.cost_sum / (double)ua[ui].seg_cost) + u.G) : all;
     }
     const bool wave_listed = wave_cap < wave_slots / 2;
@@ -1872,7 +1888,8 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             e = wave_launch_persistent<T>((unsigned)grid, hand, cache.br[bi], plan.units.as<CountArgs<T>>(),
                                           plan.items.as<WorkItem>() + ioff[cl], ncl,
                                           plan.queue.as<unsigned long long>() + cl, wave_segmented,
-                                          wave_listed ? plan.wave_list.p : nullptr, wave_cap);
+                                          wave_listed ? plan.wave_list.p : nullptr, wave_cap,
+                                          wave_take(wave_listed ? wave_cap : wave_slots, wave_cost, wave_most, waves));
             continue;
         }
         if (laneN[cl]) {

@@ -725,6 +725,7 @@ struct WaveSlots {
     const int64_t *list;   // null: all
     const int64_t *total;  // listed slots
     int64_t cap;
+    int take;              // slots a wave takes from the queue at a time
     __device__ __forceinline__ int64_t count() const {
         if (!list) return n_items * kW;
         const int64_t t = bcast(*total);
@@ -741,17 +742,19 @@ __global__ __launch_bounds__(kW) void k_wave_persistent(const CountArgs<T> *__re
     const int64_t n = slots.count();
     while (true) {
         rejoin();
-        int64_t q = 0;
-        if (lane == 0) q = (int64_t)atomicAdd(queue, 1ull);
+        int64_t q0 = 0;
+        if (lane == 0) q0 = (int64_t)atomicAdd(queue, (unsigned long long)slots.take);
         rejoin();
-        q = bcast(q);
+        q0 = bcast(q0);
         // unsigned: any counter value beyond the slots ends the loop
-        if ((uint64_t)q >= (uint64_t)n) break;
-        q = slots.at(q);
-        const WorkItem it = slots.items[q / kW];
-        const CountArgs<T> &a = units[it.unit];
-        const int64_t s = it.blk * kW + (q % kW);
-        if (s < a.G) wave_item<T>(a, s, it.p, w, lane);
+        if ((uint64_t)q0 >= (uint64_t)n) break;
+        for (int64_t i = q0; i < n && i < q0 + slots.take; ++i) {
+            const int64_t q = slots.at(i);
+            const WorkItem it = slots.items[q / kW];
+            const CountArgs<T> &a = units[it.unit];
+            const int64_t s = it.blk * kW + (q % kW);
+            if (s < a.G) wave_item<T>(a, s, it.p, w, lane);
+        }
     }
 }
 
@@ -847,8 +850,8 @@ size_t wave_list_bytes(int64_t n_items, int64_t cap) {
 template <typename T>
 hipError_t wave_launch_persistent(unsigned grid, int hand, hipStream_t st, const CountArgs<T> *units,
                                   const WorkItem *items, int64_t n_items, unsigned long long *queue, bool segmented,
-                                  void *list, int64_t cap) {
-    WaveSlots slots{items, n_items, nullptr, nullptr, cap};
+                                  void *list, int64_t cap, int take) {
+    WaveSlots slots{items, n_items, nullptr, nullptr, cap, take};
     if (list) {
         if (n_items > kMostWaves) return hipErrorInvalidValue;
         int64_t *off = static_cast<int64_t *>(list), *out = off + n_items + 1;
@@ -869,8 +872,8 @@ template hipError_t wave_launch<int64_t>(const CountArgs<int64_t> &, int, hipStr
 template hipError_t wave_launch_append<int32_t>(const CountArgs<int32_t> &, int, int32_t, hipStream_t);
 template hipError_t wave_launch_append<int64_t>(const CountArgs<int64_t> &, int, int64_t, hipStream_t);
 template hipError_t wave_launch_persistent<int32_t>(unsigned, int, hipStream_t, const CountArgs<int32_t> *,
-                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t);
+                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t, int);
 template hipError_t wave_launch_persistent<int64_t>(unsigned, int, hipStream_t, const CountArgs<int64_t> *,
-                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t);
+                                                    const WorkItem *, int64_t, unsigned long long *, bool, void *, int64_t, int);
 
 }  // namespace epi
