@@ -101,6 +101,16 @@ constexpr int64_t kNearShare = 4;
 // is as fast (311 alphas: 0.24 both) and writes the chain lists besides.
 constexpr int64_t kNearAlphas = 512;
 constexpr int64_t kNearJobs = 65536, kNearPiece = 64;
+// A cluster that is not simple is walked by one wave, 2.4 to 7.8 us every 64 stream
+// positions; the list path cuts it into pieces, some 27 ps a position on the whole
+// chip.  A level whose longest cluster has more than 1 / kNearLone of all positions
+// in its clusters takes the list path (counting, ms, rows and lists: 2532 alphas of
+// 48 types of skewed rates, one cluster a busy pair's whole stream of 300,000 events,
+// 1 / 540: 36.7 and 12.0; 1984 alphas with windows of 128 events, each one cluster,
+// 1 / 1850: 2.3 and 3.2; 4337 alphas, the longest 7323 positions of 85 million: 2.0
+// and 7.0), if that is at least kNearLeast positions (a walk of some 0.1 ms).
+constexpr double kNearLone = 1500;
+constexpr int64_t kNearLeast = 2048;
 
 // One entry of a chain list: an end event of an episode (time, stream
 // position) and the latest start of an occurrence ending there.
@@ -832,6 +842,107 @@ __global__ __launch_bounds__(kBlock) void k_near(NearArgs<T> a) {
     row[M] = (unsigned long long)(uint32_t)e;
 }
 
+// Clusters of the chain lists (see the near rows at the top): per alpha, how many
+// there are, the stream positions from each one's first entry to its last, summed,
+// and the longest of them.  A workgroup an alpha, a wave a quarter of its list.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_clusters(const ChainEntry<T> *__restrict__ chain,
+                                                     const int64_t *__restrict__ cbeg,
+                                                     const int32_t *__restrict__ clen, T H,
+                                                     int64_t *__restrict__ spans, int32_t *__restrict__ heads,
+                                                     int32_t *__restrict__ longest) {
+    constexpr int kWaves = kBlock / kWave;
+    // of each wave: its clusters' spans, count and longest, the entry before its
+    // first head, and its last head (positions; -1: no head)
+    __shared__ int64_t w_span[kWaves];
+    __shared__ int32_t w_heads[kWaves], w_long[kWaves], w_before[kWaves], w_last[kWaves];
+    const int64_t alpha = blockIdx.x;
+    const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+    const int32_t n = clen[alpha];
+    const ChainEntry<T> *x = chain + cbeg[alpha];
+    const int32_t e0 = (int32_t)((int64_t)n * wv / kWaves), e1 = (int32_t)((int64_t)n * (wv + 1) / kWaves);
+    int64_t span = 0;
+    int32_t nh = 0, most = 0, before = -1, last = -1;
+    for (int32_t i0 = e0; i0 < e1; i0 += kWave) {  // uniform
+        const int32_t i = i0 + lane;
+        const bool in = i < e1;
+        const ChainEntry<T> a = x[min(i, e1 - 1)], b = x[max(min(i, e1 - 1) - 1, 0)];
+        const uint64_t hd = __ballot(in & ((i == 0) | (a.s > (T)(b.t + H))));
+        if (!hd) continue;
+        const uint64_t lower = hd & ((1ull << lane) - 1);
+        const int32_t from = __shfl(a.p, lower ? 63 - __builtin_clzll(lower) : 0, kWave);
+        const int32_t start = lower ? from : last;  // (of the cluster that ends before this lane)
+        if (((hd >> lane) & 1) && start >= 0) {
+            span += b.p - start;
+            most = max(most, b.p - start);
+        }
+        if (before < 0 && last < 0) before = __shfl(b.p, __builtin_ctzll(hd), kWave);
+        last = __shfl(a.p, 63 - __builtin_clzll(hd), kWave);
+        nh += __popcll(hd);
+    }
+    for (int d = 1; d < kWave; d <<= 1) {
+        span += __shfl_xor(span, d, kWave);
+        most = max(most, __shfl_xor(most, d, kWave));
+    }
+    if (lane == 0) {
+        w_span[wv] = span;
+        w_heads[wv] = nh;
+        w_long[wv] = most;
+        w_before[wv] = before;
+        w_last[wv] = last;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int32_t open = -1;
+    auto close = [&](int32_t end) {
+        if (open < 0) return;
+        span += end - open;
+        most = max(most, end - open);
+    };
+    span = 0, nh = 0, most = 0;
+    for (int w = 0; w < kWaves; ++w) {
+        if (w_last[w] < 0) continue;
+        close(w_before[w]);
+        span += w_span[w];
+        nh += w_heads[w];
+        most = max(most, w_long[w]);
+        open = w_last[w];
+    }
+    if (n > 0) close(x[n - 1].p);
+    spans[alpha] = span;
+    heads[alpha] = nh;
+    longest[alpha] = most;
+}
+
+// The alphas' clusters in all: out[0] spans, out[1] clusters, out[2] the longest.
+__global__ __launch_bounds__(1024) void k_clusters_sum(const int64_t *__restrict__ spans,
+                                                       const int32_t *__restrict__ heads,
+                                                       const int32_t *__restrict__ longest, int64_t nA,
+                                                       int64_t *__restrict__ out) {
+    __shared__ int64_t part[3][1024 / kWave];
+    int64_t v[3] = {0, 0, 0};
+    for (int64_t i = threadIdx.x; i < nA; i += 1024) {
+        v[0] += spans[i];
+        v[1] += heads[i];
+        v[2] = max(v[2], (int64_t)longest[i]);
+    }
+    for (int d = 1; d < kWave; d <<= 1) {
+        v[0] += __shfl_xor(v[0], d, kWave);
+        v[1] += __shfl_xor(v[1], d, kWave);
+        v[2] = max(v[2], __shfl_xor(v[2], d, kWave));
+    }
+    if (threadIdx.x % kWave == 0)
+        for (int k = 0; k < 3; ++k) part[k][threadIdx.x / kWave] = v[k];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 1024 / kWave; ++w) {
+        v[0] += part[0][w];
+        v[1] += part[1][w];
+        v[2] = max(v[2], part[2][w]);
+    }
+    for (int k = 0; k < 3; ++k) out[k] = v[k];
+}
+
 // ---- device-side bookkeeping of the levels ----------------------------------
 
 constexpr int kScanItems = 8;
@@ -1382,7 +1493,11 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     L.nA = nA;
     // ---- the candidates: alpha-major, alpha's extensions in (type, interval) order
     int64_t m;
-    DevBuf d_order, tmp;
+    DevBuf d_order, tmp, spans;
+    const T H = (T)*std::max_element(mn.menu_hi.begin(), mn.menu_hi.end());
+    bool lone = false;  // one wave would walk long after the others
+    const bool rows_may = N > 2 && (nA >= kNearAlphas || nA >= mn.list_alphas) &&
+                          P.chain_total >= s.n / kNearShare * ((s.K + 63) / 64);
     if (N == 2) {
         m = nA * (nA - 1) * M;
     } else {
@@ -1401,8 +1516,24 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
                                                cnt.as<int64_t>());
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = scan64(cnt.as<int64_t>(), nA, L.d_out_off.as<int64_t>(), tmp, st, &stage[0])) != hipSuccess) return e;
+        // what the near rows would meet (slots 4 to 6)
+        if (rows_may && nA < mn.list_alphas) {
+            if ((e = spans.alloc((sizeof(int64_t) + 2 * sizeof(int32_t)) * nA)) != hipSuccess) return e;
+            int64_t *sp = spans.as<int64_t>();
+            int32_t *heads = reinterpret_cast<int32_t *>(sp + nA), *longest = heads + nA;
+            k_clusters<T><<<(unsigned)nA, kBlock, 0, st>>>(
+                P.chain.as<ChainEntry<T>>(), P.cbeg.as<int64_t>(), P.d_fnv.as<int32_t>(), H, sp, heads, longest);
+            k_clusters_sum<<<1, 1024, 0, st>>>(sp, heads, longest, nA, &stage[4]);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         m = stage[0];
+        if (rows_may && nA < mn.list_alphas) {
+            // every cluster's entries, and a window after its last
+            const double window = (double)s.n * (double)H / std::max(1.0, (double)s.tmax - (double)s.tmin);
+            const double all = (double)stage[4] + (double)stage[5] * window;
+            lone = stage[6] >= kNearLeast && (double)stage[6] * kNearLone > all;
+        }
         // workgroups take the longest walks first, so that none is left alone
         // at the end (the list path's walks are cut into pieces)
         if ((nA >= kNearAlphas || nA >= mn.list_alphas) &&
@@ -1414,7 +1545,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     a.ty16 = mn.ty16.as<uint16_t>();
     a.times = s.times.as<T>();
     a.wend = mn.wend.as<int32_t>();
-    a.H = (T)*std::max_element(mn.menu_hi.begin(), mn.menu_hi.end());
+    a.H = H;
     a.chain = mn.chain1.as<ChainEntry<T>>();  // level 2; level >= 3 below
     a.type_off = s.type_off.as<int32_t>();
     a.M = M;
@@ -1450,8 +1581,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     auto t1 = Clock::now();
     // ---- count
     (void)hipEventRecord(mn.ev[0], st);
-    if (m > 0 && N > 2 && (nA >= kNearAlphas || nA >= mn.list_alphas) &&
-        P.chain_total >= s.n / kNearShare * ((s.K + 63) / 64)) {
+    if (m > 0 && rows_may && !lone) {
         if ((e = make_near<T>(s, mn, a, st)) != hipSuccess) return e;
         a.near = mn.near.as<unsigned long long>();
     }
