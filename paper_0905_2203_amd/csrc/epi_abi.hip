@@ -740,6 +740,17 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     longer.K = s->K;
     longer.ts_kind = s->ts_kind;
     longer.tile_cap = s->tile_cap;
+    longer.cells = s->cells;
+    if (i64) {
+        const int64_t *t = (const int64_t *)times;
+        int64_t cell = s->n > 0 ? s->tmax >> kCellBits : t[0] >> kCellBits;
+        if (s->n == 0) longer.cells = 1;
+        for (int64_t i = 0; i < n; ++i)
+            if (t[i] >> kCellBits != cell) {
+                ++longer.cells;
+                cell = t[i] >> kCellBits;
+            }
+    }
     auto make = [&]() -> hipError_t {
         hipError_t e;
         if ((e = longer.types.alloc(sizeof(int32_t) * (size_t)longer.n)) != hipSuccess) return e;

@@ -316,6 +316,7 @@ static_assert(kMinTile << (kTileSizes - 1) == kTile, "tile sizes");
 struct IngestInfo {
     static constexpr int kStride = 16;
     unsigned long long span[kTileSizes * kStride];
+    unsigned long long cells;  // int64 times: events that begin a stretch of 2^kCellBits units, but the first
     uint32_t bad;
 };
 
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
     const T *tm = src_times ? src_times : times;
     const int32_t *ty = src_types ? src_types : types;
     if (src_types || check) {
-        uint32_t bad = 0;
+        uint32_t bad = 0, cells = 0;
 #pragma unroll 4
         for (int64_t i = beg + threadIdx.x; i < end; i += kIdxBlock) {
             const int32_t y = ty[i];
@@ -340,14 +341,19 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
                 types[i] = y;
                 times[i] = t;
             }
+            const T next = tm[i + 1 < n ? i + 1 : i];
+            if constexpr (sizeof(T) == 8) cells += (next >> kCellBits) != (t >> kCellBits) ? 1 : 0;
             if (check) {
-                const T next = tm[i + 1 < n ? i + 1 : i];
                 bad |= (y < 0 || y >= K ? kBadType : 0) |
                        (t == TsLimits<T>::lo() || t == TsLimits<T>::hi() ? kBadTime : 0) |
                        (next < t ? kUnsorted : 0);
             }
         }
         if (bad) atomicOr(&info->bad, bad);
+        if constexpr (sizeof(T) == 8) {
+            for (int d = 1; d < kWave; d <<= 1) cells += __shfl_xor(cells, d, kWave);
+            if (threadIdx.x % kWave == 0 && cells) atomicAdd(&info->cells, (unsigned long long)cells);
+        }
     }
     // one wave: lane q of 16 the smallest tile q of the stretch, and from their
     // ends the larger tiles
@@ -371,6 +377,7 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
 
 __global__ void k_ingest_init(IngestInfo *info) {
     info->bad = 0;
+    info->cells = 0;
     for (int q = 0; q < kTileSizes; ++q) info->span[q * IngestInfo::kStride] = 0;
 }
 
@@ -392,6 +399,7 @@ hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, boo
         return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     *bad = h.bad;
+    if (src_types || check) s.cells = sizeof(T) == 8 ? 1 + (int64_t)h.cells : 0;
     s.tmin = ends[0];
     s.tmax = ends[1];
     for (int q = 0; q < kTileSizes; ++q) {

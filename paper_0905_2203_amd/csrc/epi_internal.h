@@ -192,6 +192,8 @@ struct DevBuf {
     }
 };
 
+constexpr int kCellBits = 34;      // a window of the wave chains spans less than 2^34 units (int64 times)
+
 struct Stream {
     int64_t n = 0;
     int32_t K = 0;
@@ -218,6 +220,7 @@ struct Stream {
     std::vector<int32_t> h_off;  // host copy of type_off
     int64_t tile_span[5] = {};       // longest tile of 256, 512, ... 4096 events (ingest_stream)
     int64_t max_tile_span = -1;      // longest time from a tile's first event to the next tile's (or the last event)
+    int64_t cells = 0;               // int64 times: stretches of 2^kCellBits units (by their high bits) with events
     // least time from one event to the 63rd, 127th after it of the same type (INT64_MAX: no type has as many)
     int64_t gap[2] = {};
     size_t ts_bytes() const { return ts_kind == EPI_TS_I64 ? 8 : 4; }
@@ -515,6 +518,7 @@ hipError_t build_type_index(Stream &s, hipStream_t st);
 // Copy a stream's events from device buffers (null: they are in s.types and
 // s.times already), check them on the device when asked to (*bad: IngestBad bits),
 // and set s's first and last time and longest tiles; before build_type_index.
+// (s.cells: only when the events are copied or checked.)
 hipError_t ingest_stream(Stream &s, const int32_t *src_types, const void *src_times, bool check, uint32_t *bad,
                          hipStream_t st);
 // ext_scratch (optional): device memory of ext_bytes for the segment records,
@@ -530,7 +534,7 @@ unsigned char *noalloc_scratch(int device);
 size_t noalloc_scratch_bytes();
 // Whether the wave chains count every episode of set c (its groups are all theirs
 // and no episode is deep).
-bool wave_counts_all(const Stream &s, const CandSet &c, const CountOptions &opt);
+bool wave_counts_all(const Stream &s, CandSet &c, const CountOptions &opt);
 // Segments of a plain count of a group of G episodes on stream s (and the
 // tiles per segment, *S_out), and the bytes of its segment records.
 int64_t plain_segments(const Stream &s, int64_t G, const CountOptions &opt, int64_t *S_out);

@@ -986,6 +986,24 @@ void candidate_costs(const Stream &s, CandSet &c) {
     c.cost_n = s.n;
 }
 
+// Whether the wave chains, which could count group g whole, are the faster ones (as
+// far as the groups' costs are known: candidate_costs).  They are not
+//   * where events are so far apart that a window, which spans less than 2^34 units,
+//     holds few: a window takes some 2 us of a wave whatever it holds (5000 episodes of
+//     2-5 nodes over 2M events of 128 types, int64 ns, ms, chains and machines: 0.05 Hz,
+//     0.9 events of a type a window, 41.5 and 25.3; 0.5 Hz 6.3 and 25.8; 2 Hz 1.9 and 24.7);
+//   * for very many episodes of a few events each, of which a machine's wave takes 64 at
+//     a time and a chain's one, 5 us (a million, ms: batched, 8 events an episode 1.41
+//     and 0.56, 27 1.49 and 0.82, 82 1.59 and 1.42, 135 1.59 and 1.88; plain, 8 1.32
+//     and 0.93, 27 1.37 and 1.58).
+bool wave_pays(const Stream &s, const CandSet &c, const Group &g, bool batched) {
+    const double G = (double)(g.end - g.begin);
+    if (c.cost_n != s.n || G < 1) return true;
+    if (s.ts_kind == EPI_TS_I64 && s.cells >= 64 && g.cost_sum < 1.4 * (double)s.cells * G * (double)g.N) return false;
+    if (!lane_rel_ok(s.max_tile_span, g.hspan)) return true;
+    return batched ? c.m < (int64_t(1) << 18) || g.cost_sum > 64 * G : c.m < (int64_t(1) << 19) || g.cost_sum > 16 * G;
+}
+
 // Segments of episodes counted by the wave chains (and the tiles per segment,
 // *S_out): the costliest (episode, segment) takes 1 / share of what each
 // resident wave has to do of the whole launch, so that no wave is left running
@@ -1112,15 +1130,15 @@ hipError_t count_t(const Stream &s, CandSet &c, const CountOptions &opt, int32_t
         const Group &g = c.groups[gi];
         const int64_t G = g.end - g.begin;
         if (G <= 0) continue;
-        if (int hand = wave_group_hand(s, c, g, opt)) {
+        const auto hand_of = [&](const Group &x) { return wave_pays(s, c, x, false) ? wave_group_hand(s, c, x, opt) : 0; };
+        if (int hand = hand_of(g)) {
             // adjacent groups in one launch (a wave takes an episode of any size)
             int64_t end = g.end;
             double cmax = g.cost_max, call = g.cost_sum;
-            while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end &&
-                   wave_group_hand(s, c, c.groups[gi + 1], opt)) {
+            while (gi + 1 < c.groups.size() && c.groups[gi + 1].begin == end && hand_of(c.groups[gi + 1])) {
                 const Group &h = c.groups[++gi];
                 end = h.end;
-                hand = std::max(hand, wave_group_hand(s, c, h, opt));
+                hand = std::max(hand, hand_of(h));
                 cmax = std::max(cmax, h.cost_max);
                 call += h.cost_sum;
             }
@@ -1288,10 +1306,11 @@ hipError_t count_append_t(const Stream &s, CandSet &c, int64_t B, const CountOpt
 
 }  // namespace
 
-bool wave_counts_all(const Stream &s, const CandSet &c, const CountOptions &opt) {
+bool wave_counts_all(const Stream &s, CandSet &c, const CountOptions &opt) {
     if (c.deep || c.groups.empty()) return false;
+    candidate_costs(s, c);
     for (const Group &g : c.groups)
-        if (!wave_group_hand(s, c, g, opt)) return false;
+        if (!wave_group_hand(s, c, g, opt) || !wave_pays(s, c, g, false)) return false;
     return true;
 }
 
@@ -1535,6 +1554,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
     double wave_cost = 0;  // of all groups the wave chains count
     for (size_t si = 0; si < sets.size(); ++si) {
         for (const Group &g : mg[si]) {
+            if (!wave_pays(*sets[si].s, *sets[si].c, g, true)) continue;
             const int h = wave_group_hand(*sets[si].s, *sets[si].c, g, opt);
             if (h) wave_cost += g.cost_sum;
             hand = std::max(hand, h);
@@ -1561,7 +1581,7 @@ hipError_t plan_t(std::vector<BatchRef> &sets, int sched, const CountOptions &op
             u.filt = c.compact && c.pred_bits && c.succ_bits;
             u.cost_sum = c.compact ? (double)G * (double)g.N * (double)s.n / std::max(1.0, (double)s.K) : g.cost_sum;
             u.cost_max = g.cost_max;
-            u.wave = wave_group_hand(s, c, g, opt) > 0;
+            u.wave = wave_pays(s, c, g, true) && wave_group_hand(s, c, g, opt) > 0;
             if (u.wave) {
                 u.P = wave_segments(s, G, u.cost_max, wave_cost, kWaveShareBatched, opt, waves, &u.S);
                 units.push_back(u);

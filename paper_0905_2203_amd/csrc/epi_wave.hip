@@ -62,6 +62,7 @@ struct Entry {
     static constexpr bool kRel = sizeof(T) == 8;  // times from the window's first event
     static constexpr int kLow = kRel ? 29 : 32;
     static constexpr uint64_t kSpan = (uint64_t(1) << (63 - kLow)) - 1;  // longest window
+    static_assert(!kRel || 63 - kLow == kCellBits, "cells of a stream are windows' spans");
     using Key = std::conditional_t<kRel, int64_t, int32_t>;   // what a search compares
     using UKey = std::make_unsigned_t<Key>;
     static constexpr int kKeyAt = kRel ? 0 : 4;               // byte of it in the entry

@@ -170,6 +170,8 @@ int hipLaunchKernel(const void *fn, Dim3 grid, Dim3 block, void **args, size_t s
     auto is = [&](const char *part) { return name.find(part) != std::string::npos; };
     int64_t *sum = is("k_scan_small") ? *(int64_t **)args[3] : is("k_scan_apply64") ? *(int64_t **)args[5] : nullptr;
     if (sum) *sum = total;
+    if (is("k_type_off"))  // 1000 events of every type
+        for (int32_t k = 0; k <= *(int32_t *)args[1]; ++k) (*(int32_t **)args[2])[k] = 1000 * k;
     if (is("k_gap_init"))
         for (uint32_t k = 0; k < block.x; ++k) (*(int64_t **)args[0])[k] = INT64_MAX;
     if (is("k_level1I"))

@@ -25,10 +25,10 @@ def episodes(rng, m, K, hi):
                 hi=np.where(live, lo + rng.integers(hi // 4, hi, size=(m, 7)), 0).astype(np.int64))
 
 
-@pytest.mark.parametrize("m,kind", [(1, 0), (63, 1), (5000, 0), (70001, 1), (300007, 0)])
-def test_light_slots_in_runs(m, kind):
+@pytest.mark.parametrize("m,n,kind", [(1, 700, 0), (63, 700, 1), (5000, 700, 0), (70001, 700, 1), (300007, 1600, 0)])
+def test_light_slots_in_runs(m, n, kind):
     rng = np.random.default_rng(m)
-    s = stream(700, 24, kind, m)
+    s = stream(n, 24, kind, m)
     c = episodes(rng, m, 24, 60000)
     want = oracle.count(s, c)
     with epi.Context(0) as ctx:
@@ -53,3 +53,52 @@ def test_light_and_heavy_sets_together():
             ctx.epi_count([cid for cid, _, _ in sets], epi.EPI_MODE_BATCHED, epi.EPI_SCHED_RR)
             for cid, m, want in sets:
                 assert np.array_equal(ctx.epi_read_counts(cid, m), want)
+
+
+@pytest.mark.parametrize("m,n", [(1 << 18, 500), ((1 << 19) + 3, 100)])
+def test_very_many_episodes_of_a_few_events(m, n):
+    """Counted by the machines (64 episodes a wave): batched at most 64 events an episode, plain at most 16."""
+    rng = np.random.default_rng(n)
+    s = stream(n, 24, 0, n)
+    c = episodes(rng, m, 24, 60000)
+    events = np.bincount(s["types"], minlength=24)
+    per = sum(np.where(c["types"][:, k] >= 0, events[c["types"][:, k]], 0) for k in range(8))
+    assert per.mean() < (64 if n == 500 else 16)
+    want = oracle.count(s, c)
+    with epi.Context(0) as ctx:
+        sid = ctx.epi_load_stream(s["types"], s["times"], s["K"])
+        cid = ctx.epi_submit_candidates(sid, c)
+        for mode in (epi.EPI_MODE_PLAIN, epi.EPI_MODE_BATCHED):
+            ctx.epi_count([cid], mode)
+            assert np.array_equal(ctx.epi_read_counts(cid, m), want)
+
+
+@pytest.mark.parametrize("per_cell", [0.7, 3.0])
+def test_events_far_apart(per_cell):
+    """int64 streams whose windows hold fewer or more events of a type than the chains need (1.4): plain, batched,
+    tracking, and appended to across many windows."""
+    rng = np.random.default_rng(int(per_cell * 10))
+    n, K = 6000, 10
+    t = np.sort(rng.integers(0, int(n / K / per_cell * (1 << 34)), size=n))
+    t[1::2] = t[::2] + rng.integers(0, 400_000_000, size=n // 2)  # (half of them follow another closely)
+    order = np.argsort(t, kind="stable")
+    s = dict(types=rng.integers(0, K, size=n).astype(np.int32)[order], times=t[order].astype(np.int64), K=K, ts_kind=1)
+    c = episodes(rng, 200, K, 170_000_000)
+    cells = 1 + int((np.diff(s["times"] >> 34) != 0).sum())
+    assert cells >= 64 and (n / K < 1.4 * cells) == (per_cell < 1)
+    want = oracle.count(s, c)
+    assert want.max() > 20
+    with epi.Context(0) as ctx:
+        sid = ctx.epi_load_stream(s["types"], s["times"], K)
+        cid = ctx.epi_submit_candidates(sid, c)
+        for mode in (epi.EPI_MODE_PLAIN, epi.EPI_MODE_BATCHED, epi.EPI_MODE_TRACKING):
+            ctx.epi_count([cid], mode)
+            assert np.array_equal(ctx.epi_read_counts(cid, 200), want)
+        sid = ctx.epi_load_stream(s["types"][:n // 2], s["times"][:n // 2], K)
+        cid = ctx.epi_submit_candidates(sid, c)
+        ctx.epi_count([cid])
+        ctx.epi_append_stream(sid, s["types"][n // 2:], s["times"][n // 2:])
+        ctx.epi_count([cid], epi.EPI_MODE_INCREMENTAL)
+        assert np.array_equal(ctx.epi_read_counts(cid, 200), want)
+        ctx.epi_count([cid])
+        assert np.array_equal(ctx.epi_read_counts(cid, 200), want)
