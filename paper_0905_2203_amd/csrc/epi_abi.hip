@@ -384,6 +384,7 @@ epi_status epi_load_stream(epi_ctx *ctx, const int32_t *types, const void *times
     if (n < 0 || n >= (int64_t(1) << 31)) return fail(ctx, EPI_ESIZE, "n must be in [0, 2^31)");
     if (n > 0 && (!types || !times)) return fail(ctx, EPI_EINVAL, "null stream pointer");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     auto s = std::make_unique<Stream>();
@@ -419,6 +420,7 @@ epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const vo
     if (n < 0 || n >= (int64_t(1) << 31)) return fail(ctx, EPI_ESIZE, "n must be in [0, 2^31)");
     if (n > 0 && (!d_types || !d_times)) return fail(ctx, EPI_EINVAL, "null stream pointer");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = pick_stream(ctx, hip_stream);
     auto s = std::make_unique<Stream>();
@@ -501,6 +503,7 @@ epi_status epi_submit_candidates(epi_ctx *ctx, int32_t stream_id, int64_t m, con
                         (long long)c);
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     auto cs = std::make_unique<CandSet>();
     cs->stream_id = stream_id;
@@ -576,7 +579,7 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
             return fail(ctx, EPI_ESTATE, "set %d has no work log to schedule by", set_ids[i]);
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
-    SpareScope spare(&ctx->c.idle);
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     hipStream_t st = pick_stream(ctx, hip_stream);
     if (mode == EPI_MODE_INCREMENTAL) {
         // sets never counted: a full count; sets counted before an append:
@@ -732,6 +735,7 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
     HIPTRY(ctx, hipDeviceSynchronize(), "sync");
     ctx->c.batch.evict_all();
     const size_t tb = s->ts_bytes();
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     // the longer stream is made beside the old one, which stays as it is when that fails
@@ -884,7 +888,6 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
     if (s->n > 0 && (s->tmax > thi - 1 - span || s->tmin < tlo + 1 + span))
         return fail(ctx, EPI_EOVERFLOW, "stream times +- the longest span leave the timestamp type");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
-    SpareScope spare(&ctx->c.idle);
     // the levels run on the context's stream, after the work already queued
     // on the caller's; every buffer of the run comes from the context's cache
     hipStream_t st = ctx->c.stream;
@@ -896,6 +899,7 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
         (void)hipEventDestroy(ev);
         HIPTRY(ctx, e, "ordering after the caller's stream");
     }
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.cache);
     auto mn = std::make_unique<Mine>();
     mn->stream_id = stream_id;
@@ -929,7 +933,7 @@ epi_status epi_mine(epi_ctx *ctx, int32_t stream_id, int32_t n_menu, const int64
                 break;
             }
         }
-        mn->near.reset();
+        extend_finish(*mn);
         epi_status f = check_flags(ctx);
         if (f != EPI_OK) return f;
     } else {
@@ -1042,6 +1046,7 @@ epi_status epi_mine_read(epi_ctx *ctx, int32_t mine_id, int32_t level, int frequ
     if (m > 0 && (!N || !types || !lo || !hi || !counts)) return fail(ctx, EPI_EINVAL, "null output");
     if (frequent_only && L.implicit) {
         HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+        SpareScope spare(&ctx->c.idle, &ctx->c.cache);
         CacheScope scope(&ctx->c.idle);
         HIPTRY(ctx, extend_read_frequent(mn, level, types, lo, hi, counts, ctx->c.stream), "reading a level");
         std::fill(N, N + m, (uint8_t)L.N);
@@ -1128,6 +1133,7 @@ epi_status epi_mlp_init(epi_ctx *ctx, int32_t n_features, uint64_t seed) {
     if (!ctx) return EPI_EINVAL;
     if (n_features < 1 || n_features > 4096) return fail(ctx, EPI_EINVAL, "n_features must be in 1..4096");
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     HIPTRY(ctx, mlp_init(ctx->c.mlp, n_features, seed), "initialising the cost model");
     return EPI_OK;
 }
@@ -1169,6 +1175,7 @@ epi_status epi_mlp_forward(epi_ctx *ctx, const float *X, int64_t B, float *y) {
     if (!ctx || (B > 0 && (!X || !y))) return fail(ctx, EPI_EINVAL, "null argument");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     HostToDev dx;
@@ -1186,6 +1193,7 @@ epi_status epi_mlp_grad(epi_ctx *ctx, const float *X, const float *t, int64_t B,
     if (!ctx || B < 1 || !X || !t || !g) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     const int64_t np = mlp_n_params(ctx->c.mlp.F);
@@ -1219,6 +1227,7 @@ epi_status epi_mlp_train(epi_ctx *ctx, const float *X, const float *t, int64_t B
     if (!ctx || B < 1 || !X || !t || epochs < 1 || batch < 1) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
     Mlp &net = ctx->c.mlp;
@@ -1241,6 +1250,7 @@ epi_status epi_costmodel_features(epi_ctx *ctx, int32_t set_id, float *X, int64_
                                                  (long long)cs->m);
     Stream *s = find_stream(ctx, cs->stream_id);
     hipStream_t st = ctx->c.stream;
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     DevBuf dX;
     HIPTRY(ctx, dX.alloc(sizeof(float) * m * kFeatures), "alloc");
     HIPTRY(ctx, candidate_features(*s, *cs, dX.as<float>(), st), "features");
@@ -1398,6 +1408,7 @@ epi_status epi_costmodel_save(epi_ctx *ctx, const char *path) {
 
 epi_status epi_costmodel_load(epi_ctx *ctx, const char *path) {
     if (!ctx || !path) return fail(ctx, EPI_EINVAL, "bad arguments");
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     FILE *f = std::fopen(path, "rb");
     if (!f) return fail(ctx, EPI_EINVAL, "cannot read %s", path);
     char magic[8];
@@ -1442,6 +1453,7 @@ epi_status epi_costmodel_predict(epi_ctx *ctx, int32_t set_id, float *y, int64_t
     if (m == 0) return EPI_OK;
     Stream *s = find_stream(ctx, cs->stream_id);
     hipStream_t st = ctx->c.stream;
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     DevBuf dX, dy;
     HIPTRY(ctx, dX.alloc(sizeof(float) * m * kFeatures), "alloc");
     HIPTRY(ctx, dy.alloc(sizeof(float) * m), "alloc");
@@ -1570,6 +1582,7 @@ epi_status epi_autotune(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int sch
         if (cs->compact || cs->stream_order)
             return fail(ctx, EPI_EINVAL, "set %d cannot be counted in batched mode", set_ids[i]);
     }
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     const std::string key = tune_key(ctx, set_ids, k, sched);
     TuneSetting best;
     best.target = ctx->c.opt.target_lanes;
@@ -1685,7 +1698,7 @@ epi_status epi_count_noalloc(epi_ctx *ctx, int32_t set_id, int64_t segments, voi
                         (long long)P, (long long)G, need, noalloc_scratch_bytes());
     }
     HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
-    SpareScope spare(&ctx->c.idle);
+    SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     hipStream_t st = pick_stream(ctx, hip_stream);
     HIPTRY(ctx, launch_count(*s, *cs, opt, ctx->c.flags.as<int32_t>(), st, scr, noalloc_scratch_bytes()),
            "launching the count");

@@ -90,7 +90,8 @@ constexpr int64_t kWriteJobs = 65536;
 // set) as the stream has events: a row costs some 8 lane instructions an event
 // of its window and word, an entry that is walked some 180, so the rows are
 // then at most a fifth of what they save.
-constexpr size_t kNearBytes = size_t(8) << 30;
+// (kNearKept: rows of more bytes go back to the device when the run ends.)
+constexpr size_t kNearBytes = size_t(8) << 30, kNearKept = size_t(64) << 20;
 constexpr int64_t kNearShare = 4;
 // A count by near rows cuts the chain lists of few alphas into pieces of whole
 // clusters, about kNearJobs workgroups of at least kNearPiece entries on average,
@@ -203,6 +204,7 @@ __device__ __forceinline__ void load_ts(const_ptr<ChainEntry<T>> e, T &t, T &s) 
 // summed after: on one counter the atomics of 65,536 workgroups took five times
 // as long as their walks (a size walk of 50k events: 365 us, now 70).
 constexpr int kWalkSlots = 256, kWalkStride = 16;
+constexpr size_t kWalkBytes = sizeof(unsigned long long) * kWalkSlots * kWalkStride;
 // (left at zero for the next level)
 __global__ __launch_bounds__(kWalkSlots) void k_sum_walked(unsigned long long *__restrict__ w,
                                                            int64_t *__restrict__ sum) {
@@ -1445,14 +1447,16 @@ hipError_t order_by_length(const int32_t *clen, const int32_t *idx, int64_t n, D
 }
 
 // The near rows of the stream, made for the first level that counts enough with
-// them; without the memory for them every window is walked.
+// them; without the memory for them, or for a level's lists beside them
+// (extend_level), every window is walked.
 template <typename T>
 hipError_t make_near(const Stream &s, Mine &mn, const WalkArgs<T> &w, hipStream_t st) {
-    if (mn.near.p) return hipSuccess;
+    if (mn.near.p || mn.no_near) return hipSuccess;
     const int64_t words = (s.K + 63) / 64;
     const size_t bytes = sizeof(unsigned long long) * (size_t)(w.M + 1) * (size_t)s.n * (size_t)words;
     if (bytes > kNearBytes || mn.near.alloc(bytes) != hipSuccess) {
         (void)hipGetLastError();
+        mn.no_near = true;
         return hipSuccess;
     }
     NearArgs<T> a{};
@@ -1924,8 +1928,24 @@ hipError_t extend_level1(const Stream &s, Mine &mn, hipStream_t st) {
 }
 
 hipError_t extend_level(const Stream &s, Mine &mn, int N, hipStream_t st) {
-    if (s.ts_kind == EPI_TS_I64) return level_t<int64_t>(s, mn, N, st);
-    return level_t<int32_t>(s, mn, N, st);
+    auto level = [&] { return s.ts_kind == EPI_TS_I64 ? level_t<int64_t>(s, mn, N, st) : level_t<int32_t>(s, mn, N, st); };
+    hipError_t e = level();
+    if ((e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) && mn.near.p) {
+        // the level once more without the rows (what it had is given back)
+        (void)hipGetLastError();
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        mn.near.drop();
+        mn.no_near = true;
+        if ((e = hipMemsetAsync(mn.walked.p, 0, kWalkBytes, st)) != hipSuccess) return e;
+        e = level();
+    }
+    return e;
+}
+
+void extend_finish(Mine &mn) {
+    // small rows are kept for the context's next run
+    if (mn.near.bytes > kNearKept) mn.near.drop();
+    else mn.near.reset();
 }
 
 // Bytes the window walk of a level must read and write: the stream positions
@@ -1951,7 +1971,6 @@ hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st) {
     hipError_t e;
     if ((e = mn.ty16.alloc(sizeof(uint16_t) * (size_t)s.n)) != hipSuccess) return e;
     if ((e = mn.wend.alloc(sizeof(int32_t) * (size_t)s.n)) != hipSuccess) return e;
-    constexpr size_t kWalkBytes = sizeof(unsigned long long) * kWalkSlots * kWalkStride;
     if ((e = mn.walked.alloc(kWalkBytes)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(mn.walked.p, 0, kWalkBytes, st)) != hipSuccess) return e;
     for (hipEvent_t &ev : mn.ev)

@@ -47,7 +47,7 @@ struct TsLimits {
 // 1 MiB); new ones come from hipMalloc.  At most `limit` bytes are kept; every
 // block is freed by release(), which the owner calls after synchronising, and
 // which an allocation that fails calls, too, for its own cache and for the
-// thread's spare one (SpareScope).
+// thread's spare ones (SpareScope).
 class BlockCache {
 public:
     explicit BlockCache(size_t limit = SIZE_MAX) : limit_(limit) {}
@@ -83,22 +83,25 @@ public:
         kept_ = 0;
     }
     // hipMalloc; where memory is out, once more after the kept blocks of `own`
-    // (may be null) and of the thread's spare cache went back to the device
+    // (may be null) and of the thread's spare caches went back to the device
     // (once no queued work can use them).
     static hipError_t fresh(void **p, size_t b, BlockCache *own) {
         hipError_t e = hipMalloc(p, b);
-        if ((e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) && (own || spare())) {
+        if ((e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) && (own || spare().a)) {
             (void)hipGetLastError();
             (void)hipDeviceSynchronize();
-            if (own) own->release();
-            if (spare()) spare()->release();
+            for (BlockCache *c : {own, spare().a, spare().b})
+                if (c) c->release();
             e = hipMalloc(p, b);
         }
         return e;
     }
-    static BlockCache *&spare() {
-        static thread_local BlockCache *c = nullptr;
-        return c;
+    struct Spare {
+        BlockCache *a, *b;
+    };
+    static Spare &spare() {
+        static thread_local Spare s{nullptr, nullptr};
+        return s;
     }
 
 private:
@@ -106,11 +109,11 @@ private:
     size_t limit_, kept_ = 0;
 };
 
-// While alive, failing allocations of the calling thread give back this cache's
+// While alive, failing allocations of the calling thread give back these caches'
 // blocks, too.
 struct SpareScope {
-    BlockCache *prev;
-    explicit SpareScope(BlockCache *c) : prev(BlockCache::spare()) { BlockCache::spare() = c; }
+    BlockCache::Spare prev;
+    SpareScope(BlockCache *a, BlockCache *b) : prev(BlockCache::spare()) { BlockCache::spare() = {a, b}; }
     ~SpareScope() { BlockCache::spare() = prev; }
     SpareScope(const SpareScope &) = delete;
     SpareScope &operator=(const SpareScope &) = delete;
@@ -168,6 +171,12 @@ struct DevBuf {
         p = nullptr;
         bytes = 0;
         cache = nullptr;
+    }
+    // The block goes back to the device, not to its cache (hipFree waits for the
+    // work that uses it).
+    void drop() {
+        cache = nullptr;
+        reset();
     }
     hipError_t alloc(size_t b) {
         reset();
@@ -391,6 +400,7 @@ struct Mine {
     // menu interval end)
     DevBuf ty16, wend;
     DevBuf near;    // near rows of the stream (made by the first level counted with them)
+    bool no_near = false;  // there is no memory for them
     DevBuf chain1;  // the per-type index as chain entries (level 2's alphas)
     // list path: device bytes the end-event lists of every candidate of a
     // level may take (larger: count and write walks)
@@ -579,6 +589,8 @@ constexpr int kExtMaxMenu = 8;
 hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st);
 hipError_t extend_level1(const Stream &s, Mine &mn, hipStream_t st);
 hipError_t extend_level(const Stream &s, Mine &mn, int N, hipStream_t st);
+// What only the counting of the levels needs is given back.
+void extend_finish(Mine &mn);
 // algorithmic bytes of an extension-engine level (computed on first use)
 int64_t extend_level_bytes(const Stream &s, Mine &mn, int level);
 // Host copies of an extension-engine run's levels 2..level, for reading back.

@@ -151,3 +151,56 @@ ctx.epi_count([cid], epi.EPI_MODE_INCREMENTAL)
 at = launches("k_wave_append")
 assert [stub.stub_launch_grid(i) for i in at] == [1 << 20, 1 << 20, 5]
 """)
+
+
+MINE = """
+K, n = 64, 2_300_000
+ty, t = events(n, K)
+menu = [(0, 5000), (5000, 10000), (10000, 20000)]
+rows = (len(menu) + 1) * 8 * n  # the near rows of the stream: 70 MiB
+sid = ctx.epi_load_stream(ty, t, K)
+stub.stub_total(1 << 20)  # every level has as many candidates, frequent ones and list entries
+def mine():
+    mid = ctx.epi_mine(sid, menu, 4, 100)
+    made = len(launches("k_near"))
+    levels = [ctx.epi_mine_level_info(mid, i + 1)[1] for i in range(ctx.epi_mine_levels(mid))]
+    ctx.epi_mine_release(mid)
+    return made, levels
+"""
+
+
+def test_discovery_without_the_memory_for_near_rows_beside_its_lists(stub):
+    """Rows that fit but leave no room for a level's lists are given back, and the level walks every window."""
+    run(stub, MINE + """
+before = stub.stub_used()
+made, levels = mine()
+most = stub.stub_most() - before
+assert made == 1 and len(levels) == 4
+ctx.close()
+for less in (0, rows // 4, rows // 2, rows - (8 << 20)):
+    ctx = epi.Context(0)
+    stub.stub_reset()
+    sid = ctx.epi_load_stream(ty, t, K)
+    stub.stub_limit(stub.stub_used() + most - less)
+    assert mine()[1] == levels, less
+    ctx.close()
+""")
+
+
+def test_memory_kept_by_discovery_serves_other_calls(stub):
+    """Large near rows are not kept after a run, and what is kept goes back when another call runs out of memory."""
+    run(stub, MINE + """
+mine()
+kept = stub.stub_used()
+mine()
+assert stub.stub_used() == kept  # (no more with every run)
+before = stub.stub_most()
+stub.stub_limit(kept + (1 << 20))
+assert code(ctx.epi_load_stream, ty[:500000], t[:500000], K) == epi.EPI_OK
+stub.stub_limit(1 << 40)
+used = stub.stub_used()
+stub.stub_reset()
+made, levels = mine()
+assert made == 1
+assert stub.stub_most() - stub.stub_used() >= rows  # freed by the end of the run
+""")
