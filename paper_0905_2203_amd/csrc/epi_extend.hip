@@ -151,7 +151,7 @@ struct WalkArgs {
     const uint16_t *flast;    // last type of each frequent episode of the previous level
     const uint8_t *fliv;      // its last interval id
     int32_t *counts, *nvalid;
-    unsigned long long *walked;  // stream positions walked, summed over the jobs in kWalkSlots counters
+    unsigned long long *walked;  // stream positions walked and row words read, summed over the jobs in kWalkSlots counters
     // write pass: each job's range of the frequent list
     const int64_t *job_f;     // [njobs + 1]
     const uint16_t *w_type;
@@ -205,16 +205,22 @@ __device__ __forceinline__ void load_ts(const_ptr<ChainEntry<T>> e, T &t, T &s) 
 // as long as their walks (a size walk of 50k events: 365 us, now 70).
 constexpr int kWalkSlots = 256, kWalkStride = 16;
 constexpr size_t kWalkBytes = sizeof(unsigned long long) * kWalkSlots * kWalkStride;
-// (left at zero for the next level)
+// sum[0] = positions, sum[kRowWords] = row words.  (The counters are left at zero
+// for the next level.)
+constexpr int kRowWords = 7;
 __global__ __launch_bounds__(kWalkSlots) void k_sum_walked(unsigned long long *__restrict__ w,
                                                            int64_t *__restrict__ sum) {
-    __shared__ unsigned long long part[kWalkSlots / 64];
-    unsigned long long v = w[threadIdx.x * kWalkStride];
-    w[threadIdx.x * kWalkStride] = 0;
-    for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
-    if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = v;
+    __shared__ unsigned long long part[2][kWalkSlots / 64];
+    for (int k = 0; k < 2; ++k) {
+        unsigned long long v = w[threadIdx.x * kWalkStride + k];
+        w[threadIdx.x * kWalkStride + k] = 0;
+        for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d, 64);
+        if (threadIdx.x % 64 == 0) part[k][threadIdx.x / 64] = v;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) *sum = (int64_t)(part[0] + part[1] + part[2] + part[3]);
+    if (threadIdx.x < 2)
+        sum[threadIdx.x * kRowWords] = (int64_t)(part[threadIdx.x][0] + part[threadIdx.x][1] + part[threadIdx.x][2] +
+                                                 part[threadIdx.x][3]);
 }
 
 // Walk kinds: count (greedy counts and end-event counts per candidate),
@@ -383,7 +389,8 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
 #pragma unroll
         for (int m = 0; m < MP; ++m) evr[kWave].s[m] = kMin;
     }
-    unsigned long long in_windows = 0;  // stream positions of this lane's runs, all rounds
+    unsigned long long in_windows = 0;  // stream positions of this lane's runs that are walked, all rounds
+    unsigned long long row_words = 0;   // (uniform)
     const int64_t rowlen = M + 1;  // words of a near row
     // rounds of up to 64 distinct extension types (one lane each)
     for (int64_t r_start = 0; r_start < R;) {
@@ -515,6 +522,7 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
 #pragma unroll
                     for (int m = 0; m < MP; ++m) v[m] = kExact || m < M ? row[m] : 0ull;
                     e = (int32_t)row[M];
+                    row_words += (unsigned)(take * rowlen);
 #pragma unroll
                     for (int m = 0; m < MP; ++m) {
                         if (!kExact && m >= M) continue;  // uniform
@@ -532,13 +540,13 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
             const int32_t beg = max(p + 1, prev_e);
             int32_t len = ci ? max(0, e - beg) : 0;
             carry = max(carry, __builtin_amdgcn_readlane(e, 63 - __builtin_clzll(__ballot(ci))));
-            in_windows += (unsigned)len;
             if (MODE == kCount && a.near) {  // uniform
                 if (vis == 0) continue;
                 if (!((vis >> lane) & 1)) len = 0;
                 // an end event is preceded only by entries of its cluster
                 if (!joined || !(vis & 1)) ilo = max(ilo, i0 + __builtin_ctzll(vis));
             }
+            in_windows += (unsigned)len;
             // the entry visited after q (all but the simple clusters')
             auto after = [&](int32_t q) -> int32_t {
                 ++q;
@@ -741,7 +749,9 @@ __global__ __launch_bounds__(kWave) void k_ext_walk(WalkArgs<T> a) {
     if ((MODE == kCount || MODE == kSize) && a.walked) {
         unsigned long long w = in_windows;
         for (int d = 1; d < kWave; d <<= 1) w += __shfl_xor(w, d, kWave);
-        if (lane == 0) atomicAdd(a.walked + (blockIdx.x % kWalkSlots) * kWalkStride, w);
+        unsigned long long *to = a.walked + (blockIdx.x % kWalkSlots) * kWalkStride;
+        if (lane == 0) atomicAdd(to, w);
+        if (lane == 0 && row_words) atomicAdd(to + 1, row_words);
     }
 }
 
@@ -1658,6 +1668,7 @@ hipError_t level_t(const Stream &s, Mine &mn, int N, hipStream_t st) {
     if (e != hipSuccess) return e;
     L.kernel_ms = kms;
     L.walked = stage[0];
+    L.row_words = a.near ? stage[kRowWords] : -1;
     if (nb > 0) nf = stage[1];
     L.nf = nf;
     const size_t nfa = (size_t)std::max<int64_t>(1, nf);
@@ -1948,9 +1959,10 @@ void extend_finish(Mine &mn) {
     else mn.near.reset();
 }
 
-// Bytes the window walk of a level must read and write: the stream positions
-// it walked (type and time of each), the alphas' chain lists (one entry and
-// its window end each), and each candidate's count and end-event count.
+// Bytes the counting of a level must read and write: the stream positions it
+// walked (type and time of each), the alphas' chain lists (one entry and its window
+// end each), and each candidate's count and end-event count; by near rows, the words
+// of the rows (a window end among them) instead of the ends, and no end-event counts.
 int64_t extend_level_bytes(const Stream &s, Mine &mn, int level) {
     MineLevel &L = mn.levels[level - 1];
     if (L.alg_bytes >= 0) return L.alg_bytes;
@@ -1963,7 +1975,9 @@ int64_t extend_level_bytes(const Stream &s, Mine &mn, int level) {
         entries = P.chain_total;
     }
     const int64_t entry = tsb == 8 ? (int64_t)sizeof(ChainEntry<int64_t>) : (int64_t)sizeof(ChainEntry<int32_t>);
-    L.alg_bytes = L.walked * (2 + tsb) + entries * (entry + 4) + L.m * 8;
+    const bool near = L.row_words >= 0;
+    L.alg_bytes = L.walked * (2 + tsb) + entries * (entry + (near ? 0 : 4)) + (near ? L.row_words * 8 : 0) +
+                  L.m * (near ? 4 : 8);
     return L.alg_bytes;
 }
 

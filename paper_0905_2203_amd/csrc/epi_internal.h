@@ -384,6 +384,7 @@ struct MineLevel {
     int64_t chain_total = 0;       // entries in the chain lists of the frequent episodes
     int32_t list_seg = 0;          // list path: pieces per alpha (0: not taken)
     int64_t walked = 0;            // stream positions the extension walk visited (counting pass)
+    int64_t row_words = -1;        // words of near rows it read (-1: not counted with them)
 };
 
 struct Mine {
@@ -411,7 +412,7 @@ struct Mine {
     // several per synchronisation
     int64_t *stage = nullptr;
     void *rows = nullptr;  // pinned room of kStageBytes (the context's): level 1's counts, few patterns read back
-    DevBuf walked;  // counters of the positions in the walked windows
+    DevBuf walked;  // counters of the walked positions and the row words read
     hipEvent_t ev[2] = {nullptr, nullptr};  // around a level's counting kernels
     ~Mine() {
         for (hipEvent_t x : ev)
@@ -583,7 +584,7 @@ int queue_class_of(int64_t bound);
 // then count level N (>= 2) from level N-1's frequent episodes and chain lists,
 // select its frequent episodes and write their chain lists.  Menus of up to
 // kExtMaxMenu intervals.
-constexpr int kStageSlots = 8;     // pinned host slots of a mining run
+constexpr int kStageSlots = 8;     // pinned host slots of a mining run (8 bytes each)
 constexpr size_t kStageBytes = size_t(1) << 20;
 constexpr int kExtMaxMenu = 8;
 hipError_t extend_prepare(const Stream &s, Mine &mn, hipStream_t st);

@@ -65,3 +65,43 @@ def test_route_by_the_longest_cluster(busy):
                        for i in range(c["N"].size)}
                 assert got == want
             ctx.epi_mine_release(mid)
+
+
+def test_bytes_of_a_level_counted_by_rows():
+    """epi_mine_level_bytes of such a level: the entries and the rows they read, the positions of the windows that are
+    walked (clusters with two occurrences that do not overlap), and the counts."""
+    s = stream(0, 4)
+    theta, M = 5, len(MENU)
+    ref = apriori.mine(s, MENU, 3, theta)
+    frequent = set(ref[1]["frequent"])
+    starts = {}
+    for (a, b), iv in frequent:
+        starts.setdefault(a, []).append(b)
+    t = s["times"].astype(np.int64)
+    pos = [np.flatnonzero(s["types"] == k) for k in range(K)]
+    wend = np.searchsorted(t, t + H, side="right")
+    entries = rows = walked = 0
+    for (a, b), iv in frequent:
+        lo, hi = MENU[iv[0]]
+        ta, tb = t[pos[a]], t[pos[b]]
+        i = np.searchsorted(ta, tb - lo, side="left") - 1
+        ok = (i >= 0) & (tb - ta[np.maximum(i, 0)] <= hi)
+        e, st, p = tb[ok], ta[i[ok]], pos[b][ok]
+        entries += e.size
+        if not any(c != a for c in starts.get(b, [])):
+            continue  # no extension: nothing is counted
+        rows += e.size * (M + 1)
+        first = np.flatnonzero(np.concatenate([[True], st[1:] > e[:-1] + H]))
+        for f, l in zip(first, np.concatenate([first[1:], [e.size]])):
+            if st[l - 1] > e[f]:  # not simple
+                covered = 0
+                for j in range(f, l):
+                    walked += max(0, wend[p[j]] - max(p[j] + 1, covered))
+                    covered = max(covered, wend[p[j]])
+    assert walked > 0
+    with epi.Context(0) as ctx:
+        sid = ctx.epi_load_stream(s["types"], s["times"], K)
+        mid = ctx.epi_mine(sid, MENU, 3, theta)
+        m = ctx.epi_mine_level_info(mid, 3)[0]
+        assert m == len(ref[2]["counts"])
+        assert ctx.epi_mine_level_bytes(mid, 3) == walked * (2 + 4) + entries * 12 + rows * 8 + m * 4
