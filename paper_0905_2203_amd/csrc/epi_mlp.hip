@@ -36,8 +36,8 @@ __host__ __device__ inline int64_t n_params_of(int F) { return (int64_t)F * kH +
 // thread a sample with all weights broadcast from LDS (79 us), then one thread a
 // parameter with a load to wait for at each of 512 samples (134 us), then the loss
 // fetched by the host took 262 us a step; a wave a tile spreads the batch over 128
-// waves, and the sums over the batch keep 64 loads in flight (an epoch of 16 steps of
-// 512 and 50k predictions, host copies included: 4.3 -> 0.96 ms).
+// waves, and the sums over the batch keep 192 samples' loads in flight (an epoch of 16 steps of
+// 512 and 50k predictions, host copies included: 4.2 -> 0.67 ms).
 //
 // Every sum is one chain of FP32 fused multiply-adds in a fixed order: over the inputs,
 // over the units, over the samples.  Adam divides a gradient by its own size, and a
@@ -48,10 +48,14 @@ constexpr int kMlpWaves = 4;     // waves per workgroup, sharing the staged W2
 constexpr int kRow = kH + 1;     // W2's row in LDS: rows and columns free of bank conflicts
 constexpr int kRowT = kH + 4;    // h2's row in LDS (16-byte aligned)
 
-// What a training step keeps of every sample, for the sums over the batch: [B][64]
-// activations and terms, [B] dy and squared errors.
+// What a training step keeps of every sample, for the sums over the batch:
+// activations and terms, a tile of 4 samples after the other, [tile][64] of 4 each (a
+// lane of the sums loads its unit's 4 samples at once: a wave has at most 63 loads in
+// flight), [B] dy (room for whole tiles) and squared errors.
+constexpr int kTileS = 4;
 struct MlpRows {
-    float *h1, *dz1, *dz2, *h2, *dy, *sqerr;
+    float4 *h1, *dz1, *dz2, *h2;
+    float *dy, *sqerr;
 };
 
 // y[s] for every sample; TRAIN also its terms of the gradient of the loss over B
@@ -164,20 +168,20 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
                 rows.sqerr[s0 + j] = r * r;
                 rows.dy[s0 + j] = dy1;
             }
-            float dz1[S];
+            static_assert(!TRAIN || S == kTileS, "a tile's samples are kept together");
+            float dz1[S], dz2[S];
 #pragma unroll
             for (int q = 0; q < S; ++q) {
                 const float dy = __shfl(dy1, q, 64);
-                const float h2q = z2[q] > 0.f ? z2[q] : 0.f, dz2 = z2[q] > 0.f ? dy * vw3 : 0.f;
-                h[j][q] = dz2;
+                dz2[q] = z2[q] > 0.f ? dy * vw3 : 0.f;
+                z2[q] = z2[q] > 0.f ? z2[q] : 0.f;  // now h2
+                h[j][q] = dz2[q];
                 dz1[q] = 0.f;
-                if (q < ns) {  // uniform
-                    const int64_t o = (s0 + q) * kH + j;
-                    rows.h1[o] = h1[q];
-                    rows.h2[o] = h2q;
-                    rows.dz2[o] = dz2;
-                }
             }
+            const int64_t o = s0 / S * kH + j;
+            rows.h1[o] = make_float4(h1[0], h1[1], h1[2], h1[3]);
+            rows.h2[o] = make_float4(z2[0], z2[1], z2[2], z2[3]);
+            rows.dz2[o] = make_float4(dz2[0], dz2[1], dz2[2], dz2[3]);
             lds_order();
 #pragma unroll 8
             for (int k = 0; k < kH; ++k) {  // lane j = unit j of the first layer
@@ -186,8 +190,8 @@ __global__ __launch_bounds__(64 * kMlpWaves) void k_mlp_rows(const float *__rest
                 for (int q = 0; q < S; ++q) dz1[q] = fmaf(h[k][q], wt, dz1[q]);
             }
 #pragma unroll
-            for (int q = 0; q < S; ++q)
-                if (q < ns) rows.dz1[(s0 + q) * kH + j] = h1[q] > 0.f ? dz1[q] : 0.f;  // uniform
+            for (int q = 0; q < S; ++q) dz1[q] = h1[q] > 0.f ? dz1[q] : 0.f;
+            rows.dz1[o] = make_float4(dz1[0], dz1[1], dz1[2], dz1[3]);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -207,24 +211,27 @@ __device__ __forceinline__ void adam(float *__restrict__ p, float *__restrict__ 
 // Gradients of parameters 64 row .. 64 row + 63, each the chain acc = u_i v_i + acc
 // over the samples i in order (a bias: u = 1); ADAM: and the step with them.
 // Lane j: parameter j of the row.  u is the same for all lanes (the last row, the
-// output's bias, has one parameter).  Chunks of 64 samples, the next one's loads in
-// flight under this one's chain.
+// output's bias, has one parameter).  Chunks of 64 samples: the loads of the next two
+// are in flight under one's chain (what was written a launch before comes from beyond
+// L2, some 2 us away).
 template <bool ADAM>
 __global__ __launch_bounds__(64) void k_mlp_reduce(int F, const float *__restrict__ X, int64_t B, MlpRows rows,
                                                    float *__restrict__ g, float *__restrict__ p,
                                                    float *__restrict__ m, float *__restrict__ v, float lr, float b1,
                                                    float b2, float eps, float c1, float c2) {
     const int row = blockIdx.x, j = threadIdx.x;
-    const float *u = nullptr, *e = rows.dz1 + j;
-    int64_t us = 0, es = kH;
+    constexpr int kTiles = kH / kTileS;  // of a chunk
+    // u of sample i: u[i * us], or of a unit's activations (us = 0); e of tile i: e[i * et]
+    const float *u = nullptr;
+    const float4 *e = rows.dz1 + j;
+    int64_t us = 0, et = kH;
     int r = row;
     if (r < F) {  // W1[f][j]: x_f dz1_j
         u = X + r;
         us = F;
     } else if ((r -= F) == 0) {  // b1
     } else if ((r -= 1) < kH) {  // W2[a][j]: h1_a dz2_j
-        u = rows.h1 + r;
-        us = kH;
+        u = reinterpret_cast<const float *>(rows.h1 + r);
         e = rows.dz2 + j;
     } else if ((r -= kH) == 0) {  // b2
         e = rows.dz2 + j;
@@ -233,27 +240,30 @@ __global__ __launch_bounds__(64) void k_mlp_reduce(int F, const float *__restric
         us = 1;
         e = rows.h2 + j;
     } else {  // b3
-        e = rows.dy;
-        es = 1;
+        e = reinterpret_cast<const float4 *>(rows.dy);
+        et = 1;
     }
     struct Chunk {
-        float e[kH], u;
+        float4 e[kTiles];
+        float u;
     };
+    const int64_t last = B - 1, last_tile = last / kTileS;
     auto load = [&](Chunk &c, int64_t i0) __attribute__((always_inline)) {
-        const int64_t last = B - 1;
-        const int64_t iu = i0 + j < last ? i0 + j : last;
-        c.u = u ? u[iu * us] : 1.f;
+        if (i0 >= B) return;  // uniform
+        const int64_t i = i0 + j < last ? i0 + j : last;
+        c.u = u ? u[us ? i * us : i / kTileS * kH * kTileS + i % kTileS] : 1.f;
 #pragma unroll
-        for (int k = 0; k < kH; ++k) {
-            const int64_t i = i0 + k < last ? i0 + k : last;
-            c.e[k] = e[i * es];
+        for (int k = 0; k < kTiles; ++k) {
+            const int64_t t = i0 / kTileS + k < last_tile ? i0 / kTileS + k : last_tile;
+            c.e[k] = e[t * et];
         }
     };
     float acc = 0.f;
     auto chain = [&](const Chunk &c, int64_t i0) __attribute__((always_inline)) {
         auto term = [&](int k) __attribute__((always_inline)) {
             const float uk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c.u), k));
-            acc = fmaf(uk, c.e[k], acc);
+            const float4 &q = c.e[k / kTileS];
+            acc = fmaf(uk, k % kTileS == 0 ? q.x : k % kTileS == 1 ? q.y : k % kTileS == 2 ? q.z : q.w, acc);
         };
         if (B - i0 >= kH) {  // uniform
 #pragma unroll
@@ -265,14 +275,19 @@ __global__ __launch_bounds__(64) void k_mlp_reduce(int F, const float *__restric
                 if (k < n) term(k);  // uniform
         }
     };
-    Chunk c0, c1b;
-    load(c0, 0);
-    for (int64_t i0 = 0; i0 < B; i0 += 2 * kH) {
-        if (i0 + kH < B) load(c1b, i0 + kH);
-        chain(c0, i0);
+    Chunk ca, cb, cc;
+    load(ca, 0);
+    load(cb, kH);
+    load(cc, 2 * kH);
+    for (int64_t i0 = 0; i0 < B; i0 += 3 * kH) {
+        chain(ca, i0);
+        load(ca, i0 + 3 * kH);
         if (i0 + kH >= B) break;
-        if (i0 + 2 * kH < B) load(c0, i0 + 2 * kH);
-        chain(c1b, i0 + kH);
+        chain(cb, i0 + kH);
+        load(cb, i0 + 4 * kH);
+        if (i0 + 2 * kH >= B) break;
+        chain(cc, i0 + 2 * kH);
+        load(cc, i0 + 5 * kH);
     }
     const int64_t q = (int64_t)row * kH + j;
     if (q >= n_params_of(F)) return;
@@ -360,18 +375,18 @@ static hipError_t grad_launch(Mlp &net, const float *dX, const float *dt, int64_
                               hipStream_t st) {
     hipError_t e;
     if (!mlp_fits(net)) return hipErrorInvalidValue;
-    constexpr int S = 4;
-    const int64_t np = n_params_of(net.F);
-    const size_t need = sizeof(float) * (size_t)B * (4 * kH + 2);
+    constexpr int S = kTileS;
+    const int64_t np = n_params_of(net.F), tiles = (B + S - 1) / S;
+    const size_t need = sizeof(float) * (size_t)tiles * S * (4 * kH + 2);
     if (net.act.bytes < need) {
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
         if ((e = net.act.alloc(need)) != hipSuccess) return e;
     }
-    const size_t w = (size_t)B * kH;
-    float *base = net.act.as<float>();
-    MlpRows rows{base, base + w, base + 2 * w, base + 3 * w, base + 4 * w, sq};
-    float *ys = rows.dy + B;
-    const int64_t blocks = ((B + S - 1) / S + kMlpWaves - 1) / kMlpWaves;
+    const size_t w = (size_t)tiles * kH;
+    float4 *base = net.act.as<float4>();
+    MlpRows rows{base, base + w, base + 2 * w, base + 3 * w, reinterpret_cast<float *>(base + 4 * w), sq};
+    float *ys = rows.dy + tiles * S;
+    const int64_t blocks = (tiles + kMlpWaves - 1) / kMlpWaves;
     k_mlp_rows<true, S><<<(unsigned)std::min<int64_t>(blocks, 1024), 64 * kMlpWaves, 0, st>>>(
         net.p.as<float>(), net.F, dX, dt, B, ys, rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
