@@ -749,11 +749,10 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
         const int64_t *t = (const int64_t *)times;
         int64_t cell = s->n > 0 ? s->tmax >> kCellBits : t[0] >> kCellBits;
         if (s->n == 0) longer.cells = 1;
-        for (int64_t i = 0; i < n && t[n - 1] >> kCellBits != cell; ++i)
-            if (t[i] >> kCellBits != cell) {
-                ++longer.cells;
-                cell = t[i] >> kCellBits;
-            }
+        for (const int64_t *at = t; t[n - 1] >> kCellBits != cell; cell = *at >> kCellBits) {
+            at = std::lower_bound(at, t + n, (cell + 1) * (int64_t(1) << kCellBits));
+            ++longer.cells;
+        }
     }
     auto make = [&]() -> hipError_t {
         hipError_t e;
