@@ -466,6 +466,7 @@ epi_status epi_read_type_index(epi_ctx *ctx, int32_t stream_id, int32_t *off, vo
     if (!s) return fail(ctx, EPI_ESTATE, "unknown stream id %d", stream_id);
     HIPTRY(ctx, hipStreamSynchronize(ctx->c.stream), "sync");
     HIPTRY(ctx, hipMemcpy(off, s->type_off.p, sizeof(int32_t) * (s->K + 1), hipMemcpyDeviceToHost), "copy");
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     if (s->n > 0)
         HIPTRY(ctx, hipMemcpy(ts_by_type, s->ts_by_type.p, s->ts_bytes() * s->n, hipMemcpyDeviceToHost), "copy");
     return EPI_OK;
@@ -477,6 +478,7 @@ epi_status epi_release_stream(epi_ctx *ctx, int32_t stream_id) {
     for (auto &kv : ctx->c.sets)
         if (kv.second->stream_id == stream_id)
             return fail(ctx, EPI_ESTATE, "stream %d still has candidate set %d", stream_id, kv.first);
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     ctx->c.batch.evict_all();
     (void)hipDeviceSynchronize();
     ctx->c.streams.erase(stream_id);
@@ -553,6 +555,7 @@ epi_status epi_submit_candidates(epi_ctx *ctx, int32_t stream_id, int64_t m, con
 epi_status epi_release_set(epi_ctx *ctx, int32_t set_id) {
     if (!ctx) return EPI_EINVAL;
     if (!find_set(ctx, set_id)) return fail(ctx, EPI_ESTATE, "unknown set id %d", set_id);
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     ctx->c.batch.evict_set(set_id);
     (void)hipDeviceSynchronize();
     ctx->c.sets.erase(set_id);
@@ -1094,6 +1097,7 @@ epi_status epi_mine_level_bytes(epi_ctx *ctx, int32_t mine_id, int32_t level, in
 
 epi_status epi_mine_release(epi_ctx *ctx, int32_t mine_id) {
     if (!ctx) return EPI_EINVAL;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     if (!ctx->c.mines.erase(mine_id)) return fail(ctx, EPI_ESTATE, "unknown mining id %d", mine_id);
     return EPI_OK;
 }
@@ -1174,6 +1178,7 @@ epi_status epi_mlp_forward(epi_ctx *ctx, const float *X, int64_t B, float *y) {
     if (!ctx || (B > 0 && (!X || !y))) return fail(ctx, EPI_EINVAL, "null argument");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
@@ -1192,6 +1197,7 @@ epi_status epi_mlp_grad(epi_ctx *ctx, const float *X, const float *t, int64_t B,
     if (!ctx || B < 1 || !X || !t || !g) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
@@ -1213,6 +1219,7 @@ epi_status epi_mlp_adam_step(epi_ctx *ctx, const float *g, float lr) {
     if (!ctx || !g) return fail(ctx, EPI_EINVAL, "null argument");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     const int64_t np = mlp_n_params(ctx->c.mlp.F);
     HIPTRY(ctx, hipMemcpy(ctx->c.mlp.g.p, g, sizeof(float) * np, hipMemcpyHostToDevice), "copy");
     ctx->c.mlp.lr = lr;
@@ -1226,6 +1233,7 @@ epi_status epi_mlp_train(epi_ctx *ctx, const float *X, const float *t, int64_t B
     if (!ctx || B < 1 || !X || !t || epochs < 1 || batch < 1) return fail(ctx, EPI_EINVAL, "bad arguments");
     epi_status v = need_mlp(ctx, -1);
     if (v != EPI_OK) return v;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     CacheScope scope(&ctx->c.idle);
     hipStream_t st = ctx->c.stream;
@@ -1247,6 +1255,7 @@ epi_status epi_costmodel_features(epi_ctx *ctx, int32_t set_id, float *X, int64_
     if (cs->compact) return fail(ctx, EPI_EINVAL, "set %d has no features", set_id);
     if (m != cs->m || (m > 0 && !X)) return fail(ctx, EPI_EINVAL, "set %d holds %lld candidates", set_id,
                                                  (long long)cs->m);
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     Stream *s = find_stream(ctx, cs->stream_id);
     hipStream_t st = ctx->c.stream;
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
@@ -1407,6 +1416,7 @@ epi_status epi_costmodel_save(epi_ctx *ctx, const char *path) {
 
 epi_status epi_costmodel_load(epi_ctx *ctx, const char *path) {
     if (!ctx || !path) return fail(ctx, EPI_EINVAL, "bad arguments");
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     FILE *f = std::fopen(path, "rb");
     if (!f) return fail(ctx, EPI_EINVAL, "cannot read %s", path);
@@ -1450,6 +1460,7 @@ epi_status epi_costmodel_predict(epi_ctx *ctx, int32_t set_id, float *y, int64_t
     if (m != cs->m || (m > 0 && !y)) return fail(ctx, EPI_EINVAL, "set %d holds %lld candidates", set_id,
                                                  (long long)cs->m);
     if (m == 0) return EPI_OK;
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     Stream *s = find_stream(ctx, cs->stream_id);
     hipStream_t st = ctx->c.stream;
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
@@ -1581,6 +1592,7 @@ epi_status epi_autotune(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int sch
         if (cs->compact || cs->stream_order)
             return fail(ctx, EPI_EINVAL, "set %d cannot be counted in batched mode", set_ids[i]);
     }
+    HIPTRY(ctx, hipSetDevice(ctx->c.device), "hipSetDevice");
     SpareScope spare(&ctx->c.idle, &ctx->c.cache);
     const std::string key = tune_key(ctx, set_ids, k, sched);
     TuneSetting best;

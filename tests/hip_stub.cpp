@@ -19,9 +19,12 @@ struct Launch {
 };
 static std::map<const void *, std::string> names;
 static std::map<char *, size_t> blocks;  // device memory
+static std::map<char *, int> home;       // and the device it is on
+static int device = 0;                   // the current one, of two
 static std::vector<Launch> launches;
 static std::string fail_kernel;
-static int64_t limit = INT64_MAX, used = 0, most = 0, queued = 0, total = 0;
+static int64_t limit = INT64_MAX, used = 0, most = 0, queued_on[2] = {}, total = 0;
+#define queued queued_on[device]
 static int err = 0;
 static char *first = nullptr;
 static struct {
@@ -39,7 +42,12 @@ void stub_reset() { launches.clear(); fail_kernel.clear(); limit = INT64_MAX; mo
 void stub_limit(int64_t bytes) { limit = bytes; }
 void stub_fail_kernel(const char *part) { fail_kernel = part; }
 void stub_total(int64_t v) { total = v; }
-int64_t stub_queued() { return queued; }
+int64_t stub_queued() { return queued_on[0]; }
+int64_t stub_used_on(int d) {
+    int64_t n = 0;
+    for (auto &b : blocks) n += home[b.first] == d ? (int64_t)b.second : 0;
+    return n;
+}
 int64_t stub_used() { return used; }
 int64_t stub_most() { return most; }
 void *stub_first_block() { return first; }
@@ -51,6 +59,7 @@ void *stub_device_block(int64_t bytes, int fill) {
     char *p = (char *)std::calloc(1, bytes);
     std::memset(p, fill, bytes);
     blocks[p] = bytes;
+    home[p] = device;
     used += bytes;
     return p;
 }
@@ -61,6 +70,7 @@ int hipMalloc(void **p, size_t n) {
     if (!q) return set(kNoMemory);
     if (!first) first = q;
     blocks[q] = n;
+    home[q] = device;
     used += n;
     most = used > most ? used : most;
     *p = q;
@@ -73,7 +83,8 @@ int hipFree(void *p) {
     used -= it->second;
     std::free(p);
     blocks.erase(it);
-    queued = 0;  // (waits for the device)
+    queued_on[home[(char *)p]] = 0;  // (waits for the device)
+    home.erase((char *)p);
     return 0;
 }
 int hipMemGetAddressRange(void **base, size_t *size, void *p) {
@@ -110,9 +121,9 @@ int hipMemset(void *d, int v, size_t n) { std::memset(d, v, n); queued = 0; retu
 int hipMemsetAsync(void *d, int v, size_t n, void *) { std::memset(d, v, n); ++queued; return 0; }
 int hipDeviceSynchronize() { queued = 0; return 0; }
 int hipStreamSynchronize(void *) { queued = 0; return 0; }
-int hipGetDeviceCount(int *n) { *n = 1; return 0; }
-int hipGetDevice(int *d) { *d = 0; return 0; }
-int hipSetDevice(int) { return 0; }
+int hipGetDeviceCount(int *n) { *n = 2; return 0; }
+int hipGetDevice(int *d) { *d = device; return 0; }
+int hipSetDevice(int d) { device = d; return 0; }
 int hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 int hipGetLastError() { const int e = err; err = 0; return e; }
 const char *hipGetErrorString(int e) { return e == kNoMemory ? "out of memory" : "stub error"; }

@@ -13,7 +13,7 @@ import ctypes, os, sys
 import numpy as np
 sys.path.insert(0, {root!r})
 stub = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
-for f in ("stub_queued", "stub_used", "stub_most", "stub_launches", "stub_launch_grid"):
+for f in ("stub_queued", "stub_used_on", "stub_used", "stub_most", "stub_launches", "stub_launch_grid"):
     getattr(stub, f).restype = ctypes.c_int64
 stub.stub_launch_name.restype = ctypes.c_char_p
 for f in ("stub_first_block", "stub_device_block", "stub_launch_arg"):
@@ -203,4 +203,41 @@ stub.stub_reset()
 made, levels = mine()
 assert made == 1
 assert stub.stub_most() - stub.stub_used() >= rows  # freed by the end of the run
+""")
+
+
+def test_calls_work_on_their_contexts_device(stub):
+    """A thread whose current device is another one (a second context's): what is released is waited for on the
+    context's device before its memory is kept for reuse, and what is allocated is that device's."""
+    run(stub, """
+sid = ctx.epi_load_stream(*events(2000), 4)
+cid = ctx.epi_submit_candidates(sid, pairs(8))
+ctx.epi_count([cid])
+assert stub.stub_queued() > 0
+stub.hipSetDevice(1)
+ctx.epi_release_set(cid)
+assert stub.stub_queued() == 0
+cid = ctx.epi_submit_candidates(sid, pairs(8))
+ctx.epi_count([cid])
+ctx.epi_release_set(cid)
+cid = ctx.epi_submit_candidates(sid, pairs(8))
+ctx.epi_count([cid])
+stub.hipSetDevice(1)
+ctx.epi_release_set(cid)
+ctx.epi_release_stream(sid)
+assert stub.stub_queued() == 0
+X, t = np.ones((9, 24), np.float32), np.ones(9, np.float32)
+for call in (lambda: ctx.epi_mlp_init(24, 1), lambda: ctx.epi_mlp_forward(X), lambda: ctx.epi_mlp_grad(X, t),
+             lambda: ctx.epi_mlp_train(X, t, 1, 4, 1e-3)):
+    stub.hipSetDevice(1)
+    call()
+    assert stub.stub_used_on(1) == 0
+sid = ctx.epi_load_stream(*events(2000), 4)
+cid = ctx.epi_submit_candidates(sid, pairs(8))
+ctx.epi_count([cid])
+for call in (lambda: ctx.epi_costmodel_features(cid, 8), lambda: ctx.epi_costmodel_predict(cid, 8),
+             lambda: ctx.epi_autotune([cid])):
+    stub.hipSetDevice(1)
+    code(call)
+    assert stub.stub_used_on(1) == 0
 """)
