@@ -22,7 +22,11 @@
  *   - host inputs are copied before the call returns; "_device" inputs are
  *     borrowed until epi_sync() returns;
  *   - outputs go to caller-owned buffers; device memory made by the library
- *     is owned by the context and freed by epi_release_* and epi_destroy;
+ *     is owned by the context.  What epi_release_* and finished calls give
+ *     back is kept for the context's next calls (up to 4 GiB of streams',
+ *     sets' and calls' memory, and the memory of discovery runs) until
+ *     epi_destroy or until one of the context's own allocations runs out;
+ *     other allocators in the process do not get it sooner;
  *   - there is no CPU fallback: every count is computed by HIP kernels.
  *
  * Timestamps are unit-agnostic integers, int32 (EPI_TS_I32) or int64
@@ -114,8 +118,10 @@ epi_status epi_load_stream(epi_ctx *ctx, const int32_t *types, const void *times
 
 /* Same, from device buffers (int32 types, int32/int64 times) enqueued on
  * `hip_stream` (hipStream_t; null = the context's stream).  The inputs are
- * validated on the device; a violation is reported as EPI_EUNSORTED or
- * EPI_ETYPE by this call (it synchronises once to read the result). */
+ * validated on the device; a violation is reported as EPI_EUNSORTED,
+ * EPI_ETYPE or EPI_EOVERFLOW by this call (it synchronises to read the
+ * result).  Buffers that this device does not hold whole are copied by the
+ * runtime, which may refuse them. */
 epi_status epi_load_stream_device(epi_ctx *ctx, const int32_t *d_types, const void *d_times,
                                   int64_t n, int ts_kind, int32_t K, void *hip_stream,
                                   int32_t *stream_id);
@@ -183,7 +189,8 @@ epi_status epi_release_set(epi_ctx *ctx, int32_t set_id);
  *                     the set for its next count; no work log; returns when
  *                     done.  The only mode for sets submitted under
  *                     EPI_OPT_STREAM_ORDER.
- * sched (batched mode): EPI_SCHED_RR keeps submission order;
+ * sched (batched mode): EPI_SCHED_RR keeps submission order within a launch
+ * group (groups counted by one-wave counts are queued costliest first);
  * EPI_SCHED_LEARNED orders each class's episodes by the cost model's
  * predicted work (see epi_costmodel_train; without a trained model it falls
  * back to EPI_SCHED_RR), cuts costly lane blocks into more time segments and
@@ -197,7 +204,8 @@ epi_status epi_count(epi_ctx *ctx, const int32_t *set_ids, int32_t k, int mode, 
                      void *hip_stream);
 
 /* Streaming (the streaming direction of the paper's Future Work section,
- * here exact): append n events to a loaded stream.  Same checks as
+ * here exact): append n events to a loaded stream (a failure leaves it as it
+ * was).  Same checks as
  * epi_load_stream, and the first appended time must not precede the
  * stream's last one (EPI_EUNSORTED).  The per-type index is rebuilt;
  * synchronous (the device is idle when it returns).  Sets on the stream keep
@@ -258,10 +266,15 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         lists, listed by walks cut into pieces, when they
  *                         fit; else one walk per parent counts it and a
  *                         second writes its chain lists (0 = always the
- *                         latter).  Levels of 512 and more parents are
- *                         counted by waves that walk only what
- *                         per-position rows of near types do not settle,
- *                         whatever the lists would take
+ *                         latter).  Levels >= 3 of 512 and more parents,
+ *                         whose chain lists have at least a quarter as many
+ *                         entries (times K / 64, rounded up) as the stream
+ *                         has events, are instead counted by waves that walk
+ *                         only what per-position rows of near types do not
+ *                         settle, if the rows fit 8 GiB and the device's
+ *                         memory, and if no wave would walk long after the
+ *                         others (an episode whose end events follow each
+ *                         other closely through much of the stream)
  *   EPI_OPT_MINE_LIST_ALPHAS  level-wise discovery, extension engine: levels
  *                         with fewer frequent parent episodes than this
  *                         (default 65536) take the list path when it fits;
@@ -295,8 +308,10 @@ epi_status epi_append_stream(epi_ctx *ctx, int32_t stream_id, const int32_t *typ
  *                         per (episode, time segment), parallel over events,
  *                         where no type of the stream has 128 events within
  *                         the set's largest lower bound, spans are below
- *                         2^29 time units and no work log is kept; else the
- *                         state machines keep their
+ *                         2^29 time units and no work log is kept (but not
+ *                         very many episodes of a few events each, nor int64
+ *                         times so far apart that 2^34 units hold few events
+ *                         of a type); else the state machines keep their
  *                         bookkeeping in registers and, per node, a ring of
  *                         exactly that interval's bound in LDS (lane
  *                         machines), wherever the stream's tiles allow int32
@@ -435,7 +450,9 @@ epi_status epi_mlp_adam_step(epi_ctx *ctx, const float *g, float lr);
 
 /* Train on B host samples for `epochs` passes of consecutive mini-batches
  * of `batch` samples (order as given); losses[epochs] (may be null)
- * receives each epoch's mean loss. */
+ * receives each epoch's mean loss.  Every sum is one chain of FP32 fused
+ * multiply-adds in input, unit and sample order, so the results are the same
+ * on every call. */
 epi_status epi_mlp_train(epi_ctx *ctx, const float *X, const float *t, int64_t B, int32_t epochs, int32_t batch,
                          float lr, float *losses);
 
@@ -523,8 +540,9 @@ epi_status epi_mine_read(epi_ctx *ctx, int32_t mine_id, int32_t level, int frequ
 epi_status epi_mine_read_at(epi_ctx *ctx, int32_t mine_id, int32_t level, int64_t k, const int64_t *idx,
                             uint8_t *N, int32_t *types, int64_t *lo, int64_t *hi, int32_t *counts);
 
-/* Bytes the level's counting method must read and write (inputs per
- * candidate plus its outputs), for bandwidth accounting. */
+/* Bytes the level's counting method must read and write (the stream positions,
+ * chain entries and rows it reads, and its outputs; state machines: inputs
+ * per candidate plus its outputs), for bandwidth accounting. */
 epi_status epi_mine_level_bytes(epi_ctx *ctx, int32_t mine_id, int32_t level, int64_t *alg_bytes);
 
 epi_status epi_mine_release(epi_ctx *ctx, int32_t mine_id);

@@ -43,7 +43,9 @@
 // the stream position of x alone: a row of 64-bit words per position, made
 // once a run, has a bit for it (k_near).  A wave loads the rows of 64 entries,
 // transposes the words so that a lane holds its type's bits, and counts the
-// clusters with a bit set.  Only the windows of the other clusters are walked.
+// clusters with a bit set.  Only the windows of the other clusters are walked, each
+// by one wave: a level with a cluster that one would walk long after the others takes
+// the list path (kNearLone).
 // What bounds it: instructions a walked batch (184 vector instructions for 64
 // events, 68 batches an alpha) against some 200 for 64 entries.  788,381
 // alphas of 170 entries, 83.5M candidates: 18.5 ms walked, 2.6 ms so.  A level

@@ -656,7 +656,8 @@ __global__ __launch_bounds__(kW) void k_wave_append(CountArgs<T> a, T B) {
 // one counter takes about 5 ns a slot: the slots at work are listed first, in
 // the items' order, and the queue runs over the list (with half as many
 // segments again, which the list makes cheap: 5.4 ms -> 4.6 ms; 438 episodes
-// of 1-2 nodes over skewed rates: 2.3 ms -> 0.52).
+// of 1-2 nodes over skewed rates: 2.3 ms -> 0.52).  Light slots come several at
+// a turn (WaveSlots::take).
 // masks[i]: item i's slots at work.
 template <typename T>
 __global__ __launch_bounds__(kW) void k_wave_live(const CountArgs<T> *__restrict__ units,
