@@ -25,6 +25,7 @@
 // to one XCD, whose L2 joins their runs to whole lines.  One wave a tile with 64
 // broadcasts for each rank took 451 us for 9M events of 128 types; now 97 us (3.7 TB/s).
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "epi_count.h"
@@ -317,6 +318,7 @@ struct IngestInfo {
     static constexpr int kStride = 16;
     unsigned long long span[kTileSizes * kStride];
     unsigned long long cells;  // int64 times: events that begin a stretch of 2^kCellBits units, but the first
+    int64_t ends[2];  // the first and the last event's time
     uint32_t bad;
 };
 
@@ -355,6 +357,8 @@ __global__ __launch_bounds__(kIdxBlock) void k_ingest(const int32_t *__restrict_
             if (threadIdx.x % kWave == 0 && cells) atomicAdd(&info->cells, (unsigned long long)cells);
         }
     }
+    if (threadIdx.x == 0 && beg == 0) info->ends[0] = (int64_t)tm[0];
+    if (threadIdx.x == 0 && end == n) info->ends[1] = (int64_t)tm[n - 1];
     // one wave: lane q of 16 the smallest tile q of the stretch, and from their
     // ends the larger tiles
     if (threadIdx.x >= kTile / kMinTile) return;
@@ -393,15 +397,11 @@ hipError_t ingest_t(Stream &s, const int32_t *src_types, const T *src_times, boo
     if ((e = hipGetLastError()) != hipSuccess) return e;
     IngestInfo h;
     if ((e = hipMemcpyAsync(&h, info.p, sizeof(h), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    T ends[2];
-    if ((e = hipMemcpyAsync(&ends[0], s.times.as<T>(), sizeof(T), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(&ends[1], s.times.as<T>() + (s.n - 1), sizeof(T), hipMemcpyDeviceToHost, st)) != hipSuccess)
-        return e;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     *bad = h.bad;
     if (src_types || check) s.cells = sizeof(T) == 8 ? 1 + (int64_t)h.cells : 0;
-    s.tmin = ends[0];
-    s.tmax = ends[1];
+    s.tmin = h.ends[0];
+    s.tmax = h.ends[1];
     for (int q = 0; q < kTileSizes; ++q) {
         const unsigned long long d = h.span[q * IngestInfo::kStride];
         s.tile_span[q] = d > (unsigned long long)INT64_MAX ? INT64_MAX : (int64_t)d;
@@ -451,7 +451,9 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
     s.B = B;
     s.max_tile_span = n > 0 ? longest_tile(s, TT) : 0;
     for (int64_t &g : s.gap) g = INT64_MAX;
-    if ((e = s.type_off.alloc(sizeof(int32_t) * (K + 1))) != hipSuccess) return e;
+    // (the offsets, and behind them the gaps: one copy brings both to the host)
+    const size_t gap_at = (sizeof(int32_t) * ((size_t)K + 1) + 7) & ~(size_t)7;
+    if ((e = s.type_off.alloc(gap_at + sizeof(s.gap))) != hipSuccess) return e;
     // (padded: the wave chains load whole windows)
     if ((e = s.ts_by_type.alloc(s.ts_bytes() * ((size_t)n + kWaveChunks * kWave))) != hipSuccess) return e;
     if ((e = s.pos_by_type.alloc(sizeof(int32_t) * (size_t)n)) != hipSuccess) return e;
@@ -464,11 +466,11 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
         return hipStreamSynchronize(st);
     }
     const int64_t nc = (B + kColTiles - 1) / kColTiles;
-    DevBuf cnt, sums, tot, gap;
+    DevBuf cnt, sums, tot;
+    auto *gap = reinterpret_cast<unsigned long long *>(s.type_off.as<char>() + gap_at);
     if ((e = cnt.alloc(sizeof(int32_t) * (size_t)B * K)) != hipSuccess) return e;
     if ((e = sums.alloc(sizeof(int32_t) * (size_t)nc * K)) != hipSuccess) return e;
     if ((e = tot.alloc(sizeof(int32_t) * (size_t)K)) != hipSuccess) return e;
-    if ((e = gap.alloc(sizeof(s.gap))) != hipSuccess) return e;
     k_hist<<<tile_grid(B), kIdxBlock, sizeof(int32_t) * (size_t)K, st>>>(s.types.as<int32_t>(), n, K, TT, B,
                                                                        cnt.as<int32_t>());
     const dim3 cols((unsigned)nc, (unsigned)((K + kIdxBlock - 1) / kIdxBlock));
@@ -490,19 +492,20 @@ hipError_t build_type_index(Stream &s, hipStream_t st) {
         k_scatter<T><<<tile_grid(B), kIdxBlock, lds, st>>>(
             s.types.as<int32_t>(), s.times.as<T>(), n, K, bits, B, cnt.as<int32_t>(), s.ts_by_type.as<T>(),
             s.pos_by_type.as<int32_t>(), s.tiled_ts.as<T>(), s.tile_loff.as<uint16_t>(), s.tile_t0.as<T>(), TT);
-        k_gap_init<<<1, kWaveHands, 0, st>>>(gap.as<unsigned long long>());
+        k_gap_init<<<1, kWaveHands, 0, st>>>(gap);
         if (n > kWaveGap[0])
             k_gap<T><<<(unsigned)((n + kGapBlock * kGapItems - 1) / (kGapBlock * kGapItems)), kGapBlock, 0, st>>>(
-                s.ts_by_type.as<T>(), n, s.type_off.as<int32_t>(), K, gap.as<unsigned long long>());
+                s.ts_by_type.as<T>(), n, s.type_off.as<int32_t>(), K, gap);
         return hipGetLastError();
     };
     if ((e = s.ts_kind == EPI_TS_I64 ? scatter(int64_t()) : scatter(int32_t())) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(s.gap, gap.p, sizeof(s.gap), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(s.h_off.data(), s.type_off.p, sizeof(int32_t) * (K + 1), hipMemcpyDeviceToHost, st)) !=
-        hipSuccess)
-        return e;
+    std::vector<char> host(gap_at + sizeof(s.gap));
+    if ((e = hipMemcpyAsync(host.data(), s.type_off.p, host.size(), hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     // the temporaries are freed when this returns: wait for the kernels first
-    return hipStreamSynchronize(st);
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    std::memcpy(s.h_off.data(), host.data(), sizeof(int32_t) * ((size_t)K + 1));
+    std::memcpy(s.gap, host.data() + gap_at, sizeof(s.gap));
+    return hipSuccess;
 }
 
 }  // namespace epi
