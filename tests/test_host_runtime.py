@@ -1,6 +1,6 @@
 """The library's host side on the CPU, over a HIP runtime without a device (hip_stub.cpp): what stays queued and what
 is kept when a call fails, launches within the limits of a dispatch, memory that runs out.  Each case runs in a
-process of its own, which loads the stub before the library (and no torch)."""
+process of its own, which loads the stub before the library."""
 import os
 import subprocess
 import sys
